@@ -1,107 +1,277 @@
-// fp32 jagged attention, forward and backward, in plain FMA arithmetic (no matrix cores): the
-// small-tolerance path.  Same structure as the bf16 kernels -- persistent workgroups pull
-// (sample, head, row-block) tiles from the offsets-driven schedule, stream the sample's keys
-// through LDS and keep an online softmax in registers (paper Section 2.1) -- but one row is owned
-// by four neighbouring lanes, each holding every fourth element of the row.
+// fp32 jagged attention, forward and backward, on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32): fp32 products,
+// fp32 accumulation, the small-tolerance path (paper Section 2.1; the backward recomputes P from the stored log-sum-exp).
+//
+// Bound: the fp32 matrix pipe (a 32x32x2 instruction is 4096 flops in 64 clocks; a library product of 8192^3 reaches
+// 153 TFLOP/s on this chip).  A block of 32 x 32 scores costs D / 2 instructions per product against 16 exponentials
+// per lane and at most one LDS read per instruction, so vector work and LDS are far from being the limit, and what the
+// shape of the kernels has to provide is occupancy of all four matrix pipes on short and ragged samples.  Hence
+//   * a tile is 64 stationary rows and a stage 64 streamed rows; the four waves of a workgroup are the four 32 x 32
+//     quarters of that square: wave w owns stationary rows 32 (w & 1) .. + 31 and in every stage the streamed rows
+//     32 (w >> 1) .. + 31.  The two waves that share stationary rows add their results through LDS at the tile's end
+//     (fixed order: deterministic).  A sample of up to 64 rows is then one step of each wave instead of two steps of two;
+//   * streamed rows go to LDS directly (global_load_lds), the next stage's while the present one is multiplied, and
+//     two workgroups share a compute unit (D <= 64), so that one computes while the other starts or ends a tile.
+// Operand layout of the instruction: lane l holds row (A) or column (B) l % 32 and contraction slot l / 32.  Slots are
+// dummies: four consecutive instructions take features 8 g + 4 (l / 32) .. + 3, one 16-byte read per lane.  Scores are
+// computed with the streamed rows on the accumulator's row axis and the stationary rows on its column (= lane) axis;
+// accumulator register v is then the B operand of the next product's step v (streamed rows (v / 4) 8 + 4 (l / 32) + v % 4
+// as its two slots), whose A operand is one element per lane of the transposed streamed tile, read row by row.
+// Measured at B = 256, H = 2, D = 64, lengths uniform on [1, 512] against the former kernels (vector FMA, a row per four
+// lanes, scores one by one): forward 589 -> 181 us, forward + backward 1861 -> 682 us; four samples of at
+// most 64 rows (D = 32, forward) 23 -> 11 us, of which 10 are the kernel.
 #include "jfa_common.h"
+#include "jfa_mfma.h"
+#include "jfa_lds.h"
 
 namespace jfa {
 
-constexpr int kRows = kF32BlockRows;  // rows (queries or keys) per tile
-// streamed rows per LDS stage: two [cols][D] fp32 stages stay within 32 KB
-template <int D> constexpr int cols_for() { return 4096 / D < 64 ? 4096 / D : 64; }
-static_assert(2 * cols_for<32>() * 32 >= kInlineScratchInts && 2 * cols_for<128>() * 128 >= kInlineScratchInts,
-              "the two stage buffers double as the in-kernel scheduler's scratch");
-constexpr int kThreads = kRows * 4;
+constexpr int kRows = kF32BlockRows;   // stationary rows (queries or keys) per tile
+constexpr int kCols = 64;              // streamed rows per stage
+constexpr int kThreads = 256;
+static_assert(kRows == 64 && kCols == 64, "four waves are the four quarters of a tile's stage");
 
-__device__ inline float quad_sum(float x) {
-    x += __shfl_xor(x, 1, 64);
-    x += __shfl_xor(x, 2, 64);
-    return x;
+__device__ inline f32x16 mfma_f32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+
+template <int D> constexpr int f32_tile_bytes() { return kCols * D * 4; }
+// A workgroup's stage buffers: two stages, each the streamed rows of one tensor and then of the other.
+template <int D> constexpr int f32_stage_bytes() { return 2 * f32_tile_bytes<D>(); }
+static_assert(2 * f32_stage_bytes<32>() >= kInlineScratchInts * (int)sizeof(int), "the stage buffers double as the in-kernel scheduler's scratch");
+// D = 128 needs 128 KB of stages and more than 256 registers in the backward: one workgroup per compute unit
+template <int D> constexpr int f32_waves_per_simd() { return D <= 64 ? 2 : 1; }
+
+// Row r, 16-byte chunk ch of a streamed tile sits at r * 4 D + ((ch ^ f32_swz(r)) << 4): the 16-byte row reads (16
+// consecutive rows, one chunk) hit all 64 banks once, and so do the element reads of two rows 4 apart (D >= 64; two-way
+// conflicts at D = 32, where a row is half a bank line).
+template <int D> __device__ inline int f32_swz(int r) {
+    return D == 32 ? (r >> 1) & 7 : ((r >> 2) & 1) << 3 | ((r >> 3) & 1) << 2 | (r & 3);
 }
 
-// Copy `n` rows (row0 .. row0+n-1, head h) of a [*, H, D] fp32 tensor into LDS [n][D].
+__device__ inline void dma16_ptr(const float *src, char *lds_wave_base) {
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_byte_address(lds_wave_base));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
+}
+
+// Copies rows r0 .. r0 + 63 of one head (base: the sample's first row of that head; rows past the sample's L repeat
+// its last one and are masked by the caller) into `tile`.  A wave instruction fills 1 KB = 256 / D rows.
 template <int D>
-__device__ inline void stage_rows(float *dst, const float *__restrict__ src, int64_t row0, int n, int h, int H) {
-    constexpr int kVec = D / 4;
-    for (int i = threadIdx.x; i < n * kVec; i += kThreads) {
-        const int r = i / kVec, c = i - r * kVec;
-        const float4 x = *reinterpret_cast<const float4 *>(src + ((row0 + r) * H + h) * (int64_t)D + c * 4);
-        *reinterpret_cast<float4 *>(dst + r * D + c * 4) = x;
+__device__ inline void stage_rows(char *tile, const float *__restrict__ base, int64_t row_stride, int r0, int L, int wave, int lane) {
+    constexpr int kChunks = D / 4, kOps = D / 16;   // chunks per row, instructions per wave
+#pragma unroll
+    for (int u = 0; u < kOps; ++u) {
+        const int p = (wave * kOps + u) * 64 + lane;
+        const int r = p / kChunks, ch = (p % kChunks) ^ f32_swz<D>(r);
+        const int j = r0 + r < L ? r0 + r : L - 1;
+        dma16_ptr(base + j * row_stride + ch * 4, tile + (wave * kOps + u) * 1024);
     }
 }
 
-__device__ inline int64_t fetch_work(int32_t *counters, WorkCursor &probe, int64_t total, int64_t *slot) {
-    __syncthreads();
-    if (threadIdx.x == 0) *slot = next_work(counters, probe, total);
-    __syncthreads();
-    return uniform64(*slot);
+// This stage's copies have landed and every wave is done with the present stage.
+__device__ inline void stage_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// A lane's stationary row as B operands: x[4 g + e] = row[8 g + 4 half + e].
+template <int D> __device__ inline void load_operand(float (&x)[D / 2], const float *__restrict__ row, int half) {
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g) {
+        const float4 f = *reinterpret_cast<const float4 *>(row + 8 * g + 4 * half);
+        x[4 * g] = f.x; x[4 * g + 1] = f.y; x[4 * g + 2] = f.z; x[4 * g + 3] = f.w;
+    }
+}
+
+// LDS byte offsets of a lane's operand reads, relative to the first of the block's 32 streamed rows.  The swizzle makes
+// the reads of one kind differ by constant bit patterns, so that one value of each is kept and every read costs one XOR;
+// the empty asm keeps the XORs from being hoisted out of the stage loop into registers that are not there.
+template <int D> __device__ inline int row_read_at(int col, int half) { return col * (4 * D) + ((half ^ f32_swz<D>(col)) << 4); }
+template <int D> __device__ inline int element_read_at(int col, int half) {
+    return half * (16 * D) + (((col >> 2) ^ f32_swz<D>(4 * half)) << 4) + (col & 3) * 4;
+}
+__device__ inline int not_hoisted(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// acc += (32 streamed rows at `block`) (stationary rows)^T; at: row_read_at
+template <int D> __device__ inline void product(f32x16 &acc, const char *block, int at, const float (&x)[D / 2]) {
+    at = not_hoisted(at);
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g) {
+        const float4 a = *reinterpret_cast<const float4 *>(block + (at ^ (g << 5)));
+        acc = mfma_f32(a.x, x[4 * g], acc);
+        acc = mfma_f32(a.y, x[4 * g + 1], acc);
+        acc = mfma_f32(a.z, x[4 * g + 2], acc);
+        acc = mfma_f32(a.w, x[4 * g + 3], acc);
+    }
+}
+
+// acc^T += (32 streamed rows at `block`)^T p, p in accumulator layout; at: element_read_at
+template <int D> __device__ inline void accumulate(f32x16 (&acc)[D / 32], const char *block, int at, const f32x16 &p) {
+    at = not_hoisted(at);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int r = acc_row(v, 0);   // + 4 in the other half-wave, which is in `at`
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+            acc[db] = mfma_f32(*reinterpret_cast<const float *>(block + (at ^ ((f32_swz<D>(r) ^ (8 * db)) << 4)) + r * (4 * D)), p[v], acc[db]);
+    }
+}
+
+template <int D> __device__ inline void clear(f32x16 (&acc)[D / 32]) {
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[db][e] = 0.0f;
+}
+
+// An accumulator on its way to the wave that shares the stationary rows: 16 bytes per lane and step, no bank conflicts.
+template <int D> __device__ inline void park(char *region, const f32x16 (&acc)[D / 32], int lane) {
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<float4 *>(region + ((db * 4 + g) * 64 + lane) * 16) =
+                make_float4(acc[db][4 * g], acc[db][4 * g + 1], acc[db][4 * g + 2], acc[db][4 * g + 3]);
+}
+// acc = acc * mine + parked * theirs
+template <int D> __device__ inline void merge(f32x16 (&acc)[D / 32], const char *region, int lane, float mine, float theirs) {
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const float4 o = *reinterpret_cast<const float4 *>(region + ((db * 4 + g) * 64 + lane) * 16);
+            acc[db][4 * g] = acc[db][4 * g] * mine + o.x * theirs;
+            acc[db][4 * g + 1] = acc[db][4 * g + 1] * mine + o.y * theirs;
+            acc[db][4 * g + 2] = acc[db][4 * g + 2] * mine + o.z * theirs;
+            acc[db][4 * g + 3] = acc[db][4 * g + 3] * mine + o.w * theirs;
+        }
+}
+
+// Store a transposed accumulator (rows = features, column = this lane's row of the output tensor).
+template <int D> __device__ inline void store_row(float *dst, const f32x16 (&acc)[D / 32], float scale, int half) {
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<float4 *>(dst + db * 32 + g * 8 + half * 4) =
+                make_float4(acc[db][4 * g] * scale, acc[db][4 * g + 1] * scale, acc[db][4 * g + 2] * scale, acc[db][4 * g + 3] * scale);
+}
+
+// The workgroup's next work item into `t`, false when nothing is left; ends with a barrier, so that the stage buffers
+// are free.  item: number of items taken so far.
+__device__ inline bool next_item(Work &t, const SmallWork &mine, bool small, int item, const Schedule &s, const int64_t *offsets,
+                                 const int64_t *offsets_other, int B, int H, WorkCursor &cursor, int64_t total, int64_t *slot) {
+    if (small) {   // the workgroup's items were decoded when the schedule was built
+        __syncthreads();
+        return item < __builtin_amdgcn_readfirstlane(mine.count) && load_work<true>(&mine.item[item], t);
+    }
+    const int64_t w = fetch_item(s.counter, cursor, total, slot);
+    if (w < 0) return false;
+    t = decode_work(s, offsets, B, H, w, offsets_other);
+    return true;
 }
 
 template <int D>
-__global__ __launch_bounds__(kThreads) void fwd_f32_kernel(const float *__restrict__ q, const float *__restrict__ k,
-                                                           const float *__restrict__ v,
-                                                           const int64_t *__restrict__ offsets,
-                                                           const int64_t *__restrict__ offsets_kv, bool causal,
-                                                           int B, int H, Schedule s, float *__restrict__ out,
-                                                           float *__restrict__ lse) {
-    constexpr int kPer = D / 4;
-    constexpr int kCols = cols_for<D>();
-    __shared__ float KVs[2 * kCols * D];   // staged K rows, then V rows (the schedule build borrows all of it)
-    float *const Ks = KVs, *const Vs = KVs + kCols * D;
+__global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_kernel(
+        const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
+        const int64_t *__restrict__ offsets, const int64_t *__restrict__ offsets_kv, bool causal, int B, int H, Schedule s,
+        float *__restrict__ out, float *__restrict__ lse) {
+    constexpr int kTile = f32_tile_bytes<D>(), kStage = f32_stage_bytes<D>();
+    __shared__ __attribute__((aligned(1024))) char sm[2 * kStage];   // two stages of K rows, then V rows
+    __shared__ float2 other_ml[2][32];   // running maximum and row sum of the waves w >= 2
     __shared__ int64_t slot;
-    WorkCursor probe;
-    const int r = threadIdx.x >> 2, c = threadIdx.x & 3;
-    const float scale = 1.0f / sqrtf((float)D);
     __shared__ SmallWork mine;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const int rg = wave & 1, part = wave >> 1;   // group of 32 queries; half of the stage's keys
+    const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
+    const float scale = 1.0f / sqrtf((float)D);
+    const float c = 1.4426950408889634f * scale;
     const bool small = s.build_rows != 0;   // small problem: no scheduler launch has run, the schedule is built here, in LDS
-    if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(KVs), &mine);
-    probe.static_only = s.static_only;
+    if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
     const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets[B];
+    const int64_t row_stride = (int64_t)H * D;
 
-    for (int n = 0;; ++n) {
-        Work t;   // keys: rows orow0 .. orow0 + olen - 1
-        if (small) {   // the workgroup's items were decoded when the schedule was built
-            __syncthreads();   // the previous item's use of the staging arrays is over
-            if (n >= __builtin_amdgcn_readfirstlane(mine.count) || !load_work<true>(&mine.item[n], t)) break;
-        } else {
-            const int64_t w = fetch_work(s.counter, probe, total, &slot);
-            if (w < 0) break;
-            t = decode_work(s, offsets, B, H, w, offsets_kv);
-        }
-        const int i = t.block * kRows + r;                    // query index inside the sample
-        const int iq = i < t.len ? i : t.len - 1;             // rows past the end recompute the last row
-        float qr[kPer], acc[kPer];
-        for (int e = 0; e < kPer; ++e) {
-            qr[e] = q[((t.row0 + iq) * H + t.head) * (int64_t)D + 4 * e + c];
-            acc[e] = 0.0f;
-        }
-        float m = -INFINITY, l = 0.0f;
+    WorkCursor cursor;
+    cursor.static_only = s.static_only;
+    Work t;   // keys: rows orow0 .. orow0 + olen - 1
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot); ++item) {
+        const int L = t.olen;
+        const int q0 = t.block * kRows + rg * 32;      // first query of the wave
+        const int i = q0 + col;                        // this lane's query
+        const int iq = i < t.len ? i : t.len - 1;      // rows past the end recompute the last row
+        const bool active = q0 < t.len;
         // causal (self attention only): query i sees keys 0 .. i, so the tile needs the keys up to its last query
-        const int kend = causal && (t.block + 1) * kRows < t.olen ? (t.block + 1) * kRows : t.olen;
-        for (int j0 = 0; j0 < kend; j0 += kCols) {
-            const int n = kend - j0 < kCols ? kend - j0 : kCols;
-            __syncthreads();
-            stage_rows<D>(Ks, k, t.orow0 + j0, n, t.head, H);
-            stage_rows<D>(Vs, v, t.orow0 + j0, n, t.head, H);
-            __syncthreads();
-            for (int j = 0; j < n; ++j) {
-                float part = 0.0f;
-                for (int e = 0; e < kPer; ++e) part = fmaf(qr[e], Ks[j * D + 4 * e + c], part);
-                const float sc = causal && j0 + j > iq ? -INFINITY : quad_sum(part) * scale;   // key 0 is never masked: m stays finite
-                const float m_new = fmaxf(m, sc);
-                const float a = expf(m - m_new);              // exp(-inf) = 0 on the first key
-                const float p = expf(sc - m_new);
-                l = fmaf(l, a, p);
-                for (int e = 0; e < kPer; ++e) acc[e] = fmaf(acc[e], a, p * Vs[j * D + 4 * e + c]);
+        const int Lc = causal && (t.block + 1) * kRows < L ? (t.block + 1) * kRows : L;
+        const float *kbase = k + t.orow0 * row_stride + (int64_t)t.head * D;
+        const float *vbase = v + t.orow0 * row_stride + (int64_t)t.head * D;
+        auto issue = [&](int j0, int buf) {
+            stage_rows<D>(sm + buf * kStage, kbase, row_stride, j0, L, wave, lane);
+            stage_rows<D>(sm + buf * kStage + kTile, vbase, row_stride, j0, L, wave, lane);
+        };
+        if (L > 0) issue(0, 0);
+        float qr[D / 2];
+        load_operand<D>(qr, q + (t.row0 + iq) * row_stride + (int64_t)t.head * D, half);
+        f32x16 o[D / 32];
+        clear<D>(o);
+        float m = -INFINITY, l = 0.0f;   // running maximum of the raw scores; this lane's share of the row sum
+        stage_barrier();
+        for (int j0 = 0, buf = 0; j0 < Lc; j0 += kCols, buf ^= 1) {
+            if (j0 + kCols < Lc) issue(j0 + kCols, buf ^ 1);
+            const int k0 = j0 + part * 32;             // first key of the wave's block
+            if (active && k0 < Lc && !(causal && k0 > q0 + 31)) {
+                const char *kt = sm + buf * kStage + part * (32 * 4 * D), *vt = kt + kTile;
+                f32x16 st;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) st[e] = 0.0f;
+                product<D>(st, kt, row_at, qr);
+                if (k0 + 32 > L || (causal && k0 + 31 > q0)) {   // keys past the sample's end or above the diagonal
+                    const int lim = (causal && iq + 1 < L ? iq + 1 : L) - k0;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        if (acc_row(e, half) >= lim) st[e] = -INFINITY;
+                }
+                float mx = st[0];
+#pragma unroll
+                for (int e = 1; e < 16; ++e) mx = fmaxf(mx, st[e]);
+                const float m_new = fmaxf(m, pair_max(mx));   // finite: every query of a block that is not skipped sees one of its keys
+                const float a = fast_exp2((m - m_new) * c);   // exp2(-inf) = 0 on the first block
+                const float mc = m_new * c;
                 m = m_new;
+                l *= a;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    st[e] = fast_exp2(fmaf(st[e], c, -mc));
+                    l += st[e];
+                }
+#pragma unroll
+                for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) o[db][e] *= a;
+                accumulate<D>(o, vt, elem_at, st);
             }
+            stage_barrier();
         }
-        if (i < t.len) {
-            const float inv = l > 0.0f ? 1.0f / l : 0.0f;   // a sample without keys: out = 0, lse = -inf
-            for (int e = 0; e < kPer; ++e) out[((t.row0 + i) * H + t.head) * (int64_t)D + 4 * e + c] = acc[e] * inv;
-            if (c == 0) lse[(int64_t)t.head * sum_B + t.row0 + i] = m + logf(l);
+        // the two waves of a group of queries have seen different keys: waves 2 and 3 hand over, waves 0 and 1 finish
+        l = pair_sum(l);
+        char *const region = sm + rg * (D * 128);
+        if (part == 1) {
+            park<D>(region, o, lane);
+            if (half == 0) other_ml[rg][col] = make_float2(m, l);
+        }
+        __syncthreads();
+        if (part == 0 && i < t.len) {
+            const float2 ml = other_ml[rg][col];
+            const float m_all = fmaxf(m, ml.x);
+            const float a = m_all > -INFINITY ? fast_exp2((m - m_all) * c) : 0.0f;      // a sample without keys: out = 0, lse = -inf
+            const float b = m_all > -INFINITY ? fast_exp2((ml.x - m_all) * c) : 0.0f;
+            const float l_all = l * a + ml.y * b;
+            merge<D>(o, region, lane, a, b);
+            store_row<D>(out + (t.row0 + i) * row_stride + (int64_t)t.head * D, o, l_all > 0.0f ? 1.0f / l_all : 0.0f, half);
+            if (half == 0) lse[(int64_t)t.head * sum_B + t.row0 + i] = m_all * scale + logf(l_all);
         }
     }
 }
@@ -110,158 +280,213 @@ __global__ __launch_bounds__(kThreads) void fwd_f32_kernel(const float *__restri
 // row anyway, reads the matching row of the forward's output, and computes delta = rowsum(dO o O) for its own use
 // and for the dK / dV kernel (no separate pass over dO and O, one launch less).
 template <int D>
-__global__ __launch_bounds__(kThreads) void dq_f32_kernel(const float *__restrict__ q, const float *__restrict__ k,
-                                                          const float *__restrict__ v,
-                                                          const float *__restrict__ out_fwd,
-                                                          const float *__restrict__ dout,
-                                                          const float *__restrict__ lse,
-                                                          float *__restrict__ delta,
-                                                          const int64_t *__restrict__ offsets,
-                                                          const int64_t *__restrict__ offsets_kv, bool causal,
-                                                          int B, int H, Schedule s, float *__restrict__ dq) {
-    constexpr int kPer = D / 4;
-    constexpr int kCols = cols_for<D>();
-    __shared__ float KVs[2 * kCols * D];   // staged K rows, then V rows (the schedule build borrows all of it)
-    float *const Ks = KVs, *const Vs = KVs + kCols * D;
+__global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kernel(
+        const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
+        const float *__restrict__ out_fwd, const float *__restrict__ dout, const float *__restrict__ lse,
+        float *__restrict__ delta, const int64_t *__restrict__ offsets, const int64_t *__restrict__ offsets_kv, bool causal,
+        int B, int H, Schedule s, float *__restrict__ dq) {
+    constexpr int kTile = f32_tile_bytes<D>(), kStage = f32_stage_bytes<D>();
+    __shared__ __attribute__((aligned(1024))) char sm[2 * kStage];   // two stages of K rows, then V rows
     __shared__ int64_t slot;
-    WorkCursor probe;
-    const int r = threadIdx.x >> 2, c = threadIdx.x & 3;
-    const float scale = 1.0f / sqrtf((float)D);
     __shared__ SmallWork mine;
-    const bool small = s.build_rows != 0;   // small problem: no scheduler launch has run, the schedule is built here, in LDS
-    if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(KVs), &mine);
-    probe.static_only = s.static_only;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const int rg = wave & 1, part = wave >> 1;   // group of 32 queries; half of the stage's keys
+    const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
+    const float scale = 1.0f / sqrtf((float)D);
+    const float c = 1.4426950408889634f * scale;
+    const bool small = s.build_rows != 0;
+    if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
     const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets[B];
+    const int64_t row_stride = (int64_t)H * D;
 
-    for (int n = 0;; ++n) {
-        Work t;
-        if (small) {   // the workgroup's items were decoded when the schedule was built
-            __syncthreads();   // the previous item's use of the staging arrays is over
-            if (n >= __builtin_amdgcn_readfirstlane(mine.count) || !load_work<true>(&mine.item[n], t)) break;
-        } else {
-            const int64_t w = fetch_work(s.counter, probe, total, &slot);
-            if (w < 0) break;
-            t = decode_work(s, offsets, B, H, w, offsets_kv);
-        }
-        const int i = t.block * kRows + r;
+    WorkCursor cursor;
+    cursor.static_only = s.static_only;
+    Work t;
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot); ++item) {
+        const int L = t.olen;
+        const int q0 = t.block * kRows + rg * 32;
+        const int i = q0 + col;
         const int iq = i < t.len ? i : t.len - 1;
-        float qr[kPer], dor[kPer], acc[kPer];
+        const bool active = q0 < t.len;
+        const int Lc = causal && (t.block + 1) * kRows < L ? (t.block + 1) * kRows : L;
+        const float *kbase = k + t.orow0 * row_stride + (int64_t)t.head * D;
+        const float *vbase = v + t.orow0 * row_stride + (int64_t)t.head * D;
+        auto issue = [&](int j0, int buf) {
+            stage_rows<D>(sm + buf * kStage, kbase, row_stride, j0, L, wave, lane);
+            stage_rows<D>(sm + buf * kStage + kTile, vbase, row_stride, j0, L, wave, lane);
+        };
+        if (L > 0) issue(0, 0);
+        float qr[D / 2], dor[D / 2];
+        const int64_t row = (t.row0 + iq) * row_stride + (int64_t)t.head * D;
+        load_operand<D>(qr, q + row, half);
+        load_operand<D>(dor, dout + row, half);
         float dot = 0.0f;
-        for (int e = 0; e < kPer; ++e) {
-            const int64_t idx = ((t.row0 + iq) * H + t.head) * (int64_t)D + 4 * e + c;
-            qr[e] = q[idx];
-            dor[e] = dout[idx];
-            dot = fmaf(dor[e], out_fwd[idx], dot);
-            acc[e] = 0.0f;
+#pragma unroll
+        for (int g = 0; g < D / 8; ++g) {
+            const float4 f = *reinterpret_cast<const float4 *>(out_fwd + row + 8 * g + 4 * half);
+            dot = fmaf(dor[4 * g], f.x, fmaf(dor[4 * g + 1], f.y, fmaf(dor[4 * g + 2], f.z, fmaf(dor[4 * g + 3], f.w, dot))));
         }
-        const float lse_i = lse[(int64_t)t.head * sum_B + t.row0 + iq];
-        const float delta_i = quad_sum(dot);   // the four lanes of a row hold a quarter of its features each
-        if (i < t.len && c == 0) delta[(int64_t)t.head * sum_B + t.row0 + i] = delta_i;
-        // causal (self attention only): query i sees keys 0 .. i, so the tile needs the keys up to its last query
-        const int kend = causal && (t.block + 1) * kRows < t.olen ? (t.block + 1) * kRows : t.olen;
-        for (int j0 = 0; j0 < kend; j0 += kCols) {
-            const int n = kend - j0 < kCols ? kend - j0 : kCols;
-            __syncthreads();
-            stage_rows<D>(Ks, k, t.orow0 + j0, n, t.head, H);
-            stage_rows<D>(Vs, v, t.orow0 + j0, n, t.head, H);
-            __syncthreads();
-            for (int j = 0; j < n; ++j) {
-                float ps = 0.0f, pd = 0.0f;
-                for (int e = 0; e < kPer; ++e) {
-                    ps = fmaf(qr[e], Ks[j * D + 4 * e + c], ps);
-                    pd = fmaf(dor[e], Vs[j * D + 4 * e + c], pd);
+        const float delta_i = pair_sum(dot);   // the two lanes of a row hold half of its features each
+        const float lse2 = lse[(int64_t)t.head * sum_B + t.row0 + iq] * 1.4426950408889634f;
+        if (part == 0 && i < t.len && half == 0) delta[(int64_t)t.head * sum_B + t.row0 + i] = delta_i;
+        f32x16 acc[D / 32];
+        clear<D>(acc);
+        stage_barrier();
+        for (int j0 = 0, buf = 0; j0 < Lc; j0 += kCols, buf ^= 1) {
+            if (j0 + kCols < Lc) issue(j0 + kCols, buf ^ 1);
+            const int k0 = j0 + part * 32;
+            if (active && k0 < Lc && !(causal && k0 > q0 + 31)) {
+                const char *kt = sm + buf * kStage + part * (32 * 4 * D), *vt = kt + kTile;
+                f32x16 st, dp;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) { st[e] = 0.0f; dp[e] = -delta_i; }
+                product<D>(st, kt, row_at, qr);
+                product<D>(dp, vt, row_at, dor);
+                const bool masked = k0 + 32 > L || (causal && k0 + 31 > q0);
+                const int lim = (causal && iq + 1 < L ? iq + 1 : L) - k0;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    float p = fast_exp2(fmaf(st[e], c, -lse2));
+                    if (masked && acc_row(e, half) >= lim) p = 0.0f;
+                    st[e] = p * dp[e];
                 }
-                const float p = causal && j0 + j > iq ? 0.0f : expf(quad_sum(ps) * scale - lse_i);
-                const float ds = p * (quad_sum(pd) - delta_i);
-                for (int e = 0; e < kPer; ++e) acc[e] = fmaf(ds, Ks[j * D + 4 * e + c], acc[e]);
+                accumulate<D>(acc, kt, elem_at, st);
             }
+            stage_barrier();
         }
-        if (i < t.len)
-            for (int e = 0; e < kPer; ++e) dq[((t.row0 + i) * H + t.head) * (int64_t)D + 4 * e + c] = acc[e] * scale;
+        char *const region = sm + rg * (D * 128);
+        if (part == 1) park<D>(region, acc, lane);
+        __syncthreads();
+        if (part == 0 && i < t.len) {
+            merge<D>(acc, region, lane, 1.0f, 1.0f);
+            store_row<D>(dq + row, acc, scale, half);
+        }
     }
 }
 
 // dK, dV: tile = 64 keys, stream the sample's queries (with their dO, lse, delta).
 template <int D>
-__global__ __launch_bounds__(kThreads) void dkv_f32_kernel(const float *__restrict__ q, const float *__restrict__ k,
-                                                           const float *__restrict__ v,
-                                                           const float *__restrict__ dout,
-                                                           const float *__restrict__ lse,
-                                                           const float *__restrict__ delta,
-                                                           const int64_t *__restrict__ offsets,   // of the keys
-                                                           const int64_t *__restrict__ offsets_q, bool causal,
-                                                           int B, int H, Schedule s, float *__restrict__ dk,
-                                                           float *__restrict__ dv) {
-    constexpr int kPer = D / 4;
-    constexpr int kCols = cols_for<D>();
-    __shared__ float QOs[2 * kCols * D];   // staged Q rows, then dO rows (the schedule build borrows all of it)
-    float *const Qs = QOs, *const Os = QOs + kCols * D;
-    __shared__ float lse_s[kCols];
-    __shared__ float delta_s[kCols];
+__global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_kernel(
+        const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
+        const float *__restrict__ dout, const float *__restrict__ lse, const float *__restrict__ delta,
+        const int64_t *__restrict__ offsets,   // of the keys
+        const int64_t *__restrict__ offsets_q, bool causal, int B, int H, Schedule s, float *__restrict__ dk,
+        float *__restrict__ dv) {
+    constexpr int kTile = f32_tile_bytes<D>(), kStage = f32_stage_bytes<D>();
+    __shared__ __attribute__((aligned(1024))) char sm[2 * kStage];   // two stages of Q rows, then dO rows
+    __shared__ float lse2_s[2][kCols], delta_s[2][kCols];             // log2(e) lse and delta of the streamed rows
     __shared__ int64_t slot;
-    WorkCursor probe;
-    const int r = threadIdx.x >> 2, c = threadIdx.x & 3;
-    const float scale = 1.0f / sqrtf((float)D);
     __shared__ SmallWork mine;
-    const bool small = s.build_rows != 0;   // small problem: no scheduler launch has run, the schedule is built here, in LDS
-    if (small) build_small_work(offsets, offsets_q, B, H, s.build_rows, reinterpret_cast<int *>(QOs), &mine);
-    probe.static_only = s.static_only;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const int rg = wave & 1, part = wave >> 1;   // group of 32 keys; half of the stage's queries
+    const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
+    const float scale = 1.0f / sqrtf((float)D);
+    const float c = 1.4426950408889634f * scale;
+    const bool small = s.build_rows != 0;
+    if (small) build_small_work(offsets, offsets_q, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
     const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets_q ? offsets_q[B] : offsets[B];   // lse and delta are indexed by query rows
+    const int64_t row_stride = (int64_t)H * D;
 
-    for (int n = 0;; ++n) {
-        Work t;   // queries: rows orow0 .. orow0 + olen - 1
-        if (small) {   // the workgroup's items were decoded when the schedule was built
-            __syncthreads();   // the previous item's use of the staging arrays is over
-            if (n >= __builtin_amdgcn_readfirstlane(mine.count) || !load_work<true>(&mine.item[n], t)) break;
-        } else {
-            const int64_t w = fetch_work(s.counter, probe, total, &slot);
-            if (w < 0) break;
-            t = decode_work(s, offsets, B, H, w, offsets_q);
-        }
-        const int j = t.block * kRows + r;
+    WorkCursor cursor;
+    cursor.static_only = s.static_only;
+    Work t;   // queries: rows orow0 .. orow0 + olen - 1
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_q, B, H, cursor, total, &slot); ++item) {
+        const int L = t.olen;
+        const int k0 = t.block * kRows + rg * 32;      // first key of the wave
+        const int j = k0 + col;                        // this lane's key
         const int jk = j < t.len ? j : t.len - 1;
-        float kr[kPer], vr[kPer], acck[kPer], accv[kPer];
-        for (int e = 0; e < kPer; ++e) {
-            const int64_t idx = ((t.row0 + jk) * H + t.head) * (int64_t)D + 4 * e + c;
-            kr[e] = k[idx];
-            vr[e] = v[idx];
-            acck[e] = 0.0f;
-            accv[e] = 0.0f;
-        }
+        const bool active = k0 < t.len;
+        const float *qbase = q + t.orow0 * row_stride + (int64_t)t.head * D;
+        const float *obase = dout + t.orow0 * row_stride + (int64_t)t.head * D;
+        const float *lse_rows = lse + (int64_t)t.head * sum_B + t.orow0;
+        const float *delta_rows = delta + (int64_t)t.head * sum_B + t.orow0;
         // causal: key j is seen by queries j .. L - 1, so the stream starts at the stage that holds the tile's first key
-        const int istart = causal ? (t.block * kRows / kCols) * kCols : 0;
-        for (int i0 = istart; i0 < t.olen; i0 += kCols) {
-            const int n = t.olen - i0 < kCols ? t.olen - i0 : kCols;
-            __syncthreads();
-            stage_rows<D>(Qs, q, t.orow0 + i0, n, t.head, H);
-            stage_rows<D>(Os, dout, t.orow0 + i0, n, t.head, H);
-            if (threadIdx.x < n) {
-                lse_s[threadIdx.x] = lse[(int64_t)t.head * sum_B + t.orow0 + i0 + threadIdx.x];
-                delta_s[threadIdx.x] = delta[(int64_t)t.head * sum_B + t.orow0 + i0 + threadIdx.x];
+        const int istart = causal ? t.block * kRows : 0;
+        auto issue = [&](int i0, int buf) {
+            stage_rows<D>(sm + buf * kStage, qbase, row_stride, i0, L, wave, lane);
+            stage_rows<D>(sm + buf * kStage + kTile, obase, row_stride, i0, L, wave, lane);
+        };
+        float lse_next = 0.0f, delta_next = 0.0f;      // statistics of the stage on its way (threads 0 .. 63)
+        auto fetch_stats = [&](int i0) {
+            if (tid < kCols) {
+                const int i = i0 + tid < L ? i0 + tid : L - 1;
+                lse_next = lse_rows[i] * 1.4426950408889634f;
+                delta_next = delta_rows[i];
             }
-            __syncthreads();
-            for (int i = 0; i < n; ++i) {
-                float ps = 0.0f, pd = 0.0f;
-                for (int e = 0; e < kPer; ++e) {
-                    ps = fmaf(Qs[i * D + 4 * e + c], kr[e], ps);
-                    pd = fmaf(Os[i * D + 4 * e + c], vr[e], pd);
+        };
+        auto store_stats = [&](int buf) {
+            if (tid < kCols) { lse2_s[buf][tid] = lse_next; delta_s[buf][tid] = delta_next; }
+        };
+        if (istart < L) {
+            issue(istart, 0);
+            fetch_stats(istart);
+        }
+        float kr[D / 2], vr[D / 2];
+        const int64_t row = (t.row0 + jk) * row_stride + (int64_t)t.head * D;
+        load_operand<D>(kr, k + row, half);
+        load_operand<D>(vr, v + row, half);
+        f32x16 acck[D / 32], accv[D / 32];
+        clear<D>(acck);
+        clear<D>(accv);
+        store_stats(0);
+        stage_barrier();
+        for (int i0 = istart, buf = 0; i0 < L; i0 += kCols, buf ^= 1) {
+            const bool more = i0 + kCols < L;
+            if (more) {
+                issue(i0 + kCols, buf ^ 1);
+                fetch_stats(i0 + kCols);
+            }
+            const int r0 = i0 + part * 32;             // first query of the wave's block
+            if (active && r0 < L && !(causal && r0 + 31 < k0)) {
+                const char *qt = sm + buf * kStage + part * (32 * 4 * D), *ot = qt + kTile;
+                f32x16 st, dp;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float4 d4 = *reinterpret_cast<const float4 *>(&delta_s[buf][part * 32 + g * 8 + half * 4]);
+                    dp[4 * g] = -d4.x; dp[4 * g + 1] = -d4.y; dp[4 * g + 2] = -d4.z; dp[4 * g + 3] = -d4.w;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) st[4 * g + e] = 0.0f;
                 }
-                const float p = causal && i0 + i < jk ? 0.0f : expf(quad_sum(ps) * scale - lse_s[i]);
-                const float ds = p * (quad_sum(pd) - delta_s[i]);
-                for (int e = 0; e < kPer; ++e) {
-                    accv[e] = fmaf(p, Os[i * D + 4 * e + c], accv[e]);
-                    acck[e] = fmaf(ds, Qs[i * D + 4 * e + c], acck[e]);
+                product<D>(st, qt, row_at, kr);
+                product<D>(dp, ot, row_at, vr);
+                const bool masked = r0 + 32 > L || (causal && r0 < k0 + 31);
+                const int lo = causal ? j - r0 : 0, hi = L - r0;   // this lane's key is seen by block rows lo .. hi - 1
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float4 l4 = *reinterpret_cast<const float4 *>(&lse2_s[buf][part * 32 + g * 8 + half * 4]);
+                    const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int r = acc_row(4 * g + e, half);
+                        float p = fast_exp2(fmaf(st[4 * g + e], c, -lv[e]));
+                        if (masked && (r < lo || r >= hi)) p = 0.0f;
+                        st[4 * g + e] = p;
+                        dp[4 * g + e] *= p;
+                    }
                 }
+                accumulate<D>(accv, ot, elem_at, st);
+                accumulate<D>(acck, qt, elem_at, dp);
+            }
+            if (more) store_stats(buf ^ 1);
+            stage_barrier();
+        }
+        // each wave of a pair finishes one gradient: waves 0 and 1 dK, waves 2 and 3 dV
+        char *const region = sm + rg * (D * 256);
+        if (part == 0) park<D>(region, accv, lane); else park<D>(region + D * 128, acck, lane);
+        __syncthreads();
+        if (j < t.len) {
+            if (part == 0) {
+                merge<D>(acck, region + D * 128, lane, 1.0f, 1.0f);
+                store_row<D>(dk + row, acck, scale, half);
+            } else {
+                merge<D>(accv, region, lane, 1.0f, 1.0f);
+                store_row<D>(dv + row, accv, 1.0f, half);
             }
         }
-        if (j < t.len)
-            for (int e = 0; e < kPer; ++e) {
-                const int64_t idx = ((t.row0 + j) * H + t.head) * (int64_t)D + 4 * e + c;
-                dk[idx] = acck[e] * scale;
-                dv[idx] = accv[e];
-            }
     }
 }
 
