@@ -491,7 +491,7 @@ hipError_t launch_bwd_f32(const float *q, const float *k, const float *v, const 
                           hipStream_t stream);
 // (the dQ kernel of every path runs first and computes delta[h, row] = sum_d dout * out for the kernels after it)
 
-// bf16 attention, register-staged kernels (any supported D, short samples)
+// bf16 attention, register-staged kernels (D = 128, short samples; backward: any supported D)
 constexpr int kFwdBlockRows = 128;
 constexpr int kBwdBlockRows = 128;
 // In all bf16 launchers `offsets` belongs to the rows the schedule `s` was built over (queries for the forward and
@@ -508,6 +508,10 @@ hipError_t launch_dkv_bf16(const void *q, const void *k, const void *v, const vo
 hipError_t launch_dq_bf16(const void *q, const void *k, const void *v, const void *out, const void *dout, const float *lse,
                           float *delta, const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H,
                           int D, Schedule s, void *dq, int cus, hipStream_t stream);
+
+// bf16 forward for D = 32 and 64 at every length (blocks of kFwdBlockRows rows)
+hipError_t launch_fwd_narrow(const void *q, const void *k, const void *v, const int64_t *offsets, const int64_t *offsets_kv, bool causal,
+                             int B, int H, int D, Schedule s, void *out, float *lse, int cus, hipStream_t stream);
 
 // bf16 attention, direct-to-LDS kernels (D = 128, long samples; work items are blocks of kDmaBlockRows rows)
 constexpr int kDmaBlockRows = 256;

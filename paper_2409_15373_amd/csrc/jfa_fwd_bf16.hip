@@ -1,4 +1,4 @@
-// Jagged flash attention forward, bf16 on gfx950 matrix cores (paper Section 2.1).
+// Jagged flash attention forward, bf16 on gfx950 matrix cores, D = 128, short samples (paper Section 2.1).
 //
 // Work item = (sample, head, block of 128 queries), pulled by persistent workgroups from the
 // offsets-driven schedule.  A workgroup is four waves; each wave owns 32 queries and keeps, in
@@ -285,22 +285,14 @@ __global__ __launch_bounds__(kFwdThreads, 2) void fwd_bf16_kernel(const __bf16 *
 hipError_t launch_fwd_bf16(const void *q, const void *k, const void *v, const int64_t *offsets,
                            const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, void *out, float *lse,
                            int cus, hipStream_t stream) {
-    if (causal && offsets_kv) return hipErrorInvalidValue;
-#define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                        \
-    hipLaunchKernelGGL((fwd_bf16_kernel<DD, CROSS, CAUSAL>), dim3(persistent_grid<fwd_bf16_kernel<DD, CROSS, CAUSAL>>(kFwdThreads, cus)), \
+    if (D != 128 || (causal && offsets_kv)) return hipErrorInvalidValue;
+#define JFA_LAUNCH(CROSS, CAUSAL)                                                                            \
+    hipLaunchKernelGGL((fwd_bf16_kernel<128, CROSS, CAUSAL>), dim3(persistent_grid<fwd_bf16_kernel<128, CROSS, CAUSAL>>(kFwdThreads, cus)), \
                        dim3(kFwdThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, offsets, offsets_kv, B, H, s, \
                        (__bf16 *)out, lse)
-#define JFA_CASE(DD)                                                                                         \
-    case DD:                                                                                                 \
-        if (offsets_kv) JFA_LAUNCH(DD, true, false);                                                         \
-        else if (causal) JFA_LAUNCH(DD, false, true);                                                        \
-        else JFA_LAUNCH(DD, false, false);                                                                   \
-        break;
-    switch (D) {
-        JFA_CASE(32) JFA_CASE(64) JFA_CASE(128)
-        default: return hipErrorInvalidValue;
-    }
-#undef JFA_CASE
+    if (offsets_kv) JFA_LAUNCH(true, false);
+    else if (causal) JFA_LAUNCH(false, true);
+    else JFA_LAUNCH(false, false);
 #undef JFA_LAUNCH
     return hipGetLastError();
 }

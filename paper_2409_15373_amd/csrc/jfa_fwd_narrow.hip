@@ -1,0 +1,230 @@
+// Jagged flash attention forward, bf16, head sizes 32 and 64 (paper Section 2.1).
+//
+// Same mathematics and operand layouts as fwd_bf16_kernel: work item = (sample, head, 128 queries), four waves of 32
+// queries, transposed score tile S^T = K Q^T (a lane owns one query), O^T += V^T P^T with V^T from the transposing read.
+// A score costs the same vector work at every head size and a half or a quarter of the matrix work of D = 128, and the two
+// hardly overlap on a SIMD (a stage of 64 keys takes a wave's SIMD 1070 clocks at D = 64, 720 at D = 32: about 44 per
+// matrix instruction and 3.8 per vector instruction), so vector instructions are what bounds these sizes, and on short
+// samples a tile's start-up:
+//   * exponentials are taken against a FIXED reference maximum per query (the maximum over the first 64 keys): a score is
+//     one multiply-add, one exponential and half of a conversion and of a row-sum step, with no running maximum.  A row sum
+//     above 2^62 (or not finite) at the end makes the workgroup redo the tile maximum first (never on scores of one scale);
+//   * stages go directly to LDS, one ahead, into unpadded swizzled buffers (jfa_narrow.h): no staging registers, no LDS
+//     stores, one barrier per stage;
+//   * three (D = 64) or four workgroups per compute unit, which are not in step, fill each other's start-up (one more of
+//     either spills: equal on long samples, 5 % slower on short ones); the next item is claimed while the first loads
+//     travel; outputs leave as whole rows; the claim and the stage are not copied over the kernel (15 KB of instructions;
+//     at 42 KB, with three buffers and a copy of the stage for each, a tile's start took half as long again).
+// H * D = 512, microseconds before -> now: 1024 samples of 1 to 1024 rows D = 64 1220 -> 1099, D = 32 1532 -> 1370;
+// 64 samples of 4096 rows D = 64 2507 -> 2198 (1000 TFLOP/s), D = 32 3403 -> 2950; 1024 of 512 rows D = 64 928 -> 825.
+#include "jfa_narrow.h"
+
+namespace jfa {
+
+// CROSS: keys and values are the rows of a second offsets array; CAUSAL: query i sees keys 0 .. i.  See fwd_bf16_kernel.
+template <int D, bool CROSS, bool CAUSAL>
+__global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel(
+    const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, const int64_t *__restrict__ offsets,
+    const int64_t *__restrict__ offsets_kv, int B, int H, Schedule s, __bf16 *__restrict__ out, float *__restrict__ lse) {
+    using N = Narrow<D>;
+    constexpr int kKSteps = D / 16, kDBlocks = D / 32;
+    __shared__ __attribute__((aligned(1024))) char st[kNwStages * N::kStage];   // buffer b: K at b * kStage, V behind it
+    __shared__ typename NarrowWalk<CROSS>::Shared walk_mem;
+    __shared__ int restart;   // set by a wave whose reference maximum went stale beyond repair
+    static_assert(sizeof(st) >= kInlineScratchInts * sizeof(int), "the stage buffers double as the scheduler's scratch");
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const float c = 1.4426950408889634f / sqrtf((float)D);   // log2(e) / sqrt(D): exp(x / sqrt(D)) = exp2(c x)
+    const int64_t row_stride = (int64_t)H * D;
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+    const NarrowAddresses<D> at(lane);
+    const NarrowCopier<D> copier(wave, lane, row_stride);
+    NarrowWalk<CROSS> walk(&walk_mem, s, offsets, offsets_kv, B, H, reinterpret_cast<int *>(st));
+
+    Work t{};
+    int have = 0;
+    asm volatile("" : "+s"(have));   // the first pass through the loop only claims (known to be 0, it would be a second copy of the claim)
+    for (;;) {
+        __syncthreads();   // every wave has read the slot, and the previous tile's use of the stage buffers is over
+        const int Lq = t.len;                      // queries of the sample
+        const int L = CROSS ? t.olen : t.len;      // keys of the sample
+        const int64_t krow0 = CROSS ? t.orow0 : t.row0;
+        const int q0 = t.block * kFwdBlockRows + wave * 32;   // first query of this wave
+        const int i = q0 + col;                               // this lane's query; rows past the end repeat the last one
+        const int iq = i < Lq ? i : Lq - 1;
+        const bool wave_active = q0 < Lq;
+        const int Lc = CAUSAL && (t.block + 1) * kFwdBlockRows < L ? (t.block + 1) * kFwdBlockRows : L;   // keys this tile needs
+        const int n_stages = have ? (Lc + kNwStageRows - 1) / kNwStageRows : 0;
+        const __bf16 *const kbase = k + krow0 * row_stride + (int64_t)t.head * D;
+        const __bf16 *const vbase = v + krow0 * row_stride + (int64_t)t.head * D;
+        __bf16 *const obase = out + t.row0 * row_stride + (int64_t)t.head * D;
+        float *const lse_i = lse + (int64_t)t.head * offsets[B] + t.row0 + i;
+
+        bf16x8 qreg[kKSteps];
+        if (n_stages > 0) {
+            copier.copy(kbase, vbase, 0, L, st);
+            const __bf16 *qrow = q + (t.row0 + iq) * row_stride + (int64_t)t.head * D + 8 * half;
+#pragma unroll
+            for (int ks = 0; ks < kKSteps; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8 *>(qrow + 16 * ks);
+        }
+        if (wave == 0) walk.claim();   // overlaps with the loads in flight
+        if (CROSS && have && L == 0 && i < Lq) {   // no keys: an empty softmax, out = 0 and lse = -inf
+            __bf16 *orow = obase + i * row_stride + half * (D / 2);
+#pragma unroll
+            for (int e = 0; e < D / 2; e += 8) *reinterpret_cast<u32x4 *>(orow + e) = u32x4{0, 0, 0, 0};
+            if (half == 0) *lse_i = -INFINITY;
+        }
+        if (n_stages > 0) {
+            f32x16 o[kDBlocks];
+            float m = -INFINITY, lsum = 0.0f;   // reference maximum (raw scores) of this lane's query; its share of the row sum
+#pragma unroll
+            for (int db = 0; db < kDBlocks; ++db)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
+
+            // stages whose keys all exist and, if causal, lie at or below the wave's first query need no mask; if causal, the
+            // wave's 32 queries meet the diagonal in one stage and the later ones are above it
+            const int n_full = (CAUSAL && q0 + 1 < L ? q0 + 1 : L) / kNwStageRows;
+            const int n_mine = !wave_active ? 0 : CAUSAL ? q0 / kNwStageRows + 1 : n_stages;
+
+            // One stage.  safe: maximum first, with rescaling (a tile's first stage, which sets the reference, and tiles that are
+            // redone); otherwise against the reference as it is.  Both flags are the same in every lane.
+            auto run_block = [&](const char *kt, int j, bool safe, bool masked) {
+                const char *const vt = kt + N::kTile;
+                f32x16 a[2];
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) a[mb][e] = 0.0f;
+#pragma unroll
+                    for (int ks = 0; ks < kKSteps; ++ks)
+                        a[mb] = mfma_32x32x16(lds_read_b128(kt + mb * 32 * N::kRow + at.row[ks]), qreg[ks], a[mb]);
+                }
+                if (masked) {   // keys past the end of the sample (causal: and above the diagonal)
+                    const int lim = (CAUSAL && iq + 1 < L ? iq + 1 : L) - j * kNwStageRows - 4 * half;
+#pragma unroll
+                    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e)
+                            if (mb * 32 + (e >> 2) * 8 + (e & 3) >= lim) a[mb][e] = -INFINITY;
+                }
+                if (safe) {
+                    float mx = -INFINITY;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) mx = fmaxf(fmaxf(mx, a[0][e]), a[1][e]);
+                    const float n = fmaxf(m, pair_max(mx));
+                    if (j > 0) {
+                        const float alpha = fast_exp2((m - n) * c);
+                        lsum *= alpha;
+#pragma unroll
+                        for (int db = 0; db < kDBlocks; ++db)
+#pragma unroll
+                            for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+                    }
+                    m = n;
+                }
+                // Probabilities, rounded to bf16 (the values the second product and the row sum use), and O^T += V^T P^T.  Slot e
+                // of a 16-key step is key 8 (e / 4) + 4 half + e % 4.
+                const float mc = m * c;
+#pragma unroll
+                for (int ts = 0; ts < 4; ++ts) {
+                    u32x4 pw;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        bf16x2 pr;
+                        pr[0] = (__bf16)fast_exp2(fmaf(a[ts >> 1][8 * (ts & 1) + 2 * e], c, -mc));
+                        pr[1] = (__bf16)fast_exp2(fmaf(a[ts >> 1][8 * (ts & 1) + 2 * e + 1], c, -mc));
+                        lsum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum, false);
+                        pw[e] = __builtin_bit_cast(uint32_t, pr);
+                    }
+                    const bf16x8 p = __builtin_bit_cast(bf16x8, pw);
+#pragma unroll
+                    for (int db = 0; db < kDBlocks; ++db) {
+                        const char *pv = vt + ts * 16 * N::kRow;
+                        o[db] = mfma_32x32x16(concat(lds_read_tr16(pv + at.tr[0][db]), lds_read_tr16(pv + at.tr[1][db])), p, o[db]);
+                    }
+                }
+            };
+            // The copies of stage j + 1 go into the other buffer, which stage j - 1 has released, while stage j is computed.
+            auto end_stage = [&]() {
+                asm volatile("" ::: "memory");
+                wait_vm<0>();
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            };
+            if (tid == 0) restart = 0;   // nobody looks at it between the previous tile's check and this barrier
+            end_stage();   // stage 0 has landed
+            // stages unmasked for every wave of the tile (a causal tile's first wave has the fewest)
+            const int n_plain = (CAUSAL && t.block * kFwdBlockRows + 1 < L ? t.block * kFwdBlockRows + 1 : L) / kNwStageRows;
+            bool redo = false;
+            int j = 0;
+            for (;;) {
+                for (; j < n_stages; ++j) {
+                    if (!redo) {   // two steady stages at a time: buffers 1 and 0, offsets in the instructions
+                        for (; (j & 1) && j + 3 <= n_plain; j += 2) {
+                            copier.template copy<true>(kbase, vbase, (j + 1) * kNwStageRows, L, st);
+                            if (wave_active) run_block(st + N::kStage, j, false, false);
+                            end_stage();
+                            copier.template copy<true>(kbase, vbase, (j + 2) * kNwStageRows, L, st + N::kStage);
+                            if (wave_active) run_block(st, j + 1, false, false);
+                            end_stage();
+                        }
+                    }
+                    char *const here = st + (j & 1) * N::kStage, *const other = st + (~j & 1) * N::kStage;
+                    if (j + 1 < n_stages) copier.copy(kbase, vbase, (j + 1) * kNwStageRows, L, other);
+                    if (j < n_mine) run_block(here, j, redo || j == 0, j >= n_full);
+                    // a row sum this large (or not finite) means the fixed reference was too far below the true maximum
+                    if (j + 1 == n_stages && !redo && wave_active && __builtin_amdgcn_ballot_w64(!(lsum < 0x1p62f)) != 0 && lane == 0) restart = 1;
+                    end_stage();
+                }
+                if (redo || __builtin_amdgcn_readfirstlane(restart) == 0) break;
+                redo = true;   // the whole tile again, maximum first
+                copier.copy(kbase, vbase, 0, L, st);
+                m = -INFINITY;
+                lsum = 0.0f;
+#pragma unroll
+                for (int db = 0; db < kDBlocks; ++db)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
+                end_stage();
+                j = 0;
+            }
+
+            // ---- normalise and store: every wave is past the last stage's barrier and no copy is in flight ----
+            const float l_total = pair_sum(lsum);
+            if (wave_active) {
+                narrow_store<D>(st + wave * 32 * N::kRow, lane, o, 1.0f / l_total, obase, row_stride, q0, Lq);
+                if (i < Lq && half == 0) *lse_i = (m * c + fast_log2(l_total)) * 0.6931471805599453f;
+            }
+        } else {
+            __syncthreads();   // the slot is written
+        }
+        have = walk.next(t);
+        if (!have) break;
+    }
+}
+
+hipError_t launch_fwd_narrow(const void *q, const void *k, const void *v, const int64_t *offsets, const int64_t *offsets_kv, bool causal,
+                             int B, int H, int D, Schedule s, void *out, float *lse, int cus, hipStream_t stream) {
+    if (causal && offsets_kv) return hipErrorInvalidValue;
+#define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                        \
+    hipLaunchKernelGGL((fwd_narrow_kernel<DD, CROSS, CAUSAL>), dim3(persistent_grid<fwd_narrow_kernel<DD, CROSS, CAUSAL>>(kNwThreads, cus)), \
+                       dim3(kNwThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, offsets, offsets_kv, B, H, s, \
+                       (__bf16 *)out, lse)
+#define JFA_CASE(DD)                                                                                         \
+    case DD:                                                                                                 \
+        if (offsets_kv) JFA_LAUNCH(DD, true, false);                                                         \
+        else if (causal) JFA_LAUNCH(DD, false, true);                                                        \
+        else JFA_LAUNCH(DD, false, false);                                                                   \
+        break;
+    switch (D) {
+        JFA_CASE(32) JFA_CASE(64)
+        default: return hipErrorInvalidValue;
+    }
+#undef JFA_CASE
+#undef JFA_LAUNCH
+    return hipGetLastError();
+}
+
+}  // namespace jfa

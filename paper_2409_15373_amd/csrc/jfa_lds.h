@@ -24,6 +24,12 @@ __device__ inline void bd_dma16(const void *base, uint32_t byte_offset, char *ld
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  : : "s"(dst), "v"(byte_offset), "s"(base) : "memory", "m0");
 }
+// The same with a whole 64-bit address per lane.
+__device__ inline void dma16_lane(const void *src, char *lds_wave_base) {
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_byte_address(lds_wave_base));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 : : "s"(dst), "v"(src) : "memory", "m0");
+}
 __device__ inline void bd_dma4(const void *base, uint32_t byte_offset, char *lds_wave_base) {
     const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_byte_address(lds_wave_base));
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
