@@ -396,6 +396,12 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
         s_dkv.build_rows = block_rows;
     }
     // the dQ kernel goes first: it computes delta = rowsum(dO o O) for its own rows and leaves it for the dK / dV kernel
+    if (D < 128) {
+        { ScopedTimer tm("dq_bf16", s); e = jfa::launch_dq_narrow(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, (int)B, H, D, s_dq, dq, w.cus, s); }
+        if (e != hipSuccess) return hip_fail("bf16 dQ kernel", e);
+        { ScopedTimer tm("dkv_bf16", s); e = jfa::launch_dkv_narrow(q, k, v, dout, delta, offsets_k, offsets_q_other, causal, (int)B, H, D, s_dkv, dk, dv, w.cus, s); }
+        return e == hipSuccess ? JFA_OK : hip_fail("bf16 dK/dV kernel", e);
+    }
     { ScopedTimer tm("dq_bf16", s); e = jfa::launch_dq_bf16(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, (int)B, H, D, s_dq, dq, w.cus, s); }
     if (e != hipSuccess) return hip_fail("bf16 dQ kernel", e);
     { ScopedTimer tm("dkv_bf16", s); e = jfa::launch_dkv_bf16(q, k, v, dout, lse, delta, offsets_k, offsets_q_other, causal, (int)B, H, D, s_dkv, dk, dv, w.cus, s); }

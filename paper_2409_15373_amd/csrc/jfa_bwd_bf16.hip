@@ -1,4 +1,4 @@
-// Jagged flash attention backward, bf16 on gfx950 matrix cores (paper Section 2.2: every jagged
+// Jagged flash attention backward, bf16 on gfx950 matrix cores, D = 128, short samples (paper Section 2.2: every jagged
 // operator has a backward; the formulas are those of softmax attention, with P recomputed from the
 // stored log-sum-exp so that no score matrix is ever kept).
 //
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kBwdThreads, 2) void dq_bf16_kernel(const __bf16 *_
 // delta, are the rows of offsets_q.  CAUSAL: key j is seen by queries j .. L - 1: the stream starts at the stage that
 // holds the tile's first key, and streamed rows below the lane's key get P = 0.
 template <int D, bool CROSS, bool CAUSAL>
-__global__ __launch_bounds__(kBwdThreads, D <= 64 ? 2 : 1) void dkv_bf16_kernel(const __bf16 *__restrict__ q,
+__global__ __launch_bounds__(kBwdThreads, 1) void dkv_bf16_kernel(const __bf16 *__restrict__ q,
                                                                   const __bf16 *__restrict__ k,
                                                                   const __bf16 *__restrict__ v,
                                                                   const __bf16 *__restrict__ dout,
@@ -365,22 +365,14 @@ __global__ __launch_bounds__(kBwdThreads, D <= 64 ? 2 : 1) void dkv_bf16_kernel(
 hipError_t launch_dkv_bf16(const void *q, const void *k, const void *v, const void *dout, const float *lse,
                            const float *delta, const int64_t *offsets, const int64_t *offsets_q, bool causal, int B, int H,
                            int D, Schedule s, void *dk, void *dv, int cus, hipStream_t stream) {
-    if (causal && offsets_q) return hipErrorInvalidValue;
-#define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                            \
-    hipLaunchKernelGGL((dkv_bf16_kernel<DD, CROSS, CAUSAL>), dim3(persistent_grid<dkv_bf16_kernel<DD, CROSS, CAUSAL>>(kBwdThreads, cus)), \
+    if (D != 128 || (causal && offsets_q)) return hipErrorInvalidValue;
+#define JFA_LAUNCH(CROSS, CAUSAL)                                                                            \
+    hipLaunchKernelGGL((dkv_bf16_kernel<128, CROSS, CAUSAL>), dim3(persistent_grid<dkv_bf16_kernel<128, CROSS, CAUSAL>>(kBwdThreads, cus)), \
                        dim3(kBwdThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, lse, \
                        delta, offsets, offsets_q, B, H, s, (__bf16 *)dk, (__bf16 *)dv)
-#define JFA_CASE(DD)                                                                                             \
-    case DD:                                                                                                     \
-        if (offsets_q) JFA_LAUNCH(DD, true, false);                                                              \
-        else if (causal) JFA_LAUNCH(DD, false, true);                                                            \
-        else JFA_LAUNCH(DD, false, false);                                                                       \
-        break;
-    switch (D) {
-        JFA_CASE(32) JFA_CASE(64) JFA_CASE(128)
-        default: return hipErrorInvalidValue;
-    }
-#undef JFA_CASE
+    if (offsets_q) JFA_LAUNCH(true, false);
+    else if (causal) JFA_LAUNCH(false, true);
+    else JFA_LAUNCH(false, false);
 #undef JFA_LAUNCH
     return hipGetLastError();
 }
@@ -388,22 +380,14 @@ hipError_t launch_dkv_bf16(const void *q, const void *k, const void *v, const vo
 hipError_t launch_dq_bf16(const void *q, const void *k, const void *v, const void *out, const void *dout, const float *lse,
                           float *delta, const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H,
                           int D, Schedule s, void *dq, int cus, hipStream_t stream) {
-    if (causal && offsets_kv) return hipErrorInvalidValue;
-#define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                            \
-    hipLaunchKernelGGL((dq_bf16_kernel<DD, CROSS, CAUSAL>), dim3(persistent_grid<dq_bf16_kernel<DD, CROSS, CAUSAL>>(kBwdThreads, cus)), \
+    if (D != 128 || (causal && offsets_kv)) return hipErrorInvalidValue;
+#define JFA_LAUNCH(CROSS, CAUSAL)                                                                            \
+    hipLaunchKernelGGL((dq_bf16_kernel<128, CROSS, CAUSAL>), dim3(persistent_grid<dq_bf16_kernel<128, CROSS, CAUSAL>>(kBwdThreads, cus)), \
                        dim3(kBwdThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, lse, \
                        (const __bf16 *)out, delta, offsets, offsets_kv, B, H, s, (__bf16 *)dq)
-#define JFA_CASE(DD)                                                                                             \
-    case DD:                                                                                                     \
-        if (offsets_kv) JFA_LAUNCH(DD, true, false);                                                             \
-        else if (causal) JFA_LAUNCH(DD, false, true);                                                            \
-        else JFA_LAUNCH(DD, false, false);                                                                       \
-        break;
-    switch (D) {
-        JFA_CASE(32) JFA_CASE(64) JFA_CASE(128)
-        default: return hipErrorInvalidValue;
-    }
-#undef JFA_CASE
+    if (offsets_kv) JFA_LAUNCH(true, false);
+    else if (causal) JFA_LAUNCH(false, true);
+    else JFA_LAUNCH(false, false);
 #undef JFA_LAUNCH
     return hipGetLastError();
 }

@@ -491,7 +491,7 @@ hipError_t launch_bwd_f32(const float *q, const float *k, const float *v, const 
                           hipStream_t stream);
 // (the dQ kernel of every path runs first and computes delta[h, row] = sum_d dout * out for the kernels after it)
 
-// bf16 attention, register-staged kernels (D = 128, short samples; backward: any supported D)
+// bf16 attention, register-staged kernels (D = 128, short samples)
 constexpr int kFwdBlockRows = 128;
 constexpr int kBwdBlockRows = 128;
 // In all bf16 launchers `offsets` belongs to the rows the schedule `s` was built over (queries for the forward and
@@ -509,7 +509,14 @@ hipError_t launch_dq_bf16(const void *q, const void *k, const void *v, const voi
                           float *delta, const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H,
                           int D, Schedule s, void *dq, int cus, hipStream_t stream);
 
-// bf16 forward for D = 32 and 64 at every length (blocks of kFwdBlockRows rows)
+// bf16 attention for D = 32 and 64 at every length (blocks of kFwdBlockRows / kBwdBlockRows rows).  The dQ launch comes first and
+// fills `stats` [2, H, sum_B] (delta, -lse * sqrt(D)) for the dK / dV launch.
+hipError_t launch_dq_narrow(const void *q, const void *k, const void *v, const void *out, const void *dout, const float *lse, float *stats,
+                            const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, void *dq,
+                            int cus, hipStream_t stream);
+hipError_t launch_dkv_narrow(const void *q, const void *k, const void *v, const void *dout, const float *stats, const int64_t *offsets,
+                             const int64_t *offsets_q, bool causal, int B, int H, int D, Schedule s, void *dk, void *dv, int cus,
+                             hipStream_t stream);
 hipError_t launch_fwd_narrow(const void *q, const void *k, const void *v, const int64_t *offsets, const int64_t *offsets_kv, bool causal,
                              int B, int H, int D, Schedule s, void *out, float *lse, int cus, hipStream_t stream);
 

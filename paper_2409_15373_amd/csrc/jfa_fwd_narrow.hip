@@ -37,6 +37,7 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
     const int col = lane & 31, half = lane >> 5;
     const float c = 1.4426950408889634f / sqrtf((float)D);   // log2(e) / sqrt(D): exp(x / sqrt(D)) = exp2(c x)
     const int64_t row_stride = (int64_t)H * D;
+    const int64_t sum_B = offsets[B];
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
     const NarrowAddresses<D> at(lane);
     const NarrowCopier<D> copier(wave, lane, row_stride);
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
         const __bf16 *const kbase = k + krow0 * row_stride + (int64_t)t.head * D;
         const __bf16 *const vbase = v + krow0 * row_stride + (int64_t)t.head * D;
         __bf16 *const obase = out + t.row0 * row_stride + (int64_t)t.head * D;
-        float *const lse_i = lse + (int64_t)t.head * offsets[B] + t.row0 + i;
+        float *const lse_i = lse + (int64_t)t.head * sum_B + t.row0 + i;
 
         bf16x8 qreg[kKSteps];
         if (n_stages > 0) {

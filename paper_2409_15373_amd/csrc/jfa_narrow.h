@@ -24,7 +24,6 @@ struct Narrow {
     static constexpr int kTile = kNwStageRows * kRow;
     static constexpr int kStage = 2 * kTile;                  // the two streamed tensors of a stage
     static constexpr int kRowsPerCopy = 64 / kChunks;         // one copy instruction moves 64 lanes x 16 bytes
-    static constexpr int kCopies = kNwStageRows / kRowsPerCopy / (kNwThreads / 64);   // per wave and tile
     __device__ static inline int swz(int r) { return D == 64 ? ((r & 2) << 1) | ((r >> 2) & 3) : (r >> 2) & 3; }
 };
 
@@ -48,50 +47,53 @@ struct NarrowAddresses {
     }
 };
 
-// Copies of one wave into a tile: instruction u fills rows (wave * kCopies + u) * kRowsPerCopy + lane / kChunks; rows past
-// the end repeat the last row (masked by the caller).  The byte offsets inside a stage fit 32 bits while H * D <= 2^24;
-// wider rows take 64-bit addresses.
+// Copies of a wave: one instruction moves kRowsPerCopy rows, lane l chunk l % kChunks of row l / kChunks of them.  What a lane
+// fetches depends on its row modulo 16 only (the swizzle), so that the lane offsets of 16 rows are kept for the whole kernel
+// and everything else is in the scalar base.  They fit 32 bits while H * D <= 2^24; wider rows take 64-bit addresses.
+// Rows past the end repeat the last row (masked by the caller).
 template <int D>
 struct NarrowCopier {
     using N = Narrow<D>;
-    uint32_t off[N::kCopies];   // of a full stage: the same for every stage
+    static constexpr int kPer16 = 16 / N::kRowsPerCopy;   // instructions for 16 rows
+    uint32_t off[kPer16];
     int wave, lane;
     int64_t row_stride;
     __device__ inline NarrowCopier(int wave_, int lane_, int64_t row_stride_) : wave(wave_), lane(lane_), row_stride(row_stride_) {
 #pragma unroll
-        for (int u = 0; u < N::kCopies; ++u) off[u] = 2u * (row_of(u) * (uint32_t)row_stride + (chunk_of(row_of(u)) << 3));
+        for (int u = 0; u < kPer16; ++u) off[u] = lane_offset(u * N::kRowsPerCopy + lane / N::kChunks, 16);
     }
-    __device__ inline int row_of(int u) const { return (wave * N::kCopies + u) * N::kRowsPerCopy + lane / N::kChunks; }
     __device__ inline int chunk_of(int r) const { return (lane % N::kChunks) ^ N::swz(r); }
-    // rows r0 .. r0 + 63 of the two tensors of `n` rows at `a` and `b` -> stage buffer
-    template <bool kFull = false>
-    __device__ inline void copy(const __bf16 *a, const __bf16 *b, int r0, int n, char *stage) const {
-        char *const dst = stage + wave * N::kCopies * 1024;
-        const __bf16 *const as = a + (int64_t)r0 * row_stride, *const bs = b + (int64_t)r0 * row_stride;
-        if (row_stride <= (1 << 24)) {
-            uint32_t o[N::kCopies];
+    __device__ inline uint32_t lane_offset(int r, int n) const { return 2u * ((r < n ? r : n - 1) * (uint32_t)row_stride + (chunk_of(r) << 3)); }
+    // `kRows` rows (a multiple of 16) from `base` on, the first `n` of which exist -> dst, laid out as rows of a tile
+    template <int kRows, bool kFull>
+    __device__ inline void copy16(const __bf16 *base, int n, char *dst) const {
+        if (row_stride <= (1 << 24) && (kFull || n >= kRows)) {
 #pragma unroll
-            for (int u = 0; u < N::kCopies; ++u) o[u] = off[u];
-            if (!kFull && r0 + kNwStageRows > n) {
+            for (int u = 0; u < kRows / N::kRowsPerCopy; ++u) bd_dma16(base + u / kPer16 * 16 * row_stride, off[u % kPer16], dst + u * 1024);
+        } else if (row_stride <= (1 << 24)) {
 #pragma unroll
-                for (int u = 0; u < N::kCopies; ++u) {
-                    const int r = row_of(u);
-                    o[u] = 2u * ((r0 + r < n ? r : n - 1 - r0) * (uint32_t)row_stride + (chunk_of(r) << 3));
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < N::kCopies; ++u) bd_dma16(as, o[u], dst + u * 1024);
-#pragma unroll
-            for (int u = 0; u < N::kCopies; ++u) bd_dma16(bs, o[u], dst + N::kTile + u * 1024);
+            for (int u = 0; u < kRows / N::kRowsPerCopy; ++u) bd_dma16(base, lane_offset(u * N::kRowsPerCopy + lane / N::kChunks, n), dst + u * 1024);
         } else {
 #pragma unroll 1
-            for (int u = 0; u < N::kCopies; ++u) {
-                const int r = row_of(u);
-                const int64_t lane_off = (r0 + r < n ? r : n - 1 - r0) * row_stride + (chunk_of(r) << 3);
-                dma16_lane(as + lane_off, dst + u * 1024);
-                dma16_lane(bs + lane_off, dst + N::kTile + u * 1024);
+            for (int u = 0; u < kRows / N::kRowsPerCopy; ++u) {
+                const int r = u * N::kRowsPerCopy + lane / N::kChunks;
+                dma16_lane(base + (r < n ? r : n - 1) * row_stride + (chunk_of(r) << 3), dst + u * 1024);
             }
         }
+    }
+    // The wave's 16 rows of stage rows r0 .. r0 + 63 of the two tensors of `n` rows at `a` and `b` -> stage buffer.
+    template <bool kFull = false>
+    __device__ inline void copy(const __bf16 *a, const __bf16 *b, int r0, int n, char *stage) const {
+        int w0 = r0 + wave * 16;                 // first row of this wave
+        const int left = n - w0;
+        if (!kFull && left < 1) w0 = n - 1;      // behind the end: the last row, sixteen times
+        char *const dst = stage + wave * 16 * N::kRow;
+        copy16<16, kFull>(a + w0 * row_stride, left < 1 ? 1 : left, dst);
+        copy16<16, kFull>(b + w0 * row_stride, left < 1 ? 1 : left, dst + N::kTile);
+    }
+    // A wave's 32 rows, `first` .. of the `n` rows at `base` (first < n) -> `dst`, 32 * kRow bytes of its own
+    __device__ inline void copy_rows(const __bf16 *base, int first, int n, char *dst) const {
+        copy16<32, false>(base + first * row_stride, n - first, dst);
     }
 };
 
