@@ -129,8 +129,16 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+# The handle of torch's current stream.  torch.cuda.current_stream() builds a Stream object around it, 2.6 us (5 us in a
+# backward, on the engine's thread) of the 11 us a call on a tiny batch takes; asked for directly it is 0.25 us.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _pick(dtype: torch.dtype, bf16_name: str):
