@@ -11,9 +11,10 @@
 //     multiply (or multiply-add), one exponential, one multiply and the conversions;
 //   * only stages that contain the sample's end or the diagonal mask;
 //   * stages (and the stream's statistics) go directly to LDS, one ahead; gradients leave as whole rows.
-// D = 64: three workgroups of the dQ kernel per compute unit (its rows of the forward's output pass through LDS, which leaves
-// registers for that: 1449 us on 1024 samples of 1 to 1024 rows, H = 8, against 1569 with two), two of the dK / dV kernel
-// (its 256 accumulators and operands spill at three: 5 % slower).
+// Workgroups per compute unit: dQ four at D = 32 and three at D = 64 (its rows of the forward's output pass through LDS, which
+// leaves registers for that: 1449 us on 1024 samples of 1 to 1024 rows, H = 8, against 1569 with two; see the launcher for
+// small problems), dK / dV two at D = 64 and three at D = 32 (one more spills: 5 % slower at D = 64; at D = 32 2 % faster on
+// that batch but 1 to 4 us slower a launch, for the scratch memory).
 // H * D = 512, whole backward, microseconds before -> now: 1024 samples of 1 to 1024 rows D = 64 4045 -> 3200, D = 32
 // 4572 -> 3630; 64 samples of 4096 rows D = 64 8698 -> 6942 (774 TFLOP/s), D = 32 10617 -> 7912.  A 32 x 32 block costs a SIMD
 // about 44 clocks per matrix instruction (12 + 16) and 3.8 per vector instruction (56 + 64; 134 + 96 before).
@@ -31,8 +32,9 @@ __device__ inline void narrow_end_stage() {
 }
 
 // CROSS: `offsets` belongs to the queries, offsets_kv to the keys and values; CAUSAL: query i sees keys 0 .. i.
-template <int D, bool CROSS, bool CAUSAL>
-__global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void dq_narrow_kernel(
+// kPerCu: workgroups per compute unit.
+template <int D, bool CROSS, bool CAUSAL, int kPerCu>
+__global__ __launch_bounds__(kNwThreads, kPerCu) void dq_narrow_kernel(
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, const __bf16 *__restrict__ dout,
     const float *__restrict__ lse, const __bf16 *__restrict__ out_fwd, float *__restrict__ stats, const int64_t *__restrict__ offsets,
     const int64_t *__restrict__ offsets_kv, int B, int H, Schedule s, __bf16 *__restrict__ dq) {
@@ -53,8 +55,8 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void dq_narrow_kernel(
     NarrowWalk<CROSS> walk(&walk_mem, s, offsets, offsets_kv, B, H, reinterpret_cast<int *>(st));
 
     Work t{};
-    int have = 0;
-    asm volatile("" : "+s"(have));   // the first pass through the loop only claims
+    int have = walk.small && walk.next(t);
+    asm volatile("" : "+s"(have));   // a first pass with 0 only claims (known to be 0, it would be a second copy of the claim)
     for (;;) {
         __syncthreads();   // every wave has read the slot, and the previous tile's use of the stage buffers is over
         const int Lq = t.len;                      // queries of the sample
@@ -69,13 +71,11 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void dq_narrow_kernel(
         const __bf16 *const kbase = k + krow0 * row_stride + (int64_t)t.head * D;
         const __bf16 *const vbase = v + krow0 * row_stride + (int64_t)t.head * D;
 
-        if (n_stages > 0) copier.copy(kbase, vbase, 0, L, st);
         float l = 0.0f;
         const int64_t srow = (int64_t)t.head * sum_q + t.row0 + iq;   // this lane's query in `lse` and in a plane of `stats`
         char *const own = st + N::kStage + wave * 32 * N::kRow;   // the wave's rows of the forward's output pass through the second stage buffer
         bf16x8 qreg[kKSteps], doreg[kKSteps];
         if (have) {
-            if (wave_active) copier.copy_rows(out_fwd + t.row0 * row_stride + (int64_t)t.head * D, q0, Lq, own);
             const int64_t off = (t.row0 + iq) * row_stride + (int64_t)t.head * D + 8 * half;
 #pragma unroll
             for (int ks = 0; ks < kKSteps; ++ks) {
@@ -83,6 +83,8 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void dq_narrow_kernel(
                 doreg[ks] = *reinterpret_cast<const bf16x8 *>(dout + off + 16 * ks);
             }
             l = lse[srow];
+            if (wave_active) copier.copy_rows(out_fwd + t.row0 * row_stride + (int64_t)t.head * D, q0, Lq, own);
+            if (n_stages > 0) copier.copy(kbase, vbase, 0, L, st);
         }
         if (wave == 0) walk.claim();   // overlaps with the loads in flight
         if (have) {
@@ -112,6 +114,7 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void dq_narrow_kernel(
                 const char *const vt = kt + N::kTile;
 #pragma unroll
                 for (int mb = 0; mb < 2; ++mb) {
+                    if (D == 32) __builtin_amdgcn_sched_barrier(0);   // the two blocks one after the other: side by side they spill
                     f32x16 sc, dp = ndelta;
 #pragma unroll
                     for (int e = 0; e < 16; ++e) sc[e] = 0.0f;
@@ -171,7 +174,7 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void dq_narrow_kernel(
 // CROSS: `offsets` belongs to the keys (the stationary rows), offsets_q to the queries that stream past them.  CAUSAL: key j is
 // seen by queries j .. L - 1: the stream starts at the stage that holds the tile's first key.
 template <int D, bool CROSS, bool CAUSAL>
-__global__ __launch_bounds__(kNwThreads, D == 64 ? 2 : 4) void dkv_narrow_kernel(
+__global__ __launch_bounds__(kNwThreads, D == 64 ? 2 : 3) void dkv_narrow_kernel(
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, const __bf16 *__restrict__ dout,
     const float *__restrict__ stats, const int64_t *__restrict__ offsets, const int64_t *__restrict__ offsets_q, int B, int H,
     Schedule s, __bf16 *__restrict__ dk, __bf16 *__restrict__ dv) {
@@ -193,8 +196,8 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 2 : 4) void dkv_narrow_kernel
     NarrowWalk<CROSS> walk(&walk_mem, s, offsets, offsets_q, B, H, reinterpret_cast<int *>(st));
 
     Work t{};
-    int have = 0;
-    asm volatile("" : "+s"(have));   // the first pass through the loop only claims
+    int have = walk.small && walk.next(t);
+    asm volatile("" : "+s"(have));   // a first pass with 0 only claims (known to be 0, it would be a second copy of the claim)
     for (;;) {
         __syncthreads();   // every wave has read the slot, and the previous tile's use of the stage buffers is over
         const int Lk = t.len;                      // keys of the sample
@@ -221,19 +224,23 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 2 : 4) void dkv_narrow_kernel
 
         bf16x8 kreg[kKSteps], vreg[kKSteps];
         if (have) {
-            if (n_stages > 0) issue(std::false_type{}, first, st);
             const int64_t off = (t.row0 + jk) * row_stride + (int64_t)t.head * D + 8 * half;
 #pragma unroll
             for (int ks = 0; ks < kKSteps; ++ks) {
                 kreg[ks] = *reinterpret_cast<const bf16x8 *>(k + off + 16 * ks);
-                u32x4 x = *reinterpret_cast<const u32x4 *>(v + off + 16 * ks);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] ^= 0x80008000u;   // minus V: the accumulators end as delta - dP
-                vreg[ks] = __builtin_bit_cast(bf16x8, x);
+                vreg[ks] = *reinterpret_cast<const bf16x8 *>(v + off + 16 * ks);
             }
+            if (n_stages > 0) issue(std::false_type{}, first, st);
         }
         if (wave == 0) walk.claim();   // overlaps with the loads in flight
         if (have) {
+#pragma unroll
+            for (int ks = 0; ks < kKSteps; ++ks) {   // minus V: the accumulators end as delta - dP
+                u32x4 x = __builtin_bit_cast(u32x4, vreg[ks]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] ^= 0x80008000u;
+                vreg[ks] = __builtin_bit_cast(bf16x8, x);
+            }
             f32x16 acck[kDBlocks], accv[kDBlocks];
 #pragma unroll
             for (int db = 0; db < kDBlocks; ++db)
@@ -318,10 +325,18 @@ hipError_t launch_dq_narrow(const void *q, const void *k, const void *v, const v
                             const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, void *dq,
                             int cus, hipStream_t stream) {
     if (causal && offsets_kv) return hipErrorInvalidValue;
-#define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                        \
-    hipLaunchKernelGGL((dq_narrow_kernel<DD, CROSS, CAUSAL>), dim3(persistent_grid<dq_narrow_kernel<DD, CROSS, CAUSAL>>(kNwThreads, cus)), \
+#define JFA_LAUNCH_AT(DD, CROSS, CAUSAL, PER_CU)                                                                        \
+    hipLaunchKernelGGL((dq_narrow_kernel<DD, CROSS, CAUSAL, PER_CU>), dim3(persistent_grid<dq_narrow_kernel<DD, CROSS, CAUSAL, PER_CU>>(kNwThreads, cus)), \
                        dim3(kNwThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, lse, \
                        (const __bf16 *)out, stats, offsets, offsets_kv, B, H, s, (__bf16 *)dq)
+    // D = 64: the third workgroup costs a few registers spilled per tile, and the scratch memory that takes costs a launch
+    // 4 us: 100 samples of at most 1000 rows 34 us against 29, 1024 of them 1449 against 1569.  The line is where the
+    // schedule is built in the kernel, i.e. at most four tiles per compute unit.
+#define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                        \
+    do {                                                                                                     \
+        if (DD == 64 && s.build_rows != 0) JFA_LAUNCH_AT(DD, CROSS, CAUSAL, (DD == 64 ? 2 : 4));             \
+        else JFA_LAUNCH_AT(DD, CROSS, CAUSAL, (DD == 64 ? 3 : 4));                                           \
+    } while (0)
 #define JFA_CASE(DD)                                                                                         \
     case DD:                                                                                                 \
         if (offsets_kv) JFA_LAUNCH(DD, true, false);                                                         \
@@ -334,6 +349,7 @@ hipError_t launch_dq_narrow(const void *q, const void *k, const void *v, const v
     }
 #undef JFA_CASE
 #undef JFA_LAUNCH
+#undef JFA_LAUNCH_AT
     return hipGetLastError();
 }
 

@@ -44,8 +44,8 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
     NarrowWalk<CROSS> walk(&walk_mem, s, offsets, offsets_kv, B, H, reinterpret_cast<int *>(st));
 
     Work t{};
-    int have = 0;
-    asm volatile("" : "+s"(have));   // the first pass through the loop only claims (known to be 0, it would be a second copy of the claim)
+    int have = walk.small && walk.next(t);
+    asm volatile("" : "+s"(have));   // a first pass with 0 only claims (known to be 0, it would be a second copy of the claim)
     for (;;) {
         __syncthreads();   // every wave has read the slot, and the previous tile's use of the stage buffers is over
         const int Lq = t.len;                      // queries of the sample
@@ -64,10 +64,10 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
 
         bf16x8 qreg[kKSteps];
         if (n_stages > 0) {
-            copier.copy(kbase, vbase, 0, L, st);
             const __bf16 *qrow = q + (t.row0 + iq) * row_stride + (int64_t)t.head * D + 8 * half;
 #pragma unroll
             for (int ks = 0; ks < kKSteps; ++ks) qreg[ks] = *reinterpret_cast<const bf16x8 *>(qrow + 16 * ks);
+            copier.copy(kbase, vbase, 0, L, st);
         }
         if (wave == 0) walk.claim();   // overlaps with the loads in flight
         if (CROSS && have && L == 0 && i < Lq) {   // no keys: an empty softmax, out = 0 and lse = -inf
