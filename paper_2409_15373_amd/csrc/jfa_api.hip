@@ -238,7 +238,8 @@ int jfa_build_schedule(const int64_t *offsets, int64_t B, int block_rows, int32_
     Views v;
     int st = get_table(B, (hipStream_t)stream, &v);
     if (st != JFA_OK) return st;
-    hipError_t e = jfa::launch_schedule(offsets, nullptr, (int)B, block_rows, order, tile_start, v.counters, jfa::kNumCounters, (hipStream_t)stream);
+    const jfa::ScheduleJob job{offsets, nullptr, block_rows, order, tile_start};
+    hipError_t e = jfa::launch_schedules(&job, 1, (int)B, v.counters, jfa::kNumCounters, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail("schedule kernel", e);
     return JFA_OK;
 }
@@ -269,10 +270,12 @@ namespace {
 // Forward and backward behind the self- and cross-attention entry points.  offsets_kv == nullptr: self attention
 // (keys and values share the queries' offsets).  Work schedules are built over the offsets of the rows a kernel's
 // work items are blocks of: the queries' for the forward and dQ, the keys' for dK and dV.
-hipError_t schedule(const int64_t *offsets, const int64_t *offsets_other, int64_t B, int block_rows, const Views &w, int which,
-                    hipStream_t s) {
+jfa::ScheduleJob schedule_job(const int64_t *offsets, const int64_t *offsets_other, int block_rows, const Views &w, int which) {
+    return jfa::ScheduleJob{offsets, offsets_other, block_rows, w.order[which], w.tile_start[which]};
+}
+hipError_t schedule(const jfa::ScheduleJob *jobs, int n_jobs, int64_t B, const Views &w, hipStream_t s) {
     ScopedTimer tm("schedule", s);
-    return jfa::launch_schedule(offsets, offsets_other, (int)B, block_rows, w.order[which], w.tile_start[which], w.counters, jfa::kNumCounters, s);
+    return jfa::launch_schedules(jobs, n_jobs, (int)B, w.counters, jfa::kNumCounters, s);
 }
 
 // Cross attention with few queries per sample against their keys (target attention: at most kFewqRows queries,
@@ -290,7 +293,8 @@ int few_queries_schedule(const int64_t *offsets, const int64_t *offsets_kv, int6
         sc->static_only = true;
         return JFA_OK;
     }
-    const hipError_t e = schedule(offsets, offsets_kv, B, jfa::kFewqRows, w, 0, s);
+    const jfa::ScheduleJob job = schedule_job(offsets, offsets_kv, jfa::kFewqRows, w, 0);
+    const hipError_t e = schedule(&job, 1, B, w, s);
     return e == hipSuccess ? JFA_OK : hip_fail("schedule kernel", e);
 }
 
@@ -318,7 +322,8 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
         sc.build_rows = block_rows;
         sc.static_only = true;
     } else {
-        e = schedule(offsets, offsets_kv, B, block_rows, w, 0, s);
+        const jfa::ScheduleJob job = schedule_job(offsets, offsets_kv, block_rows, w, 0);
+        e = schedule(&job, 1, B, w, s);
         if (e != hipSuccess) return hip_fail("schedule kernel", e);
     }
     if (f32) { ScopedTimer tm("fwd_f32", s); e = jfa::launch_fwd_f32((const float *)q, (const float *)k, (const float *)v, offsets, offsets_kv, causal, (int)B, H, D, sc, (float *)out, lse, w.cus, s); }
@@ -349,18 +354,20 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     }
     const bool dma = !f32 && D == 128 && forward_variant(max_len > max_len_kv ? max_len : max_len_kv, D, H) != kNarrow;
     const int block_rows = f32 ? jfa::kF32BlockRows : (dma ? jfa::kDmaBlockRows : jfa::kBwdBlockRows);
-    // Schedule 0: blocks of queries.  Schedule 1: blocks of keys, only different from schedule 0 for cross attention.
-    // Both launches clear all work counters, and both run before the first kernel that uses one.  Small problems on
-    // the register-staged and fp32 kernels have no scheduler launch: those kernels build their schedule themselves.
-    const bool in_kernel = !dma && small_problem(B, max_len > max_len_kv ? max_len : max_len_kv, H, block_rows, w.cus);
-    if (!in_kernel) {
-        e = schedule(offsets, offsets_kv, B, block_rows, w, 0, s);
-        if (e == hipSuccess && offsets_kv && !dma) e = schedule(offsets_kv, offsets, B, block_rows, w, 1, s);
-        if (e != hipSuccess) return hip_fail("schedule kernel", e);
-    }
+    // Schedule 0: blocks of queries.  Schedule 1: blocks of keys, where they differ: cross attention, and the direct-to-LDS
+    // kernels, whose dK / dV blocks are shorter.  One launch builds both and clears all work counters before the first
+    // kernel that uses one.  Small problems on the other kernels have no scheduler launch: those kernels build their
+    // schedule themselves.
     const int kv = offsets_kv ? 1 : 0;
     const int64_t *const offsets_k = offsets_kv ? offsets_kv : offsets;   // the keys' offsets
     const int64_t *const offsets_q_other = offsets_kv ? offsets : nullptr;   // the queries', as the second array of dK / dV
+    const bool in_kernel = !dma && small_problem(B, max_len > max_len_kv ? max_len : max_len_kv, H, block_rows, w.cus);
+    if (!in_kernel) {
+        const jfa::ScheduleJob jobs[2] = {schedule_job(offsets, offsets_kv, block_rows, w, 0),
+                                          schedule_job(offsets_k, offsets_q_other, dma ? jfa::kDkvBlockRows : block_rows, w, 1)};
+        e = schedule(jobs, dma || offsets_kv ? 2 : 1, B, w, s);
+        if (e != hipSuccess) return hip_fail("schedule kernel", e);
+    }
     if (f32) {
         jfa::Schedule s_dq{w.order[0], w.tile_start[0], w.counters};
         jfa::Schedule s_dkv{w.order[kv], w.tile_start[kv], w.counters + jfa::kXcds};
@@ -378,8 +385,6 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     if (dma) {
         // long samples at D = 128: dQ (which also fills both statistics planes) on schedule 0, then dK and dV together on
         // 128-key blocks (schedule 1: blocks of keys, for cross attention from the keys' offsets)
-        e = schedule(offsets_k, offsets_q_other, B, jfa::kDkvBlockRows, w, 1, s);
-        if (e != hipSuccess) return hip_fail("schedule kernel", e);
         jfa::Schedule s_dq{w.order[0], w.tile_start[0], w.counters};
         jfa::Schedule s_dkv{w.order[1], w.tile_start[1], w.counters + jfa::kXcds};
         { ScopedTimer tm("dq_bf16_dma", s); e = jfa::launch_bwd_dq_dma(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, (int)B, H, D, s_dq, dq, w.cus, s); }
@@ -528,7 +533,7 @@ int unfused_begin(const char *who, int64_t B, int64_t max_len, int H, int D, con
     if (st != JFA_OK || B == 0) return st;
     if ((st = get_table(B, s, w)) != JFA_OK) return st;
     hipError_t e;
-    { ScopedTimer tm("schedule", s); e = jfa::launch_schedule(offsets, nullptr, (int)B, 128, w->order[0], w->tile_start[0], w->counters, jfa::kNumCounters, s); }
+    { ScopedTimer tm("schedule", s); const jfa::ScheduleJob job{offsets, nullptr, 128, w->order[0], w->tile_start[0]}; e = jfa::launch_schedules(&job, 1, (int)B, w->counters, jfa::kNumCounters, s); }
     if (e != hipSuccess) return hip_fail("schedule kernel", e);
     *sc = jfa::Schedule{w->order[0], w->tile_start[0], w->counters};
     return JFA_OK;

@@ -470,11 +470,15 @@ __device__ inline bool load_work(const WorkSlot *slot, Work &t) {
 
 // ---- launchers (each enqueues on `stream` and returns the launch status; `cus` = compute units of the device) ----
 
-// Scheduler: fills order / tile_start for the given row-block size and zeroes `n_counters` counters.  Blocks are
-// counted over `offsets`; samples are ordered by the length of the rows that stream past a block (offsets_other:
-// cross attention; nullptr: the sample's own length).
-hipError_t launch_schedule(const int64_t *offsets, const int64_t *offsets_other, int B, int block_rows, int32_t *order,
-                           int32_t *tile_start, int32_t *counters, int n_counters, hipStream_t stream);
+// Scheduler: fills order / tile_start of one or two schedules (jobs[0 .. n_jobs - 1]) of B samples and zeroes `n_counters`
+// counters.  Blocks of block_rows rows are counted over `offsets`; samples are ordered by the length of the rows that
+// stream past a block (offsets_other: cross attention; nullptr: the sample's own length).
+struct ScheduleJob {
+    const int64_t *offsets, *offsets_other;
+    int block_rows;
+    int32_t *order, *tile_start;
+};
+hipError_t launch_schedules(const ScheduleJob *jobs, int n_jobs, int B, int32_t *counters, int n_counters, hipStream_t stream);
 hipError_t launch_check_offsets(const int64_t *offsets, int B, int64_t max_len, int *flags, hipStream_t stream);
 
 // fp32 path
