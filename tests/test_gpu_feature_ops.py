@@ -102,3 +102,47 @@ def test_feature_ops_on_a_table_sized_workload():
     scaled_gate("jagged_dense_bmm", f64(binding.jfa_jagged_dense_bmm(xd, wd, offd, 200)), fo.jagged_dense_bmm(x, w, off))
     scaled_gate("jagged_jagged_bmm", f64(binding.jfa_jagged_jagged_bmm(xd, yd, offd, 200)), fo.jagged_jagged_bmm(x, y, off))
     gate_bf16("jagged_softmax", f64(binding.jfa_jagged_softmax(xd, offd, 200)), fo.jagged_softmax(x, off))
+
+
+@pytest.mark.parametrize("B", [1, 37, 6001])   # one workgroup, fewer samples than workgroups, more (claims decide who does what)
+def test_operators_follow_each_other_on_one_work_counter(B):
+    """The operators share a work counter that each leaves cleared for the next: back to back, behind other calls that use the
+    same work table, after the table has grown, and replayed from a graph, every result equals the first one bit for bit."""
+    from paper_2409_15373_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(58)
+    lens = torch.randint(0, 40, (B,), generator=torch.Generator().manual_seed(59))
+    off = torch.cat([torch.zeros(1, dtype=torch.int64), lens.cumsum(0)]).cuda()
+    n, D, T = max(int(off[-1]), 1), 32, 64
+    x, y = (torch.randn(n, d, device="cuda", generator=gen, dtype=torch.bfloat16) for d in (D, T))
+    w = torch.randn(B, D, T, device="cuda", generator=gen, dtype=torch.bfloat16)
+    big = torch.arange(20001, dtype=torch.int64, device="cuda")   # a larger batch: a new work table
+
+    def step():
+        return (binding.jfa_jagged_softmax(x, off, 64), binding.jfa_jagged_dense_bmm(x, w, off, 64),
+                binding.jfa_jagged_jagged_bmm(x, y, off, 64), binding.jfa_jagged_softmax_backward(x, x, off, 64))
+
+    def same(a, b):
+        return all(torch.equal(p, q) for p, q in zip(a, b))
+
+    s = torch.cuda.Stream()   # a stream of its own: its work table is new
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        first = [t.clone() for t in step()]
+        scale = float(first[1].float().abs().max()) + 1.0
+        ref = (torch.stack([x[i].float() @ w[b].float() for b in range(min(B, 40)) for i in range(int(off[b]), int(off[b + 1]))])
+               if int(off[-1]) else first[1][:0].float())
+        assert (first[1][:ref.shape[0]].float() - ref).abs().max() <= 1e-2 * scale if ref.numel() else True
+        assert same(step(), first)
+        binding.jfa_build_schedule(big, 128)   # grows the table, clears its counters
+        assert same(step(), first) and same(step(), first)
+        graph = torch.cuda.CUDAGraph()
+        s.synchronize()
+        with torch.cuda.graph(graph, stream=s):
+            out = step()
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert same(out, first)
+        with torch.cuda.stream(s):
+            assert same(step(), first)
+        torch.cuda.synchronize()
