@@ -1,4 +1,5 @@
-"""Check of the hand-placed waits in the fused dK/dV kernel and the few-query cross backward, on the compiler's assembly listing.
+"""Check of the hand-placed waits in the fused dK/dV kernel and the few-query cross backward, and of the wait states in front
+of the hand-written global -> LDS copies of all kernels, on the compiler's assembly listing.
 
     python -m paper_2409_15373_amd.check_lds_waits [source.hip ...]
 
@@ -23,6 +24,10 @@ import tempfile
 
 from . import build as _build
 
+# the sources whose kernels copy with bd_dma16 / bd_dma4 (jfa_lds.h)
+HAND_WRITTEN_COPIES = ["jfa_bwd_cross_fewq.hip", "jfa_bwd_dkv_dma.hip", "jfa_bwd_dq_dma.hip", "jfa_bwd_narrow.hip",
+                       "jfa_fwd_bf16_dma.hip", "jfa_fwd_cross_fewq.hip", "jfa_fwd_narrow.hip"]
+
 _REG = re.compile(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b")
 
 
@@ -33,6 +38,16 @@ def _regs(text: str) -> set:
             out.update(range(int(m.group(1)), int(m.group(2)) + 1))
         else:
             out.add(int(m.group(3)))
+    return out
+
+
+_SREG = re.compile(r"\bs\[(\d+):(\d+)\]|\bs(\d+)\b")
+
+
+def _scalar_regs(text: str) -> set:
+    out = set()
+    for m in _SREG.finditer(text):
+        out.update(range(int(m.group(1)), int(m.group(2)) + 1) if m.group(1) is not None else [int(m.group(3))])
     return out
 
 
@@ -99,6 +114,39 @@ def behind_partial_vmcnt_wait(listing: str, count: int) -> list:
     return found
 
 
+def scalar_operand_hazards(listing: str, needed: int = 5) -> list:
+    """Vector-memory instructions that read a scalar register fewer than `needed` wait states after a vector instruction
+    wrote it, as (line number, instruction, wait states in between).
+
+    The hardware does not hold such an instruction back: it may use the register's old value as its address.  The compiler
+    puts the wait states in front of its own instructions, but it does not look into inline assembly, and the scalar base
+    of a hand-written copy can come out of a vector instruction whenever scalar registers are spilled (v_readlane).  The
+    scan is linear in program order; an instruction counts one wait state, s_nop n counts n + 1.
+    """
+    written = {}   # scalar register -> wait states passed when a vector instruction wrote it last
+    now, found = 0, []
+    for ln, line in enumerate(listing.splitlines(), 1):
+        t = line.split(";")[0].strip()
+        if not t or t.startswith(".") or t.endswith(":"):
+            continue
+        op, _, rest = t.partition(" ")
+        if op == "s_nop":
+            now += int(rest, 0) + 1
+            continue
+        if op.startswith(("global_", "buffer_", "scratch_", "flat_")):
+            since = [now - written[r] for r in _scalar_regs(rest) if r in written]
+            if since and min(since) < needed:
+                found.append((ln, t, min(since)))
+        now += 1
+        dest = rest.split(",")[0]
+        if op.startswith("v_"):
+            written.update((r, now) for r in _scalar_regs(dest))
+        elif op.startswith("s_"):
+            for r in _scalar_regs(dest):
+                written.pop(r, None)
+    return found
+
+
 def listing_of(source: str) -> str:
     """The device assembly of one .hip source, compiled with the library's own flags."""
     with tempfile.TemporaryDirectory() as tmp:
@@ -125,6 +173,10 @@ def main(argv) -> int:
         found = behind_partial_vmcnt_wait(listing_of(os.path.join(_build.CSRC, "jfa_bwd_cross_fewq.hip")), 16)
         print(f"jfa_bwd_cross_fewq.hip: vmcnt(16) waits followed by (copies, stores, other vector-memory instructions) = {found}")
         bad += found != [(16, 16, 0)]
+        for name in HAND_WRITTEN_COPIES:
+            hazards = scalar_operand_hazards(listing_of(os.path.join(_build.CSRC, name)))
+            print(f"{name}: {len(hazards)} vector-memory instructions too close behind the write of their scalar base {hazards[:5]}")
+            bad += len(hazards)
     return 1 if bad else 0
 
 

@@ -77,3 +77,29 @@ def test_the_few_query_backward_leaves_exactly_its_stores_in_flight():
     dK and dV that may stay in flight, and no other vector-memory instruction (no scratch) in the block loop."""
     listing = check_lds_waits.listing_of(os.path.join(build.CSRC, "jfa_bwd_cross_fewq.hip"))
     assert check_lds_waits.behind_partial_vmcnt_wait(listing, 16) == [(16, 16, 0)]
+
+
+def test_scalar_operand_model():
+    close = """
+        v_readlane_b32 s5, v255, 18
+        s_mov_b32 m0, s1
+        s_nop 0
+        global_load_lds_dword v0, s[4:5]
+    """
+    assert [h[2] for h in check_lds_waits.scalar_operand_hazards(close)] == [2]
+    assert check_lds_waits.scalar_operand_hazards(close.replace("s_nop 0", "s_nop 3")) == []
+    assert len(check_lds_waits.scalar_operand_hazards(close.replace("s_nop 0", "s_nop 2"))) == 1
+    # a scalar instruction that writes the register in between: the vector instruction's value is not what is read
+    assert check_lds_waits.scalar_operand_hazards(close.replace("s_nop 0", "s_mov_b64 s[4:5], s[8:9]")) == []
+    # another register, or a vector address
+    assert check_lds_waits.scalar_operand_hazards(close.replace("s[4:5]", "s[6:7]")) == []
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs hipcc")
+@pytest.mark.parametrize("source", check_lds_waits.HAND_WRITTEN_COPIES)
+def test_no_copy_reads_its_scalar_base_too_early(source):
+    """The base of a hand-written copy may come out of a spill (v_readlane) right in front of it; the copy itself has to bring
+    the wait states that the hardware needs between the two."""
+    listing = check_lds_waits.listing_of(os.path.join(build.CSRC, source))
+    assert "global_load_lds" in listing
+    assert check_lds_waits.scalar_operand_hazards(listing) == []
