@@ -31,6 +31,9 @@
  *     work has run.  The library keeps a small private work table per (device, stream), O(B)
  *     bytes, see jfa_workspace_bytes; it is grown with hipMalloc on the first call that needs a
  *     larger one (never inside later calls of the same or smaller B) and kept until process exit.
+ *     Nothing in the table outlives a call.  Calls on one stream follow each other; what must not
+ *     overlap in time are executions that use the same stream's table, i.e. replays, on different
+ *     streams, of graphs captured on the same stream, or such a replay and calls on that stream.
  *   - Outputs must not alias inputs.  Rows >= sum_B of any buffer are neither read nor written.
  *   - Supported shapes: D in {32, 64, 128}; H >= 1; 0 <= B < 2^31 / 2; sum over samples of
  *     ceil(L_b / 64) times H below 2^31.

@@ -81,11 +81,6 @@ int get_table(int64_t B, hipStream_t stream, Views *v) {
         void *p = nullptr;
         e = hipMalloc(&p, need);
         if (e != hipSuccess) return fail(JFA_ERR_ALLOC, "hipMalloc(%zu) for the work table: %s", need, hipGetErrorString(e));
-        e = jfa::launch_zero_counters((int32_t *)p, jfa::kNumCounters, stream);
-        if (e != hipSuccess) {
-            (void)hipFree(p);
-            return fail(JFA_ERR_HIP, "clearing the work counters: %s", hipGetErrorString(e));
-        }
         t.base = (char *)p;
         t.bytes = need;
     }
@@ -683,7 +678,7 @@ int jfa_jagged_dense_bmm(const void *x, const void *w, const int64_t *offsets, i
     int st = feature_begin("jfa_jagged_dense_bmm", B, max_len, D, T, ptrs, 4, s, &v);
     if (st != JFA_OK || B == 0) return st;
     hipError_t e;
-    { ScopedTimer tm("jagged_dense_bmm", s); e = jfa::launch_jagged_dense_bmm(x, w, offsets, (int)B, D, T, v.counters + jfa::kFeatureCounter, out, v.cus, s); }
+    { ScopedTimer tm("jagged_dense_bmm", s); e = jfa::launch_jagged_dense_bmm(x, w, offsets, (int)B, D, T, v.counters, out, v.cus, s); }
     if (e != hipSuccess) return hip_fail("jagged_dense_bmm kernel", e);
     return JFA_OK;
 }
@@ -696,7 +691,7 @@ int jfa_jagged_jagged_bmm(const void *x, const void *y, const int64_t *offsets, 
     int st = feature_begin("jfa_jagged_jagged_bmm", B, max_len, D, T, ptrs, 4, s, &v);
     if (st != JFA_OK || B == 0) return st;
     hipError_t e;
-    { ScopedTimer tm("jagged_jagged_bmm", s); e = jfa::launch_jagged_jagged_bmm(x, y, offsets, (int)B, D, T, v.counters + jfa::kFeatureCounter, out, v.cus, s); }
+    { ScopedTimer tm("jagged_jagged_bmm", s); e = jfa::launch_jagged_jagged_bmm(x, y, offsets, (int)B, D, T, v.counters, out, v.cus, s); }
     if (e != hipSuccess) return hip_fail("jagged_jagged_bmm kernel", e);
     return JFA_OK;
 }
@@ -708,7 +703,7 @@ int jfa_jagged_softmax(const void *x, const int64_t *offsets, int64_t B, int64_t
     int st = feature_begin("jfa_jagged_softmax", B, max_len, D, 32, ptrs, 3, s, &v);
     if (st != JFA_OK || B == 0) return st;
     hipError_t e;
-    { ScopedTimer tm("jagged_softmax", s); e = jfa::launch_jagged_softmax(false, x, nullptr, offsets, (int)B, D, v.counters + jfa::kFeatureCounter, y, v.cus, s); }
+    { ScopedTimer tm("jagged_softmax", s); e = jfa::launch_jagged_softmax(false, x, nullptr, offsets, (int)B, D, v.counters, y, v.cus, s); }
     if (e != hipSuccess) return hip_fail("jagged_softmax kernel", e);
     return JFA_OK;
 }
@@ -721,7 +716,7 @@ int jfa_jagged_softmax_backward(const void *y, const void *dy, const int64_t *of
     int st = feature_begin("jfa_jagged_softmax_backward", B, max_len, D, 32, ptrs, 4, s, &v);
     if (st != JFA_OK || B == 0) return st;
     hipError_t e;
-    { ScopedTimer tm("jagged_softmax_bwd", s); e = jfa::launch_jagged_softmax(true, y, dy, offsets, (int)B, D, v.counters + jfa::kFeatureCounter, dx, v.cus, s); }
+    { ScopedTimer tm("jagged_softmax_bwd", s); e = jfa::launch_jagged_softmax(true, y, dy, offsets, (int)B, D, v.counters, dx, v.cus, s); }
     if (e != hipSuccess) return hip_fail("jagged_softmax backward kernel", e);
     return JFA_OK;
 }

@@ -479,8 +479,6 @@ struct ScheduleJob {
     int32_t *order, *tile_start;
 };
 hipError_t launch_schedules(const ScheduleJob *jobs, int n_jobs, int B, int32_t *counters, int n_counters, hipStream_t stream);
-// Zeroes `n` work counters: a new table's, before its first use.
-hipError_t launch_zero_counters(int32_t *counters, int n, hipStream_t stream);
 hipError_t launch_check_offsets(const int64_t *offsets, int B, int64_t max_len, int *flags, hipStream_t stream);
 
 // fp32 path
@@ -572,8 +570,7 @@ hipError_t launch_unfused_apply(const float *probs, const void *v, const int64_t
 hipError_t launch_convert(bool to_dense, const void *src, void *dst, const int64_t *offsets, int B, int64_t max_len,
                           int64_t row_chunks, uint32_t pad, int cus, hipStream_t stream);
 
-// Jagged feature operators (Table 1); `counter`: a work counter that is zero before every kernel and zero again after it.
-constexpr int kFeatureCounter = 32;   // where it is in the work table: nothing else uses it
+// Jagged feature operators (Table 1); `counter` is one work counter, cleared by the launcher where the kernel looks at it.
 hipError_t launch_jagged_dense_bmm(const void *x, const void *w, const int64_t *offsets, int B, int D, int T,
                                    int32_t *counter, void *out, int cus, hipStream_t stream);
 hipError_t launch_jagged_jagged_bmm(const void *x, const void *y, const int64_t *offsets, int B, int D, int T,

@@ -34,36 +34,32 @@ __device__ inline bf16x8 tr_operand(const char *tile, int off, int step, int blo
 
 // Per-sample work items in sample order: the first statically, the rest by one atomic each (dynamic claims even out
 // samples of different lengths; an offsets-sorted order would cost a scheduler launch that takes longer than it saves).
-// The counter is zero when a kernel starts and the last claim leaves it so.  Cleared by a launch of its own before every
-// operator it cost 1.5 to 5 us: five operators on a small batch 21.5 -> 16 us.  (Counting the workgroups that are done instead
-// costs an atomic each at the end, 8 us of contention per operator on 16384 samples.)
-__global__ void zero_counters_kernel(int32_t *counters, int n) { if ((int)threadIdx.x < n) counters[threadIdx.x] = 0; }
-
 // Samples are claimed kClaimGroup consecutive ones at a time (`group` holds the current group between calls).  With
 // 64-byte rows a sample is a few kilobytes and a claim per sample costs more than moving it: two per claim took the
 // operators at D = T = 32 from 2.6 - 3.8 to 2.9 - 5.3 TB/s; with longer rows pairs only unbalance the workgroups (2 - 4 %
 // slower at 128- and 256-byte rows), so those claim one at a time.
-// Every workgroup with a static group makes one claim after each complete group that it has done, so a kernel makes
-// B / kClaimGroup claims (a last, incomplete group ends its workgroup without one), whatever the grid: the claim that
-// returns the last of these numbers is the last access to the counter.
+// A batch of at most one group per workgroup is all static: no counter is looked at, and the launcher does not clear one.
+// For larger ones the counter is cleared by a launch before every operator.  (A counter that the last claim of a kernel
+// leaves cleared for the next would save that launch, 1.5 us, but whatever disturbs it once -- a table first used while a
+// graph is captured, two replays that overlap -- makes later operators skip samples.)
+__global__ void reset_counter_kernel(int32_t *counter) { if (threadIdx.x == 0) *counter = 0; }
+template <int kClaimGroup> __host__ __device__ inline bool all_static(int B, int grid) { return (int64_t)grid * kClaimGroup >= B; }
+
 template <int kClaimGroup>
 __device__ inline int claim_sample(int32_t *counter, int B, int n_claimed, int *slot, int &group) {
     __syncthreads();
     if (n_claimed % kClaimGroup == 0) {
-        if (threadIdx.x == 0) {
-            int next = blockIdx.x;
-            if (n_claimed != 0) {
-                next = atomicAdd(counter, 1);
-                if (next == B / kClaimGroup - 1) atomicExch(counter, 0);
-                next += gridDim.x;
-            }
-            *slot = next;
-        }
+        if (n_claimed != 0 && all_static<kClaimGroup>(B, (int)gridDim.x)) return B;
+        if (threadIdx.x == 0) *slot = n_claimed == 0 ? (int)blockIdx.x : (int)gridDim.x + atomicAdd(counter, 1);
         __syncthreads();
         group = __builtin_amdgcn_readfirstlane(*slot);
     }
     return group * kClaimGroup + n_claimed % kClaimGroup;
 }
+
+// Samples per claim: bytes of a sample's row in all the tensors that follow its lengths.
+template <int D, int T> constexpr int bmm_claim_group() { return D + T <= 64 ? 2 : 1; }
+template <int D> constexpr int softmax_claim_group() { return D <= 32 ? 2 : 1; }
 
 // ---- jagged_dense_bmm: out^T = w_b^T x^T, one sample per workgroup step, 128 rows at a time ----
 // w_b goes to LDS once per sample.  Wave w owns rows 32 w .. 32 w + 31 of every 128-row block: its x rows and,
@@ -87,7 +83,7 @@ __global__ __launch_bounds__(kFoThreads) void jagged_dense_bmm_kernel(const __bf
     char *mine = xt + wave * kRegion;
     int group = 0;
     for (int n_claimed = 0;; ++n_claimed) {
-        const int p = claim_sample<(D + T <= 64 ? 2 : 1)>(counter, B, n_claimed, &slot, group);   // also: the previous sample's LDS tiles are free
+        const int p = claim_sample<bmm_claim_group<D, T>()>(counter, B, n_claimed, &slot, group);   // also: the previous sample's LDS tiles are free
         if (p >= B) break;
         const int b = p;
         const int64_t row0 = offsets[b];
@@ -186,7 +182,7 @@ __global__ __launch_bounds__(kFoThreads) void jagged_jagged_bmm_kernel(const __b
     const int xoff = tr_lane_offset(lane, kXRow), yoff = tr_lane_offset(lane, kYRow);
     int group = 0;
     for (int n_claimed = 0;; ++n_claimed) {
-        const int p = claim_sample<(D + T <= 64 ? 2 : 1)>(counter, B, n_claimed, &slot, group);   // also: the previous sample's LDS tiles are free
+        const int p = claim_sample<bmm_claim_group<D, T>()>(counter, B, n_claimed, &slot, group);   // also: the previous sample's LDS tiles are free
         if (p >= B) break;
         const int b = p;
         const int64_t row0 = offsets[b];
@@ -283,7 +279,7 @@ __global__ __launch_bounds__(kFoThreads) void jagged_softmax_kernel(const __bf16
     const int cg = tid % kGroups, rl = tid / kGroups;
     int group = 0;
     for (int n_claimed = 0;; ++n_claimed) {
-        const int p = claim_sample<(D <= 32 ? 2 : 1)>(counter, B, n_claimed, &slot, group);   // also: the previous sample's statistics have been read
+        const int p = claim_sample<softmax_claim_group<D>()>(counter, B, n_claimed, &slot, group);   // also: the previous sample's statistics have been read
         if (p >= B) break;
         const int b = p;
         const int64_t row0 = offsets[b];
@@ -410,23 +406,21 @@ __global__ __launch_bounds__(kFoThreads) void jagged_softmax_kernel(const __bf16
     }
 #define JFA_DT_CASE(KERNEL, DD, TT, ...)                                                                         \
     case DD * 1000 + TT:                                                                                         \
-        hipLaunchKernelGGL((KERNEL<DD, TT>), dim3(persistent_grid<KERNEL<DD, TT>>(kFoThreads, cus)), dim3(kFoThreads), 0, \
-                           stream, __VA_ARGS__);                                                                 \
+        grid = persistent_grid<KERNEL<DD, TT>>(kFoThreads, cus);                                                 \
+        if (!all_static<bmm_claim_group<DD, TT>()>(B, grid)) hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, stream, counter); \
+        hipLaunchKernelGGL((KERNEL<DD, TT>), dim3(grid), dim3(kFoThreads), 0, stream, __VA_ARGS__);              \
         break;
-
-hipError_t launch_zero_counters(int32_t *counters, int n, hipStream_t stream) {
-    hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, stream, counters, n);
-    return hipGetLastError();
-}
 
 hipError_t launch_jagged_dense_bmm(const void *x, const void *w, const int64_t *offsets, int B, int D, int T, int32_t *counter,
                                    void *out, int cus, hipStream_t stream) {
+    int grid;
     JFA_DT_CASES(jagged_dense_bmm_kernel, (const __bf16 *)x, (const __bf16 *)w, offsets, B, counter, (__bf16 *)out)
     return hipGetLastError();
 }
 
 hipError_t launch_jagged_jagged_bmm(const void *x, const void *y, const int64_t *offsets, int B, int D, int T, int32_t *counter,
                                     void *out, int cus, hipStream_t stream) {
+    int grid;
     JFA_DT_CASES(jagged_jagged_bmm_kernel, (const __bf16 *)x, (const __bf16 *)y, offsets, B, counter, (__bf16 *)out)
     return hipGetLastError();
 }
@@ -436,12 +430,10 @@ hipError_t launch_jagged_jagged_bmm(const void *x, const void *y, const int64_t 
 template <int D>
 static hipError_t launch_softmax_d(bool backward, const __bf16 *a, const __bf16 *g, const int64_t *offsets, int B, int32_t *s,
                                    __bf16 *out, int cus, hipStream_t stream) {
-    if (backward)
-        hipLaunchKernelGGL((jagged_softmax_kernel<D, true>), dim3(persistent_grid<jagged_softmax_kernel<D, true>>(kFoThreads, cus)),
-                           dim3(kFoThreads), 0, stream, a, g, offsets, B, s, out);
-    else
-        hipLaunchKernelGGL((jagged_softmax_kernel<D, false>), dim3(persistent_grid<jagged_softmax_kernel<D, false>>(kFoThreads, cus)),
-                           dim3(kFoThreads), 0, stream, a, g, offsets, B, s, out);
+    const int grid = backward ? persistent_grid<jagged_softmax_kernel<D, true>>(kFoThreads, cus) : persistent_grid<jagged_softmax_kernel<D, false>>(kFoThreads, cus);
+    if (!all_static<softmax_claim_group<D>()>(B, grid)) hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, stream, s);
+    if (backward) hipLaunchKernelGGL((jagged_softmax_kernel<D, true>), dim3(grid), dim3(kFoThreads), 0, stream, a, g, offsets, B, s, out);
+    else hipLaunchKernelGGL((jagged_softmax_kernel<D, false>), dim3(grid), dim3(kFoThreads), 0, stream, a, g, offsets, B, s, out);
     return hipGetLastError();
 }
 
