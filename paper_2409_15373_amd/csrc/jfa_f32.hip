@@ -17,8 +17,7 @@
 // accumulator register v is then the B operand of the next product's step v (streamed rows (v / 4) 8 + 4 (l / 32) + v % 4
 // as its two slots), whose A operand is one element per lane of the transposed streamed tile, read row by row.
 // Measured at B = 256, H = 2, D = 64, lengths uniform on [1, 512] against the former kernels (vector FMA, a row per four
-// lanes, scores one by one): forward 589 -> 181 us, forward + backward 1861 -> 682 us; four samples of at
-// most 64 rows (D = 32, forward) 23 -> 11 us, of which 10 are the kernel.
+// lanes, scores one by one): forward 589 -> 182 us, forward + backward 1861 -> 689 us.
 #include "jfa_common.h"
 #include "jfa_mfma.h"
 #include "jfa_lds.h"
@@ -94,17 +93,38 @@ __device__ inline int not_hoisted(int x) {
     return x;
 }
 
-// acc += (32 streamed rows at `block`) (stationary rows)^T; at: row_read_at
-template <int D> __device__ inline void product(f32x16 &acc, const char *block, int at, const float (&x)[D / 2]) {
+// exp(x).  The argument is a difference (score minus maximum or log-sum-exp) of numbers that may be much larger than it:
+// scaled in one rounding together with the subtraction, and only the difference times log2(e).  (Both sides of the difference
+// times log2(e) first, one vector instruction less per score: the gradients' error was 1.3 times this at scores of standard
+// deviation 1 and 1.4 times at 16.)
+__device__ inline float exp_f32(float x) { return fast_exp2(x * 1.4426950408889634f); }
+
+// (32 streamed rows at `block`) (stationary rows)^T; at: row_read_at.  A score's error grows with the length of the chains of
+// additions it comes from, and the exponential turns it into a relative error of the probability: the D features are summed
+// in four chains, as four lanes of a vector kernel would.  One chain: the gradients' error at scores of standard deviation 16
+// is 1.5 (D = 32), 1.8 (64) and 2.1 times this (128); eight chains: 0.99 and 0.92 times at D = 64 and 128, time + 5 %.
+// Both together, microseconds of forward and backward at B = 256, H = 2, lengths to 512: D = 32 85 + 279 -> 94 + 290,
+// D = 64 180 + 510 -> 182 + 514, D = 128 325 + 1166 -> 336 + 1166.
+template <int D> __device__ inline f32x16 product(const char *block, int at, const float (&x)[D / 2]) {
+    constexpr int kChains = 4, kGroups = D / 8 / kChains;   // a chain's 16-byte reads
+    f32x16 sum;
     at = not_hoisted(at);
 #pragma unroll
-    for (int g = 0; g < D / 8; ++g) {
-        const float4 a = *reinterpret_cast<const float4 *>(block + (at ^ (g << 5)));
-        acc = mfma_f32(a.x, x[4 * g], acc);
-        acc = mfma_f32(a.y, x[4 * g + 1], acc);
-        acc = mfma_f32(a.z, x[4 * g + 2], acc);
-        acc = mfma_f32(a.w, x[4 * g + 3], acc);
+    for (int ch = 0; ch < kChains; ++ch) {
+        f32x16 acc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+#pragma unroll
+        for (int g = ch * kGroups; g < (ch + 1) * kGroups; ++g) {
+            const float4 a = *reinterpret_cast<const float4 *>(block + (at ^ (g << 5)));
+            acc = mfma_f32(a.x, x[4 * g], acc);
+            acc = mfma_f32(a.y, x[4 * g + 1], acc);
+            acc = mfma_f32(a.z, x[4 * g + 2], acc);
+            acc = mfma_f32(a.w, x[4 * g + 3], acc);
+        }
+        sum = ch == 0 ? acc : sum + acc;
     }
+    return sum;
 }
 
 // acc^T += (32 streamed rows at `block`)^T p, p in accumulator layout; at: element_read_at
@@ -188,7 +208,6 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
     const int rg = wave & 1, part = wave >> 1;   // group of 32 queries; half of the stage's keys
     const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
     const float scale = 1.0f / sqrtf((float)D);
-    const float c = 1.4426950408889634f * scale;
     const bool small = s.build_rows != 0;   // small problem: no scheduler launch has run, the schedule is built here, in LDS
     if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
     const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
@@ -217,17 +236,14 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
         load_operand<D>(qr, q + (t.row0 + iq) * row_stride + (int64_t)t.head * D, half);
         f32x16 o[D / 32];
         clear<D>(o);
-        float m = -INFINITY, l = 0.0f;   // running maximum of the raw scores; this lane's share of the row sum
+        float m = -INFINITY, l = 0.0f;   // running maximum of the scores; this lane's share of the row sum
         stage_barrier();
         for (int j0 = 0, buf = 0; j0 < Lc; j0 += kCols, buf ^= 1) {
             if (j0 + kCols < Lc) issue(j0 + kCols, buf ^ 1);
             const int k0 = j0 + part * 32;             // first key of the wave's block
             if (active && k0 < Lc && !(causal && k0 > q0 + 31)) {
                 const char *kt = sm + buf * kStage + part * (32 * 4 * D), *vt = kt + kTile;
-                f32x16 st;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) st[e] = 0.0f;
-                product<D>(st, kt, row_at, qr);
+                f32x16 st = product<D>(kt, row_at, qr);
                 if (k0 + 32 > L || (causal && k0 + 31 > q0)) {   // keys past the sample's end or above the diagonal
                     const int lim = (causal && iq + 1 < L ? iq + 1 : L) - k0;
 #pragma unroll
@@ -237,14 +253,13 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
                 float mx = st[0];
 #pragma unroll
                 for (int e = 1; e < 16; ++e) mx = fmaxf(mx, st[e]);
-                const float m_new = fmaxf(m, pair_max(mx));   // finite: every query of a block that is not skipped sees one of its keys
-                const float a = fast_exp2((m - m_new) * c);   // exp2(-inf) = 0 on the first block
-                const float mc = m_new * c;
+                const float m_new = fmaxf(m, pair_max(mx) * scale);   // finite: every query of a block that is not skipped sees one of its keys
+                const float a = exp_f32(m - m_new);   // exp(-inf) = 0 on the first block
                 m = m_new;
                 l *= a;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    st[e] = fast_exp2(fmaf(st[e], c, -mc));
+                    st[e] = exp_f32(fmaf(st[e], scale, -m));
                     l += st[e];
                 }
 #pragma unroll
@@ -266,12 +281,12 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
         if (part == 0 && i < t.len) {
             const float2 ml = other_ml[rg][col];
             const float m_all = fmaxf(m, ml.x);
-            const float a = m_all > -INFINITY ? fast_exp2((m - m_all) * c) : 0.0f;      // a sample without keys: out = 0, lse = -inf
-            const float b = m_all > -INFINITY ? fast_exp2((ml.x - m_all) * c) : 0.0f;
+            const float a = m_all > -INFINITY ? exp_f32(m - m_all) : 0.0f;      // a sample without keys: out = 0, lse = -inf
+            const float b = m_all > -INFINITY ? exp_f32(ml.x - m_all) : 0.0f;
             const float l_all = l * a + ml.y * b;
             merge<D>(o, region, lane, a, b);
             store_row<D>(out + (t.row0 + i) * row_stride + (int64_t)t.head * D, o, l_all > 0.0f ? 1.0f / l_all : 0.0f, half);
-            if (half == 0) lse[(int64_t)t.head * sum_B + t.row0 + i] = m_all * scale + logf(l_all);
+            if (half == 0) lse[(int64_t)t.head * sum_B + t.row0 + i] = m_all + logf(l_all);
         }
     }
 }
@@ -294,7 +309,6 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kern
     const int rg = wave & 1, part = wave >> 1;   // group of 32 queries; half of the stage's keys
     const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
     const float scale = 1.0f / sqrtf((float)D);
-    const float c = 1.4426950408889634f * scale;
     const bool small = s.build_rows != 0;
     if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
     const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
@@ -329,7 +343,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kern
             dot = fmaf(dor[4 * g], f.x, fmaf(dor[4 * g + 1], f.y, fmaf(dor[4 * g + 2], f.z, fmaf(dor[4 * g + 3], f.w, dot))));
         }
         const float delta_i = pair_sum(dot);   // the two lanes of a row hold half of its features each
-        const float lse2 = lse[(int64_t)t.head * sum_B + t.row0 + iq] * 1.4426950408889634f;
+        const float lse_i = lse[(int64_t)t.head * sum_B + t.row0 + iq];
         if (part == 0 && i < t.len && half == 0) delta[(int64_t)t.head * sum_B + t.row0 + i] = delta_i;
         f32x16 acc[D / 32];
         clear<D>(acc);
@@ -339,18 +353,15 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kern
             const int k0 = j0 + part * 32;
             if (active && k0 < Lc && !(causal && k0 > q0 + 31)) {
                 const char *kt = sm + buf * kStage + part * (32 * 4 * D), *vt = kt + kTile;
-                f32x16 st, dp;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) { st[e] = 0.0f; dp[e] = -delta_i; }
-                product<D>(st, kt, row_at, qr);
-                product<D>(dp, vt, row_at, dor);
+                f32x16 st = product<D>(kt, row_at, qr);
+                const f32x16 dp = product<D>(vt, row_at, dor);
                 const bool masked = k0 + 32 > L || (causal && k0 + 31 > q0);
                 const int lim = (causal && iq + 1 < L ? iq + 1 : L) - k0;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    float p = fast_exp2(fmaf(st[e], c, -lse2));
+                    float p = exp_f32(fmaf(st[e], scale, -lse_i));
                     if (masked && acc_row(e, half) >= lim) p = 0.0f;
-                    st[e] = p * dp[e];
+                    st[e] = p * (dp[e] - delta_i);
                 }
                 accumulate<D>(acc, kt, elem_at, st);
             }
@@ -376,7 +387,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
         float *__restrict__ dv) {
     constexpr int kTile = f32_tile_bytes<D>(), kStage = f32_stage_bytes<D>();
     __shared__ __attribute__((aligned(1024))) char sm[2 * kStage];   // two stages of Q rows, then dO rows
-    __shared__ float lse2_s[2][kCols], delta_s[2][kCols];             // log2(e) lse and delta of the streamed rows
+    __shared__ float lse_s[2][kCols], delta_s[2][kCols];              // lse and delta of the streamed rows
     __shared__ int64_t slot;
     __shared__ SmallWork mine;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -384,7 +395,6 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
     const int rg = wave & 1, part = wave >> 1;   // group of 32 keys; half of the stage's queries
     const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
     const float scale = 1.0f / sqrtf((float)D);
-    const float c = 1.4426950408889634f * scale;
     const bool small = s.build_rows != 0;
     if (small) build_small_work(offsets, offsets_q, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
     const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
@@ -414,12 +424,12 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
         auto fetch_stats = [&](int i0) {
             if (tid < kCols) {
                 const int i = i0 + tid < L ? i0 + tid : L - 1;
-                lse_next = lse_rows[i] * 1.4426950408889634f;
+                lse_next = lse_rows[i];
                 delta_next = delta_rows[i];
             }
         };
         auto store_stats = [&](int buf) {
-            if (tid < kCols) { lse2_s[buf][tid] = lse_next; delta_s[buf][tid] = delta_next; }
+            if (tid < kCols) { lse_s[buf][tid] = lse_next; delta_s[buf][tid] = delta_next; }
         };
         if (istart < L) {
             issue(istart, 0);
@@ -443,29 +453,21 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
             const int r0 = i0 + part * 32;             // first query of the wave's block
             if (active && r0 < L && !(causal && r0 + 31 < k0)) {
                 const char *qt = sm + buf * kStage + part * (32 * 4 * D), *ot = qt + kTile;
-                f32x16 st, dp;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const float4 d4 = *reinterpret_cast<const float4 *>(&delta_s[buf][part * 32 + g * 8 + half * 4]);
-                    dp[4 * g] = -d4.x; dp[4 * g + 1] = -d4.y; dp[4 * g + 2] = -d4.z; dp[4 * g + 3] = -d4.w;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) st[4 * g + e] = 0.0f;
-                }
-                product<D>(st, qt, row_at, kr);
-                product<D>(dp, ot, row_at, vr);
+                f32x16 st = product<D>(qt, row_at, kr);
+                f32x16 dp = product<D>(ot, row_at, vr);
                 const bool masked = r0 + 32 > L || (causal && r0 < k0 + 31);
                 const int lo = causal ? j - r0 : 0, hi = L - r0;   // this lane's key is seen by block rows lo .. hi - 1
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const float4 l4 = *reinterpret_cast<const float4 *>(&lse2_s[buf][part * 32 + g * 8 + half * 4]);
-                    const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
+                    const f32x4 l4 = *reinterpret_cast<const f32x4 *>(&lse_s[buf][part * 32 + g * 8 + half * 4]);
+                    const f32x4 d4 = *reinterpret_cast<const f32x4 *>(&delta_s[buf][part * 32 + g * 8 + half * 4]);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int r = acc_row(4 * g + e, half);
-                        float p = fast_exp2(fmaf(st[4 * g + e], c, -lv[e]));
+                        float p = exp_f32(fmaf(st[4 * g + e], scale, -l4[e]));
                         if (masked && (r < lo || r >= hi)) p = 0.0f;
                         st[4 * g + e] = p;
-                        dp[4 * g + e] *= p;
+                        dp[4 * g + e] = p * (dp[4 * g + e] - d4[e]);
                     }
                 }
                 accumulate<D>(accv, ot, elem_at, st);
