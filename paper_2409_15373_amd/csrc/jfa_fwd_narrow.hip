@@ -6,9 +6,10 @@
 // hardly overlap on a SIMD (a stage of 64 keys takes a wave's SIMD 1070 clocks at D = 64, 720 at D = 32: about 44 per
 // matrix instruction and 3.8 per vector instruction), so vector instructions are what bounds these sizes, and on short
 // samples a tile's start-up:
-//   * exponentials are taken against a FIXED reference maximum per query (the maximum over the first 64 keys): a score is
-//     one multiply-add, one exponential and half of a conversion and of a row-sum step, with no running maximum.  A row sum
-//     above 2^62 (or not finite) at the end makes the workgroup redo the tile maximum first (never on scores of one scale);
+//   * exponentials are taken against a reference maximum per query that is left alone while it does (the maximum over the
+//     first 64 keys at first): a score is one multiply-add, one exponential and half of a conversion and of a row-sum step,
+//     with no running maximum.  A stage in which a lane's 32 probabilities add up to 2^8 (kStale; so surely one with a
+//     probability of 2^8, and surely none whose probabilities are all below 2^3) is taken again maximum first;
 //   * stages go directly to LDS, one ahead, into unpadded swizzled buffers (jfa_narrow.h): no staging registers, no LDS
 //     stores, one barrier per stage;
 //   * three (D = 64) or four workgroups per compute unit, which are not in step, fill each other's start-up (one more of
@@ -21,6 +22,9 @@
 
 namespace jfa {
 
+// Sum of a lane's 32 probabilities of a stage from which on the reference maximum is stale.
+constexpr float kStale = 0x1p8f;
+
 // CROSS: keys and values are the rows of a second offsets array; CAUSAL: query i sees keys 0 .. i.  See fwd_bf16_kernel.
 template <int D, bool CROSS, bool CAUSAL>
 __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel(
@@ -30,12 +34,12 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
     constexpr int kKSteps = D / 16, kDBlocks = D / 32;
     __shared__ __attribute__((aligned(1024))) char st[kNwStages * N::kStage];   // buffer b: K at b * kStage, V behind it
     __shared__ typename NarrowWalk<CROSS>::Shared walk_mem;
-    __shared__ int restart;   // set by a wave whose reference maximum went stale beyond repair
     static_assert(sizeof(st) >= kInlineScratchInts * sizeof(int), "the stage buffers double as the scheduler's scratch");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
     const float c = 1.4426950408889634f / sqrtf((float)D);   // log2(e) / sqrt(D): exp(x / sqrt(D)) = exp2(c x)
+    const float tau = 8.0f / c;                              // a factor of 2^8
     const int64_t row_stride = (int64_t)H * D;
     const int64_t sum_B = offsets[B];
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
@@ -89,9 +93,14 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
             const int n_full = (CAUSAL && q0 + 1 < L ? q0 + 1 : L) / kNwStageRows;
             const int n_mine = !wave_active ? 0 : CAUSAL ? q0 / kNwStageRows + 1 : n_stages;
 
-            // One stage.  safe: maximum first, with rescaling (a tile's first stage, which sets the reference, and tiles that are
-            // redone); otherwise against the reference as it is.  Both flags are the same in every lane.
-            auto run_block = [&](const char *kt, int j, bool safe, bool masked) {
+            // One stage.  maximum_first: a reference that the stage's largest score exceeds by more than 2^8 is raised to it, with
+            // rescaling, before the exponentials are taken (a tile's first stage sets the reference that way).  Otherwise they
+            // are taken against the reference as it is; if their sum says that it may be stale, once more maximum first, and so
+            // in all the tile's later stages of this wave: scores that rise that far do so again.  The flags are the same in
+            // every lane.  (`raise` is false by itself in the steady stages: a test of maximum_first between the score products
+            // and the exponentials keeps them from overlapping, 3 to 5 % of the kernel.)
+            bool maximum_first = true;
+            auto run_block = [&](const char *kt, bool raise, bool masked, int j) {
                 const char *const vt = kt + N::kTile;
                 f32x16 a[2];
 #pragma unroll
@@ -110,42 +119,51 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
                         for (int e = 0; e < 16; ++e)
                             if (mb * 32 + (e >> 2) * 8 + (e & 3) >= lim) a[mb][e] = -INFINITY;
                 }
-                if (safe) {
-                    float mx = -INFINITY;
+                // Probabilities, rounded to bf16 (the values the second product and the row sum use).
+                u32x4 pw[4];
+                float stage_sum;
+                for (;;) {
+                    if (raise) {
+                        float mx = -INFINITY;
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) mx = fmaxf(fmaxf(mx, a[0][e]), a[1][e]);
-                    const float n = fmaxf(m, pair_max(mx));
-                    if (j > 0) {
-                        const float alpha = fast_exp2((m - n) * c);
-                        lsum *= alpha;
+                        for (int e = 0; e < 16; ++e) mx = fmaxf(fmaxf(mx, a[0][e]), a[1][e]);
+                        mx = pair_max(mx);
+                        if (__builtin_amdgcn_ballot_w64(mx > m + tau) != 0) {
+                            const float n = fmaxf(m, mx);
+                            const float alpha = fast_exp2((m - n) * c);   // exp2(-inf) = 0 in the first stage
+                            m = n;
+                            lsum *= alpha;
 #pragma unroll
-                        for (int db = 0; db < kDBlocks; ++db)
+                            for (int db = 0; db < kDBlocks; ++db)
 #pragma unroll
-                            for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+                                for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
+                        }
                     }
-                    m = n;
+                    const float mc = m * c;
+                    float part[2] = {0.0f, 0.0f};
+#pragma unroll
+                    for (int ts = 0; ts < 4; ++ts)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            bf16x2 pr;
+                            pr[0] = (__bf16)fast_exp2(fmaf(a[ts >> 1][8 * (ts & 1) + 2 * e], c, -mc));
+                            pr[1] = (__bf16)fast_exp2(fmaf(a[ts >> 1][8 * (ts & 1) + 2 * e + 1], c, -mc));
+                            part[ts & 1] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, part[ts & 1], false);
+                            pw[ts][e] = __builtin_bit_cast(uint32_t, pr);
+                        }
+                    stage_sum = part[0] + part[1];
+                    if (raise || __builtin_amdgcn_ballot_w64(!(stage_sum < kStale)) == 0) break;
+                    raise = maximum_first = true;
                 }
-                // Probabilities, rounded to bf16 (the values the second product and the row sum use), and O^T += V^T P^T.  Slot e
-                // of a 16-key step is key 8 (e / 4) + 4 half + e % 4.
-                const float mc = m * c;
+                lsum += stage_sum;
+                // O^T += V^T P^T.  Slot e of a 16-key step is key 8 (e / 4) + 4 half + e % 4.
 #pragma unroll
-                for (int ts = 0; ts < 4; ++ts) {
-                    u32x4 pw;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        bf16x2 pr;
-                        pr[0] = (__bf16)fast_exp2(fmaf(a[ts >> 1][8 * (ts & 1) + 2 * e], c, -mc));
-                        pr[1] = (__bf16)fast_exp2(fmaf(a[ts >> 1][8 * (ts & 1) + 2 * e + 1], c, -mc));
-                        lsum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum, false);
-                        pw[e] = __builtin_bit_cast(uint32_t, pr);
-                    }
-                    const bf16x8 p = __builtin_bit_cast(bf16x8, pw);
+                for (int ts = 0; ts < 4; ++ts)
 #pragma unroll
                     for (int db = 0; db < kDBlocks; ++db) {
                         const char *pv = vt + ts * 16 * N::kRow;
-                        o[db] = mfma_32x32x16(concat(lds_read_tr16(pv + at.tr[0][db]), lds_read_tr16(pv + at.tr[1][db])), p, o[db]);
+                        o[db] = mfma_32x32x16(concat(lds_read_tr16(pv + at.tr[0][db]), lds_read_tr16(pv + at.tr[1][db])), __builtin_bit_cast(bf16x8, pw[ts]), o[db]);
                     }
-                }
             };
             // The copies of stage j + 1 go into the other buffer, which stage j - 1 has released, while stage j is computed.
             auto end_stage = [&]() {
@@ -154,42 +172,23 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
             };
-            if (tid == 0) restart = 0;   // nobody looks at it between the previous tile's check and this barrier
             end_stage();   // stage 0 has landed
             // stages unmasked for every wave of the tile (a causal tile's first wave has the fewest)
             const int n_plain = (CAUSAL && t.block * kFwdBlockRows + 1 < L ? t.block * kFwdBlockRows + 1 : L) / kNwStageRows;
-            bool redo = false;
-            int j = 0;
-            for (;;) {
-                for (; j < n_stages; ++j) {
-                    if (!redo) {   // two steady stages at a time: buffers 1 and 0, offsets in the instructions
-                        for (; (j & 1) && j + 3 <= n_plain; j += 2) {
-                            copier.template copy<true>(kbase, vbase, (j + 1) * kNwStageRows, L, st);
-                            if (wave_active) run_block(st + N::kStage, j, false, false);
-                            end_stage();
-                            copier.template copy<true>(kbase, vbase, (j + 2) * kNwStageRows, L, st + N::kStage);
-                            if (wave_active) run_block(st, j + 1, false, false);
-                            end_stage();
-                        }
-                    }
-                    char *const here = st + (j & 1) * N::kStage, *const other = st + (~j & 1) * N::kStage;
-                    if (j + 1 < n_stages) copier.copy(kbase, vbase, (j + 1) * kNwStageRows, L, other);
-                    if (j < n_mine) run_block(here, j, redo || j == 0, j >= n_full);
-                    // a row sum this large (or not finite) means the fixed reference was too far below the true maximum
-                    if (j + 1 == n_stages && !redo && wave_active && __builtin_amdgcn_ballot_w64(!(lsum < 0x1p62f)) != 0 && lane == 0) restart = 1;
+            for (int j = 0; j < n_stages; ++j) {
+                for (; (j & 1) && j + 3 <= n_plain && !maximum_first; j += 2) {   // two steady stages at a time: buffers 1 and 0, offsets in the instructions
+                    copier.template copy<true>(kbase, vbase, (j + 1) * kNwStageRows, L, st);
+                    if (wave_active) run_block(st + N::kStage, false, false, j);
+                    end_stage();
+                    copier.template copy<true>(kbase, vbase, (j + 2) * kNwStageRows, L, st + N::kStage);
+                    if (wave_active) run_block(st, false, false, j + 1);
                     end_stage();
                 }
-                if (redo || __builtin_amdgcn_readfirstlane(restart) == 0) break;
-                redo = true;   // the whole tile again, maximum first
-                copier.copy(kbase, vbase, 0, L, st);
-                m = -INFINITY;
-                lsum = 0.0f;
-#pragma unroll
-                for (int db = 0; db < kDBlocks; ++db)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
+                char *const here = st + (j & 1) * N::kStage, *const other = st + (~j & 1) * N::kStage;
+                if (j + 1 < n_stages) copier.copy(kbase, vbase, (j + 1) * kNwStageRows, L, other);
+                if (j < n_mine) run_block(here, maximum_first, j >= n_full, j);
+                if (j == 0) maximum_first = false;
                 end_stage();
-                j = 0;
             }
 
             // ---- normalise and store: every wave is past the last stage's barrier and no copy is in flight ----

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2409_15373_amd.synthetic import make_custom, round_to_bf16_bits
+from paper_2409_15373_amd.synthetic import bf16_bits_to_f32, make_custom, round_to_bf16_bits
 import test_gpu_bf16_bwd
 import test_gpu_bf16_fwd
 import test_gpu_causal
@@ -82,6 +82,84 @@ def test_stale_reference_maximum(oracle, D, causal):
         r_out, r_lse = oracle.forward(w.q, w.k, w.v, w.offsets)
     gate_bf16("out", f64(out), r_out)
     gate_bf16("lse", f64(lse), r_lse, abs_tol=2e-2 * max(1.0, float(np.abs(r_lse).max()) / 4))
+
+
+def forward_of(mode, w):
+    """(out, lse) of the GPU and of the oracle; cross: the sample's rows as its keys and again as its queries."""
+    from oracle import causal as causal_oracle, cross as cross_oracle
+    from paper_2409_15373_amd import binding
+    d = test_gpu_bf16_fwd.to_device(w, names=("q", "k", "v"))
+    if mode == "cross":
+        got = binding.jfa_forward_cross(d["q"], d["k"], d["v"], d["offsets"], d["offsets"], w.max_len, w.max_len)
+        ref = cross_oracle.forward(w.q, w.k, w.v, w.offsets, w.offsets)
+    else:
+        got = binding.jfa_forward(d["q"], d["k"], d["v"], d["offsets"], w.max_len, causal=mode == "causal")
+        ref = causal_oracle.forward(w.q, w.k, w.v, w.offsets) if mode == "causal" else cross_oracle.forward(w.q, w.k, w.v, w.offsets, w.offsets)
+    return [f64(x) for x in got], ref
+
+
+def rising_scores(D, rise, lengths, v_scale=1.0, seed=61):
+    """Queries along one direction (plus noise), keys whose score along it is rise(j) for key j: maxima that go up on the way."""
+    w = make_custom("rising", lengths, 2, D, dtype="bf16", seed=seed, dout=False, max_len=512)
+    rng = np.random.default_rng(seed)
+    w.q, w.k = rng.standard_normal(w.q.shape).astype(np.float32) * 0.25, rng.standard_normal(w.k.shape).astype(np.float32) * 0.25
+    w.q[:, :, 0] = 8.0
+    for b, L in enumerate(lengths):
+        w.k[int(w.offsets[b]):int(w.offsets[b]) + L, :, 0] = np.array([rise(j) for j in range(L)], dtype=np.float32)[:, None] * D ** 0.5 / 8
+    w.v = w.v * np.float32(v_scale)
+    for n in ("q", "k", "v"):
+        w.bits[n] = round_to_bf16_bits(getattr(w, n))
+        setattr(w, n, bf16_bits_to_f32(w.bits[n]))
+    return w
+
+
+@pytest.mark.parametrize("mode", ["self", "causal", "cross"])
+@pytest.mark.parametrize("step", [1.5, 4.0, 7.0])   # per 64-key stage; e^5.5 = 2^8 is where the reference goes stale
+@pytest.mark.parametrize("D", [32, 64])
+def test_maxima_that_rise_from_stage_to_stage(D, step, mode):
+    """Rescale factors between 0 and 1 at every rise, row sums of many sizes, samples with and without a ragged last stage."""
+    w = rising_scores(D, lambda j: step * (j / 64.0), [300, 500, 60, 448, 1])
+    (out, lse), (r_out, r_lse) = forward_of(mode, w)
+    gate_bf16("out", out, r_out)
+    gate_bf16("lse", lse, r_lse, abs_tol=2e-2 * max(1.0, float(np.abs(r_lse).max()) / 4))
+
+
+@pytest.mark.parametrize("mode", ["self", "causal", "cross"])
+@pytest.mark.parametrize("D", [32, 64])
+def test_large_values_behind_a_stale_maximum(D, mode):
+    """Values of 1e25, and keys from 70 on that score 34 above the first 64: against the first stage's maximum their
+    probabilities are up to e^37, and those times the values are beyond fp32."""
+    w = rising_scores(D, lambda j: 34.0 * (j >= 70), [300, 500, 60], v_scale=1e25)
+    (out, lse), (r_out, r_lse) = forward_of(mode, w)
+    assert np.isfinite(out).all()
+    gate_bf16("out", out / 1e25, r_out / 1e25)
+    gate_bf16("lse", lse, r_lse, abs_tol=2e-2 * max(1.0, float(np.abs(r_lse).max()) / 4))
+
+
+@pytest.mark.parametrize("D", [32, 64])
+def test_row_sums_of_large_scores(D):
+    """Scores of standard deviation 16, where one key has most of a row's weight: its probability is rounded to bf16 unless
+    the reference is that very score, so how closely the reference follows shows in the log-sum-exp.  The bound is the error
+    of a reference that is raised, for the 32 queries of a wave together, where a stage's maximum exceeds it by 2^8,
+    evaluated on the host in fp64 but for that rounding; 1.2 times for the few rows whose sums are rounded elsewhere."""
+    L = 960
+    w = make_custom("large", [L], 2, D, dtype="bf16", seed=62, sigma=4.0, dout=False, max_len=1024)
+    (_, lse), (_, exact) = forward_of("self", w)
+    err = np.empty_like(exact)
+    for h in range(2):
+        s = w.q[:, h].astype(np.float64) @ w.k[:, h].astype(np.float64).T / (D ** 0.5 * np.log(2.0))
+        for q0 in range(0, L, 32):
+            m, l = np.full(32, -np.inf), np.zeros(32)
+            for j in range(0, L, 64):
+                x = s[q0:q0 + 32, j:j + 64]
+                if (x.max(axis=1) > m + 8).any():
+                    n = np.maximum(m, x.max(axis=1))
+                    m, l = n, l * np.exp2(m - n)
+                l += bf16_bits_to_f32(round_to_bf16_bits(np.exp2(x - m[:, None]).astype(np.float32))).astype(np.float64).sum(axis=1)
+            err[h, q0:q0 + 32] = (m + np.log2(l)) * np.log(2.0) - exact[h, q0:q0 + 32]
+    rms = lambda x: float(np.sqrt(np.mean(x * x)))
+    print(f"D {D}: {rms(lse - exact):.2e}, bound {1.2 * rms(err):.2e}", flush=True)
+    assert rms(lse - exact) <= 1.2 * rms(err)
 
 
 def test_rows_wider_than_32_bit_offsets():
