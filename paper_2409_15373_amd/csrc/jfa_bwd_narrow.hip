@@ -6,15 +6,18 @@
 // The split and the operand layouts of dq_bf16_kernel / dkv_bf16_kernel (jfa_bwd_bf16.hip): 128 stationary rows per tile, 32
 // per wave, on the lanes; the other rows stream past them in stages of 64; no atomics on results.  At these head sizes a
 // score's vector work is what counts (see jfa_fwd_narrow.hip), so there is as little of it as possible:
-//   * dP's accumulators start at minus delta (dQ) or, with V negated, at delta (dK / dV), the scores of the dK / dV kernel at
-//     minus lse * sqrt(D): the stream's statistics are read from LDS straight into the accumulators, and P and dS are one
-//     multiply (or multiply-add), one exponential, one multiply and the conversions;
+//   * dP's accumulators start at minus delta (dQ, D = 32) or, with V negated, at delta (dK / dV), the scores of the dK / dV
+//     kernel at minus lse * sqrt(D): the stream's statistics are read from LDS straight into the accumulators, and P and dS
+//     are one multiply (or multiply-add), one exponential, one multiply and the conversions;
 //   * only stages that contain the sample's end or the diagonal mask;
 //   * stages (and the stream's statistics) go directly to LDS, one ahead; gradients leave as whole rows.
-// Workgroups per compute unit: dQ four at D = 32 and three at D = 64 (its rows of the forward's output pass through LDS, which
-// leaves registers for that: 1449 us on 1024 samples of 1 to 1024 rows, H = 8, against 1569 with two; see the launcher for
-// small problems), dK / dV two at D = 64 and three at D = 32 (one more spills: 5 % slower at D = 64; at D = 32 2 % faster on
-// that batch but 1 to 4 us slower a launch, for the scratch memory).
+// Workgroups per compute unit: dQ four at D = 32 and three at D = 64.  Its rows of the forward's output pass through LDS and,
+// at D = 64, delta is subtracted from every dP, sixteen vector instructions more per block, which leaves registers for the third
+// without any spilled: 1024 samples of 1 to 1024 rows, H = 8, 1401 us (1457 with the addend and 15 registers spilled, 1569
+// with two workgroups); 256 samples of 64 rows on average, H = 2, 570 tiles, 16.4 us (20.3 and 22.6: scratch memory costs a
+// launch 4 us, and 512 places a second round); 64 samples of 4096 rows 1049 (1033).  D = 32 fits with the addend: subtracting
+// is 6 to 10 % slower there.  dK / dV two at D = 64 and three at D = 32 (one more spills: 5 % slower at D = 64; at D = 32 2 %
+// faster on that batch but 1 to 4 us slower a launch, for the scratch memory).
 // H * D = 512, whole backward, microseconds before -> now: 1024 samples of 1 to 1024 rows D = 64 4045 -> 3200, D = 32
 // 4572 -> 3630; 64 samples of 4096 rows D = 64 8698 -> 6942 (774 TFLOP/s), D = 32 10617 -> 7912.  A 32 x 32 block costs a SIMD
 // about 44 clocks per matrix instruction (12 + 16) and 3.8 per vector instruction (56 + 64; 134 + 96 before).
@@ -32,14 +35,14 @@ __device__ inline void narrow_end_stage() {
 }
 
 // CROSS: `offsets` belongs to the queries, offsets_kv to the keys and values; CAUSAL: query i sees keys 0 .. i.
-// kPerCu: workgroups per compute unit.
-template <int D, bool CROSS, bool CAUSAL, int kPerCu>
-__global__ __launch_bounds__(kNwThreads, kPerCu) void dq_narrow_kernel(
+template <int D, bool CROSS, bool CAUSAL>
+__global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void dq_narrow_kernel(
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, const __bf16 *__restrict__ dout,
     const float *__restrict__ lse, const __bf16 *__restrict__ out_fwd, float *__restrict__ stats, const int64_t *__restrict__ offsets,
     const int64_t *__restrict__ offsets_kv, int B, int H, Schedule s, __bf16 *__restrict__ dq) {
     using N = Narrow<D>;
     constexpr int kKSteps = D / 16, kDBlocks = D / 32;
+    constexpr bool kSubtract = D == 64;   // delta is subtracted from every dP: as their sums' addend it takes sixteen registers
     __shared__ __attribute__((aligned(1024))) char st[kNwStages * N::kStage];   // buffer b: K at b * kStage, V behind it
     __shared__ typename NarrowWalk<CROSS>::Shared walk_mem;
     static_assert(sizeof(st) >= kInlineScratchInts * sizeof(int), "the stage buffers double as the scheduler's scratch");
@@ -105,8 +108,8 @@ __global__ __launch_bounds__(kNwThreads, kPerCu) void dq_narrow_kernel(
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[db][e] = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) ndelta[e] = -delta;
-            asm volatile("" : "+v"(ndelta));   // sixteen real registers: the matrix product reads its addend from them
+            for (int e = 0; e < 16; ++e) ndelta[e] = kSubtract ? 0.0f : -delta;
+            if (!kSubtract) asm volatile("" : "+v"(ndelta));   // sixteen real registers: the matrix product reads its addend from them
 
             const int n_full = (CAUSAL && q0 + 1 < L ? q0 + 1 : L) / kNwStageRows;   // unmasked stages of this wave; see the forward
             const int n_mine = !wave_active ? 0 : CAUSAL ? q0 / kNwStageRows + 1 : n_stages;
@@ -114,7 +117,7 @@ __global__ __launch_bounds__(kNwThreads, kPerCu) void dq_narrow_kernel(
                 const char *const vt = kt + N::kTile;
 #pragma unroll
                 for (int mb = 0; mb < 2; ++mb) {
-                    if (D == 32) __builtin_amdgcn_sched_barrier(0);   // the two blocks one after the other: side by side they spill
+                    __builtin_amdgcn_sched_barrier(0);   // the two blocks one after the other: side by side they spill
                     f32x16 sc, dp = ndelta;
 #pragma unroll
                     for (int e = 0; e < 16; ++e) sc[e] = 0.0f;
@@ -129,7 +132,7 @@ __global__ __launch_bounds__(kNwThreads, kPerCu) void dq_narrow_kernel(
                             if ((e >> 2) * 8 + (e & 3) >= lim) sc[e] = -INFINITY;
                     }
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) dp[e] *= fast_exp2(fmaf(sc[e], c, -lse2));
+                    for (int e = 0; e < 16; ++e) dp[e] = (kSubtract ? dp[e] - delta : dp[e]) * fast_exp2(fmaf(sc[e], c, -lse2));
                     // dQ^T += K^T dS^T
 #pragma unroll
                     for (int ts = 0; ts < 2; ++ts) {
@@ -325,18 +328,10 @@ hipError_t launch_dq_narrow(const void *q, const void *k, const void *v, const v
                             const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, void *dq,
                             int cus, hipStream_t stream) {
     if (causal && offsets_kv) return hipErrorInvalidValue;
-#define JFA_LAUNCH_AT(DD, CROSS, CAUSAL, PER_CU)                                                                        \
-    hipLaunchKernelGGL((dq_narrow_kernel<DD, CROSS, CAUSAL, PER_CU>), dim3(persistent_grid<dq_narrow_kernel<DD, CROSS, CAUSAL, PER_CU>>(kNwThreads, cus)), \
+#define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                        \
+    hipLaunchKernelGGL((dq_narrow_kernel<DD, CROSS, CAUSAL>), dim3(persistent_grid<dq_narrow_kernel<DD, CROSS, CAUSAL>>(kNwThreads, cus)), \
                        dim3(kNwThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, lse, \
                        (const __bf16 *)out, stats, offsets, offsets_kv, B, H, s, (__bf16 *)dq)
-    // D = 64: the third workgroup costs a few registers spilled per tile, and the scratch memory that takes costs a launch
-    // 4 us: 100 samples of at most 1000 rows 34 us against 29, 1024 of them 1449 against 1569.  The line is where the
-    // schedule is built in the kernel, i.e. at most four tiles per compute unit.
-#define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                        \
-    do {                                                                                                     \
-        if (DD == 64 && s.build_rows != 0) JFA_LAUNCH_AT(DD, CROSS, CAUSAL, (DD == 64 ? 2 : 4));             \
-        else JFA_LAUNCH_AT(DD, CROSS, CAUSAL, (DD == 64 ? 3 : 4));                                           \
-    } while (0)
 #define JFA_CASE(DD)                                                                                         \
     case DD:                                                                                                 \
         if (offsets_kv) JFA_LAUNCH(DD, true, false);                                                         \
@@ -349,7 +344,6 @@ hipError_t launch_dq_narrow(const void *q, const void *k, const void *v, const v
     }
 #undef JFA_CASE
 #undef JFA_LAUNCH
-#undef JFA_LAUNCH_AT
     return hipGetLastError();
 }
 

@@ -6,6 +6,7 @@ pinned on small listings written here: a correct sequence, one with a wait count
 compiler would have moved a copy in front of the wait.
 """
 import os
+import re
 
 import pytest
 
@@ -103,3 +104,11 @@ def test_no_copy_reads_its_scalar_base_too_early(source):
     listing = check_lds_waits.listing_of(os.path.join(build.CSRC, source))
     assert "global_load_lds" in listing
     assert check_lds_waits.scalar_operand_hazards(listing) == []
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs hipcc")
+def test_the_head_size_64_gradient_kernels_use_no_scratch_memory():
+    """Spilled registers cost every launch of these kernels 4 us, a fifth of a small batch's dQ."""
+    listing = check_lds_waits.listing_of(os.path.join(build.CSRC, "jfa_bwd_narrow.hip"))
+    sizes = dict(re.findall(r"\.amdhsa_kernel (\S*Li64\S*)\s+(?:\.\S.*\s+)*?\.amdhsa_private_segment_fixed_size (\d+)", listing))
+    assert len(sizes) == 6 and set(sizes.values()) == {"0"}, sizes
