@@ -232,6 +232,10 @@ __device__ inline void narrow_store(char *region, int lane, const f32x16 (&acc)[
             for (int e = 0; e < 4; ++e) x[e] = (__bf16)(acc[db][4 * g + e] * scale);
             *reinterpret_cast<bf16x4 *>(region + col * N::kRow + (((db * 4 + g) ^ (col & (N::kChunks - 1))) << 4) + half * 8) = x;
         }
+    // lanes read what other lanes of the wave wrote: neither the compiler nor the LDS may turn that round
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     __bf16 *p = dst + (first + lane / N::kChunks) * row_stride + (lane % N::kChunks) * 8;
 #pragma unroll
     for (int it = 0; it < 32 / N::kRowsPerCopy; ++it, p += N::kRowsPerCopy * row_stride) {
@@ -239,6 +243,8 @@ __device__ inline void narrow_store(char *region, int lane, const f32x16 (&acc)[
         const u32x4 piece = *reinterpret_cast<const u32x4 *>(region + r * N::kRow + ((ch ^ (r & (N::kChunks - 1))) << 4));
         if (first + r < n) *reinterpret_cast<u32x4 *>(p) = piece;
     }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the region may be written again (dK, then dV)
+    __builtin_amdgcn_wave_barrier();
 }
 
 // Wait until at most `N` vector-memory operations and no LDS operation of this wave are pending.
