@@ -45,11 +45,6 @@ template <int D> __device__ inline int f32_swz(int r) {
     return D == 32 ? (r >> 1) & 7 : ((r >> 2) & 1) << 3 | ((r >> 3) & 1) << 2 | (r & 3);
 }
 
-__device__ inline void dma16_ptr(const float *src, char *lds_wave_base) {
-    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_byte_address(lds_wave_base));
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(src) : "memory", "m0");
-}
-
 // Copies rows r0 .. r0 + 63 of one head (base: the sample's first row of that head; rows past the sample's L repeat
 // its last one and are masked by the caller) into `tile`.  A wave instruction fills 1 KB = 256 / D rows.
 template <int D>
@@ -60,7 +55,7 @@ __device__ inline void stage_rows(char *tile, const float *__restrict__ base, in
         const int p = (wave * kOps + u) * 64 + lane;
         const int r = p / kChunks, ch = (p % kChunks) ^ f32_swz<D>(r);
         const int j = r0 + r < L ? r0 + r : L - 1;
-        dma16_ptr(base + j * row_stride + ch * 4, tile + (wave * kOps + u) * 1024);
+        dma16_lane(base + j * row_stride + ch * 4, tile + (wave * kOps + u) * 1024);
     }
 }
 
@@ -387,7 +382,8 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
         float *__restrict__ dv) {
     constexpr int kTile = f32_tile_bytes<D>(), kStage = f32_stage_bytes<D>();
     __shared__ __attribute__((aligned(1024))) char sm[2 * kStage];   // two stages of Q rows, then dO rows
-    __shared__ float lse_s[2][kCols], delta_s[2][kCols];              // lse and delta of the streamed rows
+    __shared__ __attribute__((aligned(16))) float lse_s[2][kCols], delta_s[2][kCols];   // lse and delta of the streamed rows
+    static_assert(__alignof__(lse_s) >= 16 && __alignof__(delta_s) >= 16, "read four at a time");
     __shared__ int64_t slot;
     __shared__ SmallWork mine;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
