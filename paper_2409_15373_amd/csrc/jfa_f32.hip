@@ -46,7 +46,7 @@ template <int D> __device__ inline int f32_swz(int r) {
 }
 
 // Copies rows r0 .. r0 + 63 of one head (base: the sample's first row of that head; rows past the sample's L repeat
-// its last one and are masked by the caller) into `tile`.  A wave instruction fills 1 KB = 256 / D rows.
+// its last one until stage_landed) into `tile`.  A wave instruction fills 1 KB = 256 / D rows.
 template <int D>
 __device__ inline void stage_rows(char *tile, const float *__restrict__ base, int64_t row_stride, int r0, int L, int wave, int lane) {
     constexpr int kChunks = D / 4, kOps = D / 16;   // chunks per row, instructions per wave
@@ -65,6 +65,22 @@ __device__ inline void stage_barrier() {
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+}
+
+// The same for the stage of rows r0 .. at `stage`, and zeroes in place of its rows past the sample's L: their scores are
+// masked, but a probability of 0 times the repeated row is not 0 where that holds an infinity.  Each wave clears what it has
+// copied itself (16 rows of both tiles), behind the wait for its copies.
+template <int D> __device__ inline void stage_landed(char *stage, int r0, int L, int wave, int lane) {
+    const int first = L - r0 > 16 * wave ? L - r0 : 16 * wave;
+    if (first < 16 * wave + 16 && r0 < L) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+        asm volatile("" ::: "memory");
+#pragma unroll 1
+        for (int p = first * (D / 4) + lane; p < (16 * wave + 16) * (D / 4); p += 64)
+            *reinterpret_cast<float4 *>(stage + p * 16) = *reinterpret_cast<float4 *>(stage + f32_tile_bytes<D>() + p * 16) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+    stage_barrier();
 }
 
 // A lane's stationary row as B operands: x[4 g + e] = row[8 g + 4 half + e].
@@ -232,7 +248,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
         f32x16 o[D / 32];
         clear<D>(o);
         float m = -INFINITY, l = 0.0f;   // running maximum of the scores; this lane's share of the row sum
-        stage_barrier();
+        stage_landed<D>(sm, 0, L, wave, lane);
         for (int j0 = 0, buf = 0; j0 < Lc; j0 += kCols, buf ^= 1) {
             if (j0 + kCols < Lc) issue(j0 + kCols, buf ^ 1);
             const int k0 = j0 + part * 32;             // first key of the wave's block
@@ -263,7 +279,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
                     for (int e = 0; e < 16; ++e) o[db][e] *= a;
                 accumulate<D>(o, vt, elem_at, st);
             }
-            stage_barrier();
+            if (j0 + kCols < Lc) stage_landed<D>(sm + (buf ^ 1) * kStage, j0 + kCols, L, wave, lane); else stage_barrier();
         }
         // the two waves of a group of queries have seen different keys: waves 2 and 3 hand over, waves 0 and 1 finish
         l = pair_sum(l);
@@ -342,7 +358,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kern
         if (part == 0 && i < t.len && half == 0) delta[(int64_t)t.head * sum_B + t.row0 + i] = delta_i;
         f32x16 acc[D / 32];
         clear<D>(acc);
-        stage_barrier();
+        stage_landed<D>(sm, 0, L, wave, lane);
         for (int j0 = 0, buf = 0; j0 < Lc; j0 += kCols, buf ^= 1) {
             if (j0 + kCols < Lc) issue(j0 + kCols, buf ^ 1);
             const int k0 = j0 + part * 32;
@@ -360,7 +376,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kern
                 }
                 accumulate<D>(acc, kt, elem_at, st);
             }
-            stage_barrier();
+            if (j0 + kCols < Lc) stage_landed<D>(sm + (buf ^ 1) * kStage, j0 + kCols, L, wave, lane); else stage_barrier();
         }
         char *const region = sm + rg * (D * 128);
         if (part == 1) park<D>(region, acc, lane);
@@ -439,7 +455,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
         clear<D>(acck);
         clear<D>(accv);
         store_stats(0);
-        stage_barrier();
+        stage_landed<D>(sm, istart, L, wave, lane);
         for (int i0 = istart, buf = 0; i0 < L; i0 += kCols, buf ^= 1) {
             const bool more = i0 + kCols < L;
             if (more) {
@@ -470,7 +486,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
                 accumulate<D>(acck, qt, elem_at, dp);
             }
             if (more) store_stats(buf ^ 1);
-            stage_barrier();
+            if (more) stage_landed<D>(sm + (buf ^ 1) * kStage, i0 + kCols, L, wave, lane); else stage_barrier();
         }
         // each wave of a pair finishes one gradient: waves 0 and 1 dK, waves 2 and 3 dV
         char *const region = sm + rg * (D * 256);

@@ -30,3 +30,34 @@ def test_cross(D, max_len):
     keys = EDGES[4:] + EDGES[:4]
     got, ref, oq, ok = test_gpu_cross.run(EDGES, keys, 1, D, "f32", 33 + D, max_len, max_len)
     test_gpu_cross.compare(got, ref, "f32", oq, ok, EDGES, keys)
+
+
+@pytest.mark.parametrize("mode", ["self", "cross"])
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_an_infinity_in_the_last_row_stays_in_its_column(D, mode):
+    """Stages of a sample's last rows are filled up by repeating its last one, with probability 0.  An infinite value there
+    makes its column of `out` infinite, and an infinite dout its column of dv, with every probability above 0; no other
+    column changes, and nothing becomes NaN (an infinity times 0)."""
+    import numpy as np
+    import torch
+    from paper_2409_15373_amd import binding
+    w = make_custom("inf", [33, 64, 1, 40, 100, 127, 200], 2, D, dtype="f32", seed=34, max_len=200)
+    d = test_gpu_f32.to_device(w)
+    last = torch.from_numpy(w.offsets[1:] - 1).cuda()
+
+    def run():
+        if mode == "cross":
+            out, lse = binding.jfa_forward_cross(d["q"], d["k"], d["v"], d["offsets"], d["offsets"], 200, 200)
+            return out, binding.jfa_backward_cross(d["q"], d["k"], d["v"], plain_out, d["dout"], lse, d["offsets"], d["offsets"], 200, 200)[2]
+        out, lse = binding.jfa_forward(d["q"], d["k"], d["v"], d["offsets"], 200)
+        return out, binding.jfa_backward(d["q"], d["k"], d["v"], plain_out, d["dout"], lse, d["offsets"], 200)[2]
+
+    plain_out = binding.jfa_forward(d["q"], d["k"], d["v"], d["offsets"], 200)[0]
+    out, dv = run()
+    d["v"][last, :, 3] = float("inf")
+    d["dout"][last, :, 5] = float("-inf")
+    inf_out, inf_dv = run()
+    assert (inf_out[:, :, 3] == float("inf")).all() and (inf_dv[:, :, 5] == float("-inf")).all()
+    others = lambda x, c: torch.cat([x[:, :, :c], x[:, :, c + 1:]], dim=2)
+    assert torch.equal(others(inf_out, 3), others(out, 3)) and torch.equal(others(inf_dv, 5), others(dv, 5))
+    assert np.isfinite(test_gpu_f32.f64(others(inf_out, 3))).all()
