@@ -45,18 +45,28 @@ template <int D> __device__ inline int f32_swz(int r) {
     return D == 32 ? (r >> 1) & 7 : ((r >> 2) & 1) << 3 | ((r >> 3) & 1) << 2 | (r & 3);
 }
 
-// Copies rows r0 .. r0 + 63 of one head (base: the sample's first row of that head; rows past the sample's L repeat
-// its last one until stage_landed) into `tile`.  A wave instruction fills 1 KB = 256 / D rows.
+// What rows past a sample's end are copied from.  Their scores are masked, but a probability of 0 times a repeated row is not 0
+// where that row holds an infinity.
+static __device__ const __attribute__((aligned(16))) float zeros[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+
+__device__ inline int not_hoisted(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// Copies rows r0 .. r0 + 63 of one head (base: the sample's first row of that head; zeroes for rows past the sample's L) into
+// `tile`.  A wave instruction fills 1 KB = 256 / D rows.  Addresses are made anew for every stage: kept, they take registers
+// that are not there.
 template <int D>
 __device__ inline void stage_rows(char *tile, const float *__restrict__ base, int64_t row_stride, int r0, int L, int wave, int lane) {
-    constexpr int kChunks = D / 4, kOps = D / 16;   // chunks per row, instructions per wave
+    constexpr int kChunks = D / 4, kOps = D / 16, kOpRows = 64 / kChunks;   // chunks per row, instructions per wave, rows per instruction
+    lane = not_hoisted(lane);
+    const int first = r0 + 16 * wave + lane / kChunks;
+    const int ch = (lane % kChunks) ^ f32_swz<D>(lane / kChunks);   // the swizzle of a sum of row bits is the XOR of theirs
+    const float *src = base + first * row_stride;
 #pragma unroll
-    for (int u = 0; u < kOps; ++u) {
-        const int p = (wave * kOps + u) * 64 + lane;
-        const int r = p / kChunks, ch = (p % kChunks) ^ f32_swz<D>(r);
-        const int j = r0 + r < L ? r0 + r : L - 1;
-        dma16_lane(base + j * row_stride + ch * 4, tile + (wave * kOps + u) * 1024);
-    }
+    for (int u = 0; u < kOps; ++u, src += kOpRows * row_stride)
+        dma16_lane(first + u * kOpRows < L ? src + (ch ^ f32_swz<D>(u * kOpRows)) * 4 : zeros, tile + (wave * kOps + u) * 1024);
 }
 
 // This stage's copies have landed and every wave is done with the present stage.
@@ -65,22 +75,6 @@ __device__ inline void stage_barrier() {
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-}
-
-// The same for the stage of rows r0 .. at `stage`, and zeroes in place of its rows past the sample's L: their scores are
-// masked, but a probability of 0 times the repeated row is not 0 where that holds an infinity.  Each wave clears what it has
-// copied itself (16 rows of both tiles), behind the wait for its copies.
-template <int D> __device__ inline void stage_landed(char *stage, int r0, int L, int wave, int lane) {
-    const int first = L - r0 > 16 * wave ? L - r0 : 16 * wave;
-    if (first < 16 * wave + 16 && r0 < L) {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
-        asm volatile("" ::: "memory");
-#pragma unroll 1
-        for (int p = first * (D / 4) + lane; p < (16 * wave + 16) * (D / 4); p += 64)
-            *reinterpret_cast<float4 *>(stage + p * 16) = *reinterpret_cast<float4 *>(stage + f32_tile_bytes<D>() + p * 16) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
-    stage_barrier();
 }
 
 // A lane's stationary row as B operands: x[4 g + e] = row[8 g + 4 half + e].
@@ -99,10 +93,6 @@ template <int D> __device__ inline int row_read_at(int col, int half) { return c
 template <int D> __device__ inline int element_read_at(int col, int half) {
     return half * (16 * D) + (((col >> 2) ^ f32_swz<D>(4 * half)) << 4) + (col & 3) * 4;
 }
-__device__ inline int not_hoisted(int x) {
-    asm volatile("" : "+v"(x));
-    return x;
-}
 
 // exp(x).  The argument is a difference (score minus maximum or log-sum-exp) of numbers that may be much larger than it:
 // scaled in one rounding together with the subtraction, and only the difference times log2(e).  (Both sides of the difference
@@ -114,8 +104,8 @@ __device__ inline float exp_f32(float x) { return fast_exp2(x * 1.44269504088896
 // additions it comes from, and the exponential turns it into a relative error of the probability: the D features are summed
 // in four chains, as four lanes of a vector kernel would.  One chain: the gradients' error at scores of standard deviation 16
 // is 1.5 (D = 32), 1.8 (64) and 2.1 times this (128); eight chains: 0.99 and 0.92 times at D = 64 and 128, time + 5 %.
-// Both together, microseconds of forward and backward at B = 256, H = 2, lengths to 512: D = 32 85 + 279 -> 94 + 290,
-// D = 64 180 + 510 -> 182 + 514, D = 128 325 + 1166 -> 336 + 1166.
+// Both together, microseconds of forward and backward at B = 256, H = 2, lengths to 512: D = 32 85 + 275 -> 94 + 293,
+// D = 64 179 + 503 -> 185 + 509, D = 128 324 + 1165 -> 343 + 1201.
 template <int D> __device__ inline f32x16 product(const char *block, int at, const float (&x)[D / 2]) {
     constexpr int kChains = 4, kGroups = D / 8 / kChains;   // a chain's 16-byte reads
     f32x16 sum;
@@ -248,7 +238,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
         f32x16 o[D / 32];
         clear<D>(o);
         float m = -INFINITY, l = 0.0f;   // running maximum of the scores; this lane's share of the row sum
-        stage_landed<D>(sm, 0, L, wave, lane);
+        stage_barrier();
         for (int j0 = 0, buf = 0; j0 < Lc; j0 += kCols, buf ^= 1) {
             if (j0 + kCols < Lc) issue(j0 + kCols, buf ^ 1);
             const int k0 = j0 + part * 32;             // first key of the wave's block
@@ -279,7 +269,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
                     for (int e = 0; e < 16; ++e) o[db][e] *= a;
                 accumulate<D>(o, vt, elem_at, st);
             }
-            if (j0 + kCols < Lc) stage_landed<D>(sm + (buf ^ 1) * kStage, j0 + kCols, L, wave, lane); else stage_barrier();
+            stage_barrier();
         }
         // the two waves of a group of queries have seen different keys: waves 2 and 3 hand over, waves 0 and 1 finish
         l = pair_sum(l);
@@ -358,7 +348,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kern
         if (part == 0 && i < t.len && half == 0) delta[(int64_t)t.head * sum_B + t.row0 + i] = delta_i;
         f32x16 acc[D / 32];
         clear<D>(acc);
-        stage_landed<D>(sm, 0, L, wave, lane);
+        stage_barrier();
         for (int j0 = 0, buf = 0; j0 < Lc; j0 += kCols, buf ^= 1) {
             if (j0 + kCols < Lc) issue(j0 + kCols, buf ^ 1);
             const int k0 = j0 + part * 32;
@@ -376,7 +366,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kern
                 }
                 accumulate<D>(acc, kt, elem_at, st);
             }
-            if (j0 + kCols < Lc) stage_landed<D>(sm + (buf ^ 1) * kStage, j0 + kCols, L, wave, lane); else stage_barrier();
+            stage_barrier();
         }
         char *const region = sm + rg * (D * 128);
         if (part == 1) park<D>(region, acc, lane);
@@ -455,7 +445,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
         clear<D>(acck);
         clear<D>(accv);
         store_stats(0);
-        stage_landed<D>(sm, istart, L, wave, lane);
+        stage_barrier();
         for (int i0 = istart, buf = 0; i0 < L; i0 += kCols, buf ^= 1) {
             const bool more = i0 + kCols < L;
             if (more) {
@@ -486,7 +476,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
                 accumulate<D>(acck, qt, elem_at, dp);
             }
             if (more) store_stats(buf ^ 1);
-            if (more) stage_landed<D>(sm + (buf ^ 1) * kStage, i0 + kCols, L, wave, lane); else stage_barrier();
+            stage_barrier();
         }
         // each wave of a pair finishes one gradient: waves 0 and 1 dK, waves 2 and 3 dV
         char *const region = sm + rg * (D * 256);
