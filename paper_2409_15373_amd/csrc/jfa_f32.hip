@@ -38,6 +38,13 @@ static_assert(2 * f32_stage_bytes<32>() >= kInlineScratchInts * (int)sizeof(int)
 // D = 128 needs 128 KB of stages and more than 256 registers in the backward: one workgroup per compute unit
 template <int D> constexpr int f32_waves_per_simd() { return D <= 64 ? 2 : 1; }
 
+// Up to this many items per workgroup are dealt round-robin from the sorted schedule, without claims.  A claim is an atomic on
+// one of eight counters that share a cache line, and its latency heads everything a tile does: at D <= 64 that costs more than
+// the last tiles' imbalance (B = 256, H = 2, lengths to 512, 4.5 items: D = 64 forward 184 -> 158 us, backward 509 -> 495; 4096
+// samples of at most 20 rows, 8 items, D = 32: backward 190 -> 101).  At D = 128, with half the workgroups and twice the time
+// per tile, balance is worth more (9 items: 343 -> 358), and next_work()'s own limit of four holds.
+template <int D> constexpr int64_t f32_static_items() { return D <= 64 ? 16 : 0; }
+
 // Row r, 16-byte chunk ch of a streamed tile sits at r * 4 D + ((ch ^ f32_swz(r)) << 4): the 16-byte row reads (16
 // consecutive rows, one chunk) hit all 64 banks once, and so do the element reads of two rows 4 apart (D >= 64; two-way
 // conflicts at D = 32, where a row is half a bank line).
@@ -216,7 +223,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
     const int64_t row_stride = (int64_t)H * D;
 
     WorkCursor cursor;
-    cursor.static_only = s.static_only;
+    cursor.static_only = s.static_only || total <= f32_static_items<D>() * (int64_t)gridDim.x;
     Work t;   // keys: rows orow0 .. orow0 + olen - 1
     for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot); ++item) {
         const int L = t.olen;
@@ -317,7 +324,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kern
     const int64_t row_stride = (int64_t)H * D;
 
     WorkCursor cursor;
-    cursor.static_only = s.static_only;
+    cursor.static_only = s.static_only || total <= f32_static_items<D>() * (int64_t)gridDim.x;
     Work t;
     for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot); ++item) {
         const int L = t.olen;
@@ -404,7 +411,7 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
     const int64_t row_stride = (int64_t)H * D;
 
     WorkCursor cursor;
-    cursor.static_only = s.static_only;
+    cursor.static_only = s.static_only || total <= f32_static_items<D>() * (int64_t)gridDim.x;
     Work t;   // queries: rows orow0 .. orow0 + olen - 1
     for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_q, B, H, cursor, total, &slot); ++item) {
         const int L = t.olen;

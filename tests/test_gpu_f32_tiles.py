@@ -61,3 +61,11 @@ def test_an_infinity_in_the_last_row_stays_in_its_column(D, mode):
     others = lambda x, c: torch.cat([x[:, :, :c], x[:, :, c + 1:]], dim=2)
     assert torch.equal(others(inf_out, 3), others(out, 3)) and torch.equal(others(inf_dv, 5), others(dv, 5))
     assert np.isfinite(test_gpu_f32.f64(others(inf_out, 3))).all()
+
+
+@pytest.mark.parametrize("B", [300, 5000, 13000])   # up to four items per workgroup, up to sixteen (dealt without claims at D <= 64), more (claimed)
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_many_short_samples(oracle, D, B):
+    import numpy as np
+    lengths = np.random.default_rng(35).integers(0, 21, size=B)
+    test_gpu_f32.run_case(oracle, make_custom("many", lengths, 2, D, dtype="f32", seed=36 + D, max_len=20))
