@@ -316,7 +316,7 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
         return e == hipSuccess ? JFA_OK : hip_fail("fwd_cross_fewq", e);
     }
     const FwdVariant variant = f32 ? kNarrow : forward_variant(max_len > max_len_kv ? max_len : max_len_kv, D, H);
-    const int block_rows = f32 ? jfa::kF32BlockRows : (variant == kNarrow ? jfa::kFwdBlockRows : jfa::kDmaBlockRows);
+    const int block_rows = f32 ? jfa::f32_block_rows(max_len_kv, !small_problem(B, max_len, H, jfa::kF32BlockRows, w.cus)) : (variant == kNarrow ? jfa::kFwdBlockRows : jfa::kDmaBlockRows);
     jfa::Schedule sc{w.order[0], w.tile_start[0], w.counters};
     if (variant == kNarrow && small_problem(B, max_len, H, block_rows, w.cus)) {
         sc.build_rows = block_rows;
@@ -326,7 +326,7 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
         e = schedule(&job, 1, B, w, s);
         if (e != hipSuccess) return hip_fail("schedule kernel", e);
     }
-    if (f32) { ScopedTimer tm("fwd_f32", s); e = jfa::launch_fwd_f32((const float *)q, (const float *)k, (const float *)v, offsets, offsets_kv, causal, (int)B, H, D, sc, (float *)out, lse, w.cus, s); }
+    if (f32) { ScopedTimer tm("fwd_f32", s); e = jfa::launch_fwd_f32((const float *)q, (const float *)k, (const float *)v, offsets, offsets_kv, causal, (int)B, H, D, sc, block_rows, (float *)out, lse, w.cus, s); }
     else if (variant == kDma) { ScopedTimer tm("fwd_bf16_dma", s); e = jfa::launch_fwd_bf16_dma(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
     else if (D < 128) { ScopedTimer tm("fwd_bf16", s); e = jfa::launch_fwd_narrow(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
     else { ScopedTimer tm("fwd_bf16", s); e = jfa::launch_fwd_bf16(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
@@ -353,7 +353,10 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
         return e == hipSuccess ? JFA_OK : hip_fail("bwd_cross_fewq", e);
     }
     const bool dma = !f32 && D == 128 && forward_variant(max_len > max_len_kv ? max_len : max_len_kv, D, H) != kNarrow;
-    const int block_rows = f32 ? jfa::kF32BlockRows : (dma ? jfa::kDmaBlockRows : jfa::kBwdBlockRows);
+    const int64_t longest = max_len > max_len_kv ? max_len : max_len_kv;
+    const bool many = !small_problem(B, longest, H, jfa::kF32BlockRows, w.cus);
+    const int block_rows = f32 ? jfa::f32_block_rows(max_len_kv, many) : (dma ? jfa::kDmaBlockRows : jfa::kBwdBlockRows);   // of queries
+    const int key_rows = f32 ? jfa::f32_block_rows(max_len, many) : (dma ? jfa::kDkvBlockRows : block_rows);                // of keys
     // Schedule 0: blocks of queries.  Schedule 1: blocks of keys, where they differ: cross attention, and the direct-to-LDS
     // kernels, whose dK / dV blocks are shorter.  One launch builds both and clears all work counters before the first
     // kernel that uses one.  Small problems on the other kernels have no scheduler launch: those kernels build their
@@ -361,10 +364,10 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     const int kv = offsets_kv ? 1 : 0;
     const int64_t *const offsets_k = offsets_kv ? offsets_kv : offsets;   // the keys' offsets
     const int64_t *const offsets_q_other = offsets_kv ? offsets : nullptr;   // the queries', as the second array of dK / dV
-    const bool in_kernel = !dma && small_problem(B, max_len > max_len_kv ? max_len : max_len_kv, H, block_rows, w.cus);
+    const bool in_kernel = !dma && small_problem(B, longest, H, block_rows < key_rows ? block_rows : key_rows, w.cus);
     if (!in_kernel) {
         const jfa::ScheduleJob jobs[2] = {schedule_job(offsets, offsets_kv, block_rows, w, 0),
-                                          schedule_job(offsets_k, offsets_q_other, dma ? jfa::kDkvBlockRows : block_rows, w, 1)};
+                                          schedule_job(offsets_k, offsets_q_other, key_rows, w, 1)};
         e = schedule(jobs, dma || offsets_kv ? 2 : 1, B, w, s);
         if (e != hipSuccess) return hip_fail("schedule kernel", e);
     }
@@ -374,11 +377,11 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
         if (in_kernel) {   // every kernel builds the schedule of its own work items, in LDS
             s_dq.static_only = s_dkv.static_only = true;
             s_dq.build_rows = block_rows;
-            s_dkv.build_rows = block_rows;
+            s_dkv.build_rows = key_rows;
         }
         ScopedTimer tm_bwd("bwd_f32", s);
         e = jfa::launch_bwd_f32((const float *)q, (const float *)k, (const float *)v, (const float *)out, (const float *)dout, lse,
-                                offsets, offsets_kv, causal, (int)B, H, D, s_dq, s_dkv, (float *)dq, (float *)dk, (float *)dv, delta, w.cus, s);
+                                offsets, offsets_kv, causal, (int)B, H, D, s_dq, block_rows, s_dkv, key_rows, (float *)dq, (float *)dk, (float *)dv, delta, w.cus, s);
         if (e != hipSuccess) return hip_fail("fp32 backward kernels", e);
         return JFA_OK;
     }

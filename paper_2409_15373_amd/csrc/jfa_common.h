@@ -212,7 +212,7 @@ __device__ inline void build_small_work(const int64_t *offsets, const int64_t *o
         nblk[b] = (int)((len + block_rows - 1) / block_rows);
         keys[b] = (uint8_t)(key < kInlineBins - 1 ? key : kInlineBins - 1);
     }
-    if (threadIdx.x < 2 * kInlineBins) bins[threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < 2 * kInlineBins; i += blockDim.x) bins[i] = 0;
     __syncthreads();
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
@@ -482,17 +482,26 @@ hipError_t launch_schedules(const ScheduleJob *jobs, int n_jobs, int B, int32_t 
 hipError_t launch_check_offsets(const int64_t *offsets, int B, int64_t max_len, int *flags, hipStream_t stream);
 
 // fp32 path
-constexpr int kF32BlockRows = 64;
+// Rows per block (and per streamed stage) of an fp32 kernel, which is its workgroup size: 64 rows are four waves, the quarters
+// of a 64 x 64 square, 32 rows one wave.  Where at most 32 rows stream past a block two or three of the four waves have nothing
+// to do; up to 64 rows single waves that are not in step still fill a compute unit better, if there are enough of them
+// (`many`: more tiles than are dealt in the kernel).  Four waves -> one, microseconds, D = 128, backward: 4096 samples of at
+// most 20 rows 538 -> 163, of at most 48 605 -> 434, 2000 x 2 heads of at most 64 621 -> 475; four samples of at most 64 41 -> 53.
+constexpr int kF32BlockRows = 64, kF32ShortBlockRows = 32;
+inline int f32_block_rows(int64_t max_streamed, bool many) {
+    return max_streamed <= 32 || (many && max_streamed <= 64) ? kF32ShortBlockRows : kF32BlockRows;
+}
 // Cross attention: offsets = the queries' offsets, offsets_kv = the keys' (nullptr: the same array); schedules are
 // built over the stationary side's offsets (s, s_dq: queries; s_dkv: keys).
 // causal (self attention only, offsets_kv == nullptr): row i attends to rows 0 .. i of its sample.
+// block_rows, rows_dq, rows_dkv: kF32BlockRows or kF32ShortBlockRows, what the kernel's schedule was built with.
 hipError_t launch_fwd_f32(const float *q, const float *k, const float *v, const int64_t *offsets,
-                          const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, float *out, float *lse,
+                          const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, int block_rows, float *out, float *lse,
                           int cus, hipStream_t stream);
 hipError_t launch_bwd_f32(const float *q, const float *k, const float *v, const float *out, const float *dout,
                           const float *lse, const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H,
-                          int D, Schedule s_dq, Schedule s_dkv, float *dq, float *dk, float *dv, float *delta, int cus,
-                          hipStream_t stream);
+                          int D, Schedule s_dq, int rows_dq, Schedule s_dkv, int rows_dkv, float *dq, float *dk, float *dv, float *delta,
+                          int cus, hipStream_t stream);
 // (the dQ kernel of every path runs first and computes delta[h, row] = sum_d dout * out for the kernels after it)
 
 // bf16 attention, register-staged kernels (D = 128, short samples)

@@ -10,7 +10,9 @@
 //     32 (w >> 1) .. + 31.  The two waves that share stationary rows add their results through LDS at the tile's end
 //     (fixed order: deterministic).  A sample of up to 64 rows is then one step of each wave instead of two steps of two;
 //   * streamed rows go to LDS directly (global_load_lds), the next stage's while the present one is multiplied, and
-//     two workgroups share a compute unit (D <= 64), so that one computes while the other starts or ends a tile.
+//     two workgroups share a compute unit (D <= 64), so that one computes while the other starts or ends a tile;
+//   * for streams of a block or two a workgroup is one wave, with a 32 x 32 square and one stage: more tiles at once per compute
+//     unit, nothing to add up.
 // Operand layout of the instruction: lane l holds row (A) or column (B) l % 32 and contraction slot l / 32.  Slots are
 // dummies: four consecutive instructions take features 8 g + 4 (l / 32) .. + 3, one 16-byte read per lane.  Scores are
 // computed with the streamed rows on the accumulator's row axis and the stationary rows on its column (= lane) axis;
@@ -24,25 +26,28 @@
 
 namespace jfa {
 
-constexpr int kRows = kF32BlockRows;   // stationary rows (queries or keys) per tile
-constexpr int kCols = 64;              // streamed rows per stage
-constexpr int kThreads = 256;
-static_assert(kRows == 64 && kCols == 64, "four waves are the four quarters of a tile's stage");
+// W: waves per workgroup, four or, for short streams, one (see f32_block_rows): stationary rows per tile, streamed rows per stage
+template <int W> constexpr int f32_rows() { return W == 4 ? kF32BlockRows : kF32ShortBlockRows; }
+static_assert(f32_rows<4>() == 64 && f32_rows<1>() == 32, "a wave is a 32 x 32 square: all of it or a quarter");
 
 __device__ inline f32x16 mfma_f32(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
 
-template <int D> constexpr int f32_tile_bytes() { return kCols * D * 4; }
-// A workgroup's stage buffers: two stages, each the streamed rows of one tensor and then of the other.
-template <int D> constexpr int f32_stage_bytes() { return 2 * f32_tile_bytes<D>(); }
-static_assert(2 * f32_stage_bytes<32>() >= kInlineScratchInts * (int)sizeof(int), "the stage buffers double as the in-kernel scheduler's scratch");
+template <int D, int W> constexpr int f32_tile_bytes() { return f32_rows<W>() * D * 4; }
+// A workgroup's stage buffers: two stages (one wave: one), each the streamed rows of one tensor and then of the other.  They
+// double as the in-kernel scheduler's scratch.
+template <int D, int W> constexpr int f32_stage_bytes() { return 2 * f32_tile_bytes<D, W>(); }
+template <int D, int W> constexpr int f32_lds_bytes() {
+    constexpr int stages = (W == 4 ? 2 : 1) * f32_stage_bytes<D, W>(), scratch = kInlineScratchInts * (int)sizeof(int);
+    return stages > scratch ? stages : scratch;
+}
 // D = 128 needs 128 KB of stages and more than 256 registers in the backward: one workgroup per compute unit
 template <int D> constexpr int f32_waves_per_simd() { return D <= 64 ? 2 : 1; }
 
 // Up to this many items per workgroup are dealt round-robin from the sorted schedule, without claims.  A claim is an atomic on
 // one of eight counters that share a cache line, and its latency heads everything a tile does: at D <= 64 that costs more than
-// the last tiles' imbalance (B = 256, H = 2, lengths to 512, 4.5 items: D = 64 forward 184 -> 158 us, backward 509 -> 495; 4096
-// samples of at most 20 rows, 8 items, D = 32: backward 190 -> 101).  At D = 128, with half the workgroups and twice the time
-// per tile, balance is worth more (9 items: 343 -> 358), and next_work()'s own limit of four holds.
+// the last tiles' imbalance (B = 256, H = 2, lengths to 512, 4.5 items: D = 64 forward 184 -> 158 us, backward 509 -> 495; 500
+// samples of at most 100 rows, H = 8, 6 to 8 items, D = 32: 125 -> 56 and 240 -> 163).  At D = 128, with half the workgroups and
+// twice the time per tile, balance is worth more (9 items: 343 -> 358), and next_work()'s own limit of four holds.
 template <int D> constexpr int64_t f32_static_items() { return D <= 64 ? 16 : 0; }
 
 // Row r, 16-byte chunk ch of a streamed tile sits at r * 4 D + ((ch ^ f32_swz(r)) << 4): the 16-byte row reads (16
@@ -61,14 +66,15 @@ __device__ inline int not_hoisted(int x) {
     return x;
 }
 
-// Copies rows r0 .. r0 + 63 of one head (base: the sample's first row of that head; zeroes for rows past the sample's L) into
+// Copies a stage's rows r0 .. of one head (base: the sample's first row of that head; zeroes for rows past the sample's L) into
 // `tile`.  A wave instruction fills 1 KB = 256 / D rows.  Addresses are made anew for every stage: kept, they take registers
 // that are not there.
-template <int D>
+template <int D, int W>
 __device__ inline void stage_rows(char *tile, const float *__restrict__ base, int64_t row_stride, int r0, int L, int wave, int lane) {
-    constexpr int kChunks = D / 4, kOps = D / 16, kOpRows = 64 / kChunks;   // chunks per row, instructions per wave, rows per instruction
+    constexpr int kChunks = D / 4, kOpRows = 64 / kChunks;                  // chunks per row, rows per instruction
+    constexpr int kWaveRows = f32_rows<W>() / W, kOps = kWaveRows / kOpRows;   // rows and instructions per wave
     lane = not_hoisted(lane);
-    const int first = r0 + 16 * wave + lane / kChunks;
+    const int first = r0 + kWaveRows * wave + lane / kChunks;
     const int ch = (lane % kChunks) ^ f32_swz<D>(lane / kChunks);   // the swizzle of a sum of row bits is the XOR of theirs
     const float *src = base + first * row_stride;
 #pragma unroll
@@ -201,19 +207,19 @@ __device__ inline bool next_item(Work &t, const SmallWork &mine, bool small, int
     return true;
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_kernel(
+template <int D, int W>
+__global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void fwd_f32_kernel(
         const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
         const int64_t *__restrict__ offsets, const int64_t *__restrict__ offsets_kv, bool causal, int B, int H, Schedule s,
         float *__restrict__ out, float *__restrict__ lse) {
-    constexpr int kTile = f32_tile_bytes<D>(), kStage = f32_stage_bytes<D>();
-    __shared__ __attribute__((aligned(1024))) char sm[2 * kStage];   // two stages of K rows, then V rows
+    constexpr int kRows = f32_rows<W>(), kCols = kRows, kTile = f32_tile_bytes<D, W>(), kStage = f32_stage_bytes<D, W>();
+    __shared__ __attribute__((aligned(1024))) char sm[f32_lds_bytes<D, W>()];   // two stages of K rows, then V rows
     __shared__ float2 other_ml[2][32];   // running maximum and row sum of the waves w >= 2
     __shared__ int64_t slot;
     __shared__ SmallWork mine;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
-    const int rg = wave & 1, part = wave >> 1;   // group of 32 queries; half of the stage's keys
+    const int rg = W == 4 ? wave & 1 : 0, part = W == 4 ? wave >> 1 : 0;   // group of 32 queries; half of the stage's keys
     const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
     const float scale = 1.0f / sqrtf((float)D);
     const bool small = s.build_rows != 0;   // small problem: no scheduler launch has run, the schedule is built here, in LDS
@@ -236,8 +242,8 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
         const float *kbase = k + t.orow0 * row_stride + (int64_t)t.head * D;
         const float *vbase = v + t.orow0 * row_stride + (int64_t)t.head * D;
         auto issue = [&](int j0, int buf) {
-            stage_rows<D>(sm + buf * kStage, kbase, row_stride, j0, L, wave, lane);
-            stage_rows<D>(sm + buf * kStage + kTile, vbase, row_stride, j0, L, wave, lane);
+            stage_rows<D, W>(sm + buf * kStage, kbase, row_stride, j0, L, wave, lane);
+            stage_rows<D, W>(sm + buf * kStage + kTile, vbase, row_stride, j0, L, wave, lane);
         };
         if (L > 0) issue(0, 0);
         float qr[D / 2];
@@ -246,8 +252,8 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
         clear<D>(o);
         float m = -INFINITY, l = 0.0f;   // running maximum of the scores; this lane's share of the row sum
         stage_barrier();
-        for (int j0 = 0, buf = 0; j0 < Lc; j0 += kCols, buf ^= 1) {
-            if (j0 + kCols < Lc) issue(j0 + kCols, buf ^ 1);
+        for (int j0 = 0, buf = 0; j0 < Lc; j0 += kCols, buf ^= W == 4) {
+            if (W == 4 && j0 + kCols < Lc) issue(j0 + kCols, buf ^ 1);
             const int k0 = j0 + part * 32;             // first key of the wave's block
             if (active && k0 < Lc && !(causal && k0 > q0 + 31)) {
                 const char *kt = sm + buf * kStage + part * (32 * 4 * D), *vt = kt + kTile;
@@ -277,22 +283,28 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
                 accumulate<D>(o, vt, elem_at, st);
             }
             stage_barrier();
+            if (W == 1 && j0 + kCols < Lc) {   // one buffer: the other workgroups of the compute unit fill the gap
+                issue(j0 + kCols, 0);
+                stage_barrier();
+            }
         }
         // the two waves of a group of queries have seen different keys: waves 2 and 3 hand over, waves 0 and 1 finish
         l = pair_sum(l);
         char *const region = sm + rg * (D * 128);
-        if (part == 1) {
-            park<D>(region, o, lane);
-            if (half == 0) other_ml[rg][col] = make_float2(m, l);
+        if (W == 4) {
+            if (part == 1) {
+                park<D>(region, o, lane);
+                if (half == 0) other_ml[rg][col] = make_float2(m, l);
+            }
+            __syncthreads();
         }
-        __syncthreads();
         if (part == 0 && i < t.len) {
-            const float2 ml = other_ml[rg][col];
+            const float2 ml = W == 4 ? other_ml[rg][col] : make_float2(-INFINITY, 0.0f);
             const float m_all = fmaxf(m, ml.x);
             const float a = m_all > -INFINITY ? exp_f32(m - m_all) : 0.0f;      // a sample without keys: out = 0, lse = -inf
             const float b = m_all > -INFINITY ? exp_f32(ml.x - m_all) : 0.0f;
             const float l_all = l * a + ml.y * b;
-            merge<D>(o, region, lane, a, b);
+            if (W == 4) merge<D>(o, region, lane, a, b);
             store_row<D>(out + (t.row0 + i) * row_stride + (int64_t)t.head * D, o, l_all > 0.0f ? 1.0f / l_all : 0.0f, half);
             if (half == 0) lse[(int64_t)t.head * sum_B + t.row0 + i] = m_all + logf(l_all);
         }
@@ -302,19 +314,19 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void fwd_f32_ker
 // dQ: tile = 64 queries, stream the sample's keys.  The kernel is the first of the backward: it holds each query's dO
 // row anyway, reads the matching row of the forward's output, and computes delta = rowsum(dO o O) for its own use
 // and for the dK / dV kernel (no separate pass over dO and O, one launch less).
-template <int D>
-__global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kernel(
+template <int D, int W>
+__global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void dq_f32_kernel(
         const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
         const float *__restrict__ out_fwd, const float *__restrict__ dout, const float *__restrict__ lse,
         float *__restrict__ delta, const int64_t *__restrict__ offsets, const int64_t *__restrict__ offsets_kv, bool causal,
         int B, int H, Schedule s, float *__restrict__ dq) {
-    constexpr int kTile = f32_tile_bytes<D>(), kStage = f32_stage_bytes<D>();
-    __shared__ __attribute__((aligned(1024))) char sm[2 * kStage];   // two stages of K rows, then V rows
+    constexpr int kRows = f32_rows<W>(), kCols = kRows, kTile = f32_tile_bytes<D, W>(), kStage = f32_stage_bytes<D, W>();
+    __shared__ __attribute__((aligned(1024))) char sm[f32_lds_bytes<D, W>()];   // two stages of K rows, then V rows
     __shared__ int64_t slot;
     __shared__ SmallWork mine;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
-    const int rg = wave & 1, part = wave >> 1;   // group of 32 queries; half of the stage's keys
+    const int rg = W == 4 ? wave & 1 : 0, part = W == 4 ? wave >> 1 : 0;   // group of 32 queries; half of the stage's keys
     const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
     const float scale = 1.0f / sqrtf((float)D);
     const bool small = s.build_rows != 0;
@@ -336,8 +348,8 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kern
         const float *kbase = k + t.orow0 * row_stride + (int64_t)t.head * D;
         const float *vbase = v + t.orow0 * row_stride + (int64_t)t.head * D;
         auto issue = [&](int j0, int buf) {
-            stage_rows<D>(sm + buf * kStage, kbase, row_stride, j0, L, wave, lane);
-            stage_rows<D>(sm + buf * kStage + kTile, vbase, row_stride, j0, L, wave, lane);
+            stage_rows<D, W>(sm + buf * kStage, kbase, row_stride, j0, L, wave, lane);
+            stage_rows<D, W>(sm + buf * kStage + kTile, vbase, row_stride, j0, L, wave, lane);
         };
         if (L > 0) issue(0, 0);
         float qr[D / 2], dor[D / 2];
@@ -356,8 +368,8 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kern
         f32x16 acc[D / 32];
         clear<D>(acc);
         stage_barrier();
-        for (int j0 = 0, buf = 0; j0 < Lc; j0 += kCols, buf ^= 1) {
-            if (j0 + kCols < Lc) issue(j0 + kCols, buf ^ 1);
+        for (int j0 = 0, buf = 0; j0 < Lc; j0 += kCols, buf ^= W == 4) {
+            if (W == 4 && j0 + kCols < Lc) issue(j0 + kCols, buf ^ 1);
             const int k0 = j0 + part * 32;
             if (active && k0 < Lc && !(causal && k0 > q0 + 31)) {
                 const char *kt = sm + buf * kStage + part * (32 * 4 * D), *vt = kt + kTile;
@@ -374,34 +386,40 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dq_f32_kern
                 accumulate<D>(acc, kt, elem_at, st);
             }
             stage_barrier();
+            if (W == 1 && j0 + kCols < Lc) {   // one buffer: the other workgroups of the compute unit fill the gap
+                issue(j0 + kCols, 0);
+                stage_barrier();
+            }
         }
         char *const region = sm + rg * (D * 128);
-        if (part == 1) park<D>(region, acc, lane);
-        __syncthreads();
+        if (W == 4) {
+            if (part == 1) park<D>(region, acc, lane);
+            __syncthreads();
+        }
         if (part == 0 && i < t.len) {
-            merge<D>(acc, region, lane, 1.0f, 1.0f);
+            if (W == 4) merge<D>(acc, region, lane, 1.0f, 1.0f);
             store_row<D>(dq + row, acc, scale, half);
         }
     }
 }
 
 // dK, dV: tile = 64 keys, stream the sample's queries (with their dO, lse, delta).
-template <int D>
-__global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_kernel(
+template <int D, int W>
+__global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void dkv_f32_kernel(
         const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
         const float *__restrict__ dout, const float *__restrict__ lse, const float *__restrict__ delta,
         const int64_t *__restrict__ offsets,   // of the keys
         const int64_t *__restrict__ offsets_q, bool causal, int B, int H, Schedule s, float *__restrict__ dk,
         float *__restrict__ dv) {
-    constexpr int kTile = f32_tile_bytes<D>(), kStage = f32_stage_bytes<D>();
-    __shared__ __attribute__((aligned(1024))) char sm[2 * kStage];   // two stages of Q rows, then dO rows
+    constexpr int kRows = f32_rows<W>(), kCols = kRows, kTile = f32_tile_bytes<D, W>(), kStage = f32_stage_bytes<D, W>();
+    __shared__ __attribute__((aligned(1024))) char sm[f32_lds_bytes<D, W>()];   // two stages of Q rows, then dO rows
     __shared__ __attribute__((aligned(16))) float lse_s[2][kCols], delta_s[2][kCols];   // lse and delta of the streamed rows
     static_assert(__alignof__(lse_s) >= 16 && __alignof__(delta_s) >= 16, "read four at a time");
     __shared__ int64_t slot;
     __shared__ SmallWork mine;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
-    const int rg = wave & 1, part = wave >> 1;   // group of 32 keys; half of the stage's queries
+    const int rg = W == 4 ? wave & 1 : 0, part = W == 4 ? wave >> 1 : 0;   // group of 32 keys; half of the stage's queries
     const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
     const float scale = 1.0f / sqrtf((float)D);
     const bool small = s.build_rows != 0;
@@ -426,8 +444,8 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
         // causal: key j is seen by queries j .. L - 1, so the stream starts at the stage that holds the tile's first key
         const int istart = causal ? t.block * kRows : 0;
         auto issue = [&](int i0, int buf) {
-            stage_rows<D>(sm + buf * kStage, qbase, row_stride, i0, L, wave, lane);
-            stage_rows<D>(sm + buf * kStage + kTile, obase, row_stride, i0, L, wave, lane);
+            stage_rows<D, W>(sm + buf * kStage, qbase, row_stride, i0, L, wave, lane);
+            stage_rows<D, W>(sm + buf * kStage + kTile, obase, row_stride, i0, L, wave, lane);
         };
         float lse_next = 0.0f, delta_next = 0.0f;      // statistics of the stage on its way (threads 0 .. 63)
         auto fetch_stats = [&](int i0) {
@@ -453,9 +471,9 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
         clear<D>(accv);
         store_stats(0);
         stage_barrier();
-        for (int i0 = istart, buf = 0; i0 < L; i0 += kCols, buf ^= 1) {
+        for (int i0 = istart, buf = 0; i0 < L; i0 += kCols, buf ^= W == 4) {
             const bool more = i0 + kCols < L;
-            if (more) {
+            if (W == 4 && more) {
                 issue(i0 + kCols, buf ^ 1);
                 fetch_stats(i0 + kCols);
             }
@@ -482,19 +500,28 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
                 accumulate<D>(accv, ot, elem_at, st);
                 accumulate<D>(acck, qt, elem_at, dp);
             }
-            if (more) store_stats(buf ^ 1);
+            if (W == 4 && more) store_stats(buf ^ 1);
             stage_barrier();
+            if (W == 1 && more) {
+                issue(i0 + kCols, 0);
+                fetch_stats(i0 + kCols);
+                store_stats(0);
+                stage_barrier();
+            }
         }
         // each wave of a pair finishes one gradient: waves 0 and 1 dK, waves 2 and 3 dV
         char *const region = sm + rg * (D * 256);
-        if (part == 0) park<D>(region, accv, lane); else park<D>(region + D * 128, acck, lane);
-        __syncthreads();
+        if (W == 4) {
+            if (part == 0) park<D>(region, accv, lane); else park<D>(region + D * 128, acck, lane);
+            __syncthreads();
+        }
         if (j < t.len) {
             if (part == 0) {
-                merge<D>(acck, region + D * 128, lane, 1.0f, 1.0f);
+                if (W == 4) merge<D>(acck, region + D * 128, lane, 1.0f, 1.0f);
                 store_row<D>(dk + row, acck, scale, half);
-            } else {
-                merge<D>(accv, region, lane, 1.0f, 1.0f);
+            }
+            if (W == 1 || part == 1) {
+                if (W == 4) merge<D>(accv, region, lane, 1.0f, 1.0f);
                 store_row<D>(dv + row, accv, 1.0f, half);
             }
         }
@@ -502,37 +529,49 @@ __global__ __launch_bounds__(kThreads, f32_waves_per_simd<D>()) void dkv_f32_ker
 }
 
 hipError_t launch_fwd_f32(const float *q, const float *k, const float *v, const int64_t *offsets,
-                          const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, float *out, float *lse,
+                          const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, int block_rows, float *out, float *lse,
                           int cus, hipStream_t stream) {
+#define JFA_LAUNCH(DD, W)                                                                                         \
+    hipLaunchKernelGGL((fwd_f32_kernel<DD, W>), dim3(persistent_grid<fwd_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
+                       q, k, v, offsets, offsets_kv, causal, B, H, s, out, lse)
 #define JFA_CASE(DD)                                                                                              \
     case DD:                                                                                                      \
-        hipLaunchKernelGGL(fwd_f32_kernel<DD>, dim3(persistent_grid<fwd_f32_kernel<DD>>(kThreads, cus)), dim3(kThreads), 0, stream, q, k, v, offsets, offsets_kv, causal, B, H, s, \
-                           out, lse);                                                                             \
+        if (block_rows == f32_rows<1>()) JFA_LAUNCH(DD, 1);                                                       \
+        else JFA_LAUNCH(DD, 4);                                                                                   \
         break;
     switch (D) {
         JFA_CASE(32) JFA_CASE(64) JFA_CASE(128)
         default: return hipErrorInvalidValue;
     }
 #undef JFA_CASE
+#undef JFA_LAUNCH
     return hipGetLastError();
 }
 
 hipError_t launch_bwd_f32(const float *q, const float *k, const float *v, const float *out, const float *dout,
                           const float *lse, const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H,
-                          int D, Schedule s_dq, Schedule s_dkv, float *dq, float *dk, float *dv, float *delta, int cus,
-                          hipStream_t stream) {
+                          int D, Schedule s_dq, int rows_dq, Schedule s_dkv, int rows_dkv, float *dq, float *dk, float *dv, float *delta,
+                          int cus, hipStream_t stream) {
+#define JFA_DQ(DD, W)                                                                                              \
+    hipLaunchKernelGGL((dq_f32_kernel<DD, W>), dim3(persistent_grid<dq_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
+                       q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, B, H, s_dq, dq)
+#define JFA_DKV(DD, W)                                                                                             \
+    hipLaunchKernelGGL((dkv_f32_kernel<DD, W>), dim3(persistent_grid<dkv_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
+                       q, k, v, dout, lse, delta, offsets_kv ? offsets_kv : offsets, offsets_kv ? offsets : nullptr, causal, B, H, s_dkv, dk, dv)
 #define JFA_CASE(DD)                                                                                               \
     case DD:                                                                                                       \
-        hipLaunchKernelGGL(dq_f32_kernel<DD>, dim3(persistent_grid<dq_f32_kernel<DD>>(kThreads, cus)), dim3(kThreads), 0, stream, q, k, v, out, dout, lse, delta,   \
-                           offsets, offsets_kv, causal, B, H, s_dq, dq);                                           \
-        hipLaunchKernelGGL(dkv_f32_kernel<DD>, dim3(persistent_grid<dkv_f32_kernel<DD>>(kThreads, cus)), dim3(kThreads), 0, stream, q, k, v, dout, lse, delta,  \
-                           offsets_kv ? offsets_kv : offsets, offsets_kv ? offsets : nullptr, causal, B, H, s_dkv, dk, dv);  \
+        if (rows_dq == f32_rows<1>()) JFA_DQ(DD, 1);                                                               \
+        else JFA_DQ(DD, 4);                                                                                        \
+        if (rows_dkv == f32_rows<1>()) JFA_DKV(DD, 1);                                                             \
+        else JFA_DKV(DD, 4);                                                                                       \
         break;
     switch (D) {
         JFA_CASE(32) JFA_CASE(64) JFA_CASE(128)
         default: return hipErrorInvalidValue;
     }
 #undef JFA_CASE
+#undef JFA_DKV
+#undef JFA_DQ
     return hipGetLastError();
 }
 

@@ -69,3 +69,35 @@ def test_many_short_samples(oracle, D, B):
     import numpy as np
     lengths = np.random.default_rng(35).integers(0, 21, size=B)
     test_gpu_f32.run_case(oracle, make_custom("many", lengths, 2, D, dtype="f32", seed=36 + D, max_len=20))
+
+
+SHORT = [1, 31, 32, 0, 7, 8, 9, 16, 30, 2]
+LONG = [70, 5, 0, 33, 64, 96, 1, 200, 31, 32]
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("form", ["causal", "short queries", "short keys", "both short"])
+def test_one_wave_workgroups(D, form):
+    """Streams of at most 32 rows: one-wave workgroups for the kernels they stream through (the keys through forward and dQ, the
+    queries through dK / dV), the others as before, in one call."""
+    if form == "causal":
+        return test_gpu_causal.run(make_custom("short", SHORT, 2, D, dtype="f32", seed=37 + D), 32)
+    lq, lk = (LONG if form == "short keys" else SHORT), (LONG if form == "short queries" else SHORT[::-1])
+    got, ref, oq, ok = test_gpu_cross.run(lq, lk, 2, D, "f32", 38 + D, max(lq), max(lk))
+    test_gpu_cross.compare(got, ref, "f32", oq, ok, lq, lk)
+
+
+@pytest.mark.parametrize("D", [32, 64, 128])
+@pytest.mark.parametrize("form", ["self", "causal", "cross"])
+def test_one_wave_workgroups_of_two_stages(oracle, D, form):
+    """Streams of at most 64 rows in a batch of more tiles than are dealt in the kernel: one-wave workgroups with up to two
+    stages, blocks of 32 rows, the schedule kernel."""
+    import numpy as np
+    rng = np.random.default_rng(39)
+    lengths = rng.integers(0, 65, size=700)
+    if form == "cross":
+        other = rng.integers(0, 65, size=700)
+        got, ref, oq, ok = test_gpu_cross.run(lengths, other, 2, D, "f32", 40 + D, 64, 64)
+        return test_gpu_cross.compare(got, ref, "f32", oq, ok, lengths, other)
+    w = make_custom("two", lengths, 2, D, dtype="f32", seed=41 + D, max_len=64)
+    test_gpu_causal.run(w, 64) if form == "causal" else test_gpu_f32.run_case(oracle, w)
