@@ -9,11 +9,14 @@
 //   * dP's accumulators start at minus delta (dQ, D = 32) or, with V negated, at delta (dK / dV), the scores of the dK / dV
 //     kernel at minus lse * sqrt(D): the stream's statistics are read from LDS straight into the accumulators, and P and dS
 //     are one multiply (or multiply-add), one exponential, one multiply and the conversions;
-//   * only stages that contain the sample's end or the diagonal mask;
+//   * only stages that contain the sample's end or the diagonal mask, and those skip a block of 32 rows that no lane needs
+//     (training step on 1024 samples of 1 to 1024 rows, H = 8, D = 64, 4494 -> 4446 us; 1000 of at most 20, H = 2: backward
+//     50 -> 41);
 //   * stages (and the stream's statistics) go directly to LDS, one ahead; gradients leave as whole rows.
 // Workgroups per compute unit: dQ four at D = 32 and three at D = 64.  Its rows of the forward's output pass through LDS and,
 // at D = 64, delta is subtracted from every dP, sixteen vector instructions more per block, which leaves registers for the third
-// without any spilled: 1024 samples of 1 to 1024 rows, H = 8, 1401 us (1457 with the addend and 15 registers spilled, 1569
+// without any spilled: 1024 samples of 1 to 1024 rows, H = 8, 1371 us (1401 before empty blocks
+// were skipped, 1457 with the addend and 15 registers spilled, 1569
 // with two workgroups); 256 samples of 64 rows on average, H = 2, 570 tiles, 16.4 us (20.3 and 22.6: scratch memory costs a
 // launch 4 us, and 512 places a second round); 64 samples of 4096 rows 1049 (1033).  D = 32 fits with the addend: subtracting
 // is 6 to 10 % slower there.  dK / dV two at D = 64 and three at D = 32 (one more spills: 5 % slower at D = 64; at D = 32 2 %
@@ -117,6 +120,7 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void dq_narrow_kernel(
                 const char *const vt = kt + N::kTile;
 #pragma unroll
                 for (int mb = 0; mb < 2; ++mb) {
+                    if (masked && mb == 1 && (CAUSAL && q0 + 32 < L ? q0 + 32 : L) - j * kNwStageRows <= 32) break;   // no key for any lane
                     __builtin_amdgcn_sched_barrier(0);   // the two blocks one after the other: side by side they spill
                     f32x16 sc, dp = ndelta;
 #pragma unroll
@@ -254,6 +258,7 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 2 : 3) void dkv_narrow_kernel
                 const char *const dot = qt + N::kTile;
 #pragma unroll
                 for (int mb = 0; mb < 2; ++mb) {
+                    if (masked && (mb == 1 ? L - jj * kNwStageRows <= 32 : CAUSAL && k0 - jj * kNwStageRows >= 32)) continue;   // no query for any lane
                     f32x16 sc, dp;
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
