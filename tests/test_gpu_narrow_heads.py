@@ -60,6 +60,13 @@ def test_dynamic_claims(oracle, D, B):
     run_self(oracle, make_custom("many", lengths, 8, D, dtype="bf16", seed=55 + D, max_len=2048))
 
 
+@pytest.mark.parametrize("B", [500, 700])   # static deal of a scheduler kernel's schedule, with and without an LDS copy of it
+@pytest.mark.parametrize("D", [32, 64])
+def test_static_deal(oracle, D, B):
+    lengths = np.random.default_rng(63).integers(0, 140, size=B)
+    run_self(oracle, make_custom("static", lengths, 2, D, dtype="bf16", seed=64 + D, max_len=2048))
+
+
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("D", [32, 64])
 def test_stale_reference_maximum(oracle, D, causal):
