@@ -62,6 +62,9 @@ typedef enum {
  * Forward, bf16 (Section 2.1).  q, k, v, out: bf16 [sum_B, H, D]; lse: fp32 [H, sum_B].
  * Scores and the P V product run on bf16 MFMA with fp32 accumulation; the softmax is fp32;
  * probabilities are rounded to bf16 before the second product; out is rounded to bf16 once.
+ * Probabilities are taken relative to a reference score of the row and normalised at the end.  The reference follows the
+ * row's maximum to within 2^8, except at D = 128 with max_len > 256, where a row's probabilities may reach 2^62 times
+ * the reference before it does: there |v| has to stay below 2^64 for the sums to stay finite in every case.
  */
 int jfa_forward(const void *q, const void *k, const void *v, const int64_t *offsets, int64_t B, int64_t max_len,
                 int H, int D, void *out, float *lse, void *stream);
@@ -83,7 +86,10 @@ int jfa_forward(const void *q, const void *k, const void *v, const int64_t *offs
 int jfa_forward_noalloc(const void *q, const void *k, const void *v, const int64_t *offsets, int64_t B,
                         int64_t max_len, int H, int D, void *out, float *lse, void *stream);
 
-/* Forward, fp32 end to end (same operation; plain FMA arithmetic, for small-tolerance use). */
+/*
+ * Forward, fp32 end to end: the same operation for small-tolerance use.  Products and sums run on the fp32 matrix
+ * instructions (fp32 products, fp32 accumulation); scores and log-sum-exp are fp32.
+ */
 int jfa_forward_f32(const float *q, const float *k, const float *v, const int64_t *offsets, int64_t B,
                     int64_t max_len, int H, int D, float *out, float *lse, void *stream);
 
@@ -232,8 +238,8 @@ int jfa_jagged_softmax_backward(const void *y, const void *dy, const int64_t *of
                                 void *dx, void *stream);
 
 /*
- * The offsets-driven work schedule on its own (the first kernel of every call above), for
- * inspection and tests.  For row blocks of block_rows rows it writes, on the device,
+ * The offsets-driven work schedule on its own (the first kernel of the attention calls on all but
+ * small problems, which build it in the attention kernel), for inspection and tests.  For row blocks of block_rows rows it writes, on the device,
  *   order      int32 [B]    sample ids, samples with more row blocks first
  *   tile_start int32 [B+1]  exclusive prefix sum of ceil(L_order[p] / block_rows); tile_start[B] = T
  * A work item w in [0, T*H) is (sample, head, row block): p = the position with

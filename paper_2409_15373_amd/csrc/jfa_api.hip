@@ -172,11 +172,10 @@ void drop_timed() {
     g_timed.clear();
 }
 
-// Forward variant: the direct-to-LDS kernel for long samples at D = 128, the register-staged one otherwise.
-enum FwdVariant { kNarrow = 0, kDma = 2 };
-FwdVariant forward_variant(int64_t max_len, int D, int H) {
-    if (D != 128 || (int64_t)H * D > (1 << 20)) return kNarrow;   // the direct-to-LDS kernels keep 32-bit row offsets
-    return max_len > 256 ? kDma : kNarrow;   // 256-query tiles only pay off when samples can be long
+// bf16 at D = 128: the direct-to-LDS kernels for long samples, the register-staged ones for short samples and for rows that the
+// former's 32-bit row offsets do not reach.  (D = 32 and 64 have kernels of their own for every length, and so has fp32.)
+bool long_samples(int64_t max_len, int D, int H) {
+    return D == 128 && (int64_t)H * D <= (1 << 20) && max_len > 256;   // 256-query tiles only pay off when samples can be long
 }
 
 // Small problems skip the scheduler launch: the attention kernels build the schedule themselves and deal the work
@@ -315,10 +314,11 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
         e = jfa::launch_fwd_cross_fewq(q, k, v, offsets, offsets_kv, (int)B, H, D, sc, out, lse, w.cus, s);
         return e == hipSuccess ? JFA_OK : hip_fail("fwd_cross_fewq", e);
     }
-    const FwdVariant variant = f32 ? kNarrow : forward_variant(max_len > max_len_kv ? max_len : max_len_kv, D, H);
-    const int block_rows = f32 ? jfa::f32_block_rows(max_len_kv, !small_problem(B, max_len, H, jfa::kF32BlockRows, w.cus)) : (variant == kNarrow ? jfa::kFwdBlockRows : jfa::kDmaBlockRows);
+    const bool dma = !f32 && long_samples(max_len > max_len_kv ? max_len : max_len_kv, D, H);
+    const bool many = !small_problem(B, max_len, H, jfa::kF32BlockRows, w.cus);
+    const int block_rows = f32 ? jfa::f32_block_rows(max_len_kv, many) : (dma ? jfa::kDmaBlockRows : jfa::kFwdBlockRows);
     jfa::Schedule sc{w.order[0], w.tile_start[0], w.counters};
-    if (variant == kNarrow && small_problem(B, max_len, H, block_rows, w.cus)) {
+    if (!dma && small_problem(B, max_len, H, block_rows, w.cus)) {
         sc.build_rows = block_rows;
         sc.static_only = true;
     } else {
@@ -327,8 +327,8 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
         if (e != hipSuccess) return hip_fail("schedule kernel", e);
     }
     if (f32) { ScopedTimer tm("fwd_f32", s); e = jfa::launch_fwd_f32((const float *)q, (const float *)k, (const float *)v, offsets, offsets_kv, causal, (int)B, H, D, sc, block_rows, (float *)out, lse, w.cus, s); }
-    else if (variant == kDma) { ScopedTimer tm("fwd_bf16_dma", s); e = jfa::launch_fwd_bf16_dma(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
-    else if (D < 128) { ScopedTimer tm("fwd_bf16", s); e = jfa::launch_fwd_narrow(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
+    else if (dma) { ScopedTimer tm("fwd_bf16_dma", s); e = jfa::launch_fwd_bf16_dma(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
+    else if (D < 128) { ScopedTimer tm("fwd_narrow", s); e = jfa::launch_fwd_narrow(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
     else { ScopedTimer tm("fwd_bf16", s); e = jfa::launch_fwd_bf16(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
     if (e != hipSuccess) return hip_fail("forward kernel", e);
     return JFA_OK;
@@ -352,8 +352,8 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
         e = jfa::launch_bwd_cross_fewq(q, k, v, out, dout, lse, delta, offsets, offsets_kv, (int)B, H, D, sc, dq, dk, dv, w.cus, s);
         return e == hipSuccess ? JFA_OK : hip_fail("bwd_cross_fewq", e);
     }
-    const bool dma = !f32 && D == 128 && forward_variant(max_len > max_len_kv ? max_len : max_len_kv, D, H) != kNarrow;
-    const int64_t longest = max_len > max_len_kv ? max_len : max_len_kv;
+        const int64_t longest = max_len > max_len_kv ? max_len : max_len_kv;
+    const bool dma = !f32 && long_samples(longest, D, H);
     const bool many = !small_problem(B, longest, H, jfa::kF32BlockRows, w.cus);
     const int block_rows = f32 ? jfa::f32_block_rows(max_len_kv, many) : (dma ? jfa::kDmaBlockRows : jfa::kBwdBlockRows);   // of queries
     const int key_rows = f32 ? jfa::f32_block_rows(max_len, many) : (dma ? jfa::kDkvBlockRows : block_rows);                // of keys
@@ -405,9 +405,9 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     }
     // the dQ kernel goes first: it computes delta = rowsum(dO o O) for its own rows and leaves it for the dK / dV kernel
     if (D < 128) {
-        { ScopedTimer tm("dq_bf16", s); e = jfa::launch_dq_narrow(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, (int)B, H, D, s_dq, dq, w.cus, s); }
+        { ScopedTimer tm("dq_narrow", s); e = jfa::launch_dq_narrow(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, (int)B, H, D, s_dq, dq, w.cus, s); }
         if (e != hipSuccess) return hip_fail("bf16 dQ kernel", e);
-        { ScopedTimer tm("dkv_bf16", s); e = jfa::launch_dkv_narrow(q, k, v, dout, delta, offsets_k, offsets_q_other, causal, (int)B, H, D, s_dkv, dk, dv, w.cus, s); }
+        { ScopedTimer tm("dkv_narrow", s); e = jfa::launch_dkv_narrow(q, k, v, dout, delta, offsets_k, offsets_q_other, causal, (int)B, H, D, s_dkv, dk, dv, w.cus, s); }
         return e == hipSuccess ? JFA_OK : hip_fail("bf16 dK/dV kernel", e);
     }
     { ScopedTimer tm("dq_bf16", s); e = jfa::launch_dq_bf16(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, (int)B, H, D, s_dq, dq, w.cus, s); }

@@ -20,11 +20,11 @@
 
 namespace jfa {
 
+constexpr int D = 128;                // head size
 constexpr int kBwdThreads = 256;
 constexpr int kBwdStage = 64;  // streamed rows per LDS stage
 
 // Global -> registers -> LDS staging of `kBwdStage` rows of one head of a [*, H, D] bf16 tensor.
-template <int D>
 struct Stage {
     static constexpr int kChunksPerRow = D / 8;
     static constexpr int kLoads = kBwdStage * kChunksPerRow / kBwdThreads;
@@ -48,7 +48,6 @@ struct Stage {
     }
 };
 
-template <int D>
 struct alignas(16) BwdSmem {
     // bytes per staged row: +80 keeps both the 16-byte row reads and the transposing reads (nearly) conflict-free
     // on the 64-bank LDS (16 lanes x 16 bytes need rows 16 bytes apart modulo 256, 4 rows x 64 bytes need them 64 apart)
@@ -61,7 +60,6 @@ struct alignas(16) BwdSmem {
 };
 
 // Store a transposed accumulator (rows = features, column = this lane's row of the output tensor).
-template <int D>
 __device__ inline void store_rows(__bf16 *dst_row, const f32x16 (&acc)[D / 32], float scale, int half) {
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
@@ -76,7 +74,7 @@ __device__ inline void store_rows(__bf16 *dst_row, const f32x16 (&acc)[D / 32], 
 
 // CROSS: keys and values are the rows of a second offsets array (offsets_kv); CAUSAL: query i sees keys 0 .. i.
 // See the forward kernel.
-template <int D, bool CROSS, bool CAUSAL>
+template <bool CROSS, bool CAUSAL>
 __global__ __launch_bounds__(kBwdThreads, 2) void dq_bf16_kernel(const __bf16 *__restrict__ q,
                                                                  const __bf16 *__restrict__ k,
                                                                  const __bf16 *__restrict__ v,
@@ -88,7 +86,7 @@ __global__ __launch_bounds__(kBwdThreads, 2) void dq_bf16_kernel(const __bf16 *_
                                                                  const int64_t *__restrict__ offsets_kv, int B, int H,
                                                                  Schedule s, __bf16 *__restrict__ dq) {
     constexpr int kKSteps = D / 16, kDBlocks = D / 32;
-    using Smem = BwdSmem<D>;
+    using Smem = BwdSmem;
     __shared__ Smem sm;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -162,7 +160,7 @@ __global__ __launch_bounds__(kBwdThreads, 2) void dq_bf16_kernel(const __bf16 *_
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[db][e] = 0.0f;
 
-        Stage<D> sk, sv;
+        Stage sk, sv;
         if (!CROSS || L > 0) {   // a sample without keys: nothing streams, dq = 0
             sk.prefetch(kbase, row_stride, 0, L);
             sv.prefetch(vbase, row_stride, 0, L);
@@ -214,14 +212,14 @@ __global__ __launch_bounds__(kBwdThreads, 2) void dq_bf16_kernel(const __bf16 *_
                 }
             }
         }
-        if (i < Lq) store_rows<D>(dq + (t.row0 + i) * row_stride + (int64_t)t.head * D, acc, scale, half);
+        if (i < Lq) store_rows(dq + (t.row0 + i) * row_stride + (int64_t)t.head * D, acc, scale, half);
     }
 }
 
 // CROSS: `offsets` are the keys' offsets (the work items are blocks of keys) and the queries, with dout, lse and
 // delta, are the rows of offsets_q.  CAUSAL: key j is seen by queries j .. L - 1: the stream starts at the stage that
 // holds the tile's first key, and streamed rows below the lane's key get P = 0.
-template <int D, bool CROSS, bool CAUSAL>
+template <bool CROSS, bool CAUSAL>
 __global__ __launch_bounds__(kBwdThreads, 1) void dkv_bf16_kernel(const __bf16 *__restrict__ q,
                                                                   const __bf16 *__restrict__ k,
                                                                   const __bf16 *__restrict__ v,
@@ -233,7 +231,7 @@ __global__ __launch_bounds__(kBwdThreads, 1) void dkv_bf16_kernel(const __bf16 *
                                                                   Schedule s, __bf16 *__restrict__ dk,
                                                                   __bf16 *__restrict__ dv) {
     constexpr int kKSteps = D / 16, kDBlocks = D / 32;
-    using Smem = BwdSmem<D>;
+    using Smem = BwdSmem;
     __shared__ Smem sm;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
@@ -288,7 +286,7 @@ __global__ __launch_bounds__(kBwdThreads, 1) void dkv_bf16_kernel(const __bf16 *
 #pragma unroll
             for (int e = 0; e < 16; ++e) { acck[db][e] = 0.0f; accv[db][e] = 0.0f; }
 
-        Stage<D> sq, sdo;
+        Stage sq, sdo;
         float lse_pre = 0.0f, delta_pre = 0.0f;
         auto prefetch_rows = [&](int i0) {
             sq.prefetch(qbase, row_stride, i0, L);
@@ -356,8 +354,8 @@ __global__ __launch_bounds__(kBwdThreads, 1) void dkv_bf16_kernel(const __bf16 *
         }
         if (j < Lk) {
             const int64_t off = (t.row0 + j) * row_stride + (int64_t)t.head * D;
-            store_rows<D>(dk + off, acck, scale, half);
-            store_rows<D>(dv + off, accv, 1.0f, half);
+            store_rows(dk + off, acck, scale, half);
+            store_rows(dv + off, accv, 1.0f, half);
         }
     }
 }
@@ -367,7 +365,7 @@ hipError_t launch_dkv_bf16(const void *q, const void *k, const void *v, const vo
                            int D, Schedule s, void *dk, void *dv, int cus, hipStream_t stream) {
     if (D != 128 || (causal && offsets_q)) return hipErrorInvalidValue;
 #define JFA_LAUNCH(CROSS, CAUSAL)                                                                            \
-    hipLaunchKernelGGL((dkv_bf16_kernel<128, CROSS, CAUSAL>), dim3(persistent_grid<dkv_bf16_kernel<128, CROSS, CAUSAL>>(kBwdThreads, cus)), \
+    hipLaunchKernelGGL((dkv_bf16_kernel<CROSS, CAUSAL>), dim3(persistent_grid<dkv_bf16_kernel<CROSS, CAUSAL>>(kBwdThreads, cus)), \
                        dim3(kBwdThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, lse, \
                        delta, offsets, offsets_q, B, H, s, (__bf16 *)dk, (__bf16 *)dv)
     if (offsets_q) JFA_LAUNCH(true, false);
@@ -382,7 +380,7 @@ hipError_t launch_dq_bf16(const void *q, const void *k, const void *v, const voi
                           int D, Schedule s, void *dq, int cus, hipStream_t stream) {
     if (D != 128 || (causal && offsets_kv)) return hipErrorInvalidValue;
 #define JFA_LAUNCH(CROSS, CAUSAL)                                                                            \
-    hipLaunchKernelGGL((dq_bf16_kernel<128, CROSS, CAUSAL>), dim3(persistent_grid<dq_bf16_kernel<128, CROSS, CAUSAL>>(kBwdThreads, cus)), \
+    hipLaunchKernelGGL((dq_bf16_kernel<CROSS, CAUSAL>), dim3(persistent_grid<dq_bf16_kernel<CROSS, CAUSAL>>(kBwdThreads, cus)), \
                        dim3(kBwdThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, lse, \
                        (const __bf16 *)out, delta, offsets, offsets_kv, B, H, s, (__bf16 *)dq)
     if (offsets_kv) JFA_LAUNCH(true, false);

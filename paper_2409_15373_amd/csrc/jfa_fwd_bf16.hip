@@ -18,10 +18,10 @@
 
 namespace jfa {
 
+constexpr int D = 128;                // head size
 constexpr int kFwdThreads = 256;
 constexpr int kFwdBN = 64;  // keys per LDS stage
 
-template <int D>
 struct alignas(16) FwdSmem {
     // 64 banks x 4 bytes: 16 lanes x 16 bytes (one pass of a 16-byte read) are conflict-free when rows are
     // 16 bytes apart modulo 256; 32 lanes x 8 bytes of the transposing read (4 rows x 64 bytes) are
@@ -36,7 +36,7 @@ struct alignas(16) FwdSmem {
 // CROSS: the keys and values of a sample are the rows of a second offsets array (cross attention); otherwise
 // offsets_kv is not looked at and the code is that of self attention.  CAUSAL (self attention only): query i
 // attends to keys 0 .. i of its sample; a tile streams the keys up to its last query and masks above the diagonal.
-template <int D, bool CROSS, bool CAUSAL>
+template <bool CROSS, bool CAUSAL>
 __global__ __launch_bounds__(kFwdThreads, 2) void fwd_bf16_kernel(const __bf16 *__restrict__ q,
                                                                   const __bf16 *__restrict__ k,
                                                                   const __bf16 *__restrict__ v,
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kFwdThreads, 2) void fwd_bf16_kernel(const __bf16 *
     constexpr int kDBlocks = D / 32;              // 32-row blocks of O^T
     constexpr int kChunksPerRow = D / 8;          // 16-byte chunks per row
     constexpr int kLoads = kFwdBN * kChunksPerRow / kFwdThreads;  // chunks per thread per tensor per stage
-    using Smem = FwdSmem<D>;
+    using Smem = FwdSmem;
     __shared__ Smem sm;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -287,7 +287,7 @@ hipError_t launch_fwd_bf16(const void *q, const void *k, const void *v, const in
                            int cus, hipStream_t stream) {
     if (D != 128 || (causal && offsets_kv)) return hipErrorInvalidValue;
 #define JFA_LAUNCH(CROSS, CAUSAL)                                                                            \
-    hipLaunchKernelGGL((fwd_bf16_kernel<128, CROSS, CAUSAL>), dim3(persistent_grid<fwd_bf16_kernel<128, CROSS, CAUSAL>>(kFwdThreads, cus)), \
+    hipLaunchKernelGGL((fwd_bf16_kernel<CROSS, CAUSAL>), dim3(persistent_grid<fwd_bf16_kernel<CROSS, CAUSAL>>(kFwdThreads, cus)), \
                        dim3(kFwdThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, offsets, offsets_kv, B, H, s, \
                        (__bf16 *)out, lse)
     if (offsets_kv) JFA_LAUNCH(true, false);
