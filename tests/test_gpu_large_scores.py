@@ -1,5 +1,5 @@
-"""Large random scores through the direct-to-LDS kernels (D = 128, samples longer than 256 rows), forward and backward,
-self, causal and cross attention.
+"""Large random scores through the direct-to-LDS kernels (D = 128, samples longer than 256 rows; D = 32 and 64), forward and
+backward, self, causal and cross attention.
 
 Queries and keys are drawn with standard deviation 2 and 4, so scaled scores q.k / sqrt(D) have standard deviation 4
 and 16 and reach +-15 and +-70: an error of relative size e in a score changes its probability by |score| * e, which is
@@ -18,12 +18,12 @@ from paper_2409_15373_amd.synthetic import offsets_from_lengths, round_to_bf16_b
 from helpers import f64, gate_bf16
 
 pytestmark = pytest.mark.gpu
-H, D = 2, 128
+H = 2
 LQ = [600, 300, 257, 1000, 40, 1]
 LK = [520, 300, 700, 64, 290, 333]
 
 
-def bf16_pair(rng, n, sigma):
+def bf16_pair(rng, n, D, sigma):
     bits = round_to_bf16_bits((rng.standard_normal((n, H, D)) * sigma).astype(np.float32))
     return bf16_bits_to_f32(bits), torch.from_numpy(bits.view(np.int16)).view(torch.bfloat16).cuda()
 
@@ -32,7 +32,7 @@ def scaled(name, got, ref):
     return gate_bf16(name, got, ref, abs_tol=2e-2 * max(1.0, float(np.abs(ref).max()) / 2))
 
 
-def nan_buffers(nq, nk):
+def nan_buffers(nq, nk, D):
     nan = float("nan")
     mk = lambda n: torch.full((n, H, D), nan, dtype=torch.bfloat16, device="cuda")
     return mk(nq), torch.full((H, nq), nan, dtype=torch.float32, device="cuda"), mk(nq), mk(nk), mk(nk)
@@ -40,16 +40,17 @@ def nan_buffers(nq, nk):
 
 @pytest.mark.parametrize("sigma", [2.0, 4.0])
 @pytest.mark.parametrize("mode", ["self", "causal", "cross"])
-def test_large_scores_on_the_direct_to_lds_kernels(oracle, mode, sigma):
+@pytest.mark.parametrize("D", [128, 64, 32])
+def test_large_scores_on_the_direct_to_lds_kernels(oracle, D, mode, sigma):
     from paper_2409_15373_amd import binding
     rng = np.random.default_rng(int(sigma) * 10 + len(mode))
     oq = offsets_from_lengths(np.array(LQ))
     ok = offsets_from_lengths(np.array(LK)) if mode == "cross" else oq
     nq, nk = int(oq[-1]), int(ok[-1])
-    (q, qd), (do, dod) = bf16_pair(rng, nq, sigma), bf16_pair(rng, nq, 1.0)
-    (k, kd), (v, vd) = bf16_pair(rng, nk, sigma), bf16_pair(rng, nk, 1.0)
+    (q, qd), (do, dod) = bf16_pair(rng, nq, D, sigma), bf16_pair(rng, nq, D, 1.0)
+    (k, kd), (v, vd) = bf16_pair(rng, nk, D, sigma), bf16_pair(rng, nk, D, 1.0)
     oqd, okd = torch.from_numpy(oq).cuda(), torch.from_numpy(ok).cuda()
-    out, lse, dq, dk, dv = nan_buffers(nq, nk)
+    out, lse, dq, dk, dv = nan_buffers(nq, nk, D)
     stats = torch.empty((2, H, nq), dtype=torch.float32, device="cuda")
     max_len = 1024                                          # > 256 at D = 128: the direct-to-LDS kernels
     if mode == "cross":
@@ -68,7 +69,7 @@ def test_large_scores_on_the_direct_to_lds_kernels(oracle, mode, sigma):
             r_out, r_lse = oracle.forward(q, k, v, oq)
             r_dq, r_dk, r_dv, _ = oracle.backward(q, k, v, do, oq)
     torch.cuda.synchronize()
-    tag = f"{mode} sigma {sigma}: "
+    tag = f"{mode} D {D} sigma {sigma}: "
     res = [gate_bf16(tag + "out", f64(out), r_out), scaled(tag + "lse", f64(lse), r_lse),
            scaled(tag + "dq", f64(dq), r_dq), scaled(tag + "dk", f64(dk), r_dk), scaled(tag + "dv", f64(dv), r_dv)]
     print(tag + "  ".join(f"{n} {a:.2e}/{r:.2e}" for n, (a, r) in zip(("out", "lse", "dq", "dk", "dv"), res)), flush=True)
