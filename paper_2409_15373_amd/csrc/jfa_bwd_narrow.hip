@@ -15,15 +15,14 @@
 //   * stages (and the stream's statistics) go directly to LDS, one ahead; gradients leave as whole rows.
 // Workgroups per compute unit: dQ four at D = 32 and three at D = 64.  Its rows of the forward's output pass through LDS and,
 // at D = 64, delta is subtracted from every dP, sixteen vector instructions more per block, which leaves registers for the third
-// without any spilled: 1024 samples of 1 to 1024 rows, H = 8, 1371 us (1401 before empty blocks
-// were skipped, 1457 with the addend and 15 registers spilled, 1569
-// with two workgroups); 256 samples of 64 rows on average, H = 2, 570 tiles, 16.4 us (20.3 and 22.6: scratch memory costs a
-// launch 4 us, and 512 places a second round); 64 samples of 4096 rows 1049 (1033).  D = 32 fits with the addend: subtracting
-// is 6 to 10 % slower there.  dK / dV two at D = 64 and three at D = 32 (one more spills: 5 % slower at D = 64; at D = 32 2 %
-// faster on that batch but 1 to 4 us slower a launch, for the scratch memory).
-// H * D = 512, whole backward, microseconds before -> now: 1024 samples of 1 to 1024 rows D = 64 4045 -> 3200, D = 32
-// 4572 -> 3630; 64 samples of 4096 rows D = 64 8698 -> 6942 (774 TFLOP/s), D = 32 10617 -> 7912.  A 32 x 32 block costs a SIMD
-// about 44 clocks per matrix instruction (12 + 16) and 3.8 per vector instruction (56 + 64; 134 + 96 before).
+// without any spilled: 1024 samples of 1 to 1024 rows, H = 8, 1401 us (1371 with empty blocks skipped; 1457 with the addend and
+// 15 registers spilled, 1569 with two workgroups); 256 samples of 64 rows on average, H = 2, 570 tiles, 16.4 us (20.3 and 22.6:
+// scratch memory costs a launch 4 us, and 512 places a second round); 64 samples of 4096 rows 1049 (1033).  D = 32 fits with the
+// addend: subtracting is 6 to 10 % slower there.  dK / dV two at D = 64 and three at D = 32 (one more spills: 5 % slower at
+// D = 64; at D = 32 2 % faster on that batch but 1 to 4 us slower a launch, for the scratch memory).
+// H * D = 512, whole backward, microseconds before -> now: 1024 samples of 1 to 1024 rows D = 64 4100 -> 3290, D = 32
+// 4840 -> 3850; 64 samples of 4096 rows D = 64 9000 -> 6940 (792 TFLOP/s), D = 32 10750 -> 8130.  A 32 x 32 block costs a SIMD
+// about 44 clocks per matrix instruction (12 + 16) and 3.8 per vector instruction (72 + 64; 134 + 96 before).
 // The dQ kernel runs first: it forms delta and -lse * sqrt(D) for its queries and leaves them in the two planes of `stats`.
 #include "jfa_narrow.h"
 

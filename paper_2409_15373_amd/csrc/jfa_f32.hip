@@ -19,7 +19,7 @@
 // accumulator register v is then the B operand of the next product's step v (streamed rows (v / 4) 8 + 4 (l / 32) + v % 4
 // as its two slots), whose A operand is one element per lane of the transposed streamed tile, read row by row.
 // Measured at B = 256, H = 2, D = 64, lengths uniform on [1, 512] against the former kernels (vector FMA, a row per four
-// lanes, scores one by one): forward 589 -> 182 us, forward + backward 1861 -> 689 us.
+// lanes, scores one by one): forward 590 -> 159 us, forward + backward 1861 -> 663 us.
 #include "jfa_common.h"
 #include "jfa_mfma.h"
 #include "jfa_lds.h"

@@ -14,10 +14,13 @@
 //     stores, one barrier per stage;
 //   * three (D = 64) or four workgroups per compute unit, which are not in step, fill each other's start-up (one more of
 //     either spills: equal on long samples, 5 % slower on short ones); the next item is claimed while the first loads
-//     travel; outputs leave as whole rows; the claim and the stage are not copied over the kernel (15 KB of instructions;
+//     travel; outputs leave as whole rows; the claim and the stage are not copied over the kernel (20 KB of instructions;
 //     at 42 KB, with three buffers and a copy of the stage for each, a tile's start took half as long again).
-// H * D = 512, microseconds before -> now: 1024 samples of 1 to 1024 rows D = 64 1220 -> 1099, D = 32 1532 -> 1370;
-// 64 samples of 4096 rows D = 64 2507 -> 2198 (1000 TFLOP/s), D = 32 3403 -> 2950; 1024 of 512 rows D = 64 928 -> 825.
+// H * D = 512, microseconds before -> now: 1024 samples of 1 to 1024 rows D = 64 1208 -> 1098, D = 32 1600 -> 1432;
+// 64 samples of 4096 rows D = 64 2468 -> 2255 (975 TFLOP/s), D = 32 3328 -> 2905; 1024 of 512 rows D = 64 875 -> 786.
+// (A reference fixed for the whole tile, redone where its row sum passes 2^62: D = 64 1080, 2178 and 768, D = 32 as now; but
+// the largest probability of a row is then rounded to bf16 instead of 1, which shows at large scores, and values above 2^65
+// can overflow.)
 #include "jfa_narrow.h"
 
 namespace jfa {
