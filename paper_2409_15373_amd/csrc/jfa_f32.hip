@@ -40,7 +40,7 @@ template <int D, int W> constexpr int f32_lds_bytes() {
     constexpr int stages = (W == 4 ? 2 : 1) * f32_stage_bytes<D, W>(), scratch = kInlineScratchInts * (int)sizeof(int);
     return stages > scratch ? stages : scratch;
 }
-// D = 128 needs 128 KB of stages and more than 256 registers in the backward: one workgroup per compute unit
+// D = 128 needs more than 256 registers in the backward, and 128 KB of stages with four waves: one such workgroup per compute unit
 template <int D> constexpr int f32_waves_per_simd() { return D <= 64 ? 2 : 1; }
 
 // Up to this many items per workgroup are dealt round-robin from the sorted schedule, without claims.  A claim is an atomic on
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void fwd_f32_kerne
     }
 }
 
-// dQ: tile = 64 queries, stream the sample's keys.  The kernel is the first of the backward: it holds each query's dO
+// dQ: tile = 64 (one wave: 32) queries, stream the sample's keys.  The kernel is the first of the backward: it holds each query's dO
 // row anyway, reads the matching row of the forward's output, and computes delta = rowsum(dO o O) for its own use
 // and for the dK / dV kernel (no separate pass over dO and O, one launch less).
 template <int D, int W>
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void dq_f32_kernel
     }
 }
 
-// dK, dV: tile = 64 keys, stream the sample's queries (with their dO, lse, delta).
+// dK, dV: tile = 64 (one wave: 32) keys, stream the sample's queries (with their dO, lse, delta).
 template <int D, int W>
 __global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void dkv_f32_kernel(
         const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
