@@ -72,7 +72,7 @@ int jfa_forward(const void *q, const void *k, const void *v, const int64_t *offs
 /*
  * jfa_forward for callers that cannot allocate device memory: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments, kernels and results (bit for bit) as jfa_forward, but the private
- * work table (64 counters and two schedules, 8 (B + 33) bytes up to alignment) lives in a fixed array in device
+ * work table (1 KB of counters and two schedules, 16 B bytes up to alignment) lives in a fixed array in device
  * memory instead of a table allocated per (device, stream): about 1 MiB that every GPU the library runs on holds
  * until the process ends.  The call allocates and frees nothing and does not synchronise; the array's address is
  * looked up once per device, on the first call made with that device current.

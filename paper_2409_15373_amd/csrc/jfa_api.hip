@@ -34,7 +34,7 @@ std::map<std::pair<int, hipStream_t>, Table> g_tables;
 std::map<int, int> g_cu_count;
 
 constexpr size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-constexpr size_t sched_bytes(int64_t B) { return align_up((size_t)(2 * B + 1) * sizeof(int32_t), 256); }
+constexpr size_t sched_bytes(int64_t B) { return align_up((size_t)(2 * B + 1) * sizeof(int32_t), 16); }
 constexpr size_t table_bytes(int64_t B) { return (size_t)jfa::kNumCounters * sizeof(int32_t) + 2 * sched_bytes(B); }
 
 struct Views {
@@ -373,7 +373,7 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     }
     if (f32) {
         jfa::Schedule s_dq{w.order[0], w.tile_start[0], w.counters};
-        jfa::Schedule s_dkv{w.order[kv], w.tile_start[kv], w.counters + jfa::kXcds};
+        jfa::Schedule s_dkv{w.order[kv], w.tile_start[kv], w.counters + 1};
         if (in_kernel) {   // every kernel builds the schedule of its own work items, in LDS
             s_dq.static_only = s_dkv.static_only = true;
             s_dq.build_rows = block_rows;
@@ -389,7 +389,7 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
         // long samples at D = 128: dQ (which also fills both statistics planes) on schedule 0, then dK and dV together on
         // 128-key blocks (schedule 1: blocks of keys, for cross attention from the keys' offsets)
         jfa::Schedule s_dq{w.order[0], w.tile_start[0], w.counters};
-        jfa::Schedule s_dkv{w.order[1], w.tile_start[1], w.counters + jfa::kXcds};
+        jfa::Schedule s_dkv{w.order[1], w.tile_start[1], w.counters + 1};
         { ScopedTimer tm("dq_bf16_dma", s); e = jfa::launch_bwd_dq_dma(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, (int)B, H, D, s_dq, dq, w.cus, s); }
         if (e != hipSuccess) return hip_fail("dq_bf16_dma", e);
         { ScopedTimer tm("dkv_bf16_dma", s); e = jfa::launch_bwd_dkv_dma(q, k, v, dout, delta, offsets_k, offsets_q_other, causal, (int)B, H, D, s_dkv, dk, dv, w.cus, s); }
@@ -397,7 +397,7 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
         return JFA_OK;
     }
     jfa::Schedule s_dq{w.order[0], w.tile_start[0], w.counters};
-    jfa::Schedule s_dkv{w.order[kv], w.tile_start[kv], w.counters + jfa::kXcds};
+    jfa::Schedule s_dkv{w.order[kv], w.tile_start[kv], w.counters + 1};
     if (in_kernel) {   // every kernel builds the schedule of its own work items, in LDS
         s_dq.static_only = s_dkv.static_only = true;
         s_dq.build_rows = block_rows;

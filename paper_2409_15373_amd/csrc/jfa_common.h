@@ -6,8 +6,14 @@
 
 namespace jfa {
 
-// Number of int32 work counters at the head of the private work table.
-constexpr int kNumCounters = 64;
+// The work counters at the head of the private work table: two schedules with kXcds queues each, a counter per queue.  A claim is
+// an atomic of the whole device, and those that meet on one 128-byte line are served one after the other: with all counters on
+// one line a workgroup of a batch of short tiles waits some 10 us for each claim.  So every queue has a line of its own (the two
+// schedules', which are never in use at the same time, share it).
+// Microseconds, one line -> lines of their own, B x H, lengths: forward 512 x 8 with up to 256 targets against up to 1024 keys,
+// D = 32, 163 -> 122; 1024 x 4 up to 200, D = 32, forward 119 -> 63, backward 241 -> 134, D = 64 115 -> 76 and 248 -> 206;
+// 4096 x 1 up to 32, D = 64, 89 -> 58 and 162 -> 102; 1024 x 4 Zipf to 1024, D = 128, forward 708 -> 700.
+constexpr int kCounterStride = 32;   // int32 words from one queue's counter to the next
 // Histogram bins of the scheduler's counting sort (samples with >= kSchedBins-1 row blocks share the top bin).
 constexpr int kSchedBins = 1024;
 
@@ -15,7 +21,7 @@ constexpr int kSchedBins = 1024;
 struct Schedule {
     const int32_t *order;       // [B]
     const int32_t *tile_start;  // [B+1]
-    int32_t *counter;           // kXcds zeroed work counters (one queue per XCD), bumped by the persistent workgroups
+    int32_t *counter;           // kXcds zeroed work counters (one queue per XCD), kCounterStride words apart, bumped by the persistent workgroups
     // Small problems (see build_small_work) run without a scheduler launch: the counters are then not valid
     // and work is dealt statically (static_only); build_rows > 0 tells the kernel to build the schedule itself, in LDS, for
     // row blocks of that many rows (order and tile_start are then not looked at), 0 that the scheduler kernel has filled them.
@@ -30,6 +36,7 @@ struct Schedule {
 // die's queue first and then helps the others, so the assumption about placement only affects locality.
 constexpr int kXcds = 8;
 constexpr int kWorkGroup = 32;
+constexpr int kNumCounters = kXcds * kCounterStride;   // schedule i's counter of queue y: word y * kCounterStride + i
 
 // Work id of local index t of queue y.
 __device__ inline int64_t work_id(int y, int t) {
@@ -79,14 +86,14 @@ __device__ inline int64_t next_work(int32_t *counters, WorkCursor &cur, int64_t 
         cur.home_done = true;  // ids grow with the local index: nothing later in this queue is valid either
     }
     if (!cur.home_done) {
-        const int64_t id = work_id(home, base + atomicAdd(&counters[home], 1));
+        const int64_t id = work_id(home, base + atomicAdd(&counters[home * kCounterStride], 1));
         if (id < total) return id;
         cur.home_done = true;
     }
     for (;;) {
         int seen[kXcds];  // all eight counters in one round of independent loads
 #pragma unroll
-        for (int y = 0; y < kXcds; ++y) seen[y] = __atomic_load_n(&counters[y], __ATOMIC_RELAXED);
+        for (int y = 0; y < kXcds; ++y) seen[y] = __atomic_load_n(&counters[y * kCounterStride], __ATOMIC_RELAXED);
         bool any = false;
 #pragma unroll
         for (int d = 1; d < kXcds; ++d) {
@@ -96,7 +103,7 @@ __device__ inline int64_t next_work(int32_t *counters, WorkCursor &cur, int64_t 
             for (int z = 0; z < kXcds; ++z) c = z == y ? seen[z] : c;
             if (work_id(y, base + c) >= total) continue;
             any = true;
-            const int64_t id = work_id(y, base + atomicAdd(&counters[y], 1));
+            const int64_t id = work_id(y, base + atomicAdd(&counters[y * kCounterStride], 1));
             if (id < total) return id;
         }
         if (!any) return -1;  // counters only grow, so this loop ends

@@ -43,8 +43,8 @@ template <int D, int W> constexpr int f32_lds_bytes() {
 // D = 128 needs more than 256 registers in the backward, and 128 KB of stages with four waves: one such workgroup per compute unit
 template <int D> constexpr int f32_waves_per_simd() { return D <= 64 ? 2 : 1; }
 
-// Up to this many items per workgroup are dealt round-robin from the sorted schedule, without claims.  A claim is an atomic on
-// one of eight counters that share a cache line, and its latency heads everything a tile does: at D <= 64 that costs more than
+// Up to this many items per workgroup are dealt round-robin from the sorted schedule, without claims.  A claim is an atomic
+// of the whole device, and its latency heads everything a tile does: at D <= 64 that costs more than
 // the last tiles' imbalance (B = 256, H = 2, lengths to 512, 4.5 items: D = 64 forward 184 -> 158 us, backward 509 -> 495; 500
 // samples of at most 100 rows, H = 8, 6 to 8 items, D = 32: 125 -> 56 and 240 -> 163).  At D = 128, with half the workgroups and
 // twice the time per tile, balance is worth more (9 items: 343 -> 358), and next_work()'s own limit of four holds.

@@ -157,13 +157,13 @@ struct NarrowWalk {
         int open = home_done ? 0 : 1;          // queues to ask, a bit per lane
         for (;;) {
             if (open == 0) {   // look at all queues with plain loads, spend an atomic only on one that still shows work
-                const bool more = lane < kXcds && work_id(y, base + __atomic_load_n(&s.counter[y], __ATOMIC_RELAXED)) < total;
+                const bool more = lane < kXcds && work_id(y, base + __atomic_load_n(&s.counter[y * kCounterStride], __ATOMIC_RELAXED)) < total;
                 open = (int)__builtin_amdgcn_ballot_w64(more);
                 if (open == 0) return -1;   // counters only grow, so this loop ends
             }
             const int ask = __builtin_ctz(open);
             int64_t id = 0;
-            if (lane == ask) id = work_id(y, base + atomicAdd(&s.counter[y], 1));
+            if (lane == ask) id = work_id(y, base + atomicAdd(&s.counter[y * kCounterStride], 1));
             const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)id, ask), hi = __builtin_amdgcn_readlane((uint32_t)((uint64_t)id >> 32), ask);
             id = (int64_t)(((uint64_t)hi << 32) | lo);
             if (id < total) return id;
