@@ -181,10 +181,28 @@ bool long_samples(int64_t max_len, int D, int H) {
 // Small problems skip the scheduler launch: the attention kernels build the schedule themselves and deal the work
 // statically (see build_small_work).  max_len bounds every sample's length, so B * blocks(max_len) * H bounds
 // the number of work items; at most four per workgroup is the size up to which static dealing is used anyway.
-bool small_problem(int64_t B, int64_t max_len, int H, int block_rows, int cus) {
+bool small_problem(int64_t B, int64_t max_len, int H, int block_rows, int cus, int per_cu = jfa::kSmallItems) {
     if (B > jfa::kInlineCap) return false;
     const int64_t blocks = (max_len + block_rows - 1) / block_rows;
-    return B * (blocks > 0 ? blocks : 1) * (int64_t)H <= 4 * (int64_t)cus;
+    return B * (blocks > 0 ? blocks : 1) * (int64_t)H <= per_cu * (int64_t)cus;
+}
+
+// The same for the kernels for head sizes 32 and 64.  Their two-wave workgroups are at least two to a compute unit, which makes it
+// eight items; but with many samples the sort in one wave takes longer than the launch it saves (1000 x 2 samples of at most 20
+// rows, D = 32: 24 us, 15.5 with the launch).
+bool narrow_small_problem(int64_t B, int64_t max_len, int H, int block_rows, int cus) {
+    return small_problem(B, max_len, H, block_rows, cus, block_rows == jfa::kNarrowShortBlockRows && B <= 256 ? 2 * jfa::kSmallItems : jfa::kSmallItems);
+}
+
+// Rows per tile at head sizes 32 and 64; streamed: the rows that pass a tile.  A small backward at D = 64 takes 64-row tiles of keys
+// up to 256 rows as well: its dK / dV kernel has two workgroups per compute unit and 128-row tiles often need a second round
+// (256 samples of 64 rows on average, H = 2, 570 tiles: backward 36.8 -> 30.6 us).
+int narrow_rows(int64_t max_len, int64_t max_streamed, int64_t B, int H, int cus) {
+    return jfa::narrow_block_rows(max_len, max_streamed, small_problem(B, max_len, H, jfa::kNarrowBlockRows, cus));
+}
+int narrow_key_rows(int64_t max_len, int64_t max_streamed, int64_t B, int H, int D, int cus) {
+    if (D == 64 && max_len <= 256 && max_streamed <= 256 && narrow_small_problem(B, max_len, H, jfa::kNarrowShortBlockRows, cus)) return jfa::kNarrowShortBlockRows;
+    return narrow_rows(max_len, max_streamed, B, H, cus);
 }
 
 int hip_fail(const char *what, hipError_t e) { return fail(JFA_ERR_HIP, "%s: %s", what, hipGetErrorString(e)); }
@@ -316,9 +334,11 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
     }
     const bool dma = !f32 && long_samples(max_len > max_len_kv ? max_len : max_len_kv, D, H);
     const bool many = !small_problem(B, max_len, H, jfa::kF32BlockRows, w.cus);
-    const int block_rows = f32 ? jfa::f32_block_rows(max_len_kv, many) : (dma ? jfa::kDmaBlockRows : jfa::kFwdBlockRows);
+    const int block_rows = f32 ? jfa::f32_block_rows(max_len_kv, many) : dma ? jfa::kDmaBlockRows : D < 128 ? narrow_rows(max_len, max_len_kv, B, H, w.cus) : jfa::kFwdBlockRows;
     jfa::Schedule sc{w.order[0], w.tile_start[0], w.counters};
-    if (!dma && small_problem(B, max_len, H, block_rows, w.cus)) {
+    sc.fixed_items = jfa::narrow_fixed_items(max_len_kv);
+    const bool narrow = !f32 && D < 128;
+    if (!dma && (narrow ? narrow_small_problem(B, max_len, H, block_rows, w.cus) : small_problem(B, max_len, H, block_rows, w.cus))) {
         sc.build_rows = block_rows;
         sc.static_only = true;
     } else {
@@ -328,7 +348,7 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
     }
     if (f32) { ScopedTimer tm("fwd_f32", s); e = jfa::launch_fwd_f32((const float *)q, (const float *)k, (const float *)v, offsets, offsets_kv, causal, (int)B, H, D, sc, block_rows, (float *)out, lse, w.cus, s); }
     else if (dma) { ScopedTimer tm("fwd_bf16_dma", s); e = jfa::launch_fwd_bf16_dma(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
-    else if (D < 128) { ScopedTimer tm("fwd_narrow", s); e = jfa::launch_fwd_narrow(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
+    else if (D < 128) { ScopedTimer tm("fwd_narrow", s); e = jfa::launch_fwd_narrow(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, block_rows, out, lse, w.cus, s); }
     else { ScopedTimer tm("fwd_bf16", s); e = jfa::launch_fwd_bf16(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
     if (e != hipSuccess) return hip_fail("forward kernel", e);
     return JFA_OK;
@@ -352,23 +372,26 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
         e = jfa::launch_bwd_cross_fewq(q, k, v, out, dout, lse, delta, offsets, offsets_kv, (int)B, H, D, sc, dq, dk, dv, w.cus, s);
         return e == hipSuccess ? JFA_OK : hip_fail("bwd_cross_fewq", e);
     }
-        const int64_t longest = max_len > max_len_kv ? max_len : max_len_kv;
+    const int64_t longest = max_len > max_len_kv ? max_len : max_len_kv;
     const bool dma = !f32 && long_samples(longest, D, H);
     const bool many = !small_problem(B, longest, H, jfa::kF32BlockRows, w.cus);
-    const int block_rows = f32 ? jfa::f32_block_rows(max_len_kv, many) : (dma ? jfa::kDmaBlockRows : jfa::kBwdBlockRows);   // of queries
-    const int key_rows = f32 ? jfa::f32_block_rows(max_len, many) : (dma ? jfa::kDkvBlockRows : block_rows);                // of keys
+    const int block_rows = f32 ? jfa::f32_block_rows(max_len_kv, many) : dma ? jfa::kDmaBlockRows : D < 128 ? narrow_rows(max_len, max_len_kv, B, H, w.cus) : jfa::kBwdBlockRows;   // of queries
+    const int key_rows = f32 ? jfa::f32_block_rows(max_len, many) : dma ? jfa::kDkvBlockRows : D < 128 ? narrow_key_rows(max_len_kv, max_len, B, H, D, w.cus) : jfa::kBwdBlockRows;   // of keys
     // Schedule 0: blocks of queries.  Schedule 1: blocks of keys, where they differ: cross attention, and the direct-to-LDS
     // kernels, whose dK / dV blocks are shorter.  One launch builds both and clears all work counters before the first
     // kernel that uses one.  Small problems on the other kernels have no scheduler launch: those kernels build their
     // schedule themselves.
-    const int kv = offsets_kv ? 1 : 0;
+    const int kv = offsets_kv || key_rows != block_rows ? 1 : 0;
     const int64_t *const offsets_k = offsets_kv ? offsets_kv : offsets;   // the keys' offsets
     const int64_t *const offsets_q_other = offsets_kv ? offsets : nullptr;   // the queries', as the second array of dK / dV
-    const bool in_kernel = !dma && small_problem(B, longest, H, block_rows < key_rows ? block_rows : key_rows, w.cus);
+    auto small = [&](int64_t longest_stationary, int rows) {
+        return !f32 && D < 128 ? narrow_small_problem(B, longest_stationary, H, rows, w.cus) : small_problem(B, longest_stationary, H, rows, w.cus);
+    };
+    const bool in_kernel = !dma && small(max_len, block_rows) && small(max_len_kv, key_rows);
     if (!in_kernel) {
         const jfa::ScheduleJob jobs[2] = {schedule_job(offsets, offsets_kv, block_rows, w, 0),
                                           schedule_job(offsets_k, offsets_q_other, key_rows, w, 1)};
-        e = schedule(jobs, dma || offsets_kv ? 2 : 1, B, w, s);
+        e = schedule(jobs, kv + 1, B, w, s);
         if (e != hipSuccess) return hip_fail("schedule kernel", e);
     }
     if (f32) {
@@ -401,13 +424,15 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     if (in_kernel) {   // every kernel builds the schedule of its own work items, in LDS
         s_dq.static_only = s_dkv.static_only = true;
         s_dq.build_rows = block_rows;
-        s_dkv.build_rows = block_rows;
+        s_dkv.build_rows = key_rows;
     }
+    s_dq.fixed_items = jfa::narrow_fixed_items(max_len_kv);
+    s_dkv.fixed_items = jfa::narrow_fixed_items(max_len);
     // the dQ kernel goes first: it computes delta = rowsum(dO o O) for its own rows and leaves it for the dK / dV kernel
     if (D < 128) {
-        { ScopedTimer tm("dq_narrow", s); e = jfa::launch_dq_narrow(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, (int)B, H, D, s_dq, dq, w.cus, s); }
+        { ScopedTimer tm("dq_narrow", s); e = jfa::launch_dq_narrow(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, (int)B, H, D, s_dq, block_rows, dq, w.cus, s); }
         if (e != hipSuccess) return hip_fail("bf16 dQ kernel", e);
-        { ScopedTimer tm("dkv_narrow", s); e = jfa::launch_dkv_narrow(q, k, v, dout, delta, offsets_k, offsets_q_other, causal, (int)B, H, D, s_dkv, dk, dv, w.cus, s); }
+        { ScopedTimer tm("dkv_narrow", s); e = jfa::launch_dkv_narrow(q, k, v, dout, delta, offsets_k, offsets_q_other, causal, (int)B, H, D, s_dkv, key_rows, dk, dv, w.cus, s); }
         return e == hipSuccess ? JFA_OK : hip_fail("bf16 dK/dV kernel", e);
     }
     { ScopedTimer tm("dq_bf16", s); e = jfa::launch_dq_bf16(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, (int)B, H, D, s_dq, dq, w.cus, s); }

@@ -27,6 +27,7 @@ struct Schedule {
     // row blocks of that many rows (order and tile_start are then not looked at), 0 that the scheduler kernel has filled them.
     int build_rows = 0;
     bool static_only = false;
+    int fixed_items = 4;   // up to this many items per workgroup are dealt without claims (kernels that walk with NarrowWalk)
 };
 
 // The chip has 8 accelerator dies (XCDs), each with its own L2, and workgroups are dealt to them round-robin
@@ -48,7 +49,9 @@ struct WorkCursor {
     bool first = true;
     bool home_done = false;
     bool static_only = false;   // the counters are not valid (schedule built in the kernel): deal statically whatever the size
+    int fixed_items = 4;   // problems of at most this many items per workgroup are dealt statically
     int64_t next = -1;   // small problems: next statically assigned id
+    int step = 0;        // ... and the distance to the one after it
     int grid = 0;        // gridDim.x, read once: the dispatch packet it comes from is a slow place to read
 };
 
@@ -68,13 +71,15 @@ __device__ inline int cursor_grid(WorkCursor &cur) {
 //     static ones, hence the gridDim / 8 base; the grid is a multiple of 8).
 //   * Once the home queue is empty the workgroup looks at all eight counters with plain loads and only
 //     spends an atomic on a queue that still shows work.
-//   * Problems of at most four items per workgroup skip all of this (see below).
+//   * Problems of at most `fixed_items` items per workgroup skip all of this (see below).
 __device__ inline int64_t next_work(int32_t *counters, WorkCursor &cur, int64_t total) {
-    // Small problems (at most four items per workgroup) are dealt round-robin with no atomics at all: the
-    // items are sorted longest-first, so the deal is even, and the claim traffic would dominate the run time.
+    // Small problems are dealt without any atomics, the claim traffic would dominate the run time: the items are sorted longest
+    // first and every other round goes backwards (whoever had the longest item of one gets the shortest of the next), so the deal
+    // is even to less than an item.
     const int grid = cursor_grid(cur);
-    if (cur.static_only || total <= 4 * (int64_t)grid) {
-        cur.next = cur.next < 0 ? blockIdx.x : cur.next + grid;
+    if (cur.static_only || total <= cur.fixed_items * (int64_t)grid) {
+        cur.step = cur.next < 0 ? 2 * (int)blockIdx.x + 1 : 2 * grid - cur.step;
+        cur.next = cur.next < 0 ? blockIdx.x : cur.next + cur.step;
         return cur.next < total ? cur.next : -1;
     }
     const int home = blockIdx.x % kXcds;
@@ -190,7 +195,7 @@ struct WorkSlot {
 // kept in LDS: every workgroup computes the same schedule -- samples in descending order of their stream's block
 // count, equal counts in sample order, the order the scheduler kernel produces (samples in their own order when there
 // is at most one item per workgroup) -- and decodes from it the at most
-// kSmallItems work items that the static deal gives it (item blockIdx + n * gridDim), so that nothing of the
+// kSmallItems work items that the static deal gives it (one of every gridDim), so that nothing of the
 // schedule is written to or read back from memory: after the one trip for the lengths, an item costs one more for
 // its sample's offsets.  Lengths are fetched once, by all threads at once, into LDS; one wave then runs a counting
 // sort over at most kInlineBins keys, in which the ranks inside a bin come from ballots, a scan of the block counts
@@ -292,7 +297,7 @@ __device__ inline void build_small_work(const int64_t *offsets, const int64_t *o
         const int64_t total = (int64_t)blocks * H;
         int my_p = 0, my_r = 0, n_items = 0;
         for (int n = 0; n < kSmallItems; ++n) {
-            const int64_t w = (int64_t)blockIdx.x + (int64_t)n * gridDim.x;
+            const int64_t w = (int64_t)n * gridDim.x + (n & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x);   // every other round backwards, as in next_work()
             if (w >= total) break;
             int lo = 0, hi = B;   // invariant: start[lo] * H <= w < start[hi] * H
             while (hi - lo > 1) {
@@ -333,13 +338,14 @@ __device__ inline void build_small_work(const int64_t *offsets, const int64_t *o
 }
 
 // Persistent-grid size for `kernel`: every compute unit filled to the kernel's occupancy, no more
-// (extra workgroups would only find the work counter exhausted).  Queried once per kernel.
-template <auto Kernel>
+// (extra workgroups would only find the work counter exhausted).  Queried once per kernel.  AtLeast: workgroups per compute unit
+// that the caller relies on (the kernel has the registers and the LDS for them; they need not be resident at the same time).
+template <auto Kernel, int AtLeast = 1>
 inline int persistent_grid(int threads, int cus) {
     static int per_cu = 0;  // one instance per kernel function
     if (per_cu == 0) {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, Kernel, threads, 0) != hipSuccess || n < 1) n = 1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, Kernel, threads, 0) != hipSuccess || n < AtLeast) n = AtLeast;
         per_cu = n;
     }
     const int grid = cus * per_cu;
@@ -529,16 +535,39 @@ hipError_t launch_dq_bf16(const void *q, const void *k, const void *v, const voi
                           float *delta, const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H,
                           int D, Schedule s, void *dq, int cus, hipStream_t stream);
 
-// bf16 attention for D = 32 and 64 at every length (blocks of kFwdBlockRows / kBwdBlockRows rows).  The dQ launch comes first and
-// fills `stats` [2, H, sum_B] (delta, -lse * sqrt(D)) for the dK / dV launch.
+// bf16 attention for D = 32 and 64 at every length.  The dQ launch comes first and fills `stats` [2, H, sum_B]
+// (delta, -lse * sqrt(D)) for the dK / dV launch.
+// Rows of a tile: 128 (four waves) or 64 (two).  With short samples most waves of a 128-row tile have no rows but take registers
+// and places; two-wave workgroups put more tiles on a compute unit at once, and a stage's copies on fewer waves, which long
+// streams pay for.  Microseconds, 128 -> 64 rows, forward and backward: 4096 samples of at most 32 rows, D = 64, 59 -> 35 and
+// 104 -> 60, D = 32 31 -> 27 and 73 -> 41; 500 x 8 of at most 100, D = 64, 39 -> 37 and 88 -> 78; 1024 x 4, 32 queries against at
+// most 200 keys, D = 64, forward 44 -> 36; but 1024 x 4 of at most 200 rows 77 -> 103 and 206 -> 272, and four samples of 4096 keys
+// with 32 queries 53 -> 60.  In small problems (see small_problem()) the second condition loses 0.5 us.
+constexpr int kNarrowBlockRows = 128, kNarrowShortBlockRows = 64;
+inline int narrow_block_rows(int64_t max_len, int64_t max_streamed, bool small) {
+    const bool two_waves = (max_len <= 128 && max_streamed <= 128) || (max_len <= 64 && max_streamed <= 256 && !small);
+    return two_waves ? kNarrowShortBlockRows : kNarrowBlockRows;
+}
+// Items per workgroup up to which work is dealt without claims.  Longest items first and every other round backwards, such a
+// deal is even to less than an item; a claim costs a short item more than that.  Long items gain nothing from it, and it parts the
+// blocks that share streamed rows.  Microseconds with 4 and with 16 items: 1024 x 8 of at most 100 rows, D = 32, forward 84 and 53,
+// backward 172 and 126; 500 x 8, 200 queries against at most 100 keys, 58 and 40, 112 and 89; 300 x 8 Zipf to 300, D = 64, 68 and 62;
+// but 1024 x 2 of at most 500, D = 32, 83 and 88, 190 and 207; 512 x 8, 256 targets against 1024 keys, D = 32, 122 and 145.
+inline int narrow_fixed_items(int64_t max_streamed) { return max_streamed <= 384 ? 16 : 4; }
 hipError_t launch_dq_narrow(const void *q, const void *k, const void *v, const void *out, const void *dout, const float *lse, float *stats,
-                            const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, void *dq,
-                            int cus, hipStream_t stream);
+                            const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, int block_rows,
+                            void *dq, int cus, hipStream_t stream);
 hipError_t launch_dkv_narrow(const void *q, const void *k, const void *v, const void *dout, const float *stats, const int64_t *offsets,
-                             const int64_t *offsets_q, bool causal, int B, int H, int D, Schedule s, void *dk, void *dv, int cus,
-                             hipStream_t stream);
+                             const int64_t *offsets_q, bool causal, int B, int H, int D, Schedule s, int block_rows, void *dk, void *dv,
+                             int cus, hipStream_t stream);
+hipError_t launch_dq_narrow_short(const void *q, const void *k, const void *v, const void *out, const void *dout, const float *lse, float *stats,
+                                  const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, void *dq,
+                                  int cus, hipStream_t stream);
+hipError_t launch_dkv_narrow_short(const void *q, const void *k, const void *v, const void *dout, const float *stats, const int64_t *offsets,
+                                   const int64_t *offsets_q, bool causal, int B, int H, int D, Schedule s, void *dk, void *dv, int cus,
+                                   hipStream_t stream);
 hipError_t launch_fwd_narrow(const void *q, const void *k, const void *v, const int64_t *offsets, const int64_t *offsets_kv, bool causal,
-                             int B, int H, int D, Schedule s, void *out, float *lse, int cus, hipStream_t stream);
+                             int B, int H, int D, Schedule s, int block_rows, void *out, float *lse, int cus, hipStream_t stream);
 
 // bf16 attention, direct-to-LDS kernels (D = 128, long samples; work items are blocks of kDmaBlockRows rows)
 constexpr int kDmaBlockRows = 256;

@@ -1,7 +1,7 @@
 // Jagged flash attention forward, bf16, head sizes 32 and 64 (paper Section 2.1).
 //
-// Same mathematics and operand layouts as fwd_bf16_kernel: work item = (sample, head, 128 queries), four waves of 32
-// queries, transposed score tile S^T = K Q^T (a lane owns one query), O^T += V^T P^T with V^T from the transposing read.
+// Same mathematics and operand layouts as fwd_bf16_kernel: work item = (sample, head, 128 queries), four waves of 32 (short
+// samples: 64 queries, two waves; see narrow_block_rows()), transposed score tile S^T = K Q^T (a lane owns one query), O^T += V^T P^T with V^T from the transposing read.
 // A score costs the same vector work at every head size and a half or a quarter of the matrix work of D = 128, and the two
 // hardly overlap on a SIMD (a stage of 64 keys takes a wave's SIMD 1070 clocks at D = 64, 720 at D = 32: about 44 per
 // matrix instruction and 3.8 per vector instruction), so vector instructions are what bounds these sizes, and on short
@@ -29,12 +29,12 @@ namespace jfa {
 constexpr float kStale = 0x1p8f;
 
 // CROSS: keys and values are the rows of a second offsets array; CAUSAL: query i sees keys 0 .. i.  See fwd_bf16_kernel.
-template <int D, bool CROSS, bool CAUSAL>
-__global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel(
+template <int D, int W, bool CROSS, bool CAUSAL>
+__global__ __launch_bounds__(64 * W, D == 64 ? (W == 4 ? 3 : 2) : 4) void fwd_narrow_kernel(
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, const int64_t *__restrict__ offsets,
     const int64_t *__restrict__ offsets_kv, int B, int H, Schedule s, __bf16 *__restrict__ out, float *__restrict__ lse) {
     using N = Narrow<D>;
-    constexpr int kKSteps = D / 16, kDBlocks = D / 32;
+    constexpr int kKSteps = D / 16, kDBlocks = D / 32, kRows = 32 * W;   // kRows: queries of a tile
     __shared__ __attribute__((aligned(1024))) char st[kNwStages * N::kStage];   // buffer b: K at b * kStage, V behind it
     __shared__ typename NarrowWalk<CROSS>::Shared walk_mem;
     static_assert(sizeof(st) >= kInlineScratchInts * sizeof(int), "the stage buffers double as the scheduler's scratch");
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
     const int64_t sum_B = offsets[B];
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
     const NarrowAddresses<D> at(lane);
-    const NarrowCopier<D> copier(wave, lane, row_stride);
+    const NarrowCopier<D, W> copier(wave, lane, row_stride);
     NarrowWalk<CROSS> walk(&walk_mem, s, offsets, offsets_kv, B, H, reinterpret_cast<int *>(st));
 
     Work t{};
@@ -58,11 +58,11 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
         const int Lq = t.len;                      // queries of the sample
         const int L = CROSS ? t.olen : t.len;      // keys of the sample
         const int64_t krow0 = CROSS ? t.orow0 : t.row0;
-        const int q0 = t.block * kFwdBlockRows + wave * 32;   // first query of this wave
+        const int q0 = t.block * kRows + wave * 32;   // first query of this wave
         const int i = q0 + col;                               // this lane's query; rows past the end repeat the last one
         const int iq = i < Lq ? i : Lq - 1;
         const bool wave_active = q0 < Lq;
-        const int Lc = CAUSAL && (t.block + 1) * kFwdBlockRows < L ? (t.block + 1) * kFwdBlockRows : L;   // keys this tile needs
+        const int Lc = CAUSAL && (t.block + 1) * kRows < L ? (t.block + 1) * kRows : L;   // keys this tile needs
         const int n_stages = have ? (Lc + kNwStageRows - 1) / kNwStageRows : 0;
         const __bf16 *const kbase = k + krow0 * row_stride + (int64_t)t.head * D;
         const __bf16 *const vbase = v + krow0 * row_stride + (int64_t)t.head * D;
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
             };
             end_stage();   // stage 0 has landed
             // stages unmasked for every wave of the tile (a causal tile's first wave has the fewest)
-            const int n_plain = (CAUSAL && t.block * kFwdBlockRows + 1 < L ? t.block * kFwdBlockRows + 1 : L) / kNwStageRows;
+            const int n_plain = (CAUSAL && t.block * kRows + 1 < L ? t.block * kRows + 1 : L) / kNwStageRows;
             for (int j = 0; j < n_stages; ++j) {
                 for (; (j & 1) && j + 3 <= n_plain && !maximum_first; j += 2) {   // two steady stages at a time: buffers 1 and 0, offsets in the instructions
                     copier.template copy<true>(kbase, vbase, (j + 1) * kNwStageRows, L, st);
@@ -209,20 +209,20 @@ __global__ __launch_bounds__(kNwThreads, D == 64 ? 3 : 4) void fwd_narrow_kernel
 }
 
 hipError_t launch_fwd_narrow(const void *q, const void *k, const void *v, const int64_t *offsets, const int64_t *offsets_kv, bool causal,
-                             int B, int H, int D, Schedule s, void *out, float *lse, int cus, hipStream_t stream) {
+                             int B, int H, int D, Schedule s, int block_rows, void *out, float *lse, int cus, hipStream_t stream) {
     if (causal && offsets_kv) return hipErrorInvalidValue;
-#define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                        \
-    hipLaunchKernelGGL((fwd_narrow_kernel<DD, CROSS, CAUSAL>), dim3(persistent_grid<fwd_narrow_kernel<DD, CROSS, CAUSAL>>(kNwThreads, cus)), \
-                       dim3(kNwThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, offsets, offsets_kv, B, H, s, \
+#define JFA_LAUNCH(DD, W, CROSS, CAUSAL)                                                                     \
+    hipLaunchKernelGGL((fwd_narrow_kernel<DD, W, CROSS, CAUSAL>), dim3(persistent_grid<fwd_narrow_kernel<DD, W, CROSS, CAUSAL>, W == 2 ? 2 : 1>(64 * W, cus)), \
+                       dim3(64 * W), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, offsets, offsets_kv, B, H, s, \
                        (__bf16 *)out, lse)
-#define JFA_CASE(DD)                                                                                         \
-    case DD:                                                                                                 \
-        if (offsets_kv) JFA_LAUNCH(DD, true, false);                                                         \
-        else if (causal) JFA_LAUNCH(DD, false, true);                                                        \
-        else JFA_LAUNCH(DD, false, false);                                                                   \
+#define JFA_CASE(DD, W)                                                                                      \
+    case DD * 1000 + 32 * W:                                                                                 \
+        if (offsets_kv) JFA_LAUNCH(DD, W, true, false);                                                      \
+        else if (causal) JFA_LAUNCH(DD, W, false, true);                                                     \
+        else JFA_LAUNCH(DD, W, false, false);                                                                \
         break;
-    switch (D) {
-        JFA_CASE(32) JFA_CASE(64)
+    switch (D * 1000 + block_rows) {
+        JFA_CASE(32, 2) JFA_CASE(32, 4) JFA_CASE(64, 2) JFA_CASE(64, 4)
         default: return hipErrorInvalidValue;
     }
 #undef JFA_CASE

@@ -7,7 +7,6 @@
 
 namespace jfa {
 
-constexpr int kNwThreads = 256;
 constexpr int kNwStageRows = 64;   // streamed rows per LDS stage
 constexpr int kNwStages = 2;       // stage buffers; stage j lives in buffer j % 2, copies run one stage ahead
 
@@ -51,9 +50,10 @@ struct NarrowAddresses {
 // fetches depends on its row modulo 16 only (the swizzle), so that the lane offsets of 16 rows are kept for the whole kernel
 // and everything else is in the scalar base.  They fit 32 bits while H * D <= 2^24; wider rows take 64-bit addresses.
 // Rows past the end repeat the last row (masked by the caller).
-template <int D>
+template <int D, int W>   // W: waves of the workgroup
 struct NarrowCopier {
     using N = Narrow<D>;
+    static constexpr int kWaveRows = kNwStageRows / W;    // rows of a stage that one wave copies
     static constexpr int kPer16 = 16 / N::kRowsPerCopy;   // instructions for 16 rows
     uint32_t off[kPer16];
     int wave, lane;
@@ -81,15 +81,15 @@ struct NarrowCopier {
             }
         }
     }
-    // The wave's 16 rows of stage rows r0 .. r0 + 63 of the two tensors of `n` rows at `a` and `b` -> stage buffer.
+    // The wave's kWaveRows rows of stage rows r0 .. r0 + 63 of the two tensors of `n` rows at `a` and `b` -> stage buffer.
     template <bool kFull = false>
     __device__ inline void copy(const __bf16 *a, const __bf16 *b, int r0, int n, char *stage) const {
-        int w0 = r0 + wave * 16;                 // first row of this wave
+        int w0 = r0 + wave * kWaveRows;          // first row of this wave
         const int left = n - w0;
-        if (!kFull && left < 1) w0 = n - 1;      // behind the end: the last row, sixteen times
-        char *const dst = stage + wave * 16 * N::kRow;
-        copy16<16, kFull>(a + w0 * row_stride, left < 1 ? 1 : left, dst);
-        copy16<16, kFull>(b + w0 * row_stride, left < 1 ? 1 : left, dst + N::kTile);
+        if (!kFull && left < 1) w0 = n - 1;      // behind the end: the last row, kWaveRows times
+        char *const dst = stage + wave * kWaveRows * N::kRow;
+        copy16<kWaveRows, kFull>(a + w0 * row_stride, left < 1 ? 1 : left, dst);
+        copy16<kWaveRows, kFull>(b + w0 * row_stride, left < 1 ? 1 : left, dst + N::kTile);
     }
     // A wave's 32 rows, `first` .. of the `n` rows at `base` (first < n) -> `dst`, 32 * kRow bytes of its own
     __device__ inline void copy_rows(const __bf16 *base, int first, int n, char *dst) const {
@@ -101,8 +101,8 @@ struct NarrowCopier {
 // built in LDS; otherwise wave 0 claims and decodes the NEXT item while the current one's first loads travel.  The claim is
 // next_work() with the queues on the lanes, at one place in the kernel: the kernels are as long as the instruction cache
 // likes without it.  For batches of at most kTabCap samples and 65535 tiles the tile starts and the sample order are kept
-// as 16-bit LDS copies, and decoding is a search in LDS and one trip to memory for the sample's offsets.  Where the workgroup
-// has four items at most, filling them pays for smaller batches only: 1000 samples of at most 20 rows, H = 2, D = 32, backward
+// as 16-bit LDS copies, and decoding is a search in LDS and one trip to memory for the sample's offsets.  Where work is
+// dealt without claims, filling them pays for smaller batches only: 1000 samples of at most 20 rows, H = 2, D = 32, backward
 // 30.0 us with, 27.8 without; 300 of at most 300, H = 8, D = 64, cross forward 32.2 with, 34.2 without.
 constexpr int kTabCapFixed = 512;
 template <bool CROSS>
@@ -118,7 +118,7 @@ struct NarrowWalk {
     int B, H, n = 0;
     int64_t total = 0, next_static = 0;
     bool small, tabled = false, fixed_deal = false, home_done = false;
-    int grid;
+    int grid, step = 0;
     // `scratch`: kInlineScratchInts ints of LDS, free until the first item starts.  Called by every thread.
     __device__ inline NarrowWalk(Shared *sh_, const Schedule &s_, const int64_t *offsets_, const int64_t *offsets_other_, int B_, int H_,
                                  int *scratch)
@@ -131,8 +131,9 @@ struct NarrowWalk {
         } else {
             const int tiles = s.tile_start[B];
             total = (int64_t)tiles * H;
-            fixed_deal = s.static_only || total <= 4 * (int64_t)grid;   // as next_work()
+            fixed_deal = s.static_only || total <= s.fixed_items * (int64_t)grid;
             next_static = blockIdx.x;
+            step = 2 * (grid - 1 - (int)blockIdx.x) + 1;   // as next_work(): every other round backwards
             if (!fixed_deal) {   // the first item of the home queue is assigned without a claim; see next_work()
                 next_static = work_id(blockIdx.x % kXcds, blockIdx.x / kXcds);
                 home_done = next_static >= total;
@@ -149,7 +150,8 @@ struct NarrowWalk {
     __device__ inline int64_t next_id() {
         if (fixed_deal || (next_static >= 0 && !home_done)) {
             const int64_t id = next_static;
-            next_static = fixed_deal ? id + grid : -1;
+            next_static = fixed_deal ? id + step : -1;
+            step = 2 * grid - step;
             return id < total ? id : -1;
         }
         const int lane = threadIdx.x & 63, home = blockIdx.x % kXcds, base = grid / kXcds;

@@ -194,3 +194,43 @@ def test_rows_wider_than_32_bit_offsets():
         for name, g, r in zip(("out", "dq", "dk", "dv"), (out, dq, dk, dv), zip(*ref)):
             r = torch.cat(r).numpy()
             gate_bf16(name, f64(g[:, h]), r, abs_tol=2e-2 * max(1.0, float(np.abs(r).max()) / 2))
+
+
+SHORT = [1, 31, 32, 33, 0, 63, 64, 65, 95, 96, 97, 127, 128]
+
+
+def everything(form, D, lq, lk, max_q, max_k, seed):
+    """out, lse, dq, dk, dv and delta of a call with these bounds on the lengths; the inputs are a function of the seed."""
+    from paper_2409_15373_amd import binding
+    from paper_2409_15373_amd.synthetic import offsets_from_lengths
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    oq, ok = (torch.from_numpy(offsets_from_lengths(np.array(x))).cuda() for x in (lq, lk))
+    q, do = (torch.randn(sum(lq), 2, D, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    k, v = (torch.randn(sum(lk), 2, D, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    if form == "cross":
+        out, lse = binding.jfa_forward_cross(q, k, v, oq, ok, max_q, max_k)
+        return (out, lse) + tuple(binding.jfa_backward_cross(q, k, v, out, do, lse, oq, ok, max_q, max_k))
+    out, lse = binding.jfa_forward(q, k, v, oq, max_q, causal=form == "causal")
+    return (out, lse) + tuple(binding.jfa_backward(q, k, v, out, do, lse, oq, max_q, causal=form == "causal"))
+
+
+@pytest.mark.parametrize("copies", [1, 400])   # schedule built in the kernel; scheduler kernel, and a fixed deal of several rounds
+@pytest.mark.parametrize("form", ["self", "causal", "cross", "few queries", "few keys", "keys in shorter blocks", "causal, keys in shorter blocks"])
+@pytest.mark.parametrize("D", [32, 64])
+def test_two_wave_workgroups(D, form, copies):
+    """64-row tiles do the same arithmetic in the same order as 128-row ones, which a large bound on the lengths selects and which
+    the tests above hold to the oracle.  They take samples of at most 128 rows on both sides, at most 64 rows against at most 256
+    in large batches, and the keys of a small backward at D = 64 with samples of up to 256 rows."""
+    lq = lk = SHORT * copies
+    if form == "cross":
+        lk = lq[4:] + lq[:4]
+    elif form.startswith("few"):
+        lq, lk = [min(x, 64) for x in lq], ([200, 256, 129] + lk)[:len(lk)]
+        lq, lk = (lq, lk) if form == "few queries" else (lk, lq)
+    elif form.endswith("shorter blocks"):
+        lq = lk = [256, 1, 130, 64, 0, 193, 65, 200] * copies
+    mode = "causal" if form.startswith("causal") else "self" if form in ("self", "keys in shorter blocks") else "cross"
+    got = everything(mode, D, lq, lk, max(lq), max(lk), 65 + D)
+    ref = everything(mode, D, lq, lk, 4096, 4096, 65 + D)
+    for name, g, r in zip(("out", "lse", "dq", "dk", "dv", "delta"), got, ref):
+        assert torch.equal(g, r) and not bool(torch.isnan(g).any()), name
