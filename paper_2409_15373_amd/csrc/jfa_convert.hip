@@ -6,7 +6,8 @@
 // prefix, so a tile is all padding (a fill, or nothing to do on the way back), all data, or data followed by padding,
 // and it is one contiguous block on the jagged side too.  All accesses are 16 bytes per lane on consecutive addresses,
 // and every store covers whole 128-byte lines (a row is a multiple of 16 bytes; anything at or above 128 bytes per
-// row keeps lines whole).
+// row keeps lines whole).  Stores go past the L2 (non-temporal; there and back, 1024 samples of up to 1024 rows of 1 KB:
+// 487 -> 472 us; loads past it as well: 477).
 #include "jfa_common.h"
 #include "jfa_mfma.h"
 
@@ -33,12 +34,12 @@ __global__ __launch_bounds__(kCvThreads) void convert_kernel(const u32x4 *__rest
             const u32x4 *s = src + (TO_DENSE ? s0 + i0 : dense0 + i0) * row_chunks;      // ... and input side
             if (n_data == 0) {   // all padding
                 if (TO_DENSE)
-                    for (int id = tid; id < n; id += kCvThreads) d[id] = padv;
+                    for (int id = tid; id < n; id += kCvThreads) __builtin_nontemporal_store(padv, d + id);
             } else if (n_data == n) {   // all data
 #pragma unroll 4
-                for (int id = tid; id < n; id += kCvThreads) d[id] = s[id];
+                for (int id = tid; id < n; id += kCvThreads) __builtin_nontemporal_store(s[id], d + id);
             } else {   // the sample ends inside the tile
-                for (int id = tid; id < (TO_DENSE ? n : n_data); id += kCvThreads) d[id] = id < n_data ? s[id] : padv;
+                for (int id = tid; id < (TO_DENSE ? n : n_data); id += kCvThreads) __builtin_nontemporal_store(id < n_data ? s[id] : padv, d + id);
             }
         }
     }

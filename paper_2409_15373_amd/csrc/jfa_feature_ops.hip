@@ -6,7 +6,13 @@
 // All four move O(sum_B (D + T)) bytes for O(sum_B D T) flops with D, T <= 128: they are bound by HBM, and the
 // matrix cores only keep the arithmetic out of the way.  Every global access is 16 bytes per lane on consecutive
 // addresses (a sample's rows are one contiguous block), operands reach the MFMA layout through LDS, and results
-// go back through LDS so that stores cover whole rows.
+// go back through LDS so that stores cover whole rows.  Rows are stored past the L2 (non-temporal): nobody in the kernel reads
+// them again, and the second sweep's rows and the matrices stay.  The memory-side cache keeps the last 256 MB that an operator
+// touched, so an operator that walks the samples the other way begins with what its predecessor ended with: jagged_dense_bmm,
+// which sits between the others in a forward and a backward pass, takes the last samples first.  Softmax, product, both gradients
+// and the softmax's gradient on 16384 samples of up to 512 rows, D = T = 64, microseconds: 1229, the order alone 1214, both 1188
+// (loads past the L2 as well: 1201; walks that claim two samples ahead, so that a sample starts without the latency of claim and
+// offsets: 1275, the workgroups' ends are a sample further apart).
 #include "jfa_common.h"
 #include "jfa_mfma.h"
 
@@ -61,7 +67,7 @@ __device__ inline int claim_sample(int32_t *counter, int B, int n_claimed, int *
 template <int D, int T> constexpr int bmm_claim_group() { return D + T <= 64 ? 2 : 1; }
 template <int D> constexpr int softmax_claim_group() { return D <= 32 ? 2 : 1; }
 
-// ---- jagged_dense_bmm: out^T = w_b^T x^T, one sample per workgroup step, 128 rows at a time ----
+// ---- jagged_dense_bmm: out^T = w_b^T x^T, one sample per workgroup step (the last sample first), 128 rows at a time ----
 // w_b goes to LDS once per sample.  Wave w owns rows 32 w .. 32 w + 31 of every 128-row block: its x rows and,
 // after the product, its output rows share one private LDS region.
 template <int D, int T>
@@ -85,7 +91,7 @@ __global__ __launch_bounds__(kFoThreads) void jagged_dense_bmm_kernel(const __bf
     for (int n_claimed = 0;; ++n_claimed) {
         const int p = claim_sample<bmm_claim_group<D, T>()>(counter, B, n_claimed, &slot, group);   // also: the previous sample's LDS tiles are free
         if (p >= B) break;
-        const int b = p;
+        const int b = B - 1 - p;
         const int64_t row0 = offsets[b];
         const int L = (int)(offsets[b + 1] - row0);
         if (L == 0) continue;
@@ -157,7 +163,7 @@ __global__ __launch_bounds__(kFoThreads) void jagged_dense_bmm_kernel(const __bf
 #pragma unroll
             for (int u = 0; u < 32 * (T / 8) / 64; ++u) {
                 const int c = lane + 64 * u, r = c / (T / 8), ch = c % (T / 8);
-                if (r < mine_rows) dst[c] = *reinterpret_cast<const u32x4 *>(mine + r * kORow + ch * 16);
+                if (r < mine_rows) __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(mine + r * kORow + ch * 16), dst + c);
             }
         }
     }
@@ -385,7 +391,7 @@ __global__ __launch_bounds__(kFoThreads) void jagged_softmax_kernel(const __bf16
 #pragma unroll
                     for (int e = 0; e < 8; ++e) r[e] = (__bf16)(__expf((float)v[u][e] - m[e]) * l[e]);
                 }
-                orow[(int64_t)i * kGroups] = r;
+                __builtin_nontemporal_store(r, orow + (int64_t)i * kGroups);
             }
         };
         emit(rl, held, held_g);
