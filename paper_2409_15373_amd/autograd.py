@@ -3,7 +3,8 @@ forward and a backward so that they can be trained through).
 
 Argument marshalling only: the forward of each function is the library's forward entry point, its backward the
 library's backward entry point on the tensors the forward saved; nothing is computed here, and a missing library
-raises as everywhere in the binding.
+raises as everywhere in the binding.  Ordinary calls go through autograd nodes in C++ (csrc/jfa_autograd.cpp), which a training
+step on a small batch spends half as much host time in; the torch.autograd.Function classes below are the same for the rest.
 
     out = jagged_flash_attention(q, k, v, offsets, max_len)                      # self attention, causal=True for the causal variant
     out = jagged_flash_cross_attention(q, k, v, offsets_q, offsets_kv, max_len_q, max_len_kv)
@@ -11,6 +12,8 @@ raises as everywhere in the binding.
 q, k, v: [rows, H, D] bf16 or fp32 on the GPU, contiguous; offsets: int64 [B + 1] on the GPU.  Gradients flow to q, k
 and v; offsets and the length bounds are not differentiable.
 """
+import ctypes
+
 import torch
 
 from . import binding
@@ -49,11 +52,45 @@ class _CrossAttention(torch.autograd.Function):
         return dq, dk, dv, None, None, None, None
 
 
+_native = None   # the C++ nodes; False where they have not been built
+_PLAIN = (torch.Tensor, torch.nn.Parameter)
+
+
+def _load_native():
+    global _native
+    try:
+        from . import _native as nodes
+    except ImportError:   # not built, or for another torch: the Python functions do the same
+        _native = False
+        return
+    lib = binding.load()
+    nodes.bind_library(lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value, binding._check)
+    _native = nodes
+
+
+def _ordinary(*tensors) -> bool:
+    """Whether a call may pass torch.autograd.Function by: tracers, function transforms and tensor subclasses have to see it."""
+    if _native is None:
+        _load_native()
+    return (_native is not False and all(type(t) in _PLAIN for t in tensors) and torch._C._get_tracing_state() is None
+            and not torch._C._are_functorch_transforms_active() and not torch.compiler.is_compiling())
+
+
 def jagged_flash_attention(q, k, v, offsets, max_len: int, causal: bool = False):
     """softmax(Q K^T / sqrt(D)) V per sample and head over the jagged rows that `offsets` delimits (Section 2.1)."""
-    return _SelfAttention.apply(q, k, v, offsets, int(max_len), bool(causal))
+    max_len, causal = int(max_len), bool(causal)
+    if _ordinary(q, k, v, offsets):
+        out = _native.self_attention(q, k, v, offsets, max_len, causal)
+        if out is not None:   # None: not in order, the function below says what is wrong
+            return out
+    return _SelfAttention.apply(q, k, v, offsets, max_len, causal)
 
 
 def jagged_flash_cross_attention(q, k, v, offsets_q, offsets_kv, max_len_q: int, max_len_kv: int):
     """The queries of sample b (rows of offsets_q) attend to its keys and values (rows of offsets_kv)."""
-    return _CrossAttention.apply(q, k, v, offsets_q, offsets_kv, int(max_len_q), int(max_len_kv))
+    max_len_q, max_len_kv = int(max_len_q), int(max_len_kv)
+    if _ordinary(q, k, v, offsets_q, offsets_kv):
+        out = _native.cross_attention(q, k, v, offsets_q, offsets_kv, max_len_q, max_len_kv)
+        if out is not None:
+            return out
+    return _CrossAttention.apply(q, k, v, offsets_q, offsets_kv, max_len_q, max_len_kv)

@@ -1,4 +1,5 @@
-"""Build libjfa.so in-tree with hipcc for gfx950 (cross-compiles without a GPU).
+"""Build libjfa.so in-tree with hipcc for gfx950 (cross-compiles without a GPU), and beside it _native.so, the autograd nodes
+(host code against the installed torch).
 
     python -m paper_2409_15373_amd.build [--force]
 """
@@ -9,11 +10,14 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libjfa.so")
+NATIVE_SRC = os.path.join(CSRC, "jfa_autograd.cpp")
+NATIVE = os.path.join(HERE, "_native.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -46,11 +50,30 @@ def _compile(src: str, force: bool, extra) -> str:
     return obj
 
 
+def _build_native(force: bool) -> None:
+    if not (force or _stale(NATIVE, [NATIVE_SRC])):
+        return
+    import torch
+    from torch.utils import cpp_extension
+    lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    includes = cpp_extension.include_paths() + [os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), sysconfig.get_paths()["include"]]
+    tmp = NATIVE + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           "-DTORCH_EXTENSION_NAME=_native", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f"-isystem{i}" for i in includes), NATIVE_SRC, "-o", tmp, f"-L{lib_dir}", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed for {NATIVE_SRC}:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, NATIVE)
+
+
 def build(force: bool = False, extra_flags=()) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+        native = ex.submit(_build_native, force)
         objs = list(ex.map(lambda s: _compile(s, force, extra_flags), srcs))
+        native.result()
     if force or _stale(LIB, objs):
         tmp = LIB + ".tmp"
         r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs,

@@ -73,3 +73,61 @@ def test_gradients_through_the_wrapper_match_the_oracle():
     gate_bf16("dq", f64(qa.grad), r_dq)
     gate_bf16("dk", f64(ka.grad), r_dk)
     gate_bf16("dv", f64(va.grad), r_dv)
+
+
+def _call(mode, dtype, node):
+    """Loss-free step of one attention with a strided dout: outputs, gradients and what the graph saved."""
+    from paper_2409_15373_amd import autograd
+    H, D = 2, 64
+    lq, lk = [70, 1, 0, 130, 33], [40, 5, 64, 0, 129]
+    oq, ok = (torch.from_numpy(offsets_from_lengths(np.array(x))).cuda() for x in (lq, lk))
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q = _rand(sum(lq), H, D, dtype, gen).requires_grad_(True)
+    k, v = (_rand(sum(lk if mode == "cross" else lq), H, D, dtype, gen).requires_grad_(True) for _ in range(2))
+    dout = _rand(sum(lq), D, H, dtype, gen).transpose(1, 2)
+    args = (q, k, v, oq, ok, 200, 200) if mode == "cross" else (q, k, v, oq, 200, mode == "causal")
+    wrapper, function = ((autograd.jagged_flash_cross_attention, autograd._CrossAttention) if mode == "cross"
+                         else (autograd.jagged_flash_attention, autograd._SelfAttention))
+    packed = []
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: packed.append(tuple(t.shape)) or t, lambda t: t):
+        out = wrapper(*args) if node == "native" else function.apply(*args)
+    return (out.detach(),) + torch.autograd.grad(out, (q, k, v), dout), packed
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("mode", ["self", "causal", "cross"])
+def test_native_nodes_equal_the_python_functions(mode, dtype):
+    from paper_2409_15373_amd import autograd
+    (got, saved), (ref, ref_saved) = _call(mode, dtype, "native"), _call(mode, dtype, "python")
+    assert autograd._native
+    assert all(torch.equal(a, b) for a, b in zip(got, ref)) and sorted(saved) == sorted(ref_saved)
+
+
+def test_what_the_native_nodes_refuse_is_refused_as_before():
+    from paper_2409_15373_amd.autograd import jagged_flash_attention as attention, jagged_flash_cross_attention as cross
+    from paper_2409_15373_amd.binding import JfaError
+    off = torch.tensor([0, 8], device="cuda")
+    x = torch.randn(8, 2, 64, device="cuda", dtype=torch.bfloat16, requires_grad=True)
+    with pytest.raises(AssertionError):
+        attention(x.transpose(0, 1).contiguous().transpose(0, 1), x, x, off, 8)
+    with pytest.raises(AssertionError):
+        attention(x, x, x, off.int(), 8)
+    with pytest.raises(AssertionError):
+        attention(x, x[:4], x, off, 8)
+    with pytest.raises(AssertionError):
+        attention(x.cpu(), x, x, off, 8)
+    with pytest.raises(TypeError):
+        attention(*(x.half(),) * 3, off, 8)
+    with pytest.raises(JfaError):
+        attention(*(x[:, :, :48].contiguous(),) * 3, off, 8)
+    with pytest.raises(JfaError):
+        cross(x, x, x, off, off, -1, 8)
+    with pytest.raises(RuntimeError):
+        torch.func.grad(lambda t: attention(t, t, t, off, 8).float().sum())(x.detach())
+    with torch.autograd.forward_ad.dual_level(), pytest.raises((RuntimeError, NotImplementedError)):
+        attention(torch.autograd.forward_ad.make_dual(x.detach(), x.detach()), x, x, off, 8)
+    out = attention(x, x, x, off, 8)
+    with torch.no_grad():
+        x.mul_(2)
+    with pytest.raises(RuntimeError):   # a saved tensor has changed
+        out.sum().backward()
