@@ -520,6 +520,11 @@ hipError_t launch_bwd_f32(const float *q, const float *k, const float *v, const 
 // bf16 attention, register-staged kernels (D = 128, short samples)
 constexpr int kFwdBlockRows = 128;
 constexpr int kBwdBlockRows = 128;
+// Items per workgroup that these kernels take without claims.  A claim heads a tile here, its latency is not hidden, and their
+// streams are short; microseconds with 4 and 16, forward and backward: 4096 samples of at most 32 rows 64 and 53, 175 and 152;
+// 1000 x 4 of at most 40 62 and 47, 176 and 157; 500 x 8 of at most 100 69 and 59, 211 and 207; 1024 x 4, 200 queries against at
+// most 200 keys 135 and 131, 472 and 477.
+constexpr int kShortFixedItems = 16;
 // In all bf16 launchers `offsets` belongs to the rows the schedule `s` was built over (queries for the forward and
 // dQ, keys for dK / dV) and the second array to the rows that stream past them (cross attention; nullptr: the same).
 // causal: self attention in which row i attends to rows 0 .. i of its sample (not together with a second array).

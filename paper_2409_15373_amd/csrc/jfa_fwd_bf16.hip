@@ -74,6 +74,7 @@ __global__ __launch_bounds__(kFwdThreads, 2) void fwd_bf16_kernel(const __bf16 *
 
     WorkCursor cursor;
     cursor.static_only = s.static_only;
+    cursor.fixed_items = kShortFixedItems;
     for (int n = 0;; ++n) {
         Work t;
         if (small) {   // the workgroup's items were decoded when the schedule was built
