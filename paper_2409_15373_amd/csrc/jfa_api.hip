@@ -706,7 +706,7 @@ int jfa_jagged_dense_bmm(const void *x, const void *w, const int64_t *offsets, i
     int st = feature_begin("jfa_jagged_dense_bmm", B, max_len, D, T, ptrs, 4, s, &v);
     if (st != JFA_OK || B == 0) return st;
     hipError_t e;
-    { ScopedTimer tm("jagged_dense_bmm", s); e = jfa::launch_jagged_dense_bmm(x, w, offsets, (int)B, D, T, v.counters, out, v.cus, s); }
+    { ScopedTimer tm("jagged_dense_bmm", s); e = jfa::launch_jagged_dense_bmm(x, w, offsets, (int)B, max_len, D, T, v.counters, out, v.cus, s); }
     if (e != hipSuccess) return hip_fail("jagged_dense_bmm kernel", e);
     return JFA_OK;
 }
@@ -731,7 +731,7 @@ int jfa_jagged_softmax(const void *x, const int64_t *offsets, int64_t B, int64_t
     int st = feature_begin("jfa_jagged_softmax", B, max_len, D, 32, ptrs, 3, s, &v);
     if (st != JFA_OK || B == 0) return st;
     hipError_t e;
-    { ScopedTimer tm("jagged_softmax", s); e = jfa::launch_jagged_softmax(false, x, nullptr, offsets, (int)B, D, v.counters, y, v.cus, s); }
+    { ScopedTimer tm("jagged_softmax", s); e = jfa::launch_jagged_softmax(false, x, nullptr, offsets, (int)B, max_len, D, v.counters, y, v.cus, s); }
     if (e != hipSuccess) return hip_fail("jagged_softmax kernel", e);
     return JFA_OK;
 }
@@ -744,7 +744,7 @@ int jfa_jagged_softmax_backward(const void *y, const void *dy, const int64_t *of
     int st = feature_begin("jfa_jagged_softmax_backward", B, max_len, D, 32, ptrs, 4, s, &v);
     if (st != JFA_OK || B == 0) return st;
     hipError_t e;
-    { ScopedTimer tm("jagged_softmax_bwd", s); e = jfa::launch_jagged_softmax(true, y, dy, offsets, (int)B, D, v.counters, dx, v.cus, s); }
+    { ScopedTimer tm("jagged_softmax_bwd", s); e = jfa::launch_jagged_softmax(true, y, dy, offsets, (int)B, max_len, D, v.counters, dx, v.cus, s); }
     if (e != hipSuccess) return hip_fail("jagged_softmax backward kernel", e);
     return JFA_OK;
 }

@@ -6,8 +6,8 @@
 // prefix, so a tile is all padding (a fill, or nothing to do on the way back), all data, or data followed by padding,
 // and it is one contiguous block on the jagged side too.  All accesses are 16 bytes per lane on consecutive addresses,
 // and every store covers whole 128-byte lines (a row is a multiple of 16 bytes; anything at or above 128 bytes per
-// row keeps lines whole).  Stores go past the L2 (non-temporal; there and back, 1024 samples of up to 1024 rows of 1 KB:
-// 487 -> 472 us; loads past it as well: 477).
+// row keeps lines whole).  Stores of large tensors go past the L2 (see past_l2(); there and back, 1024 samples of up
+// to 1024 rows of 1 KB: 487 -> 472 us; loads past it as well: 477).
 #include "jfa_common.h"
 #include "jfa_mfma.h"
 
@@ -15,7 +15,7 @@ namespace jfa {
 
 constexpr int kCvThreads = 256;
 
-template <bool TO_DENSE>
+template <bool TO_DENSE, bool kPast>
 __global__ __launch_bounds__(kCvThreads) void convert_kernel(const u32x4 *__restrict__ src, u32x4 *__restrict__ dst,
                                                              const int64_t *__restrict__ offsets, int B, int max_len,
                                                              int row_chunks, int rows, uint32_t pad) {
@@ -34,12 +34,12 @@ __global__ __launch_bounds__(kCvThreads) void convert_kernel(const u32x4 *__rest
             const u32x4 *s = src + (TO_DENSE ? s0 + i0 : dense0 + i0) * row_chunks;      // ... and input side
             if (n_data == 0) {   // all padding
                 if (TO_DENSE)
-                    for (int id = tid; id < n; id += kCvThreads) __builtin_nontemporal_store(padv, d + id);
+                    for (int id = tid; id < n; id += kCvThreads) store_streaming<kPast>(d + id, padv);
             } else if (n_data == n) {   // all data
 #pragma unroll 4
-                for (int id = tid; id < n; id += kCvThreads) __builtin_nontemporal_store(s[id], d + id);
+                for (int id = tid; id < n; id += kCvThreads) store_streaming<kPast>(d + id, s[id]);
             } else {   // the sample ends inside the tile
-                for (int id = tid; id < (TO_DENSE ? n : n_data); id += kCvThreads) __builtin_nontemporal_store(id < n_data ? s[id] : padv, d + id);
+                for (int id = tid; id < (TO_DENSE ? n : n_data); id += kCvThreads) store_streaming<kPast>(d + id, id < n_data ? s[id] : padv);
             }
         }
     }
@@ -61,12 +61,11 @@ hipError_t launch_convert(bool to_dense, const void *src, void *dst, const int64
     if (gx > tiles) gx = tiles;
     if (gx < 1) gx = 1;
     const dim3 grid((unsigned)gx, (unsigned)gy);
-    if (to_dense)
-        hipLaunchKernelGGL(convert_kernel<true>, grid, dim3(kCvThreads), 0, stream, (const u32x4 *)src, (u32x4 *)dst,
-                           offsets, B, (int)max_len, (int)row_chunks, (int)rows, pad);
-    else
-        hipLaunchKernelGGL(convert_kernel<false>, grid, dim3(kCvThreads), 0, stream, (const u32x4 *)src, (u32x4 *)dst,
-                           offsets, B, (int)max_len, (int)row_chunks, (int)rows, pad);
+    const bool past = past_l2(B, max_len, 16 * row_chunks);
+    const auto kernel = to_dense ? (past ? convert_kernel<true, true> : convert_kernel<true, false>)
+                                 : (past ? convert_kernel<false, true> : convert_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(kCvThreads), 0, stream, (const u32x4 *)src, (u32x4 *)dst, offsets, B, (int)max_len, (int)row_chunks,
+                       (int)rows, pad);
     return hipGetLastError();
 }
 

@@ -6,10 +6,10 @@
 // All four move O(sum_B (D + T)) bytes for O(sum_B D T) flops with D, T <= 128: they are bound by HBM, and the
 // matrix cores only keep the arithmetic out of the way.  Every global access is 16 bytes per lane on consecutive
 // addresses (a sample's rows are one contiguous block), operands reach the MFMA layout through LDS, and results
-// go back through LDS so that stores cover whole rows.  Rows are stored past the L2 (non-temporal): nobody in the kernel reads
-// them again, and the second sweep's rows and the matrices stay.  The memory-side cache keeps the last 256 MB that an operator
+// go back through LDS so that stores cover whole rows.  Rows of large tensors are stored past the L2 (see past_l2()): nobody in the
+// kernel reads them again, and the second sweep's rows and the matrices stay.  The memory-side cache keeps the last 256 MB that an operator
 // touched, so an operator that walks the samples the other way begins with what its predecessor ended with: jagged_dense_bmm,
-// which sits between the others in a forward and a backward pass, takes the last samples first.  Softmax, product, both gradients
+// which sits between the others in a forward and a backward pass, takes the last samples of large tensors first.  Softmax, product, both gradients
 // and the softmax's gradient on 16384 samples of up to 512 rows, D = T = 64, microseconds: 1229, the order alone 1214, both 1188
 // (loads past the L2 as well: 1201; walks that claim two samples ahead, so that a sample starts without the latency of claim and
 // offsets: 1275, the workgroups' ends are a sample further apart).
@@ -67,10 +67,10 @@ __device__ inline int claim_sample(int32_t *counter, int B, int n_claimed, int *
 template <int D, int T> constexpr int bmm_claim_group() { return D + T <= 64 ? 2 : 1; }
 template <int D> constexpr int softmax_claim_group() { return D <= 32 ? 2 : 1; }
 
-// ---- jagged_dense_bmm: out^T = w_b^T x^T, one sample per workgroup step (the last sample first), 128 rows at a time ----
+// ---- jagged_dense_bmm: out^T = w_b^T x^T, one sample per workgroup step (of large tensors the last first), 128 rows at a time ----
 // w_b goes to LDS once per sample.  Wave w owns rows 32 w .. 32 w + 31 of every 128-row block: its x rows and,
 // after the product, its output rows share one private LDS region.
-template <int D, int T>
+template <int D, int T, bool kPast>
 __global__ __launch_bounds__(kFoThreads) void jagged_dense_bmm_kernel(const __bf16 *__restrict__ x,
                                                                       const __bf16 *__restrict__ w,
                                                                       const int64_t *__restrict__ offsets, int B,
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kFoThreads) void jagged_dense_bmm_kernel(const __bf
     for (int n_claimed = 0;; ++n_claimed) {
         const int p = claim_sample<bmm_claim_group<D, T>()>(counter, B, n_claimed, &slot, group);   // also: the previous sample's LDS tiles are free
         if (p >= B) break;
-        const int b = B - 1 - p;
+        const int b = kPast ? B - 1 - p : p;   // small tensors: the L2s hold all of it, in either order
         const int64_t row0 = offsets[b];
         const int L = (int)(offsets[b + 1] - row0);
         if (L == 0) continue;
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kFoThreads) void jagged_dense_bmm_kernel(const __bf
 #pragma unroll
             for (int u = 0; u < 32 * (T / 8) / 64; ++u) {
                 const int c = lane + 64 * u, r = c / (T / 8), ch = c % (T / 8);
-                if (r < mine_rows) __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(mine + r * kORow + ch * 16), dst + c);
+                if (r < mine_rows) store_streaming<kPast>(dst + c, *reinterpret_cast<const u32x4 *>(mine + r * kORow + ch * 16));
             }
         }
     }
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kFoThreads) void jagged_jagged_bmm_kernel(const __b
 // per-column statistics (running maximum and sum of exponentials; for the backward the sum of dy y), which are
 // then combined across the threads that share columns; sweep 2 writes the result.  The second sweep's reads come
 // from cache for all but the longest samples.
-template <int D, bool BACKWARD>
+template <int D, bool BACKWARD, bool kPast>
 __global__ __launch_bounds__(kFoThreads) void jagged_softmax_kernel(const __bf16 *__restrict__ a,   // x, or y for the backward
                                                                     const __bf16 *__restrict__ g,   // dy (backward only)
                                                                     const int64_t *__restrict__ offsets, int B,
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(kFoThreads) void jagged_softmax_kernel(const __bf16
 #pragma unroll
                     for (int e = 0; e < 8; ++e) r[e] = (__bf16)(__expf((float)v[u][e] - m[e]) * l[e]);
                 }
-                __builtin_nontemporal_store(r, orow + (int64_t)i * kGroups);
+                store_streaming<kPast>(orow + (int64_t)i * kGroups, r);
             }
         };
         emit(rl, held, held_g);
@@ -403,52 +403,72 @@ __global__ __launch_bounds__(kFoThreads) void jagged_softmax_kernel(const __bf16
     }
 }
 
-#define JFA_DT_CASES(KERNEL, ...)                                                  \
-    switch (D * 1000 + T) {                                                        \
-        JFA_DT_CASE(KERNEL, 32, 32, __VA_ARGS__) JFA_DT_CASE(KERNEL, 32, 64, __VA_ARGS__) JFA_DT_CASE(KERNEL, 32, 128, __VA_ARGS__)   \
-        JFA_DT_CASE(KERNEL, 64, 32, __VA_ARGS__) JFA_DT_CASE(KERNEL, 64, 64, __VA_ARGS__) JFA_DT_CASE(KERNEL, 64, 128, __VA_ARGS__)   \
-        JFA_DT_CASE(KERNEL, 128, 32, __VA_ARGS__) JFA_DT_CASE(KERNEL, 128, 64, __VA_ARGS__) JFA_DT_CASE(KERNEL, 128, 128, __VA_ARGS__) \
-        default: return hipErrorInvalidValue;                                      \
+// One launch of a product's kernel, with the cleared counter it needs.
+template <auto Kernel, int D, int T, typename... Args>
+static void launch_bmm(int B, int32_t *counter, int cus, hipStream_t stream, Args... args) {
+    const int grid = persistent_grid<Kernel>(kFoThreads, cus);
+    if (!all_static<bmm_claim_group<D, T>()>(B, grid)) hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, stream, counter);
+    hipLaunchKernelGGL(Kernel, dim3(grid), dim3(kFoThreads), 0, stream, args...);
+}
+#define JFA_DT_CASES(CASE)                            \
+    switch (D * 1000 + T) {                           \
+        CASE(32, 32) CASE(32, 64) CASE(32, 128)       \
+        CASE(64, 32) CASE(64, 64) CASE(64, 128)       \
+        CASE(128, 32) CASE(128, 64) CASE(128, 128)    \
+        default: return hipErrorInvalidValue;         \
     }
-#define JFA_DT_CASE(KERNEL, DD, TT, ...)                                                                         \
-    case DD * 1000 + TT:                                                                                         \
-        grid = persistent_grid<KERNEL<DD, TT>>(kFoThreads, cus);                                                 \
-        if (!all_static<bmm_claim_group<DD, TT>()>(B, grid)) hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, stream, counter); \
-        hipLaunchKernelGGL((KERNEL<DD, TT>), dim3(grid), dim3(kFoThreads), 0, stream, __VA_ARGS__);              \
-        break;
 
-hipError_t launch_jagged_dense_bmm(const void *x, const void *w, const int64_t *offsets, int B, int D, int T, int32_t *counter,
+hipError_t launch_jagged_dense_bmm(const void *x, const void *w, const int64_t *offsets, int B, int64_t max_len, int D, int T, int32_t *counter,
                                    void *out, int cus, hipStream_t stream) {
-    int grid;
-    JFA_DT_CASES(jagged_dense_bmm_kernel, (const __bf16 *)x, (const __bf16 *)w, offsets, B, counter, (__bf16 *)out)
+    const bool past = past_l2(B, max_len, 2 * T);
+    const __bf16 *xb = (const __bf16 *)x, *wb = (const __bf16 *)w;
+    __bf16 *ob = (__bf16 *)out;
+#define JFA_DENSE_CASE(DD, TT)                                                                                              \
+    case DD * 1000 + TT:                                                                                                    \
+        if (past)                                                                                                           \
+            launch_bmm<jagged_dense_bmm_kernel<DD, TT, true>, DD, TT>(B, counter, cus, stream, xb, wb, offsets, B, counter, ob);  \
+        else                                                                                                                \
+            launch_bmm<jagged_dense_bmm_kernel<DD, TT, false>, DD, TT>(B, counter, cus, stream, xb, wb, offsets, B, counter, ob); \
+        break;
+    JFA_DT_CASES(JFA_DENSE_CASE)
+#undef JFA_DENSE_CASE
     return hipGetLastError();
 }
 
 hipError_t launch_jagged_jagged_bmm(const void *x, const void *y, const int64_t *offsets, int B, int D, int T, int32_t *counter,
                                     void *out, int cus, hipStream_t stream) {
-    int grid;
-    JFA_DT_CASES(jagged_jagged_bmm_kernel, (const __bf16 *)x, (const __bf16 *)y, offsets, B, counter, (__bf16 *)out)
+#define JFA_JAGGED_CASE(DD, TT)                                                                                             \
+    case DD * 1000 + TT:                                                                                                    \
+        launch_bmm<jagged_jagged_bmm_kernel<DD, TT>, DD, TT>(B, counter, cus, stream, (const __bf16 *)x, (const __bf16 *)y, \
+                                                             offsets, B, counter, (__bf16 *)out);                           \
+        break;
+    JFA_DT_CASES(JFA_JAGGED_CASE)
+#undef JFA_JAGGED_CASE
     return hipGetLastError();
 }
-#undef JFA_DT_CASE
 #undef JFA_DT_CASES
 
-template <int D>
-static hipError_t launch_softmax_d(bool backward, const __bf16 *a, const __bf16 *g, const int64_t *offsets, int B, int32_t *s,
-                                   __bf16 *out, int cus, hipStream_t stream) {
-    const int grid = backward ? persistent_grid<jagged_softmax_kernel<D, true>>(kFoThreads, cus) : persistent_grid<jagged_softmax_kernel<D, false>>(kFoThreads, cus);
+template <int D, bool BACKWARD, bool kPast>
+static hipError_t launch_softmax_d(const __bf16 *a, const __bf16 *g, const int64_t *offsets, int B, int32_t *s, __bf16 *out, int cus, hipStream_t stream) {
+    const int grid = persistent_grid<jagged_softmax_kernel<D, BACKWARD, kPast>>(kFoThreads, cus);
     if (!all_static<softmax_claim_group<D>()>(B, grid)) hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, stream, s);
-    if (backward) hipLaunchKernelGGL((jagged_softmax_kernel<D, true>), dim3(grid), dim3(kFoThreads), 0, stream, a, g, offsets, B, s, out);
-    else hipLaunchKernelGGL((jagged_softmax_kernel<D, false>), dim3(grid), dim3(kFoThreads), 0, stream, a, g, offsets, B, s, out);
+    hipLaunchKernelGGL((jagged_softmax_kernel<D, BACKWARD, kPast>), dim3(grid), dim3(kFoThreads), 0, stream, a, g, offsets, B, s, out);
     return hipGetLastError();
 }
+template <int D>
+static hipError_t launch_softmax_d(bool backward, const __bf16 *a, const __bf16 *g, const int64_t *offsets, int B, int64_t max_len, int32_t *s,
+                                   __bf16 *out, int cus, hipStream_t stream) {
+    if (past_l2(B, max_len, 2 * D))
+        return backward ? launch_softmax_d<D, true, true>(a, g, offsets, B, s, out, cus, stream) : launch_softmax_d<D, false, true>(a, g, offsets, B, s, out, cus, stream);
+    return backward ? launch_softmax_d<D, true, false>(a, g, offsets, B, s, out, cus, stream) : launch_softmax_d<D, false, false>(a, g, offsets, B, s, out, cus, stream);
+}
 
-hipError_t launch_jagged_softmax(bool backward, const void *a, const void *g, const int64_t *offsets, int B, int D,
+hipError_t launch_jagged_softmax(bool backward, const void *a, const void *g, const int64_t *offsets, int B, int64_t max_len, int D,
                                  int32_t *s, void *out, int cus, hipStream_t stream) {
     switch (D) {
-        case 32: return launch_softmax_d<32>(backward, (const __bf16 *)a, (const __bf16 *)g, offsets, B, s, (__bf16 *)out, cus, stream);
-        case 64: return launch_softmax_d<64>(backward, (const __bf16 *)a, (const __bf16 *)g, offsets, B, s, (__bf16 *)out, cus, stream);
-        case 128: return launch_softmax_d<128>(backward, (const __bf16 *)a, (const __bf16 *)g, offsets, B, s, (__bf16 *)out, cus, stream);
+        case 32: return launch_softmax_d<32>(backward, (const __bf16 *)a, (const __bf16 *)g, offsets, B, max_len, s, (__bf16 *)out, cus, stream);
+        case 64: return launch_softmax_d<64>(backward, (const __bf16 *)a, (const __bf16 *)g, offsets, B, max_len, s, (__bf16 *)out, cus, stream);
+        case 128: return launch_softmax_d<128>(backward, (const __bf16 *)a, (const __bf16 *)g, offsets, B, max_len, s, (__bf16 *)out, cus, stream);
         default: return hipErrorInvalidValue;
     }
 }
