@@ -34,6 +34,11 @@ __device__ inline int block_inclusive_scan(int x, int *wave_sums) {
 // counted over `offsets`, but a block's cost grows with the length of the stream, so samples are ordered by that.
 // One workgroup per schedule: the two of a backward are built side by side in one launch (4 us less on training steps of
 // 426 and 621 us; within the noise of steps of 4 ms).
+// What bounds it is a chain of trips to memory.  A batch of at most kSchedKept samples makes one: a thread's lengths stay in
+// registers from the histogram to the scatter, and the sorted block counts go through LDS to the scan.
+constexpr int kSchedPerThread = 4;
+constexpr int kSchedKept = kSchedThreads * kSchedPerThread;
+template <bool kKept>
 __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(ScheduleJob job0, ScheduleJob job1, int B,
                                                                  int32_t *__restrict__ counters, int n_counters) {
     const ScheduleJob &job = blockIdx.x == 0 ? job0 : job1;
@@ -46,19 +51,48 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(ScheduleJob job
     __shared__ int cursor[kSchedBins];  // next free slot of each bin
     __shared__ int wave_sums[kSchedThreads / 64];
     __shared__ int carry;
+    __shared__ int sorted_blocks[kKept ? kSchedKept : 1];   // row blocks of the sample at a position (otherwise parked in tile_start[pos + 1])
     const int tid = threadIdx.x;
 
+    // a sample's sort key, the row-block count of the stream (of the sample itself in self attention), and its row blocks
+    // (a sample's length fits 31 bits everywhere: a 32-bit division, a quarter of a 64-bit one's instructions)
+    auto blocks_of = [&](const int64_t *o, int b) {
+        const int len = (int)(o[b + 1] - o[b]);
+        return len > 0 ? (int)(((uint32_t)len + (uint32_t)block_rows - 1) / (uint32_t)block_rows) : 0;
+    };
+    auto bin_of = [&](int key) { return key < kSchedBins - 1 ? key : kSchedBins - 1; };
+    int bins[kSchedPerThread], blocks[kSchedPerThread];
+    if (kKept) {
+#pragma unroll
+        for (int u = 0; u < kSchedPerThread; ++u) {
+            const int b = tid + u * kSchedThreads;
+            bins[u] = blocks[u] = 0;
+            if (b < B) {
+                const int n = blocks_of(offsets, b);
+                blocks[u] = n;
+                bins[u] = bin_of(offsets_other ? blocks_of(offsets_other, b) : n);
+            }
+        }
+    }
     for (int i = tid; i < n_counters; i += kSchedThreads) counters[i] = 0;
     for (int i = tid; i < kSchedBins; i += kSchedThreads) { hist[i] = 0; cursor[i] = 0; }
     __syncthreads();
 
-    // 1. histogram of the sort key: the row-block count of the stream (of the sample itself in self attention)
-    auto sort_key = [&](int b) {
-        const int64_t *o = offsets_other ? offsets_other : offsets;
-        const int64_t key = (o[b + 1] - o[b] + block_rows - 1) / block_rows;
-        return key < kSchedBins - 1 ? (int)key : kSchedBins - 1;
+    // calls f(sample, bin, row blocks) for this thread's samples
+    auto for_samples = [&](auto f) {
+        if (kKept) {
+#pragma unroll
+            for (int u = 0; u < kSchedPerThread; ++u)
+                if (tid + u * kSchedThreads < B) f(tid + u * kSchedThreads, bins[u], blocks[u]);
+        } else {
+            for (int b = tid; b < B; b += kSchedThreads) {
+                const int n = blocks_of(offsets, b);
+                f(b, bin_of(offsets_other ? blocks_of(offsets_other, b) : n), n);
+            }
+        }
     };
-    for (int b = tid; b < B; b += kSchedThreads) atomicAdd(&hist[sort_key(b)], 1);
+    // 1. histogram of the sort key
+    for_samples([&](int, int bin, int) { atomicAdd(&hist[bin], 1); });
     __syncthreads();
 
     // 2. bins in descending order: first position of bin i = number of samples in bins above i.
@@ -71,22 +105,20 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(ScheduleJob job
     }
     __syncthreads();
 
-    // 3. scatter samples to their bin; the per-sample block count is parked in tile_start[pos + 1]
-    for (int b = tid; b < B; b += kSchedThreads) {
-        const int64_t len = offsets[b + 1] - offsets[b];
-        const int64_t nq = (len + block_rows - 1) / block_rows;
-        const int bin = sort_key(b);
+    // 3. scatter samples to their bin
+    for_samples([&](int b, int bin, int n) {
         const int pos = hist[bin] + atomicAdd(&cursor[bin], 1);
         order[pos] = b;
-        tile_start[pos + 1] = (int)nq;
-    }
+        if (kKept) sorted_blocks[pos] = n;
+        else tile_start[pos + 1] = n;
+    });
     if (tid == 0) { tile_start[0] = 0; carry = 0; }
     __syncthreads();
 
-    // 4. in-place inclusive scan of tile_start[1..B]
+    // 4. inclusive scan of the sorted block counts into tile_start[1..B]
     for (int base = 0; base < B; base += kSchedThreads) {
         const int i = base + tid;
-        const int x = i < B ? tile_start[i + 1] : 0;
+        const int x = i < B ? (kKept ? sorted_blocks[i] : tile_start[i + 1]) : 0;
         const int incl = block_inclusive_scan(x, wave_sums) + carry;
         if (i < B) tile_start[i + 1] = incl;
         __syncthreads();
@@ -107,7 +139,10 @@ __global__ void check_offsets_kernel(const int64_t *__restrict__ offsets, int B,
 }
 
 hipError_t launch_schedules(const ScheduleJob *jobs, int n_jobs, int B, int32_t *counters, int n_counters, hipStream_t stream) {
-    hipLaunchKernelGGL(schedule_kernel, dim3(n_jobs), dim3(kSchedThreads), 0, stream, jobs[0], jobs[n_jobs - 1], B, counters, n_counters);
+    if (B <= kSchedKept)
+        hipLaunchKernelGGL(schedule_kernel<true>, dim3(n_jobs), dim3(kSchedThreads), 0, stream, jobs[0], jobs[n_jobs - 1], B, counters, n_counters);
+    else
+        hipLaunchKernelGGL(schedule_kernel<false>, dim3(n_jobs), dim3(kSchedThreads), 0, stream, jobs[0], jobs[n_jobs - 1], B, counters, n_counters);
     return hipGetLastError();
 }
 

@@ -34,6 +34,11 @@ def test_schedule_small_and_edge_cases(block_rows):
     check_schedule(np.arange(1, 3000) % 700, block_rows)                 # B > one scan chunk, zero lengths inside
 
 
+@pytest.mark.parametrize("B", [1023, 1024, 1025, 4095, 4096, 4097])
+def test_schedule_at_the_edges_of_what_a_thread_keeps(B):
+    check_schedule(np.arange(B) * 37 % 1500, 128)                        # 1024 threads; up to four samples each stay in registers
+
+
 @pytest.mark.parametrize("name", ["c2_geom_bf16", "c3_zipf_bf16", "c4_bimodal_bf16"])
 def test_schedule_on_named_configs(name):
     from paper_2409_15373_amd.synthetic import CONFIGS, lengths_for
