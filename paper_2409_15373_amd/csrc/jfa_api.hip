@@ -334,7 +334,8 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
     }
     const bool dma = !f32 && long_samples(max_len > max_len_kv ? max_len : max_len_kv, D, H);
     const bool many = !small_problem(B, max_len, H, jfa::kF32BlockRows, w.cus);
-    const int block_rows = f32 ? jfa::f32_block_rows(max_len_kv, many) : dma ? jfa::kDmaBlockRows : D < 128 ? narrow_rows(max_len, max_len_kv, B, H, w.cus) : jfa::kFwdBlockRows;
+    const jfa::F32Form form = jfa::f32_form(D, B, max_len, H, max_len_kv, many, w.cus);
+    const int block_rows = f32 ? form.rows : dma ? jfa::kDmaBlockRows : D < 128 ? narrow_rows(max_len, max_len_kv, B, H, w.cus) : jfa::kFwdBlockRows;
     jfa::Schedule sc{w.order[0], w.tile_start[0], w.counters};
     sc.fixed_items = jfa::narrow_fixed_items(max_len_kv);
     const bool narrow = !f32 && D < 128;
@@ -346,7 +347,7 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
         e = schedule(&job, 1, B, w, s);
         if (e != hipSuccess) return hip_fail("schedule kernel", e);
     }
-    if (f32) { ScopedTimer tm("fwd_f32", s); e = jfa::launch_fwd_f32((const float *)q, (const float *)k, (const float *)v, offsets, offsets_kv, causal, (int)B, H, D, sc, block_rows, (float *)out, lse, w.cus, s); }
+    if (f32) { ScopedTimer tm("fwd_f32", s); e = jfa::launch_fwd_f32((const float *)q, (const float *)k, (const float *)v, offsets, offsets_kv, causal, (int)B, H, D, sc, form, (float *)out, lse, w.cus, s); }
     else if (dma) { ScopedTimer tm("fwd_bf16_dma", s); e = jfa::launch_fwd_bf16_dma(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
     else if (D < 128) { ScopedTimer tm("fwd_narrow", s); e = jfa::launch_fwd_narrow(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, block_rows, out, lse, w.cus, s); }
     else { ScopedTimer tm("fwd_bf16", s); e = jfa::launch_fwd_bf16(q, k, v, offsets, offsets_kv, causal, (int)B, H, D, sc, out, lse, w.cus, s); }
@@ -375,8 +376,9 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     const int64_t longest = max_len > max_len_kv ? max_len : max_len_kv;
     const bool dma = !f32 && long_samples(longest, D, H);
     const bool many = !small_problem(B, longest, H, jfa::kF32BlockRows, w.cus);
-    const int block_rows = f32 ? jfa::f32_block_rows(max_len_kv, many) : dma ? jfa::kDmaBlockRows : D < 128 ? narrow_rows(max_len, max_len_kv, B, H, w.cus) : jfa::kBwdBlockRows;   // of queries
-    const int key_rows = f32 ? jfa::f32_block_rows(max_len, many) : dma ? jfa::kDkvBlockRows : D < 128 ? narrow_key_rows(max_len_kv, max_len, B, H, D, w.cus) : jfa::kBwdBlockRows;   // of keys
+    const jfa::F32Form form_q = jfa::f32_form(D, B, max_len, H, max_len_kv, many, w.cus), form_k = jfa::f32_key_form(form_q, max_len, many);
+    const int block_rows = f32 ? form_q.rows : dma ? jfa::kDmaBlockRows : D < 128 ? narrow_rows(max_len, max_len_kv, B, H, w.cus) : jfa::kBwdBlockRows;   // of queries
+    const int key_rows = f32 ? form_k.rows : dma ? jfa::kDkvBlockRows : D < 128 ? narrow_key_rows(max_len_kv, max_len, B, H, D, w.cus) : jfa::kBwdBlockRows;   // of keys
     // Schedule 0: blocks of queries.  Schedule 1: blocks of keys, where they differ: cross attention, and the direct-to-LDS
     // kernels, whose dK / dV blocks are shorter.  One launch builds both and clears all work counters before the first
     // kernel that uses one.  Small problems on the other kernels have no scheduler launch: those kernels build their
@@ -403,9 +405,12 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
             s_dkv.build_rows = key_rows;
         }
         ScopedTimer tm_bwd("bwd_f32", s);
-        e = jfa::launch_bwd_f32((const float *)q, (const float *)k, (const float *)v, (const float *)out, (const float *)dout, lse,
-                                offsets, offsets_kv, causal, (int)B, H, D, s_dq, block_rows, s_dkv, key_rows, (float *)dq, (float *)dk, (float *)dv, delta, w.cus, s);
-        if (e != hipSuccess) return hip_fail("fp32 backward kernels", e);
+        e = jfa::launch_dq_f32((const float *)q, (const float *)k, (const float *)v, (const float *)out, (const float *)dout, lse,
+                               offsets, offsets_kv, causal, (int)B, H, D, s_dq, form_q, (float *)dq, delta, w.cus, s);
+        if (e != hipSuccess) return hip_fail("fp32 dQ kernel", e);
+        e = jfa::launch_dkv_f32((const float *)q, (const float *)k, (const float *)v, (const float *)dout, lse, delta,
+                                offsets_k, offsets_q_other, causal, (int)B, H, D, s_dkv, form_k, (float *)dk, (float *)dv, w.cus, s);
+        if (e != hipSuccess) return hip_fail("fp32 dK/dV kernel", e);
         return JFA_OK;
     }
     if (dma) {

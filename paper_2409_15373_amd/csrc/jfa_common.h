@@ -504,17 +504,43 @@ constexpr int kF32BlockRows = 64, kF32ShortBlockRows = 32;
 inline int f32_block_rows(int64_t max_streamed, bool many) {
     return max_streamed <= 32 || (many && max_streamed <= 64) ? kF32ShortBlockRows : kF32BlockRows;
 }
+// How an fp32 kernel runs: on the bf16 matrix instructions (split operands, jfa_f32_split.hip: head sizes 32 and 64) or on the fp32
+// ones, and its rows per block.  A wave of the former has 32 stationary rows to itself and a stage of 32 streamed rows is split
+// once per workgroup; the latter have the four waves share a 64 x 64 square, which fills the chip with fewer tiles and wastes
+// less of a short stream.  Fp32 -> split instructions, microseconds:
+//   forward, dQ: a workgroup per compute unit and SIMD pair has to find a tile: 32 x 2 heads of up to 256 rows, D = 64, forward 17 -> 22,
+//   64 x 4 of up to 512 87 -> 69.  Streams of at most 64 rows: 2000 x 2 heads 54 -> 81.  Up to 128 rows: D = 32, 500 x 8 heads of
+//   up to 100, 56 -> 61; D = 64 100 -> 81, but 200 x 2 heads, 200 queries against up to 100 keys (most of them few), 30 -> 34:
+//   there with twice the tiles;
+//   dK / dV as the queries' kernels: a probability is exp(score - lse), and where one score is most of the log-sum-exp their errors
+//   cancel only if both come from the same arithmetic.  (Split alone, behind the other forward: backward of 32 x 2 heads of up to
+//   256 rows, D = 64, 53 -> 48, but at scores of standard deviation 16, D = 32, dV's error is twice that of either arithmetic alone.)
+constexpr int kF32SplitRows = 128, kF32SplitKeyRows = 64;
+struct F32Form { bool split; int rows; };
+inline F32Form f32_form(int D, int64_t B, int64_t max_len, int H, int64_t max_streamed, bool many, int cus) {
+    const double tiles = (double)B * (double)((max_len + kF32SplitRows - 1) / kF32SplitRows) * H;   // at most
+    const bool worth = tiles > 2.0 * cus && (max_streamed > 128 || (D == 64 && max_streamed > 64 && tiles > 4.0 * cus));
+    if (D <= 64 && max_len > 64 && worth) return {true, kF32SplitRows};
+    return {false, f32_block_rows(max_streamed, many)};
+}
+inline F32Form f32_key_form(const F32Form &queries, int64_t max_streamed, bool many) {
+    if (queries.split) return {true, kF32SplitKeyRows};
+    return {false, f32_block_rows(max_streamed, many)};
+}
 // Cross attention: offsets = the queries' offsets, offsets_kv = the keys' (nullptr: the same array); schedules are
 // built over the stationary side's offsets (s, s_dq: queries; s_dkv: keys).
 // causal (self attention only, offsets_kv == nullptr): row i attends to rows 0 .. i of its sample.
-// block_rows, rows_dq, rows_dkv: kF32BlockRows or kF32ShortBlockRows, what the kernel's schedule was built with.
+// form: f32_form() of the queries or f32_key_form(); the kernel's schedule is built with its rows.
 hipError_t launch_fwd_f32(const float *q, const float *k, const float *v, const int64_t *offsets,
-                          const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, int block_rows, float *out, float *lse,
+                          const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, F32Form form, float *out, float *lse,
                           int cus, hipStream_t stream);
-hipError_t launch_bwd_f32(const float *q, const float *k, const float *v, const float *out, const float *dout,
-                          const float *lse, const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H,
-                          int D, Schedule s_dq, int rows_dq, Schedule s_dkv, int rows_dkv, float *dq, float *dk, float *dv, float *delta,
-                          int cus, hipStream_t stream);
+hipError_t launch_dq_f32(const float *q, const float *k, const float *v, const float *out, const float *dout, const float *lse,
+                         const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, F32Form form,
+                         float *dq, float *delta, int cus, hipStream_t stream);
+// (offsets: the keys'; offsets_q: the queries', nullptr where they are the same)
+hipError_t launch_dkv_f32(const float *q, const float *k, const float *v, const float *dout, const float *lse, const float *delta,
+                          const int64_t *offsets, const int64_t *offsets_q, bool causal, int B, int H, int D, Schedule s, F32Form form,
+                          float *dk, float *dv, int cus, hipStream_t stream);
 // (the dQ kernel of every path runs first and computes delta[h, row] = sum_d dout * out for the kernels after it)
 
 // bf16 attention, register-staged kernels (D = 128, short samples)

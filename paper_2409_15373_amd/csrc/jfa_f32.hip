@@ -19,10 +19,9 @@
 // accumulator register v is then the B operand of the next product's step v (streamed rows (v / 4) 8 + 4 (l / 32) + v % 4
 // as its two slots), whose A operand is one element per lane of the transposed streamed tile, read row by row.
 // Measured at B = 256, H = 2, D = 64, lengths uniform on [1, 512] against the former kernels (vector FMA, a row per four
-// lanes, scores one by one): forward 590 -> 159 us, forward + backward 1861 -> 663 us.
-#include "jfa_common.h"
-#include "jfa_mfma.h"
-#include "jfa_lds.h"
+// lanes, scores one by one): forward 590 -> 159 us, forward + backward 1861 -> 663 us.  Head size 128, small problems and short
+// streams run here; the rest, that size with it, on the bf16 instructions (jfa_f32_split.hip, f32_form()).
+#include "jfa_f32.h"
 
 namespace jfa {
 
@@ -43,9 +42,9 @@ template <int D, int W> constexpr int f32_lds_bytes() {
 // D = 128 needs more than 256 registers in the backward, and 128 KB of stages with four waves: one such workgroup per compute unit
 template <int D> constexpr int f32_waves_per_simd() { return D <= 64 ? 2 : 1; }
 
-// Up to this many items per workgroup are dealt round-robin from the sorted schedule, without claims.  A claim is an atomic
-// of the whole device, and its latency heads everything a tile does: at D <= 64 that costs more than
-// the last tiles' imbalance (B = 256, H = 2, lengths to 512, 4.5 items: D = 64 forward 184 -> 158 us, backward 509 -> 495; 500
+// Up to this many items per workgroup are dealt from the sorted schedule without claims.  A claim is an atomic of the
+// whole device, and its latency heads everything a tile does: at D <= 64 that costs more than the last tiles' imbalance
+// (B = 256, H = 2, lengths to 512, 4.5 items: D = 64 forward 184 -> 158 us, backward 509 -> 495; 500
 // samples of at most 100 rows, H = 8, 6 to 8 items, D = 32: 125 -> 56 and 240 -> 163).  At D = 128, with half the workgroups and
 // twice the time per tile, balance is worth more (9 items: 343 -> 358), and next_work()'s own limit of four holds.
 template <int D> constexpr int64_t f32_static_items() { return D <= 64 ? 16 : 0; }
@@ -60,11 +59,6 @@ template <int D> __device__ inline int f32_swz(int r) {
 // What rows past a sample's end are copied from.  Their scores are masked, but a probability of 0 times a repeated row is not 0
 // where that row holds an infinity.
 static __device__ const __attribute__((aligned(16))) float zeros[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-
-__device__ inline int not_hoisted(int x) {
-    asm volatile("" : "+v"(x));
-    return x;
-}
 
 // Copies a stage's rows r0 .. of one head (base: the sample's first row of that head; zeroes for rows past the sample's L) into
 // `tile`.  A wave instruction fills 1 KB = 256 / D rows.  Addresses are made anew for every stage: kept, they take registers
@@ -107,12 +101,6 @@ template <int D> __device__ inline int element_read_at(int col, int half) {
     return half * (16 * D) + (((col >> 2) ^ f32_swz<D>(4 * half)) << 4) + (col & 3) * 4;
 }
 
-// exp(x).  The argument is a difference (score minus maximum or log-sum-exp) of numbers that may be much larger than it:
-// scaled in one rounding together with the subtraction, and only the difference times log2(e).  (Both sides of the difference
-// times log2(e) first, one vector instruction less per score: the gradients' error was 1.3 times this at scores of standard
-// deviation 1 and 1.4 times at 16.)
-__device__ inline float exp_f32(float x) { return fast_exp2(x * 1.4426950408889634f); }
-
 // (32 streamed rows at `block`) (stationary rows)^T; at: row_read_at.  A score's error grows with the length of the chains of
 // additions it comes from, and the exponential turns it into a relative error of the probability: the D features are summed
 // in four chains, as four lanes of a vector kernel would.  One chain: the gradients' error at scores of standard deviation 16
@@ -153,13 +141,6 @@ template <int D> __device__ inline void accumulate(f32x16 (&acc)[D / 32], const 
     }
 }
 
-template <int D> __device__ inline void clear(f32x16 (&acc)[D / 32]) {
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[db][e] = 0.0f;
-}
-
 // An accumulator on its way to the wave that shares the stationary rows: 16 bytes per lane and step, no bank conflicts.
 template <int D> __device__ inline void park(char *region, const f32x16 (&acc)[D / 32], int lane) {
 #pragma unroll
@@ -181,30 +162,6 @@ template <int D> __device__ inline void merge(f32x16 (&acc)[D / 32], const char 
             acc[db][4 * g + 2] = acc[db][4 * g + 2] * mine + o.z * theirs;
             acc[db][4 * g + 3] = acc[db][4 * g + 3] * mine + o.w * theirs;
         }
-}
-
-// Store a transposed accumulator (rows = features, column = this lane's row of the output tensor).
-template <int D> __device__ inline void store_row(float *dst, const f32x16 (&acc)[D / 32], float scale, int half) {
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<float4 *>(dst + db * 32 + g * 8 + half * 4) =
-                make_float4(acc[db][4 * g] * scale, acc[db][4 * g + 1] * scale, acc[db][4 * g + 2] * scale, acc[db][4 * g + 3] * scale);
-}
-
-// The workgroup's next work item into `t`, false when nothing is left; ends with a barrier, so that the stage buffers
-// are free.  item: number of items taken so far.
-__device__ inline bool next_item(Work &t, const SmallWork &mine, bool small, int item, const Schedule &s, const int64_t *offsets,
-                                 const int64_t *offsets_other, int B, int H, WorkCursor &cursor, int64_t total, int64_t *slot) {
-    if (small) {   // the workgroup's items were decoded when the schedule was built
-        __syncthreads();
-        return item < __builtin_amdgcn_readfirstlane(mine.count) && load_work<true>(&mine.item[item], t);
-    }
-    const int64_t w = fetch_item(s.counter, cursor, total, slot);
-    if (w < 0) return false;
-    t = decode_work(s, offsets, B, H, w, offsets_other);
-    return true;
 }
 
 template <int D, int W>
@@ -529,49 +486,53 @@ __global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void dkv_f32_kerne
 }
 
 hipError_t launch_fwd_f32(const float *q, const float *k, const float *v, const int64_t *offsets,
-                          const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, int block_rows, float *out, float *lse,
+                          const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, F32Form form, float *out, float *lse,
                           int cus, hipStream_t stream) {
-#define JFA_LAUNCH(DD, W)                                                                                         \
-    hipLaunchKernelGGL((fwd_f32_kernel<DD, W>), dim3(persistent_grid<fwd_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
-                       q, k, v, offsets, offsets_kv, causal, B, H, s, out, lse)
-#define JFA_CASE(DD)                                                                                              \
-    case DD:                                                                                                      \
-        if (block_rows == f32_rows<1>()) JFA_LAUNCH(DD, 1);                                                       \
-        else JFA_LAUNCH(DD, 4);                                                                                   \
+    if (form.split) return launch_fwd_f32_split(q, k, v, offsets, offsets_kv, causal, B, H, D, s, out, lse, cus, stream);
+#define JFA_CASE(DD, W)                                                                                           \
+    case DD * 1000 + f32_rows<W>():                                                                               \
+        hipLaunchKernelGGL((fwd_f32_kernel<DD, W>), dim3(persistent_grid<fwd_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
+                           q, k, v, offsets, offsets_kv, causal, B, H, s, out, lse);                              \
         break;
-    switch (D) {
-        JFA_CASE(32) JFA_CASE(64) JFA_CASE(128)
+    switch (D * 1000 + form.rows) {
+        JFA_CASE(32, 1) JFA_CASE(32, 4) JFA_CASE(64, 1) JFA_CASE(64, 4) JFA_CASE(128, 1) JFA_CASE(128, 4)
         default: return hipErrorInvalidValue;
     }
 #undef JFA_CASE
-#undef JFA_LAUNCH
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_f32(const float *q, const float *k, const float *v, const float *out, const float *dout,
-                          const float *lse, const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H,
-                          int D, Schedule s_dq, int rows_dq, Schedule s_dkv, int rows_dkv, float *dq, float *dk, float *dv, float *delta,
-                          int cus, hipStream_t stream) {
-#define JFA_DQ(DD, W)                                                                                              \
-    hipLaunchKernelGGL((dq_f32_kernel<DD, W>), dim3(persistent_grid<dq_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
-                       q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, B, H, s_dq, dq)
-#define JFA_DKV(DD, W)                                                                                             \
-    hipLaunchKernelGGL((dkv_f32_kernel<DD, W>), dim3(persistent_grid<dkv_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
-                       q, k, v, dout, lse, delta, offsets_kv ? offsets_kv : offsets, offsets_kv ? offsets : nullptr, causal, B, H, s_dkv, dk, dv)
-#define JFA_CASE(DD)                                                                                               \
-    case DD:                                                                                                       \
-        if (rows_dq == f32_rows<1>()) JFA_DQ(DD, 1);                                                               \
-        else JFA_DQ(DD, 4);                                                                                        \
-        if (rows_dkv == f32_rows<1>()) JFA_DKV(DD, 1);                                                             \
-        else JFA_DKV(DD, 4);                                                                                       \
+hipError_t launch_dq_f32(const float *q, const float *k, const float *v, const float *out, const float *dout, const float *lse,
+                         const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, F32Form form,
+                         float *dq, float *delta, int cus, hipStream_t stream) {
+    if (form.split) return launch_dq_f32_split(q, k, v, out, dout, lse, offsets, offsets_kv, causal, B, H, D, s, dq, delta, cus, stream);
+#define JFA_CASE(DD, W)                                                                                            \
+    case DD * 1000 + f32_rows<W>():                                                                                \
+        hipLaunchKernelGGL((dq_f32_kernel<DD, W>), dim3(persistent_grid<dq_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
+                           q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, B, H, s, dq);              \
         break;
-    switch (D) {
-        JFA_CASE(32) JFA_CASE(64) JFA_CASE(128)
+    switch (D * 1000 + form.rows) {
+        JFA_CASE(32, 1) JFA_CASE(32, 4) JFA_CASE(64, 1) JFA_CASE(64, 4) JFA_CASE(128, 1) JFA_CASE(128, 4)
         default: return hipErrorInvalidValue;
     }
 #undef JFA_CASE
-#undef JFA_DKV
-#undef JFA_DQ
+    return hipGetLastError();
+}
+
+hipError_t launch_dkv_f32(const float *q, const float *k, const float *v, const float *dout, const float *lse, const float *delta,
+                          const int64_t *offsets, const int64_t *offsets_q, bool causal, int B, int H, int D, Schedule s, F32Form form,
+                          float *dk, float *dv, int cus, hipStream_t stream) {
+    if (form.split) return launch_dkv_f32_split(q, k, v, dout, lse, delta, offsets, offsets_q, causal, B, H, D, s, dk, dv, cus, stream);
+#define JFA_CASE(DD, W)                                                                                            \
+    case DD * 1000 + f32_rows<W>():                                                                                \
+        hipLaunchKernelGGL((dkv_f32_kernel<DD, W>), dim3(persistent_grid<dkv_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
+                           q, k, v, dout, lse, delta, offsets, offsets_q, causal, B, H, s, dk, dv);                \
+        break;
+    switch (D * 1000 + form.rows) {
+        JFA_CASE(32, 1) JFA_CASE(32, 4) JFA_CASE(64, 1) JFA_CASE(64, 4) JFA_CASE(128, 1) JFA_CASE(128, 4)
+        default: return hipErrorInvalidValue;
+    }
+#undef JFA_CASE
     return hipGetLastError();
 }
 
