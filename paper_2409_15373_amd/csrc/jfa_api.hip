@@ -325,6 +325,11 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
     Views w;
     if ((st = static_table ? get_static_table(B, &w) : get_table(B, s, &w)) != JFA_OK) return st;
     hipError_t e;
+    if (const int rows = f32 ? 0 : jfa::one_tile_rows(max_len, max_len_kv)) {
+        ScopedTimer tm("fwd_one_tile", s);
+        e = jfa::launch_fwd_one_tile(q, k, v, offsets, offsets_kv, causal, B, H, D, rows, out, lse, s);
+        return e == hipSuccess ? JFA_OK : hip_fail("fwd_one_tile", e);
+    }
     if (few_queries(f32, D, H, offsets_kv, max_len)) {
         jfa::Schedule sc;
         if ((st = few_queries_schedule(offsets, offsets_kv, B, H, w, s, &sc)) != JFA_OK) return st;
@@ -366,6 +371,11 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     Views w;
     if ((st = get_table(B, s, &w)) != JFA_OK) return st;
     hipError_t e;
+    if (const int rows = f32 ? 0 : jfa::one_tile_rows(max_len, max_len_kv)) {
+        ScopedTimer tm("bwd_one_tile", s);
+        e = jfa::launch_bwd_one_tile(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, B, H, D, rows, dq, dk, dv, s);
+        return e == hipSuccess ? JFA_OK : hip_fail("bwd_one_tile", e);
+    }
     if (few_queries(f32, D, H, offsets_kv, max_len)) {
         jfa::Schedule sc;
         if ((st = few_queries_schedule(offsets, offsets_kv, B, H, w, s, &sc)) != JFA_OK) return st;

@@ -543,6 +543,21 @@ hipError_t launch_dkv_f32(const float *q, const float *k, const float *v, const 
                           float *dk, float *dv, int cus, hipStream_t stream);
 // (the dQ kernel of every path runs first and computes delta[h, row] = sum_d dout * out for the kernels after it)
 
+// bf16 attention where no sample has more than kOneTileRows queries or keys (jfa_one_tile.hip): no schedule, every item a workgroup.
+// rows: 32 or 64, at least the longest length.
+// Every call that fits takes them: of 117 shapes (B 4 to 20000, H 1 to 8, all head sizes, self, causal, cross) none is slower, the
+// fewest-query kernels' included (4 samples of up to 20 rows, cross, D = 128, backward 9.4 -> 6.3 us); see jfa_one_tile.hip.
+constexpr int kOneTileRows = 64;
+inline int one_tile_rows(int64_t max_len, int64_t max_len_kv) {
+    const int64_t longest = max_len > max_len_kv ? max_len : max_len_kv;
+    return longest > kOneTileRows ? 0 : longest > 32 ? 64 : 32;
+}
+hipError_t launch_fwd_one_tile(const void *q, const void *k, const void *v, const int64_t *offsets, const int64_t *offsets_kv, bool causal,
+                               int64_t B, int H, int D, int rows, void *out, float *lse, hipStream_t stream);
+hipError_t launch_bwd_one_tile(const void *q, const void *k, const void *v, const void *out, const void *dout, const float *lse, float *stats,
+                               const int64_t *offsets, const int64_t *offsets_kv, bool causal, int64_t B, int H, int D, int rows, void *dq,
+                               void *dk, void *dv, hipStream_t stream);
+
 // bf16 attention, register-staged kernels (D = 128, short samples)
 constexpr int kFwdBlockRows = 128;
 constexpr int kBwdBlockRows = 128;
