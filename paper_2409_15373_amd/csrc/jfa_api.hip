@@ -172,8 +172,8 @@ void drop_timed() {
     g_timed.clear();
 }
 
-// bf16 at D = 128: the direct-to-LDS kernels for long samples, the register-staged ones for short samples and for rows that the
-// former's 32-bit row offsets do not reach.  (D = 32 and 64 have kernels of their own for every length, and so has fp32.)
+// bf16 at D = 128, more than 128 rows: the direct-to-LDS kernels for long samples, the register-staged ones for the others and for rows
+// that the former's 32-bit row offsets do not reach.  (D = 32 and 64 have kernels of their own for every length, and so has fp32.)
 bool long_samples(int64_t max_len, int D, int H) {
     return D == 128 && (int64_t)H * D <= (1 << 20) && max_len > 256;   // 256-query tiles only pay off when samples can be long
 }
@@ -287,8 +287,8 @@ namespace {
 // Forward and backward behind the self- and cross-attention entry points.  offsets_kv == nullptr: self attention
 // (keys and values share the queries' offsets).  Work schedules are built over the offsets of the rows a kernel's
 // work items are blocks of: the queries' for the forward and dQ, the keys' for dK and dV.
-jfa::ScheduleJob schedule_job(const int64_t *offsets, const int64_t *offsets_other, int block_rows, const Views &w, int which) {
-    return jfa::ScheduleJob{offsets, offsets_other, block_rows, w.order[which], w.tile_start[which]};
+jfa::ScheduleJob schedule_job(const int64_t *offsets, const int64_t *offsets_other, int block_rows, const Views &w, int which, int skip_rows = 0) {
+    return jfa::ScheduleJob{offsets, offsets_other, block_rows, w.order[which], w.tile_start[which], skip_rows};
 }
 hipError_t schedule(const jfa::ScheduleJob *jobs, int n_jobs, int64_t B, const Views &w, hipStream_t s) {
     ScopedTimer tm("schedule", s);
@@ -327,7 +327,9 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
     hipError_t e;
     if (const int rows = f32 ? 0 : jfa::one_tile_rows(max_len, max_len_kv)) {
         ScopedTimer tm("fwd_one_tile", s);
-        e = jfa::launch_fwd_one_tile(q, k, v, offsets, offsets_kv, causal, B, H, D, rows, out, lse, s);
+        const int least = jfa::one_tile_twice(false, offsets_kv != nullptr, D, B, H, rows, w.cus) ? 64 : 0;
+        e = least ? jfa::launch_fwd_one_tile(q, k, v, offsets, offsets_kv, causal, B, H, D, 0, least, out, lse, s) : hipSuccess;
+        if (e == hipSuccess) e = jfa::launch_fwd_one_tile(q, k, v, offsets, offsets_kv, causal, B, H, D, least, rows, out, lse, s);
         return e == hipSuccess ? JFA_OK : hip_fail("fwd_one_tile", e);
     }
     if (few_queries(f32, D, H, offsets_kv, max_len)) {
@@ -348,7 +350,13 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
         sc.build_rows = block_rows;
         sc.static_only = true;
     } else {
-        const jfa::ScheduleJob job = schedule_job(offsets, offsets_kv, block_rows, w, 0);
+        const int short_rows = f32 ? 0 : jfa::short_sample_rows(offsets_kv != nullptr, D, B, max_len, H, w.cus);
+        if (short_rows) {
+            ScopedTimer tm("fwd_one_tile", s);
+            e = jfa::launch_fwd_one_tile(q, k, v, offsets, offsets_kv, causal, B, H, D, 0, short_rows, out, lse, s);
+            if (e != hipSuccess) return hip_fail("fwd_one_tile", e);
+        }
+        const jfa::ScheduleJob job = schedule_job(offsets, offsets_kv, block_rows, w, 0, short_rows);
         e = schedule(&job, 1, B, w, s);
         if (e != hipSuccess) return hip_fail("schedule kernel", e);
     }
@@ -373,7 +381,9 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     hipError_t e;
     if (const int rows = f32 ? 0 : jfa::one_tile_rows(max_len, max_len_kv)) {
         ScopedTimer tm("bwd_one_tile", s);
-        e = jfa::launch_bwd_one_tile(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, B, H, D, rows, dq, dk, dv, s);
+        const int least = jfa::one_tile_twice(true, offsets_kv != nullptr, D, B, H, rows, w.cus) ? 64 : 0;
+        e = least ? jfa::launch_bwd_one_tile(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, B, H, D, 0, least, dq, dk, dv, s) : hipSuccess;
+        if (e == hipSuccess) e = jfa::launch_bwd_one_tile(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, B, H, D, least, rows, dq, dk, dv, s);
         return e == hipSuccess ? JFA_OK : hip_fail("bwd_one_tile", e);
     }
     if (few_queries(f32, D, H, offsets_kv, max_len)) {
@@ -401,8 +411,14 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     };
     const bool in_kernel = !dma && small(max_len, block_rows) && small(max_len_kv, key_rows);
     if (!in_kernel) {
-        const jfa::ScheduleJob jobs[2] = {schedule_job(offsets, offsets_kv, block_rows, w, 0),
-                                          schedule_job(offsets_k, offsets_q_other, key_rows, w, 1)};
+        const int short_rows = f32 ? 0 : jfa::short_sample_rows(offsets_kv != nullptr, D, B, max_len, H, w.cus);
+        if (short_rows) {
+            ScopedTimer tm("bwd_one_tile", s);
+            e = jfa::launch_bwd_one_tile(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, B, H, D, 0, short_rows, dq, dk, dv, s);
+            if (e != hipSuccess) return hip_fail("bwd_one_tile", e);
+        }
+        const jfa::ScheduleJob jobs[2] = {schedule_job(offsets, offsets_kv, block_rows, w, 0, short_rows),
+                                          schedule_job(offsets_k, offsets_q_other, key_rows, w, 1, short_rows)};
         e = schedule(jobs, kv + 1, B, w, s);
         if (e != hipSuccess) return hip_fail("schedule kernel", e);
     }

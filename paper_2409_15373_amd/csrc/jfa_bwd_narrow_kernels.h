@@ -342,6 +342,7 @@ hipError_t launch_dq_narrow_waves(const void *q, const void *k, const void *v, c
 #define JFA_CASE(DD)                                                                                         \
     case DD:                                                                                                 \
         if (offsets_kv) JFA_LAUNCH(DD, true, false);                                                         \
+        else if constexpr (W == 2) return hipErrorInvalidValue;   /* see narrow_block_rows() */              \
         else if (causal) JFA_LAUNCH(DD, false, true);                                                        \
         else JFA_LAUNCH(DD, false, false);                                                                   \
         break;
@@ -366,6 +367,7 @@ hipError_t launch_dkv_narrow_waves(const void *q, const void *k, const void *v, 
 #define JFA_CASE(DD)                                                                                         \
     case DD:                                                                                                 \
         if (offsets_q) JFA_LAUNCH(DD, true, false);                                                          \
+        else if constexpr (W == 2 && DD == 32) return hipErrorInvalidValue;   /* see narrow_key_rows() */    \
         else if (causal) JFA_LAUNCH(DD, false, true);                                                        \
         else JFA_LAUNCH(DD, false, false);                                                                   \
         break;

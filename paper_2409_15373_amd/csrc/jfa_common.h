@@ -490,6 +490,7 @@ struct ScheduleJob {
     const int64_t *offsets, *offsets_other;
     int block_rows;
     int32_t *order, *tile_start;
+    int skip_rows = 0;   // samples with no more rows than this (on both sides) get no blocks: another kernel does them
 };
 hipError_t launch_schedules(const ScheduleJob *jobs, int n_jobs, int B, int32_t *counters, int n_counters, hipStream_t stream);
 hipError_t launch_check_offsets(const int64_t *offsets, int B, int64_t max_len, int *flags, hipStream_t stream);
@@ -544,27 +545,56 @@ hipError_t launch_dkv_f32(const float *q, const float *k, const float *v, const 
 // (the dQ kernel of every path runs first and computes delta[h, row] = sum_d dout * out for the kernels after it)
 
 // bf16 attention where no sample has more than kOneTileRows queries or keys (jfa_one_tile.hip): no schedule, every item a workgroup.
-// rows: 32 or 64, at least the longest length.
-// Every call that fits takes them: of 117 shapes (B 4 to 20000, H 1 to 8, all head sizes, self, causal, cross) none is slower, the
-// fewest-query kernels' included (4 samples of up to 20 rows, cross, D = 128, backward 9.4 -> 6.3 us); see jfa_one_tile.hip.
-constexpr int kOneTileRows = 64;
+// Its rows: 32, 64 or 128, at least the longest length (0: longer ones).  Every call that fits takes these kernels.  Up to 64 rows, of
+// 117 shapes (B 4 to 20000, H 1 to 8, all head sizes, self, causal, cross), none is slower than in the kernels for longer samples, the
+// few-query ones included (4 samples of up to 20 rows, cross, D = 128, backward 9.4 -> 6.3 us); up to 128, of 126 one is slower than in
+// two-wave 64-row tiles (D = 64, cross, 2048 x 4 heads, one sample in ten long on each side, backward 153 -> 165), none than in 128-row
+// ones.  Microseconds, forward and backward, lengths uniform: 500 samples of up to 90 rows, D = 128, 14.7 -> 9.6, 50 -> 23; 2000 x 2 of
+// up to 128, D = 64, 53 -> 34, 118 -> 103; D = 128 82 -> 56, 322 -> 173.
+constexpr int kOneTileRows = 128;
 inline int one_tile_rows(int64_t max_len, int64_t max_len_kv) {
     const int64_t longest = max_len > max_len_kv ? max_len : max_len_kv;
-    return longest > kOneTileRows ? 0 : longest > 32 ? 64 : 32;
+    return longest > kOneTileRows ? 0 : longest > 64 ? 128 : longest > 32 ? 64 : 32;
 }
+// Whether a call of 128 rows is made in two launches, samples of at most 64 rows first: in a workgroup for 128 rows half of the waves
+// and half of the LDS would be idle for them.  In large batches that is worth a launch and a second look at every sample: backward,
+// 2048 x 4 heads, one sample in ten long, D = 64 119 -> 77 us, D = 32 58 -> 49 (cross, where fewer are short on both sides, 74 -> 76);
+// 2000 x 2, uniform, 101 -> 97, D = 128 169 -> 175.  Forward 2048 x 8 of up to 100 rows, geometric, D = 64 93 -> 84, 2000 x 2 34 -> 37;
+// D = 32 45 -> 47, cross, D = 128, 177 -> 181.
+inline bool one_tile_twice(bool backward, bool cross, int D, int64_t B, int H, int rows, int cus) {
+    const int64_t items = B * H;
+    if (rows != 128) return false;
+    return backward ? items >= 32 * (int64_t)cus && (D >= 64 || !cross) : items >= 64 * (int64_t)cus && D >= 64 && !cross;
+}
+// least: samples with no more rows than this on both sides are left out
 hipError_t launch_fwd_one_tile(const void *q, const void *k, const void *v, const int64_t *offsets, const int64_t *offsets_kv, bool causal,
-                               int64_t B, int H, int D, int rows, void *out, float *lse, hipStream_t stream);
+                               int64_t B, int H, int D, int least, int rows, void *out, float *lse, hipStream_t stream);
 hipError_t launch_bwd_one_tile(const void *q, const void *k, const void *v, const void *out, const void *dout, const float *lse, float *stats,
-                               const int64_t *offsets, const int64_t *offsets_kv, bool causal, int64_t B, int H, int D, int rows, void *dq,
-                               void *dk, void *dv, hipStream_t stream);
+                               const int64_t *offsets, const int64_t *offsets_kv, bool causal, int64_t B, int H, int D, int least, int rows,
+                               void *dq, void *dk, void *dv, hipStream_t stream);
+// Batches with longer samples: those of at most 64 rows may go to these kernels all the same (returns 64; 0: none do) while the
+// others' schedules skip them.  What that gains is in the lengths, which the host does not know; the launch and a look at every
+// sample cost some 5 us.  The line lies where lengths uniform on [1, max_len], of which few are short, lose nothing.  Self attention,
+// microseconds, all in the other kernels -> split:
+//   D = 128, 1024 x 4 heads, up to 250 rows: uniform, forward 169 -> 166, backward 627 -> 607; geometric (mean 64) 86 -> 75, 323 -> 261;
+//   up to 600: uniform 469 -> 466, 1554 -> 1553; geometric 127 -> 94, 383 -> 282; one in ten long 158 -> 116, 483 -> 362.  512 x 4 of up
+//   to 250, uniform: 85 -> 88, 340 -> 338.
+//   D = 64 (these samples' tiles are cheaper in the other kernels), 2048 x 8 heads of up to 250: uniform 311 -> 299, 842 -> 825, one in
+//   ten long 148 -> 80, 372 -> 230; of up to 600, uniform 935 -> 944, 2748 -> 2768.  1024 x 4 of up to 250, uniform: 85 -> 88, 243 -> 241.
+//   D = 32, 2048 x 8 of up to 250, Zipf lengths, backward 436 -> 468.  Cross attention, both sides uniform (fewer samples are short on
+//   both), D = 128, 1024 x 4 of up to 600: 444 -> 453, 1395 -> 1409.
+inline int short_sample_rows(bool cross, int D, int64_t B, int64_t max_len, int H, int cus) {
+    const int64_t items = B * H;
+    const bool worth = D == 128 ? items >= 16 * (int64_t)cus : D == 64 && max_len <= 256 && items >= 64 * (int64_t)cus;
+    return !cross && worth ? 64 : 0;
+}
 
 // bf16 attention, register-staged kernels (D = 128, short samples)
 constexpr int kFwdBlockRows = 128;
 constexpr int kBwdBlockRows = 128;
 // Items per workgroup that these kernels take without claims.  A claim heads a tile here, its latency is not hidden, and their
-// streams are short; microseconds with 4 and 16, forward and backward: 4096 samples of at most 32 rows 64 and 53, 175 and 152;
-// 1000 x 4 of at most 40 62 and 47, 176 and 157; 500 x 8 of at most 100 69 and 59, 211 and 207; 1024 x 4, 200 queries against at
-// most 200 keys 135 and 131, 472 and 477.
+// streams are short; microseconds with 4 and 16, forward and backward: 1024 x 4, 200 queries against at most 200 keys 135 and 131,
+// 472 and 477 (batches of shorter samples, which gained a sixth, have kernels of their own: one_tile_rows()).
 constexpr int kShortFixedItems = 16;
 // In all bf16 launchers `offsets` belongs to the rows the schedule `s` was built over (queries for the forward and
 // dQ, keys for dK / dV) and the second array to the rows that stream past them (cross attention; nullptr: the same).
@@ -585,14 +615,12 @@ hipError_t launch_dq_bf16(const void *q, const void *k, const void *v, const voi
 // (delta, -lse * sqrt(D)) for the dK / dV launch.
 // Rows of a tile: 128 (four waves) or 64 (two).  With short samples most waves of a 128-row tile have no rows but take registers
 // and places; two-wave workgroups put more tiles on a compute unit at once, and a stage's copies on fewer waves, which long
-// streams pay for.  Microseconds, 128 -> 64 rows, forward and backward: 4096 samples of at most 32 rows, D = 64, 59 -> 35 and
-// 104 -> 60, D = 32 31 -> 27 and 73 -> 41; 500 x 8 of at most 100, D = 64, 39 -> 37 and 88 -> 78; 1024 x 4, 32 queries against at
-// most 200 keys, D = 64, forward 44 -> 36; but 1024 x 4 of at most 200 rows 77 -> 103 and 206 -> 272, and four samples of 4096 keys
-// with 32 queries 53 -> 60.  In small problems (see small_problem()) the second condition loses 0.5 us.
+// streams pay for.  (Where both sides are short the whole sample is one tile, see one_tile_rows().)  Microseconds, 128 -> 64 rows:
+// 1024 x 4, 32 queries against at most 200 keys, D = 64, forward 44 -> 36; but 1024 x 4 of at most 200 rows on both sides 77 -> 103,
+// backward 206 -> 272, and four samples of 4096 keys with 32 queries 53 -> 60; in small problems (see small_problem()) 0.5 more.
 constexpr int kNarrowBlockRows = 128, kNarrowShortBlockRows = 64;
 inline int narrow_block_rows(int64_t max_len, int64_t max_streamed, bool small) {
-    const bool two_waves = (max_len <= 128 && max_streamed <= 128) || (max_len <= 64 && max_streamed <= 256 && !small);
-    return two_waves ? kNarrowShortBlockRows : kNarrowBlockRows;
+    return max_len <= 64 && max_streamed <= 256 && !small ? kNarrowShortBlockRows : kNarrowBlockRows;
 }
 // Items per workgroup up to which work is dealt without claims.  Longest items first and every other round backwards, such a
 // deal is even to less than an item; a claim costs a short item more than that.  Long items gain nothing from it, and it parts the
@@ -658,9 +686,9 @@ hipError_t launch_unfused_apply(const float *probs, const void *v, const int64_t
                                 int H, int D, Schedule s, void *out, int cus, hipStream_t stream);
 
 // Whether an operator stores its rows past the L2 (non-temporal): where the tensor, at most B * max_len rows, is larger than the
-// eight L2s and some.  The next operator finds a smaller one in them: 168 samples of up to 309 rows, D = T = 128, five operators:
-// 48.7 us, stored past the L2 49.8.
-inline bool past_l2(int64_t B, int64_t max_len, int64_t row_bytes) { return (double)B * (double)max_len * (double)row_bytes > 64e6; }
+// memory-side cache.  Of a smaller one the next operator finds more in the caches: 168 samples of up to 309 rows, D = T = 128, five
+// operators: 48.7 us, stored past the L2 49.8; padding and back, 66 samples of up to 3787 rows of 320 bytes, 32.1, past it 33.1.
+inline bool past_l2(int64_t B, int64_t max_len, int64_t row_bytes) { return (double)B * (double)max_len * (double)row_bytes > 256e6; }
 // A template parameter: given both stores behind a runtime flag the compiler makes them one and drops the hint.
 template <bool kPast, typename V> __device__ inline void store_streaming(V *dst, V x) {
     if constexpr (kPast) __builtin_nontemporal_store(x, dst);

@@ -221,10 +221,16 @@ hipError_t launch_fwd_narrow(const void *q, const void *k, const void *v, const 
         else if (causal) JFA_LAUNCH(DD, W, false, true);                                                     \
         else JFA_LAUNCH(DD, W, false, false);                                                                \
         break;
+#define JFA_SHORT_CASE(DD)   /* cross attention only: see narrow_block_rows() */                             \
+    case DD * 1000 + kNarrowShortBlockRows:                                                                  \
+        if (!offsets_kv) return hipErrorInvalidValue;                                                        \
+        JFA_LAUNCH(DD, 2, true, false);                                                                      \
+        break;
     switch (D * 1000 + block_rows) {
-        JFA_CASE(32, 2) JFA_CASE(32, 4) JFA_CASE(64, 2) JFA_CASE(64, 4)
+        JFA_SHORT_CASE(32) JFA_CASE(32, 4) JFA_SHORT_CASE(64) JFA_CASE(64, 4)
         default: return hipErrorInvalidValue;
     }
+#undef JFA_SHORT_CASE
 #undef JFA_CASE
 #undef JFA_LAUNCH
     return hipGetLastError();

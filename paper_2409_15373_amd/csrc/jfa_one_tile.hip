@@ -1,4 +1,4 @@
-// Jagged flash attention, bf16, where no sample has more than 64 queries or keys: a workgroup holds all of a (sample, head) and makes
+// Jagged flash attention, bf16, for samples of at most 128 queries and keys: a workgroup holds all of a (sample, head) and makes
 // one pass over it, forward and backward.
 //
 // What bounds such a call is neither arithmetic nor memory but the chain of latencies that every work item starts and ends with (work
@@ -8,10 +8,12 @@
 // and dV: the accumulator is then in operand position, see jfa_mfma.h) out of the same tiles, each in a wave of its own, so that one
 // kernel reads Q, K, V, dO, O once and writes all three gradients; they go to whole-row stores through tiles that have been read.
 // Microseconds against the persistent kernels with their two-kernel backward (in brackets: the time to copy what a call must move,
-// and a launch): 4096 samples of up to 32 rows, forward D = 64 36.4 -> 8.4 (10.2), D = 128 53.8 -> 15.9 (17.3), backward 61.3 -> 18.0
-// (20.5) and 153 -> 32.6 (34.7); 3000 x 8 heads of up to 64, D = 128, 297 -> 154 (169) and 1087 -> 371 (340); 4 samples of up to 20,
+// and a launch): 4096 samples of up to 32 rows, forward D = 64 36.4 -> 8.5 (10.2), D = 128 53.8 -> 16.0 (17.3), backward 61.3 -> 17.5
+// (20.5) and 153 -> 31.0 (34.7); 3000 x 8 heads of up to 64, D = 128, 297 -> 153 (169) and 1087 -> 348 (340); 4 samples of up to 20,
 // D = 64, 6.7 -> 3.9 and 12.8 -> 4.9.  One wave for both orientations of the backward: 4096 of up to 32, D = 128, 47.9.  A loop over
-// items instead of a workgroup for each: its invariants take 100 registers more, 3000 x 8, D = 64, forward 77 -> 98.
+// items instead of a workgroup for each: its invariants take 100 registers more, 3000 x 8, D = 64, forward 77 -> 98.  P and dS of all
+// of a wave's blocks kept as operands until the second barrier instead of one block at a time: 3000 x 8 of up to 64, D = 64, backward
+// 180 -> 194 (D = 128, causal, the other way about: 400 -> 384, eleven registers are spilled).
 #include "jfa_common.h"
 #include "jfa_lds.h"
 #include "jfa_mfma.h"
@@ -124,18 +126,16 @@ struct OneTile {
 struct OneTileItem {
     int b, head, Lq, Lk;
     int64_t q0, k0;
-    __device__ inline bool take(int64_t w, const int64_t *offsets_q, const int64_t *offsets_kv, int B, int H, int most) {
+    __device__ inline bool take(int64_t w, const int64_t *offsets_q, const int64_t *offsets_kv, int B, int H, int least, int most) {
         const int64_t i = w / kXcds, s = i / H * kXcds + w % kXcds;
         if (s >= B) return false;
         b = (int)s;
         head = (int)(i % H);
         q0 = offsets_q[b];
         Lq = (int)(offsets_q[b + 1] - q0);
-        Lq = Lq < most ? Lq : most;   // (max_len bounds the lengths; a caller who breaks that gets part of the sample)
         k0 = offsets_kv ? offsets_kv[b] : q0;
         Lk = offsets_kv ? (int)(offsets_kv[b + 1] - k0) : Lq;
-        Lk = Lk < most ? Lk : most;
-        return true;
+        return Lq <= most && Lk <= most && (Lq > least || Lk > least);   // the others: another launch's
     }
 };
 static inline int64_t one_tile_items(int64_t B, int H) { return (B + kXcds - 1) / kXcds * kXcds * (int64_t)H; }
@@ -151,7 +151,7 @@ template <int W, bool copies = false> __device__ inline void one_tile_barrier() 
 template <int D, int W, bool CAUSAL>
 __global__ __launch_bounds__(64 * W, 2) void fwd_one_tile_kernel(const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
                                                                  const int64_t *__restrict__ offsets, const int64_t *__restrict__ offsets_kv,
-                                                                 int B, int H, int64_t first, __bf16 *__restrict__ out, float *__restrict__ lse) {
+                                                                 int B, int H, int64_t first, int least, __bf16 *__restrict__ out, float *__restrict__ lse) {
     using T = OneTile<D>;
     __shared__ __attribute__((aligned(1024))) char kt[W][T::kTile], vt[W][T::kTile];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r0 = 32 * wave;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(64 * W, 2) void fwd_one_tile_kernel(const __bf16 *_
     const float c = 1.4426950408889634f / sqrtf((float)D);
     const int64_t sum_B = offsets[B], row_stride = (int64_t)H * D;
     OneTileItem t;
-    if (!t.take(first + blockIdx.x, offsets, offsets_kv, B, H, 32 * W)) return;
+    if (!t.take(first + blockIdx.x, offsets, offsets_kv, B, H, least, 32 * W)) return;
     const int Lq = t.Lq, Lk = t.Lk, i = r0 + col, iq = i < Lq ? i : Lq - 1;
     const int64_t kbase = (t.k0 + r0) * row_stride + (int64_t)t.head * D;
     const int64_t qbase = (t.q0 + r0) * row_stride + (int64_t)t.head * D;
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(128 * W, 2) void bwd_one_tile_kernel(const __bf16 *
                                                                   const __bf16 *__restrict__ out, const __bf16 *__restrict__ dout,
                                                                   const float *__restrict__ lse, float *__restrict__ stats,   // [2, H, sum_B]
                                                                   const int64_t *__restrict__ offsets, const int64_t *__restrict__ offsets_kv,
-                                                                  int B, int H, int64_t first, __bf16 *__restrict__ dq, __bf16 *__restrict__ dk,
+                                                                  int B, int H, int64_t first, int least, __bf16 *__restrict__ dq, __bf16 *__restrict__ dk,
                                                                   __bf16 *__restrict__ dv) {
     using T = OneTile<D>;
     __shared__ __attribute__((aligned(1024))) char qt[W][T::kTile], gt[W][T::kTile], kt[W][T::kTile], vt[W][T::kTile];   // Q, dO, K, V
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(128 * W, 2) void bwd_one_tile_kernel(const __bf16 *
     const float scale = 1.0f / sqrtf((float)D), c = 1.4426950408889634f * scale;
     const int64_t sum_B = offsets[B], row_stride = (int64_t)H * D;
     OneTileItem t;
-    if (!t.take(first + blockIdx.x, offsets, offsets_kv, B, H, 32 * W)) return;
+    if (!t.take(first + blockIdx.x, offsets, offsets_kv, B, H, least, 32 * W)) return;
     const int Lq = t.Lq, Lk = t.Lk, mine = keys ? Lk : Lq;
     const int i = r0 + col;                                                                   // this lane's query or key
     const int64_t base = ((keys ? t.k0 : t.q0) + r0) * row_stride + (int64_t)t.head * D;      // of the wave's first row
@@ -274,17 +274,17 @@ __global__ __launch_bounds__(128 * W, 2) void bwd_one_tile_kernel(const __bf16 *
             lse_i = lse[(int64_t)t.head * sum_B + t.q0 + r0 + iq];
         }
         one_tile_barrier<2, true>();
-        bf16x8 ds[W][2];   // dS, keys on the rows
+        bf16x8 qf[T::kKSteps], gf[T::kKSteps];
+        float delta = 0.0f;
+        const float lse2 = lse_i * 1.4426950408889634f;
         if (r0 < Lq) {
-            bf16x8 qf[T::kKSteps], gf[T::kKSteps];
             ln.fragments(qf, qt[tile]);
             ln.fragments(gf, gt[tile]);
-            float dot = 0.0f;
 #pragma unroll
             for (int ks = 0; ks < T::kKSteps; ++ks)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) dot = fmaf((float)of[ks][e], (float)gf[ks][e], dot);
-            const float delta = pair_sum(dot), lse2 = lse_i * 1.4426950408889634f;
+                for (int e = 0; e < 8; ++e) delta = fmaf((float)of[ks][e], (float)gf[ks][e], delta);
+            delta = pair_sum(delta);
             if (half == 0) {
                 row_lse2[i] = lse2;
                 row_delta[i] = delta;
@@ -293,52 +293,40 @@ __global__ __launch_bounds__(128 * W, 2) void bwd_one_tile_kernel(const __bf16 *
                     stats[(int64_t)H * sum_B + stat] = -lse_i * sqrtf((float)D);
                 }
             }
-            const int lim = CAUSAL && i + 1 < Lk ? i + 1 : Lk;   // this lane's query sees keys 0 .. lim - 1
-#pragma unroll
-            for (int kb = 0; kb < W; ++kb) {
-                if (kb * 32 >= Lk || (CAUSAL && kb > tile)) continue;
+        }
+        one_tile_barrier<2>();   // the statistics are there
+        f32x16 g[T::kDBlocks];
+        ln.clear(g);
+        const int lim = CAUSAL && i + 1 < Lk ? i + 1 : Lk;   // this lane's query sees keys 0 .. lim - 1
+        if (r0 < Lq)
+            for (int kb = 0; kb < W && kb * 32 < Lk && !(CAUSAL && kb > tile); ++kb) {
                 const f32x16 s = ln.product(kt[kb], qf), dp = ln.product(vt[kb], gf);
+                bf16x8 ds[2];   // dS, keys on the rows
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     const float x = fast_exp2(fmaf(s[e], c, -lse2)) * (dp[e] - delta);
-                    ds[kb][e >> 3][e & 7] = (__bf16)(kb * 32 + acc_row(e, half) < lim ? x : 0.0f);
+                    ds[e >> 3][e & 7] = (__bf16)(kb * 32 + acc_row(e, half) < lim ? x : 0.0f);
                 }
+                ln.accumulate(g, kt[kb], ds);
             }
-        }
-        one_tile_barrier<2>();   // the statistics are there; the V tiles have been read: they carry dQ
-        f32x16 g[T::kDBlocks];
-        if (r0 < Lq) {
-            ln.clear(g);
-#pragma unroll
-            for (int kb = 0; kb < W; ++kb) {
-                if (kb * 32 >= Lk || (CAUSAL && kb > tile)) continue;
-                ln.accumulate(g, kt[kb], ds[kb]);
-            }
-            ln.store(vt[tile], g, scale, dq + base, row_stride, Lq - r0);
-        }
-        if (W > 1) one_tile_barrier<2>();
+        one_tile_barrier<2>();   // the tiles have been read: they carry the results
+        if (r0 < Lq) ln.store(qt[tile], g, scale, dq + base, row_stride, Lq - r0);
     } else {   // a key per lane
         one_tile_barrier<2, true>();
-        f32x16 s[W], dp[W];
+        bf16x8 kf[T::kKSteps], vf[T::kKSteps];
+        f32x16 s, dp, gk[T::kDBlocks], gv[T::kDBlocks];
+        int qb = CAUSAL && W > 1 ? tile : 0;   // (causal: as many queries as keys, so that every key has one)
         if (r0 < Lk) {
-            bf16x8 kf[T::kKSteps], vf[T::kKSteps];
             ln.fragments(kf, kt[tile]);
             ln.fragments(vf, vt[tile]);
-#pragma unroll
-            for (int qb = 0; qb < W; ++qb) {
-                if (qb * 32 >= Lq || (CAUSAL && qb < tile)) continue;
-                s[qb] = ln.product(qt[qb], kf);
-                dp[qb] = ln.product(gt[qb], vf);
-            }
+            s = ln.product(qt[qb], kf);
+            dp = ln.product(gt[qb], vf);
         }
         one_tile_barrier<2>();
-        f32x16 gk[T::kDBlocks], gv[T::kDBlocks];
-        if (r0 < Lk) {
-            ln.clear(gk);
-            ln.clear(gv);
-#pragma unroll
-            for (int qb = 0; qb < W; ++qb) {
-                if (qb * 32 >= Lq || (CAUSAL && qb < tile)) continue;
+        ln.clear(gk);
+        ln.clear(gv);
+        if (r0 < Lk)
+            for (;;) {
                 bf16x8 p[2], ds[2];   // P and dS, queries on the rows
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
@@ -349,20 +337,21 @@ __global__ __launch_bounds__(128 * W, 2) void bwd_one_tile_kernel(const __bf16 *
                     for (int x = 0; x < 4; ++x) {
                         const int e = 4 * g + x, r = qb * 32 + acc_row(e, half);
                         const bool sees = r < Lq && !(CAUSAL && r < i);
-                        const float y = fast_exp2(fmaf(s[qb][e], c, -l[x]));
+                        const float y = fast_exp2(fmaf(s[e], c, -l[x]));
                         p[e >> 3][e & 7] = (__bf16)(sees ? y : 0.0f);
-                        ds[e >> 3][e & 7] = (__bf16)(sees ? y * (dp[qb][e] - d[x]) : 0.0f);
+                        ds[e >> 3][e & 7] = (__bf16)(sees ? y * (dp[e] - d[x]) : 0.0f);
                     }
                 }
                 ln.accumulate(gv, gt[qb], p);
                 ln.accumulate(gk, qt[qb], ds);
+                if (++qb >= W || qb * 32 >= Lq) break;
+                s = ln.product(qt[qb], kf);
+                dp = ln.product(gt[qb], vf);
             }
-        }
-        if (W > 1) one_tile_barrier<2>();   // the Q and dO tiles have been read: they carry dK and dV
-        else ln.wave_order();
+        one_tile_barrier<2>();
         if (r0 < Lk) {
-            ln.store(gt[tile], gv, 1.0f, dv + base, row_stride, Lk - r0);
-            ln.store(qt[tile], gk, scale, dk + base, row_stride, Lk - r0);
+            ln.store(vt[tile], gv, 1.0f, dv + base, row_stride, Lk - r0);
+            ln.store(kt[tile], gk, scale, dk + base, row_stride, Lk - r0);
         }
     }
 }
@@ -374,11 +363,13 @@ __global__ __launch_bounds__(128 * W, 2) void bwd_one_tile_kernel(const __bf16 *
     case DD:                                                                                                     \
         if (rows == 32 && causal) JFA_ONE_TILE(KERNEL, DD, 1, true, __VA_ARGS__);                                \
         else if (rows == 32) JFA_ONE_TILE(KERNEL, DD, 1, false, __VA_ARGS__);                                    \
-        else if (causal) JFA_ONE_TILE(KERNEL, DD, 2, true, __VA_ARGS__);                                         \
-        else JFA_ONE_TILE(KERNEL, DD, 2, false, __VA_ARGS__);                                                    \
+        else if (rows == 64 && causal) JFA_ONE_TILE(KERNEL, DD, 2, true, __VA_ARGS__);                           \
+        else if (rows == 64) JFA_ONE_TILE(KERNEL, DD, 2, false, __VA_ARGS__);                                    \
+        else if (causal) JFA_ONE_TILE(KERNEL, DD, 4, true, __VA_ARGS__);                                         \
+        else JFA_ONE_TILE(KERNEL, DD, 4, false, __VA_ARGS__);                                                    \
         break;
 #define JFA_ONE_TILE_CASES(KERNEL, ...)                                                                          \
-    if ((rows != 32 && rows != 64) || (causal && offsets_kv)) return hipErrorInvalidValue;                       \
+    if ((rows != 32 && rows != 64 && rows != 128) || (causal && offsets_kv)) return hipErrorInvalidValue;                       \
     const int64_t items = one_tile_items(B, H), most = (int64_t)1 << 22;                                         \
     for (int64_t first = 0; first < items; first += most) {                                                      \
         const int64_t grid = items - first < most ? items - first : most;                                        \
@@ -391,18 +382,18 @@ __global__ __launch_bounds__(128 * W, 2) void bwd_one_tile_kernel(const __bf16 *
     return hipGetLastError();
 
 hipError_t launch_fwd_one_tile(const void *q, const void *k, const void *v, const int64_t *offsets, const int64_t *offsets_kv, bool causal,
-                               int64_t B, int H, int D, int rows, void *out, float *lse, hipStream_t stream) {
+                               int64_t B, int H, int D, int least, int rows, void *out, float *lse, hipStream_t stream) {
     constexpr int threads = 64;
-    JFA_ONE_TILE_CASES(fwd_one_tile_kernel, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, offsets, offsets_kv, (int)B, H, first,
+    JFA_ONE_TILE_CASES(fwd_one_tile_kernel, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, offsets, offsets_kv, (int)B, H, first, least,
                        (__bf16 *)out, lse)
 }
 
 hipError_t launch_bwd_one_tile(const void *q, const void *k, const void *v, const void *out, const void *dout, const float *lse, float *stats,
-                               const int64_t *offsets, const int64_t *offsets_kv, bool causal, int64_t B, int H, int D, int rows, void *dq,
+                               const int64_t *offsets, const int64_t *offsets_kv, bool causal, int64_t B, int H, int D, int least, int rows, void *dq,
                                void *dk, void *dv, hipStream_t stream) {
     constexpr int threads = 128;
     JFA_ONE_TILE_CASES(bwd_one_tile_kernel, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)out, (const __bf16 *)dout,
-                       lse, stats, offsets, offsets_kv, (int)B, H, first, (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv)
+                       lse, stats, offsets, offsets_kv, (int)B, H, first, least, (__bf16 *)dq, (__bf16 *)dk, (__bf16 *)dv)
 }
 #undef JFA_ONE_TILE
 #undef JFA_ONE_TILE_CASE

@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(ScheduleJob job
     const ScheduleJob &job = blockIdx.x == 0 ? job0 : job1;
     const int64_t *__restrict__ const offsets = job.offsets;
     const int64_t *__restrict__ const offsets_other = job.offsets_other;
-    const int block_rows = job.block_rows;
+    const int block_rows = job.block_rows, skip_rows = job.skip_rows;
     int32_t *__restrict__ const order = job.order;
     int32_t *__restrict__ const tile_start = job.tile_start;
     __shared__ int hist[kSchedBins];    // samples per bin, then the bin's first position in `order`
@@ -56,22 +56,22 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(ScheduleJob job
 
     // a sample's sort key, the row-block count of the stream (of the sample itself in self attention), and its row blocks
     // (a sample's length fits 31 bits everywhere: a 32-bit division, a quarter of a 64-bit one's instructions)
-    auto blocks_of = [&](const int64_t *o, int b) {
-        const int len = (int)(o[b + 1] - o[b]);
-        return len > 0 ? (int)(((uint32_t)len + (uint32_t)block_rows - 1) / (uint32_t)block_rows) : 0;
+    auto length = [&](const int64_t *o, int b) { return (int)(o[b + 1] - o[b]); };
+    auto blocks_of = [&](int len) { return len > 0 ? (int)(((uint32_t)len + (uint32_t)block_rows - 1) / (uint32_t)block_rows) : 0; };
+    auto look = [&](int b, int &bin, int &n) {
+        const int len = length(offsets, b), other = offsets_other ? length(offsets_other, b) : len;
+        const bool skip = len <= skip_rows && other <= skip_rows;
+        const int key = skip ? 0 : blocks_of(other);
+        n = skip ? 0 : blocks_of(len);
+        bin = key < kSchedBins - 1 ? key : kSchedBins - 1;
     };
-    auto bin_of = [&](int key) { return key < kSchedBins - 1 ? key : kSchedBins - 1; };
     int bins[kSchedPerThread], blocks[kSchedPerThread];
     if (kKept) {
 #pragma unroll
         for (int u = 0; u < kSchedPerThread; ++u) {
             const int b = tid + u * kSchedThreads;
             bins[u] = blocks[u] = 0;
-            if (b < B) {
-                const int n = blocks_of(offsets, b);
-                blocks[u] = n;
-                bins[u] = bin_of(offsets_other ? blocks_of(offsets_other, b) : n);
-            }
+            if (b < B) look(b, bins[u], blocks[u]);
         }
     }
     for (int i = tid; i < n_counters; i += kSchedThreads) counters[i] = 0;
@@ -86,8 +86,9 @@ __global__ __launch_bounds__(kSchedThreads) void schedule_kernel(ScheduleJob job
                 if (tid + u * kSchedThreads < B) f(tid + u * kSchedThreads, bins[u], blocks[u]);
         } else {
             for (int b = tid; b < B; b += kSchedThreads) {
-                const int n = blocks_of(offsets, b);
-                f(b, bin_of(offsets_other ? blocks_of(offsets_other, b) : n), n);
+                int bin, n;
+                look(b, bin, n);
+                f(b, bin, n);
             }
         }
     };

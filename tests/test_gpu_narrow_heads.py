@@ -215,21 +215,19 @@ def everything(form, D, lq, lk, max_q, max_k, seed):
 
 
 @pytest.mark.parametrize("copies", [1, 400])   # schedule built in the kernel; scheduler kernel, and a fixed deal of several rounds
-@pytest.mark.parametrize("form", ["self", "causal", "cross", "few queries", "few keys", "keys in shorter blocks", "causal, keys in shorter blocks"])
+@pytest.mark.parametrize("form", ["few queries", "few keys", "keys in shorter blocks", "causal, keys in shorter blocks"])
 @pytest.mark.parametrize("D", [32, 64])
 def test_two_wave_workgroups(D, form, copies):
     """64-row tiles do the same arithmetic in the same order as 128-row ones, which a large bound on the lengths selects and which
-    the tests above hold to the oracle.  They take samples of at most 128 rows on both sides, at most 64 rows against at most 256
-    in large batches, and the keys of a small backward at D = 64 with samples of up to 256 rows."""
+    the tests above hold to the oracle.  They take at most 64 rows against at most 256 in large batches, and the keys of a small
+    backward at D = 64 with samples of up to 256 rows."""
     lq = lk = SHORT * copies
-    if form == "cross":
-        lk = lq[4:] + lq[:4]
-    elif form.startswith("few"):
+    if form.startswith("few"):
         lq, lk = [min(x, 64) for x in lq], ([200, 256, 129] + lk)[:len(lk)]
         lq, lk = (lq, lk) if form == "few queries" else (lk, lq)
     elif form.endswith("shorter blocks"):
         lq = lk = [256, 1, 130, 64, 0, 193, 65, 200] * copies
-    mode = "causal" if form.startswith("causal") else "self" if form in ("self", "keys in shorter blocks") else "cross"
+    mode = "causal" if form.startswith("causal") else "self" if form == "keys in shorter blocks" else "cross"
     got = everything(mode, D, lq, lk, max(lq), max(lk), 65 + D)
     ref = everything(mode, D, lq, lk, 4096, 4096, 65 + D)
     for name, g, r in zip(("out", "lse", "dq", "dk", "dv", "delta"), got, ref):
