@@ -5,7 +5,8 @@
 // 32 x 32 x 16 block against 8 x 64 on the fp32 matrix instructions, and a sum of sixteen features or rows is rounded once
 // instead of eight times.  Errors against 64 bits, normwise, D = 64, inputs of standard deviation 1 (the fp32 instructions' first):
 // out 2.7e-7, 1.4e-7; dq 4.2e-7, 3.4e-7; dk 4.2e-7, 3.4e-7; dv 4.0e-7, 3.3e-7; scores of standard deviation 16, dq 2.0e-6, 1.7e-6.
-// (A factor below 2^-110 has less than three pieces: bf16's numbers end at 2^-133.  Its error stays below that step.)
+// The last piece of a small float would lie below bf16's smallest normal number: factors are scaled by 2^24 before they are split,
+// which is exact, and products by 2^-48 where they are used anyway.
 //
 // Bound: the matrix and vector pipes together.  Splitting a streamed row takes about as many instructions as its products, so it
 // is split once per workgroup, on its way from registers to LDS, and read by four waves (or two pairs); of the products the
@@ -21,11 +22,19 @@
 namespace jfa {
 
 // ---- splitting ----
-// x[0 .. 7] -> three bf16 operands with x = p[0] + p[1] + p[2]
+// The last of a float's 24 bits is at least 2^-149: scaled by 2^24 every piece is zero or at least 2^-125, a normal number.  (Not
+// scaled, factors below 2^-110 had fewer than 24 bits: relative error 1.4e-4 at 2^-122.)  The largest factors, from 2^104 on, have
+// no split then, see below.
+constexpr float kSplitScale = 0x1p24f, kProductScale = 0x1p-48f;
+// x[0 .. 7] -> three bf16 operands with kSplitScale x = p[0] + p[1] + p[2]
 __device__ inline void split8(const float (&x)[8], bf16x8 (&p)[3]) {
     float r[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) { p[0][e] = (__bf16)x[e]; r[e] = x[e] - (float)p[0][e]; }
+    for (int e = 0; e < 8; ++e) {
+        const float y = x[e] * kSplitScale;
+        p[0][e] = (__bf16)y;
+        r[e] = y - (float)p[0][e];
+    }
 #pragma unroll
     for (int e = 0; e < 8; ++e) { p[1][e] = (__bf16)r[e]; p[2][e] = (__bf16)(r[e] - (float)p[1][e]); }
 }
@@ -86,7 +95,7 @@ template <int D> __device__ inline void load_split(bf16x8 (&y)[3][D / 16], const
     }
 }
 
-// (32 streamed rows at `tile`) (stationary rows)^T: the small products first, so that only the last D / 16 steps round at
+// (32 streamed rows at `tile`) (stationary rows)^T / kProductScale: the small products first, so that only the last D / 16 steps round at
 // the sum's own size
 template <int D> __device__ inline f32x16 product(const char *tile, const NarrowAddresses<D> &at, const bf16x8 (&y)[3][D / 16]) {
     f32x16 acc;
@@ -108,7 +117,7 @@ template <int D> __device__ inline f32x16 product(const char *tile, const Narrow
     return acc;
 }
 
-// acc^T += (32 streamed rows at `tile`)^T p, p in accumulator layout.  The block's own sum is formed first, small products before
+// acc^T += (32 streamed rows at `tile`)^T p / kProductScale, p in accumulator layout.  The block's own sum is formed first, small products before
 // large ones, and added to acc at once: one rounding at the size of acc for 32 rows.
 template <int D> __device__ inline void accumulate(f32x16 (&acc)[D / 32], const char *tile, const NarrowAddresses<D> &at, const f32x16 &p) {
     bf16x8 y[2][3];
@@ -154,9 +163,15 @@ __device__ inline void lds_barrier() {
 }
 
 // ---- values that have no split ----
-// An infinity is not a sum of three bf16 numbers: the rest is NaN, and NaN is what the products above make of it.  Results that
-// come out not finite are therefore taken again in plain fp32, one lane per row; the others stay as they are (a product of
-// rows touches no other column).
+// An infinity is not a sum of three bf16 numbers: the rest is NaN, and NaN is what the products above make of it, and of factors
+// that scaled round to infinity; scaled products of large factors may overflow.  Results that come out not finite are therefore taken
+// again in plain fp32, one lane per row; the others stay as they are (a product of rows touches no other column).
+template <int D> __device__ inline void unscale(f32x16 (&acc)[D / 32]) {
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[db][e] *= kProductScale;
+}
 template <int D> __device__ inline bool all_finite(const f32x16 (&acc)[D / 32]) {
     float s = 0.0f;
 #pragma unroll
@@ -252,7 +267,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void fwd_split_kernel(
                 float mx = st[0];
 #pragma unroll
                 for (int e = 1; e < 16; ++e) mx = fmaxf(mx, st[e]);
-                const float m_new = fmaxf(m, pair_max(mx) * scale);   // finite: every query of a block that is not skipped sees one of its keys
+                const float m_new = fmaxf(m, pair_max(mx) * (scale * kProductScale));   // finite: every query of a block that is not skipped sees one of its keys
                 if (__builtin_amdgcn_ballot_w64(m_new > m) != 0) {
                     const float a = exp_f32(m - m_new);   // exp(-inf) = 0 on the first block
                     m = m_new;
@@ -263,7 +278,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void fwd_split_kernel(
                         for (int e = 0; e < 16; ++e) o[db][e] *= a;
                 }
 #pragma unroll
-                for (int e = 0; e < 16; ++e) st[e] = exp_f32(fmaf(st[e], scale, -m));
+                for (int e = 0; e < 16; ++e) st[e] = exp_f32(fmaf(st[e], scale * kProductScale, -m));
                 l += ((st[0] + st[1]) + (st[2] + st[3])) + ((st[4] + st[5]) + (st[6] + st[7])) +
                      (((st[8] + st[9]) + (st[10] + st[11])) + ((st[12] + st[13]) + (st[14] + st[15])));
                 accumulate<D>(o, vt, at, st);
@@ -272,7 +287,10 @@ __global__ __launch_bounds__(kSpThreads, 2) void fwd_split_kernel(
             lds_barrier();
         }
         l = pair_sum(l);
+        float back = kProductScale;
         if (active && __builtin_amdgcn_ballot_w64(!all_finite<D>(o) || !(l < INFINITY)) != 0) {
+            unscale<D>(o);
+            back = 1.0f;
             const int lim = causal && iq + 1 < L ? iq + 1 : L;
             float m2 = -INFINITY, l2 = 0.0f;
             for (int j = 0; j < lim; ++j) m2 = fmaxf(m2, plain_dot<D>(qrow, kbase + j * row_stride) * scale);
@@ -298,7 +316,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void fwd_split_kernel(
             }
         }
         if (i < t.len) {   // a sample without keys: out = 0, lse = -inf
-            store_row<D>(out + (t.row0 + i) * row_stride + (int64_t)t.head * D, o, l > 0.0f ? 1.0f / l : 0.0f, half);
+            store_row<D>(out + (t.row0 + i) * row_stride + (int64_t)t.head * D, o, l > 0.0f ? back / l : 0.0f, half);
             if (half == 0) lse[(int64_t)t.head * sum_B + t.row0 + i] = m + logf(l);
         }
     }
@@ -370,9 +388,9 @@ __global__ __launch_bounds__(kSpThreads, 2) void dq_split_kernel(
                 const int lim = (causal && iq + 1 < L ? iq + 1 : L) - j0;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    float p = exp_f32(fmaf(st[e], scale, -lse_i));
+                    float p = exp_f32(fmaf(st[e], scale * kProductScale, -lse_i));
                     if (masked && acc_row(e, half) >= lim) p = 0.0f;
-                    st[e] = p * (dp[e] - delta_i);
+                    st[e] = p * fmaf(dp[e], kProductScale, -delta_i);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 accumulate<D>(acc, kt, at, st);
@@ -383,7 +401,10 @@ __global__ __launch_bounds__(kSpThreads, 2) void dq_split_kernel(
         const int lane_e = not_hoisted(lane);
         const int i_e = q0 + (lane_e & 31), half_e = lane_e >> 5, iq_e = i_e < t.len ? i_e : t.len - 1;
         const int64_t row_e = (t.row0 + iq_e) * row_stride + (int64_t)t.head * D;
+        float back = scale * kProductScale;
         if (active && __builtin_amdgcn_ballot_w64(!all_finite<D>(acc)) != 0) {
+            unscale<D>(acc);
+            back = scale;
             const int lim = causal && iq_e + 1 < L ? iq_e + 1 : L;
             const float lse_e = lse[(int64_t)t.head * sum_B + t.row0 + iq_e], delta_e = plain_dot<D>(dout + row_e, out_fwd + row_e);
             f32x16 again[D / 32];
@@ -394,7 +415,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void dq_split_kernel(
             }
             take_where_not_finite<D>(acc, again);
         }
-        if (i_e < t.len) store_row<D>(dq + row_e, acc, scale, half_e);
+        if (i_e < t.len) store_row<D>(dq + row_e, acc, back, half_e);
     }
 }
 
@@ -476,7 +497,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void dkv_split_kernel(
                 for (int g = 0; g < 4; ++g) {
                     const f32x4 stat = *reinterpret_cast<const f32x4 *>(&stat_s[buf][is_a ? 0 : 1][g * 8 + half * 4]);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) x[4 * g + e] = is_a ? exp_f32(fmaf(x[4 * g + e], scale, -stat[e])) : x[4 * g + e] - stat[e];
+                    for (int e = 0; e < 4; ++e) x[4 * g + e] = is_a ? exp_f32(fmaf(x[4 * g + e], scale * kProductScale, -stat[e])) : fmaf(x[4 * g + e], kProductScale, -stat[e]);
                 }
                 if (is_a) {
                     if (i0 + 32 > L || (causal && i0 < k0 + 31)) {
@@ -506,7 +527,10 @@ __global__ __launch_bounds__(kSpThreads, 2) void dkv_split_kernel(
             if (more) store(buf ^ 1);
             lds_barrier();
         }
+        float back = is_a ? kProductScale : scale * kProductScale;
         if (active && __builtin_amdgcn_ballot_w64(!all_finite<D>(acc)) != 0) {
+            unscale<D>(acc);
+            back = is_a ? 1.0f : scale;
             f32x16 again[D / 32];
             clear<D>(again);
             for (int i = causal ? jk : 0; i < L; ++i) {
@@ -516,7 +540,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void dkv_split_kernel(
             }
             take_where_not_finite<D>(acc, again);
         }
-        if (j < t.len) store_row<D>((is_a ? dv : dk) + row, acc, is_a ? 1.0f : scale, half);
+        if (j < t.len) store_row<D>((is_a ? dv : dk) + row, acc, back, half);
     }
 }
 

@@ -78,6 +78,24 @@ def test_error_is_that_of_fp32(D, causal, sigma):
 
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("D", [32, 64])
+@pytest.mark.parametrize("small", ["q", "k", "v", "dout"])
+def test_small_factors_keep_their_bits(D, causal, small):
+    """One factor of the products around 2^-118 (with v or dout, dS below that), where a float still has 24 bits but the last of three
+    bf16 pieces would lie below bf16's smallest number: the error stays that of fp32.  (The bound's host arithmetic rounds small
+    differences and products, some of them below 2^-126, to fp32 as well.)"""
+    def change(q, k, v, do):
+        x = dict(q=q, k=k, v=v, dout=do)[small]
+        x *= np.float32(2.0 ** -118)
+    got, exact, plain = run([200, 64, 33, 150, 1] * 2, 1, D, 1.0, causal, D, change)
+    norm = np.linalg.norm
+    for name, g, e, p in zip(("out", "dq", "dk", "dv"), got, exact, plain):
+        error, bound = norm(g - e) / norm(e), 1.25 * norm(p - e) / norm(e) + 3e-7
+        print(f"D {D} {small} {name}: {error:.2e}, bound {bound:.2e}", flush=True)
+        assert error <= bound, f"{name}: {error:.2e} > {bound:.2e}"
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("D", [32, 64])
 @pytest.mark.parametrize("what", ["inf in v", "-inf in dout", "-inf score", "near the largest float", "nan in k"])
 def test_values_without_a_split(D, causal, what):
     """Where the sums have a value, infinite or not, it is the result; what is NaN there is NaN here.  Relative error per element."""
