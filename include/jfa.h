@@ -89,8 +89,8 @@ int jfa_forward_noalloc(const void *q, const void *k, const void *v, const int64
 /*
  * Forward, fp32 end to end: the same operation for small-tolerance use.  Products and sums run on the fp32 matrix
  * instructions or, in large enough calls at D = 32 and 64, on the bf16 ones with every float split into three bf16 numbers (exactly,
- * whatever its size; errors against exact arithmetic are no larger; rows whose results are not finite, and rows of values from 2^104 on,
- * are computed again without the split, which is slow); scores and log-sum-exp are fp32.
+ * whatever its size; errors against exact arithmetic are no larger; rows whose results are not finite for another reason than
+ * a NaN among the inputs, and rows of values from 2^104 on, are computed again without the split, which is slow); scores and log-sum-exp are fp32.
  */
 int jfa_forward_f32(const float *q, const float *k, const float *v, const int64_t *offsets, int64_t B,
                     int64_t max_len, int H, int D, float *out, float *lse, void *stream);

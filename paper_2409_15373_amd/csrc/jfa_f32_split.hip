@@ -13,9 +13,9 @@
 // smallest are summed first, and the sum over 32 streamed rows is formed apart and added to the accumulator at once (added one by
 // one, the gradients' errors are 5 to 14 % above those of the fp32 instructions).  Two workgroups of four waves per compute unit:
 // 206 to 252 registers.  Tried: workgroups of two waves (the splitting is then shared by half as many), dK / dV with both operands'
-// planes in one wave (spills): both slower.  Measured at B = 256, H = 2, lengths to 512, microseconds, against the fp32
-// instructions: D = 64 forward 159 -> 104, backward 497 -> 308; D = 32 95 -> 71, 280 -> 206; 32 samples of 4096 rows, D = 64, forward
-// 870 -> 524, backward 2850 -> 1706.
+// planes in one wave (spills): both slower.  Microseconds at B = 256, H = 2, lengths to 512, against the fp32 instructions: D = 64
+// forward 168 -> 108, backward 530 -> 327; D = 32 96 -> 70, 299 -> 212; 32 samples of 4096 rows, one head, D = 64, forward 1255 -> 782,
+// backward 4115 -> 2659.  All NaN: 111 and 334; with one infinity per sample, in v, 2170 and 5260 (see "values that have no split").
 #include "jfa_f32.h"
 #include "jfa_narrow.h"
 
@@ -165,7 +165,8 @@ __device__ inline void lds_barrier() {
 // ---- values that have no split ----
 // An infinity is not a sum of three bf16 numbers: the rest is NaN, and NaN is what the products above make of it, and of factors
 // that scaled round to infinity; scaled products of large factors may overflow.  Results that come out not finite are therefore taken
-// again in plain fp32, one lane per row; the others stay as they are (a product of rows touches no other column).
+// again in plain fp32, one lane per row; the others stay as they are (a product of rows touches no other column).  Lane by lane that
+// costs some twenty times the wave's products; on the matrix instructions masked entries would be 0 times an infinity.
 template <int D> __device__ inline void unscale(f32x16 (&acc)[D / 32]) {
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
@@ -186,27 +187,103 @@ template <int D> __device__ inline void take_where_not_finite(f32x16 (&acc)[D / 
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[db][e] = fabsf(acc[db][e]) < INFINITY ? acc[db][e] : again[db][e];
 }
-template <int D> __device__ inline float plain_dot(const float *__restrict__ a, const float *__restrict__ b) {
-    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 1
-    for (int d = 0; d < D; d += 4) {
-        const float4 x = *reinterpret_cast<const float4 *>(a + d), y = *reinterpret_cast<const float4 *>(b + d);
-        s[0] = fmaf(x.x, y.x, s[0]); s[1] = fmaf(x.y, y.y, s[1]); s[2] = fmaf(x.z, y.z, s[2]); s[3] = fmaf(x.w, y.w, s[3]);
+// What a lane of this half holds of a row, in plain fp32: the features of a transposed accumulator's registers
+template <int D> struct PlainRow {
+    float x[D / 2];
+    __device__ inline void load(const float *__restrict__ row, int half) {
+#pragma unroll
+        for (int g = 0; g < D / 8; ++g) {
+            const float4 f = *reinterpret_cast<const float4 *>(row + g * 8 + half * 4);
+            x[4 * g] = f.x; x[4 * g + 1] = f.y; x[4 * g + 2] = f.z; x[4 * g + 3] = f.w;
+        }
     }
-    return (s[0] + s[1]) + (s[2] + s[3]);
+    __device__ inline bool has_nan() const {   // in either half
+        bool nan = false;
+#pragma unroll
+        for (int d = 0; d < D / 2; ++d) nan = nan || x[d] != x[d];
+        const bool other = __shfl_xor((int)nan, 32, 64);
+        return nan || other;
+    }
+};
+template <int D> __device__ inline float plain_dot(const PlainRow<D> &a, const float *__restrict__ row, int half) {
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g) {
+        const float4 f = *reinterpret_cast<const float4 *>(row + g * 8 + half * 4);
+        s[0] = fmaf(a.x[4 * g], f.x, s[0]); s[1] = fmaf(a.x[4 * g + 1], f.y, s[1]);
+        s[2] = fmaf(a.x[4 * g + 2], f.z, s[2]); s[3] = fmaf(a.x[4 * g + 3], f.w, s[3]);
+    }
+    return pair_sum((s[0] + s[1]) + (s[2] + s[3]));
 }
-// acc += x row, the features that a lane of this half holds of a transposed accumulator
+// acc += x row
 template <int D> __device__ inline void plain_add(f32x16 (&acc)[D / 32], float x, const float *__restrict__ row, int half) {
+#pragma unroll
+    for (int g = 0; g < D / 8; ++g) {
+        const float4 f = *reinterpret_cast<const float4 *>(row + g * 8 + half * 4);
+        f32x16 &y = acc[g >> 2];
+        const int e = 4 * (g & 3);
+        y[e] = fmaf(x, f.x, y[e]); y[e + 1] = fmaf(x, f.y, y[e + 1]); y[e + 2] = fmaf(x, f.z, y[e + 2]); y[e + 3] = fmaf(x, f.w, y[e + 3]);
+    }
+}
+// A NaN has no split either, but taken again it is the same NaN, and so the rows are looked through for NaN first, 32 at a time (all
+// of a batch NaN, forward and backward, 31 ms -> 0.44, one NaN per sample 31 -> 0.6; the ordinary call 0.44).
+// nan_row: the first (kLast: the last) of rows from .. n - 1 that holds one, n (kLast: -1) if none does; the same in every lane.
+template <bool kLast> __device__ inline int nearer(int a, int b) { return kLast == (a > b) ? a : b; }
+template <int D, bool kLast> struct NanScan {
+    static constexpr int kLanes = D / 4, kRows = 64 / kLanes;   // lanes to a row, rows to a load
+    const float *base;
+    int64_t row_stride;
+    int from, n, lane;
+    // calls look(row, four columns' values) for 32 rows, done() after them, until it says so
+    template <typename F, typename G> __device__ inline void run(F look, G done) const {
+        const int blocks = (n - from + 31) / 32;
+        for (int i = 0; i < blocks; ++i) {
+            const int r0 = from + 32 * (kLast ? blocks - 1 - i : i) + lane / kLanes;
+#pragma unroll
+            for (int u = 0; u < 32 / kRows; ++u) {
+                const int r = r0 + u * kRows < n ? r0 + u * kRows : n - 1;
+                look(r, *reinterpret_cast<const float4 *>(base + r * row_stride + lane % kLanes * 4));
+            }
+            if (done()) break;
+        }
+    }
+};
+template <int D, bool kLast> __device__ inline int nan_row(const float *__restrict__ base, int64_t row_stride, int from, int n, int lane) {
+    const int none = kLast ? -1 : n;
+    int found = none;
+    NanScan<D, kLast>{base, row_stride, from, n, lane}.run(
+        [&](int r, float4 f) { if (f.x != f.x || f.y != f.y || f.z != f.z || f.w != f.w) found = nearer<kLast>(found, r); },
+        [&]() { return __builtin_amdgcn_ballot_w64(found != none) != 0; });
+    for (int d = 1; d < 64; d <<= 1) found = nearer<kLast>(found, __shfl_xor(found, d, 64));
+    return found;
+}
+// The same for each column, and whether results of this lane that are not finite (columns on the accumulator's rows) may be anything
+// but the NaN of a row that counts: those before `limit` (kLast: from `limit` on).
+template <int D, bool kLast> __device__ inline bool values_besides_nan(const f32x16 (&acc)[D / 32], const float *__restrict__ base, int64_t row_stride,
+                                                                       int from, int n, int limit, int lane) {
+    using Scan = NanScan<D, kLast>;
+    const int none = kLast ? -1 : n, half = lane >> 5;
+    int found[4] = {none, none, none, none};   // of columns 4 (lane % kLanes) ..
+    Scan{base, row_stride, from, n, lane}.run(
+        [&](int r, float4 f) {
+            if (f.x != f.x) found[0] = nearer<kLast>(found[0], r);
+            if (f.y != f.y) found[1] = nearer<kLast>(found[1], r);
+            if (f.z != f.z) found[2] = nearer<kLast>(found[2], r);
+            if (f.w != f.w) found[3] = nearer<kLast>(found[3], r);
+        },
+        [&]() { return __builtin_amdgcn_ballot_w64(found[0] == none || found[1] == none || found[2] == none || found[3] == none) == 0; });
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        for (int d = Scan::kLanes; d < 64; d <<= 1) found[c] = nearer<kLast>(found[c], __shfl_xor(found[c], d, 64));
+    bool any = false;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const float4 f = *reinterpret_cast<const float4 *>(row + db * 32 + g * 8 + half * 4);
-            acc[db][4 * g] = fmaf(x, f.x, acc[db][4 * g]);
-            acc[db][4 * g + 1] = fmaf(x, f.y, acc[db][4 * g + 1]);
-            acc[db][4 * g + 2] = fmaf(x, f.z, acc[db][4 * g + 2]);
-            acc[db][4 * g + 3] = fmaf(x, f.w, acc[db][4 * g + 3]);
+        for (int e = 0; e < 16; ++e) {
+            const int row = __shfl(found[e & 3], (db * 32 + acc_row(e, half)) >> 2, 64);
+            any = any || (!(fabsf(acc[db][e]) < INFINITY) && (kLast ? row < limit : row >= limit));
         }
+    return any;
 }
 
 template <int D>
@@ -291,28 +368,44 @@ __global__ __launch_bounds__(kSpThreads, 2) void fwd_split_kernel(
         if (active && __builtin_amdgcn_ballot_w64(!all_finite<D>(o) || !(l < INFINITY)) != 0) {
             unscale<D>(o);
             back = 1.0f;
-            const int lim = causal && iq + 1 < L ? iq + 1 : L;
-            float m2 = -INFINITY, l2 = 0.0f;
-            for (int j = 0; j < lim; ++j) m2 = fmaxf(m2, plain_dot<D>(qrow, kbase + j * row_stride) * scale);
-            f32x16 o2[D / 32];
-            clear<D>(o2);
-            for (int j = 0; j < lim; ++j) {
-                const float p = exp_f32(fmaf(plain_dot<D>(qrow, kbase + j * row_stride), scale, -m2));
-                l2 += p;
-                plain_add<D>(o2, p, vbase + j * row_stride, half);
+            const int lim = causal && iq + 1 < L ? iq + 1 : L, seen = causal && q0 + 32 < L ? q0 + 32 : L;   // keys of this lane, of the wave
+            PlainRow<D> q_row;
+            q_row.load(qrow, half);
+            const bool q_nan = q_row.has_nan();
+            const int k_nan = nan_row<D, false>(kbase, row_stride, 0, seen, lane);
+            const bool nan = q_nan || k_nan < lim, scores = !(l < INFINITY) || !(fabsf(m) < INFINITY);   // scores: all of the row is taken again
+            bool again = !nan && scores;
+            if (__builtin_amdgcn_ballot_w64(!nan && !scores && !all_finite<D>(o)) != 0) {
+                const bool values = values_besides_nan<D, false>(o, vbase, row_stride, 0, seen, lim, lane);
+                again = again || (!nan && values);
             }
-            if (!(l < INFINITY) || !(fabsf(m) < INFINITY)) {   // the scores themselves: all of the row is taken again
-                m = m2;
-                l = l2;
+            if (__builtin_amdgcn_ballot_w64(again) != 0) {
+                float m2 = m, l2 = 0.0f;
+                if (__builtin_amdgcn_ballot_w64(scores) != 0) {
+                    float top = -INFINITY;
+                    for (int j = 0; j < seen; ++j) {
+                        const float s_j = plain_dot<D>(q_row, kbase + j * row_stride, half) * scale;
+                        if (j < lim) top = fmaxf(top, s_j);
+                    }
+                    if (scores) m2 = top;
+                }
+                f32x16 o2[D / 32];
+                clear<D>(o2);
+                for (int j = 0; j < seen; ++j) {
+                    const float p = exp_f32(fmaf(plain_dot<D>(q_row, kbase + j * row_stride, half), scale, -m2));
+                    if (j < lim) {
+                        l2 += p;
+                        plain_add<D>(o2, p, vbase + j * row_stride, half);
+                    }
+                }
+                if (scores) {
+                    m = m2;
+                    l = l2;
 #pragma unroll
-                for (int db = 0; db < D / 32; ++db) o[db] = o2[db];
-            } else {
-                const float same = exp_f32(m2 - m);
-#pragma unroll
-                for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) o2[db][e] *= same;
-                take_where_not_finite<D>(o, o2);
+                    for (int db = 0; db < D / 32; ++db) o[db] = o2[db];
+                } else {
+                    take_where_not_finite<D>(o, o2);
+                }
             }
         }
         if (i < t.len) {   // a sample without keys: out = 0, lse = -inf
@@ -405,15 +498,29 @@ __global__ __launch_bounds__(kSpThreads, 2) void dq_split_kernel(
         if (active && __builtin_amdgcn_ballot_w64(!all_finite<D>(acc)) != 0) {
             unscale<D>(acc);
             back = scale;
-            const int lim = causal && iq_e + 1 < L ? iq_e + 1 : L;
-            const float lse_e = lse[(int64_t)t.head * sum_B + t.row0 + iq_e], delta_e = plain_dot<D>(dout + row_e, out_fwd + row_e);
-            f32x16 again[D / 32];
-            clear<D>(again);
-            for (int j = 0; j < lim; ++j) {
-                const float p = exp_f32(fmaf(plain_dot<D>(q + row_e, kbase + j * row_stride), scale, -lse_e));
-                plain_add<D>(again, p * (plain_dot<D>(dout + row_e, vbase + j * row_stride) - delta_e), kbase + j * row_stride, half_e);
+            const int lim = causal && iq_e + 1 < L ? iq_e + 1 : L, seen = causal && q0 + 32 < L ? q0 + 32 : L;   // keys of this lane, of the wave
+            const float lse_e = lse[(int64_t)t.head * sum_B + t.row0 + iq_e];
+            PlainRow<D> q_row, g_row;
+            q_row.load(q + row_e, half_e);
+            g_row.load(dout + row_e, half_e);
+            const float delta_e = plain_dot<D>(g_row, out_fwd + row_e, half_e);
+            const bool q_nan = q_row.has_nan(), g_nan = g_row.has_nan(), own = q_nan || g_nan || lse_e != lse_e || delta_e != delta_e;
+            bool open = !own && !all_finite<D>(acc);
+            if (__builtin_amdgcn_ballot_w64(open) != 0) {
+                const int k_nan = nan_row<D, false>(kbase, row_stride, 0, seen, lane_e), v_nan = nan_row<D, false>(vbase, row_stride, 0, seen, lane_e);
+                open = open && k_nan >= lim && v_nan >= lim;
             }
-            take_where_not_finite<D>(acc, again);
+            if (__builtin_amdgcn_ballot_w64(open) != 0) {
+                f32x16 again[D / 32];
+                clear<D>(again);
+                for (int j = 0; j < seen; ++j) {
+                    const float *const key = kbase + j * row_stride;
+                    const float p = exp_f32(fmaf(plain_dot<D>(q_row, key, half_e), scale, -lse_e));
+                    const float ds = p * (plain_dot<D>(g_row, vbase + j * row_stride, half_e) - delta_e);
+                    if (j < lim) plain_add<D>(again, ds, key, half_e);
+                }
+                take_where_not_finite<D>(acc, again);
+            }
         }
         if (i_e < t.len) store_row<D>(dq + row_e, acc, back, half_e);
     }
@@ -531,14 +638,38 @@ __global__ __launch_bounds__(kSpThreads, 2) void dkv_split_kernel(
         if (active && __builtin_amdgcn_ballot_w64(!all_finite<D>(acc)) != 0) {
             unscale<D>(acc);
             back = is_a ? 1.0f : scale;
-            f32x16 again[D / 32];
-            clear<D>(again);
-            for (int i = causal ? jk : 0; i < L; ++i) {
-                const float *qi = qbase + i * row_stride, *oi = obase + i * row_stride;
-                const float p = exp_f32(fmaf(plain_dot<D>(qi, k + row), scale, -lse_rows[i]));
-                plain_add<D>(again, is_a ? p : p * (plain_dot<D>(oi, v + row) - delta_rows[i]), is_a ? oi : qi, half);
+            const int from = causal ? k0 : 0, mine_from = causal ? jk : 0;   // the first query of the wave, of this lane's key
+            PlainRow<D> k_row, v_row;
+            k_row.load(k + row, half);
+            v_row.load(v + row, half);
+            const bool own_k = k_row.has_nan(), own_v = v_row.has_nan();
+            bool open = !all_finite<D>(acc) && !own_k && (is_a || !own_v);
+            if (__builtin_amdgcn_ballot_w64(open) != 0) {
+                int stat_nan = -1;   // last query whose statistics are NaN (dV does not look at delta)
+                for (int i = from + lane; i < L; i += 64) {
+                    const float x = lse_rows[i], y = is_a ? 0.0f : delta_rows[i];
+                    if (x != x || y != y) stat_nan = i;
+                }
+                for (int d = 1; d < 64; d <<= 1) stat_nan = nearer<true>(stat_nan, __shfl_xor(stat_nan, d, 64));
+                const int q_nan = nan_row<D, true>(qbase, row_stride, from, L, lane);
+                open = open && stat_nan < mine_from && q_nan < mine_from;
             }
-            take_where_not_finite<D>(acc, again);
+            if (__builtin_amdgcn_ballot_w64(open) != 0) {   // dK takes all of a gradient's columns, dV one
+                const bool values = is_a ? values_besides_nan<D, true>(acc, obase, row_stride, from, L, mine_from, lane)
+                                         : nan_row<D, true>(obase, row_stride, from, L, lane) < mine_from;
+                open = open && values;
+            }
+            if (__builtin_amdgcn_ballot_w64(open) != 0) {
+                f32x16 again[D / 32];
+                clear<D>(again);
+                for (int i = from; i < L; ++i) {
+                    const float *const query = qbase + i * row_stride, *const grad = obase + i * row_stride;
+                    float x = exp_f32(fmaf(plain_dot<D>(k_row, query, half), scale, -lse_rows[i]));
+                    if (!is_a) x *= plain_dot<D>(v_row, grad, half) - delta_rows[i];
+                    if (i >= mine_from) plain_add<D>(again, x, is_a ? grad : query, half);
+                }
+                take_where_not_finite<D>(acc, again);
+            }
         }
         if (j < t.len) store_row<D>((is_a ? dv : dk) + row, acc, back, half);
     }
