@@ -64,7 +64,7 @@ def _load_native():
         _native = False
         return
     lib = binding.load()
-    nodes.bind_library(lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value, binding._check)
+    nodes.bind_library(lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value, binding._check, binding._ptr)
     _native = nodes
 
 

@@ -33,6 +33,7 @@ struct Library {   // [0]: bf16, [1]: fp32
     ForwardCross forward_cross[2];
     BackwardCross backward_cross[2];
     PyObject *check = nullptr;   // binding._check: raises JfaError for a status that is not JFA_OK
+    PyObject *pointer = nullptr;   // binding._ptr: raises AssertionError for a tensor that is not contiguous or not on the GPU
 };
 Library lib;
 
@@ -40,16 +41,19 @@ struct Refused {};   // the call is the Python function's
 
 void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
-// In a backward, on the engine's thread: the error that the Python binding raises for this status.
-void check_backward(int status) {
-    if (status == 0) return;
-    pybind11::gil_scoped_acquire gil;
-    PyObject *r = PyObject_CallFunction(lib.check, "i", status);
+// In a backward, on the engine's thread: the error that a Python function raises for this argument.
+void raise_from(PyObject *function, pybind11::object argument) {
+    PyObject *r = PyObject_CallFunctionObjArgs(function, argument.ptr(), nullptr);
     Py_XDECREF(r);
     if (r) throw std::runtime_error("jfa backward failed");
     python_error e;
     e.persist();
     throw std::move(e);
+}
+void check_backward(int status) {
+    if (status == 0) return;
+    pybind11::gil_scoped_acquire gil;
+    raise_from(lib.check, pybind11::int_(status));
 }
 
 bool plain(const Tensor &t) { return t.defined() && t.is_cuda() && t.is_contiguous(); }
@@ -58,6 +62,16 @@ int kind(const Tensor &q) {
     if (q.scalar_type() == at::kBFloat16) return 0;
     if (q.scalar_type() == at::kFloat) return 1;
     throw Refused{};
+}
+// What the graph gives back for a saved tensor is any tensor that a hook has made of it (and for dout what a hook of the node has made of
+// that): it has to be what the kernels take it for.
+void check_saved(const Tensor &t, at::IntArrayRef sizes, at::ScalarType type, const Tensor &dout) {
+    if (!t.defined() || !plain(t)) {
+        pybind11::gil_scoped_acquire gil;
+        raise_from(lib.pointer, pybind11::cast(t));
+    }
+    TORCH_CHECK(t.sizes() == sizes && t.scalar_type() == type && t.device() == dout.device(), "jagged attention, backward: a tensor of ", sizes, " ",
+                type, " on ", dout.device(), " was saved, ", t.sizes(), " ", t.scalar_type(), " on ", t.device(), " came back");
 }
 float *floats(const Tensor &t) { return static_cast<float *>(t.data_ptr()); }
 const int64_t *longs(const Tensor &t) { return static_cast<const int64_t *>(t.data_ptr()); }
@@ -78,13 +92,21 @@ struct SelfAttention : torch::autograd::Function<SelfAttention> {
         ctx->save_for_backward({q, k, v, out, lse, offsets});
         ctx->saved_data["max_len"] = max_len;
         ctx->saved_data["causal"] = causal;
+        ctx->saved_data["type"] = (int64_t)q.scalar_type();
+        ctx->saved_data["q"] = q.sizes();
+        ctx->saved_data["offsets"] = offsets.numel();
         return out;
     }
     static variable_list backward(AutogradContext *ctx, variable_list grads) {
         const variable_list saved = ctx->get_saved_variables();
         const Tensor &q = saved[0], &k = saved[1], &v = saved[2], &out = saved[3], &lse = saved[4], &offsets = saved[5];
         const Tensor dout = grads[0].contiguous();
-        const int f32 = kind(q);
+        const std::vector<int64_t> sizes = ctx->saved_data["q"].toIntVector(), stats_sizes = {sizes[1], sizes[0]};
+        const at::ScalarType type = (at::ScalarType)ctx->saved_data["type"].toInt();
+        for (const Tensor *t : {&dout, &q, &k, &v, &out}) check_saved(*t, sizes, type, dout);
+        check_saved(lse, stats_sizes, at::kFloat, dout);
+        check_saved(offsets, ctx->saved_data["offsets"].toInt(), at::kLong, dout);
+        const int f32 = type == at::kFloat;
         const Tensor dq = at::empty_like(q), dk = at::empty_like(q), dv = at::empty_like(q), stats = statistics(q, f32 ? 1 : 2);
         const Backward fn = (ctx->saved_data["causal"].toBool() ? lib.backward_causal : lib.backward)[f32];
         check_backward(fn(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), dout.data_ptr(), floats(lse), longs(offsets), offsets.numel() - 1,
@@ -109,13 +131,23 @@ struct CrossAttention : torch::autograd::Function<CrossAttention> {
         ctx->save_for_backward({q, k, v, out, lse, offsets_q, offsets_kv});
         ctx->saved_data["max_len_q"] = max_len_q;
         ctx->saved_data["max_len_kv"] = max_len_kv;
+        ctx->saved_data["type"] = (int64_t)q.scalar_type();
+        ctx->saved_data["q"] = q.sizes();
+        ctx->saved_data["k"] = k.sizes();
+        ctx->saved_data["offsets"] = offsets_q.numel();
         return out;
     }
     static variable_list backward(AutogradContext *ctx, variable_list grads) {
         const variable_list saved = ctx->get_saved_variables();
         const Tensor &q = saved[0], &k = saved[1], &v = saved[2], &out = saved[3], &lse = saved[4], &offsets_q = saved[5], &offsets_kv = saved[6];
         const Tensor dout = grads[0].contiguous();
-        const int f32 = kind(q);
+        const std::vector<int64_t> sizes = ctx->saved_data["q"].toIntVector(), key_sizes = ctx->saved_data["k"].toIntVector(), stats_sizes = {sizes[1], sizes[0]};
+        const at::ScalarType type = (at::ScalarType)ctx->saved_data["type"].toInt();
+        for (const Tensor *t : {&dout, &q, &out}) check_saved(*t, sizes, type, dout);
+        for (const Tensor *t : {&k, &v}) check_saved(*t, key_sizes, type, dout);
+        check_saved(lse, stats_sizes, at::kFloat, dout);
+        for (const Tensor *t : {&offsets_q, &offsets_kv}) check_saved(*t, ctx->saved_data["offsets"].toInt(), at::kLong, dout);
+        const int f32 = type == at::kFloat;
         const Tensor dq = at::empty_like(q), dk = at::empty_like(k), dv = at::empty_like(v), stats = statistics(q, f32 ? 1 : 2);
         check_backward(lib.backward_cross[f32](q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), dout.data_ptr(), floats(lse), longs(offsets_q),
                                                longs(offsets_kv), offsets_q.numel() - 1, ctx->saved_data["max_len_q"].toInt(),
@@ -150,7 +182,7 @@ std::optional<Tensor> cross_attention(const Tensor &q, const Tensor &k, const Te
 }
 
 // entry: name of an entry point -> its address
-void bind_library(const std::function<int64_t(const std::string &)> &entry, pybind11::object check) {
+void bind_library(const std::function<int64_t(const std::string &)> &entry, pybind11::object check, pybind11::object pointer) {
     const char *suffix[2] = {"", "_f32"};
     auto at = [&](const char *name, int i) { return (uintptr_t)entry(std::string(name) + suffix[i]); };
     for (int i = 0; i < 2; ++i) {
@@ -162,6 +194,7 @@ void bind_library(const std::function<int64_t(const std::string &)> &entry, pybi
         lib.backward_cross[i] = reinterpret_cast<BackwardCross>(at("jfa_backward_cross", i));
     }
     lib.check = check.release().ptr();   // kept for the life of the process
+    lib.pointer = pointer.release().ptr();
 }
 
 }  // namespace

@@ -131,3 +131,52 @@ def test_what_the_native_nodes_refuse_is_refused_as_before():
         x.mul_(2)
     with pytest.raises(RuntimeError):   # a saved tensor has changed
         out.sum().backward()
+
+
+class _Raised(Exception):
+    pass
+
+
+def _raise(t):
+    raise _Raised("from a hook")
+
+
+def _step(mode):
+    """(wrapper call, inputs) of a small attention that goes through the native nodes."""
+    from paper_2409_15373_amd import autograd
+    off = torch.tensor([0, 8, 20], device="cuda")
+    q, k, v = (torch.randn(20, 2, 64, device="cuda", requires_grad=True) for _ in range(3))
+    if mode == "cross":
+        return (lambda: autograd.jagged_flash_cross_attention(q, k, v, off, off, 12, 12)), (q, k, v)
+    return (lambda: autograd.jagged_flash_attention(q, k, v, off, 12)), (q, k, v)
+
+
+@pytest.mark.parametrize("mode", ["self", "cross"])
+def test_hooks_on_saved_tensors(mode):
+    """What a hook gives back is checked before a kernel reads it: the Python function's error for a tensor that is not on the GPU or not
+    contiguous, an error for one of another size or type.  What a hook raises reaches the caller (a recomputation by
+    torch.utils.checkpoint is stopped that way)."""
+    from torch.utils.checkpoint import checkpoint
+    call, inputs = _step(mode)
+
+    def step_with(unpack, pack=lambda t: t):
+        with torch.autograd.graph.saved_tensors_hooks(pack, unpack):
+            out = call()
+        return torch.autograd.grad(out.square().sum(), inputs)
+    expected = torch.autograd.grad(call().square().sum(), inputs)
+    assert all(torch.equal(a, b) for a, b in zip(step_with(lambda t: t.cuda(), lambda t: t.cpu()), expected))
+    got = torch.autograd.grad(checkpoint(lambda *_: call(), *inputs, use_reentrant=False).square().sum(), inputs)
+    assert all(torch.equal(a, b) for a, b in zip(got, expected))
+    floats = lambda f: lambda t: f(t) if t.dim() == 3 else t
+    for unpack in (lambda t: t.cpu(), floats(lambda t: t.cpu()), lambda t: t.cpu() if t.dim() == 1 else t,
+                   floats(lambda t: t.transpose(0, 1).contiguous().transpose(0, 1))):
+        with pytest.raises(AssertionError):
+            step_with(unpack)
+    for unpack in (floats(lambda t: t[:8]), floats(lambda t: t.bfloat16()), floats(lambda t: t.half()), lambda t: t.int() if t.dim() == 1 else t,
+                   lambda t: t[:2] if t.dim() == 1 else t, lambda t: t[:, :4].contiguous() if t.dim() == 2 else t):
+        with pytest.raises(RuntimeError, match="was saved"):
+            step_with(unpack)
+    with pytest.raises(_Raised):
+        step_with(_raise)
+    with pytest.raises(_Raised):
+        step_with(lambda t: t, _raise)
