@@ -124,7 +124,7 @@ def test_what_the_native_nodes_refuse_is_refused_as_before():
         cross(x, x, x, off, off, -1, 8)
     with pytest.raises(RuntimeError):
         torch.func.grad(lambda t: attention(t, t, t, off, 8).float().sum())(x.detach())
-    with torch.autograd.forward_ad.dual_level(), pytest.raises((RuntimeError, NotImplementedError)):
+    with torch.autograd.forward_ad.dual_level(), pytest.raises(NotImplementedError):   # a Python function's; the C++ one's is a RuntimeError
         attention(torch.autograd.forward_ad.make_dual(x.detach(), x.detach()), x, x, off, 8)
     out = attention(x, x, x, off, 8)
     with torch.no_grad():
