@@ -13,10 +13,13 @@ q, k, v: [rows, H, D] bf16 or fp32 on the GPU, contiguous; offsets: int64 [B + 1
 and v; offsets and the length bounds are not differentiable.
 """
 import ctypes
+import importlib.util
+import warnings
 
 import torch
 
 from . import binding
+from .build import native_path
 
 __all__ = ["jagged_flash_attention", "jagged_flash_cross_attention"]
 
@@ -52,15 +55,20 @@ class _CrossAttention(torch.autograd.Function):
         return dq, dk, dv, None, None, None, None
 
 
-_native = None   # the C++ nodes; False where they have not been built
+_native = None   # the C++ nodes; False where they have not been built for this torch
 _PLAIN = (torch.Tensor, torch.nn.Parameter)
 
 
 def _load_native():
     global _native
+    path = native_path(torch.__version__)
     try:
-        from . import _native as nodes
-    except ImportError:   # not built, or for another torch: the Python functions do the same
+        spec = importlib.util.spec_from_file_location(__package__ + "._native", path)
+        nodes = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(nodes)
+    except ImportError as e:
+        warnings.warn(f"The C++ autograd nodes are not there, the Python functions do their work more slowly ({e}).  "
+                      "They are built by `python -m paper_2409_15373_amd.build`.")
         _native = False
         return
     lib = binding.load()
