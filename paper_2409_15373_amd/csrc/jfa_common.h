@@ -64,6 +64,20 @@ __device__ inline int cursor_grid(WorkCursor &cur) {
     return cur.grid;
 }
 
+// A deal without claims: round n of `total` items goes to the `grid` workgroups forwards (item n * grid + workgroup) or backwards
+// (n * grid + grid - 1 - workgroup).  The items are sorted longest first and every other round goes backwards (whoever had the longest item
+// of one gets the shortest of the next), so that the deal is even to less than an item.  The last round, which is hardly ever full, goes
+// forwards: the workgroups at the front are dispatched first, and their waves come before the others' on a SIMD.  Returns whether round
+// n goes backwards where (n ^ deal_turn()) & 1.  (The quotient may be one off: then the other order is dealt, by everyone.)
+// Microseconds, all rounds forwards / every second one backwards from the second on / as here: D = 64, 4 x 8 heads of up to 4096 rows,
+// forward 116 / 130 / 117, 16 x 4 of up to 2048, backward 151 / 148 / 139; 600 x 4 of up to 500, one in ten long, forward 39.5 / 41.9 / 39.6;
+// D = 32, 300 x 3, up to 200 queries against at most 8 keys, 15.1 / 17.0 / 14.8; D = 128, 1024 x 4, 200 queries against up to 200 keys,
+// backward 751 / 708 / 707; fp32, D = 64, 256 x 2 of up to 100, backward 76 / 81 / 76.
+__device__ inline int deal_turn(int64_t total, int grid) {
+    const int rounds = (int)((float)((int)total + grid - 1) * __builtin_amdgcn_rcpf((float)grid));
+    return (rounds + 1) & 1;
+}
+
 // Next work id for this workgroup, or -1 when nothing is left.  Called by one thread.
 //   * The first item is assigned statically (queue blockIdx % 8, local index blockIdx / 8): no memory traffic,
 //     and on problems smaller than the grid the surplus workgroups leave at once.
@@ -73,13 +87,12 @@ __device__ inline int cursor_grid(WorkCursor &cur) {
 //     spends an atomic on a queue that still shows work.
 //   * Problems of at most `fixed_items` items per workgroup skip all of this (see below).
 __device__ inline int64_t next_work(int32_t *counters, WorkCursor &cur, int64_t total) {
-    // Small problems are dealt without any atomics, the claim traffic would dominate the run time: the items are sorted longest
-    // first and every other round goes backwards (whoever had the longest item of one gets the shortest of the next), so the deal
-    // is even to less than an item.
+    // Small problems are dealt without any atomics, the claim traffic would dominate the run time.
     const int grid = cursor_grid(cur);
     if (cur.static_only || total <= cur.fixed_items * (int64_t)grid) {
-        cur.step = cur.next < 0 ? 2 * (int)blockIdx.x + 1 : 2 * grid - cur.step;
-        cur.next = cur.next < 0 ? blockIdx.x : cur.next + cur.step;
+        const int at = deal_turn(total, grid) ? grid - 1 - (int)blockIdx.x : (int)blockIdx.x;
+        cur.step = cur.next < 0 ? 2 * at + 1 : 2 * grid - cur.step;
+        cur.next = cur.next < 0 ? at : cur.next + cur.step;
         return cur.next < total ? cur.next : -1;
     }
     const int home = blockIdx.x % kXcds;
@@ -295,9 +308,10 @@ __device__ inline void build_small_work(const int64_t *offsets, const int64_t *o
         // 5. this workgroup's items: the position of each in the sorted order (64 probes per round), then, a lane per
         //    item, the sample's offsets -- the only trip to memory, all items at once
         const int64_t total = (int64_t)blocks * H;
+        const int turn = deal_turn(total, (int)gridDim.x);
         int my_p = 0, my_r = 0, n_items = 0;
         for (int n = 0; n < kSmallItems; ++n) {
-            const int64_t w = (int64_t)n * gridDim.x + (n & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x);   // every other round backwards, as in next_work()
+            const int64_t w = (int64_t)n * gridDim.x + ((n ^ turn) & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x);
             if (w >= total) break;
             int lo = 0, hi = B;   // invariant: start[lo] * H <= w < start[hi] * H
             while (hi - lo > 1) {

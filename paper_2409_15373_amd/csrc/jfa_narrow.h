@@ -132,8 +132,9 @@ struct NarrowWalk {
             const int tiles = s.tile_start[B];
             total = (int64_t)tiles * H;
             fixed_deal = s.static_only || total <= s.fixed_items * (int64_t)grid;
-            next_static = blockIdx.x;
-            step = 2 * (grid - 1 - (int)blockIdx.x) + 1;   // as next_work(): every other round backwards
+            const int at = fixed_deal && deal_turn(total, grid) ? grid - 1 - (int)blockIdx.x : (int)blockIdx.x;   // see deal_turn()
+            next_static = at;
+            step = 2 * (grid - 1 - at) + 1;
             if (!fixed_deal) {   // the first item of the home queue is assigned without a claim; see next_work()
                 next_static = work_id(blockIdx.x % kXcds, blockIdx.x / kXcds);
                 home_done = next_static >= total;
