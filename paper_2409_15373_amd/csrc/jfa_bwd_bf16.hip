@@ -102,7 +102,6 @@ __global__ __launch_bounds__(kBwdThreads, 2) void dq_bf16_kernel(const __bf16 *_
 
     WorkCursor cursor;
     cursor.static_only = s.static_only;
-    cursor.fixed_items = kShortFixedItems;
     for (int n = 0;; ++n) {
         Work t;
         if (small) {   // the workgroup's items were decoded when the schedule was built
@@ -248,7 +247,6 @@ __global__ __launch_bounds__(kBwdThreads, 1) void dkv_bf16_kernel(const __bf16 *
 
     WorkCursor cursor;
     cursor.static_only = s.static_only;
-    cursor.fixed_items = kShortFixedItems;
     for (int n = 0;; ++n) {
         Work t;
         if (small) {   // the workgroup's items were decoded when the schedule was built

@@ -606,9 +606,11 @@ inline int short_sample_rows(bool cross, int D, int64_t B, int64_t max_len, int 
 // bf16 attention, register-staged kernels (D = 128, short samples)
 constexpr int kFwdBlockRows = 128;
 constexpr int kBwdBlockRows = 128;
-// Items per workgroup that these kernels take without claims.  A claim heads a tile here, its latency is not hidden, and their
-// streams are short; microseconds with 4 and 16, forward and backward: 1024 x 4, 200 queries against at most 200 keys 135 and 131,
-// 472 and 477 (batches of shorter samples, which gained a sixth, have kernels of their own: one_tile_rows()).
+// Items per workgroup that the forward takes without claims.  A claim heads a tile here, its latency is not hidden, and the streams are
+// short; in the backward, twice as long a tile, balance is worth more.  Microseconds with 4 and 16, forward and backward: 1024 x 4, up to
+// 200 queries against up to 200 keys 131 and 130, 467 and 474; 512 x 4 of up to 130 on both sides 55 and 47, 159 and 161; 600 x 4 heads of
+// up to 250 rows 102 and 99, 377 and 390, causal 97 and 93, 341 and 356; 900 x 4 of up to 250 143 and 144, 544 and 554; but 200 queries
+// against up to 200 keys 192 and 197.
 constexpr int kShortFixedItems = 16;
 // In all bf16 launchers `offsets` belongs to the rows the schedule `s` was built over (queries for the forward and
 // dQ, keys for dK / dV) and the second array to the rows that stream past them (cross attention; nullptr: the same).
