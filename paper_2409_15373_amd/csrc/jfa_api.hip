@@ -195,13 +195,20 @@ bool narrow_small_problem(int64_t B, int64_t max_len, int H, int block_rows, int
 }
 
 // Rows per tile at head sizes 32 and 64; streamed: the rows that pass a tile.  A small backward at D = 64 takes 64-row tiles of keys
-// up to 256 rows as well: its dK / dV kernel has two workgroups per compute unit and 128-row tiles often need a second round
-// (256 samples of 64 rows on average, H = 2, 570 tiles: backward 36.8 -> 30.6 us).
+// up to 256 rows as well: its dK / dV kernel has two workgroups per compute unit and 128-row tiles may need a second round.  Where
+// they do that gains up to 14 %, where the lengths leave them in one it loses up to 5 %; where they cannot need one 128-row tiles stay.
+// Beyond what is dealt in the kernel (narrow_small_problem()) 64-row tiles were not built.  Backward, microseconds, 128- and 64-row tiles:
+// 256 x 2 heads of geometric length (mean 64, 570 tiles of 128 rows) 33.5 and 30.1, causal 34.5 and 30.7, 255 x 2 33.5 and 30.1, 200 x 2
+// of up to 256, uniform (600 tiles), 42.7 and 38.9, causal 43.6 and 37.8, 100 x 4 of up to 200, one in ten long, 24.0 and 22.6; but 256 x 2
+// of up to 256, uniform (768), 50.9 and 51.8, Zipf 42.2 and 43.3, 200 x 2 geometric (445) 27.2 and 28.5, 150 x 2 25.4 and 26.4, 100 x 4
+// 25.4 and 26.3; 128 x 2 (at most 512) 23.3 and 23.7.
 int narrow_rows(int64_t max_len, int64_t max_streamed, int64_t B, int H, int cus) {
     return jfa::narrow_block_rows(max_len, max_streamed, small_problem(B, max_len, H, jfa::kNarrowBlockRows, cus));
 }
 int narrow_key_rows(int64_t max_len, int64_t max_streamed, int64_t B, int H, int D, int cus) {
-    if (D == 64 && max_len <= 256 && max_streamed <= 256 && narrow_small_problem(B, max_len, H, jfa::kNarrowShortBlockRows, cus)) return jfa::kNarrowShortBlockRows;
+    if (D == 64 && max_len <= 256 && max_streamed <= 256 && !small_problem(B, max_len, H, jfa::kNarrowBlockRows, cus, 2) &&
+        narrow_small_problem(B, max_len, H, jfa::kNarrowShortBlockRows, cus))
+        return jfa::kNarrowShortBlockRows;
     return narrow_rows(max_len, max_streamed, B, H, cus);
 }
 

@@ -220,13 +220,13 @@ def everything(form, D, lq, lk, max_q, max_k, seed):
 def test_two_wave_workgroups(D, form, copies):
     """64-row tiles do the same arithmetic in the same order as 128-row ones, which a large bound on the lengths selects and which
     the tests above hold to the oracle.  They take at most 64 rows against at most 256 in large batches, and the keys of a small
-    backward at D = 64 with samples of up to 256 rows."""
+    backward at D = 64 with samples of up to 256 rows whose 128-row tiles could be more than 512 (two per compute unit)."""
     lq = lk = SHORT * copies
     if form.startswith("few"):
         lq, lk = [min(x, 64) for x in lq], ([200, 256, 129] + lk)[:len(lk)]
         lq, lk = (lq, lk) if form == "few queries" else (lk, lq)
     elif form.endswith("shorter blocks"):
-        lq = lk = [256, 1, 130, 64, 0, 193, 65, 200] * copies
+        lq = lk = [256, 1, 130, 64, 0, 193, 65, 200] * (24 if copies == 1 else copies)   # 768 tiles of 128 rows at most, 1536 of 64
     mode = "causal" if form.startswith("causal") else "self" if form == "keys in shorter blocks" else "cross"
     got = everything(mode, D, lq, lk, max(lq), max(lk), 65 + D)
     ref = everything(mode, D, lq, lk, 4096, 4096, 65 + D)
