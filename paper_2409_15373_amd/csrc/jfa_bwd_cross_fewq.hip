@@ -17,8 +17,12 @@
 //                                                      block (the contraction runs over the item's queries) and
 //                                                      leave at once through an LDS transpose as whole row pieces.
 //                                                      Nobody reads them again here: they go past the L2, which
-//                                                      keeps what is being read (512 samples, up to 32 queries against
-//                                                      up to 4096 keys, forward and backward: 620 -> 610 us).
+//                                                      keeps what is being read, at every size.  Through the L2 -> past it,
+//                                                      microseconds: 512 samples, up to 32 queries against up to 4096 keys,
+//                                                      forward and backward 620 -> 610; backward alone, 64 x 4 heads of up to
+//                                                      256 keys 17.2 -> 14.7, 256 x 4 of up to 512 91.9 -> 77.6, 256 x 1 of up
+//                                                      to 2000 75.4 -> 63.8; with an operator behind it that reads dK and dV
+//                                                      25.7 -> 23.2, 121.9 -> 128.7 (70 MB), 512 x 8 of up to 1024 745 -> 744.
 // A lane's operand registers are the same in both orientations (its own row of the tile, read once per block for K
 // and V and once per item for Q and dO): only which side of the matrix instruction they go to differs.
 // The waves' partial dQ blocks are added in a fixed order through LDS at the end of the item: results are
