@@ -72,7 +72,9 @@ __device__ inline int cursor_grid(WorkCursor &cur) {
 // Microseconds, all rounds forwards / every second one backwards from the second on / as here: D = 64, 4 x 8 heads of up to 4096 rows,
 // forward 116 / 130 / 117, 16 x 4 of up to 2048, backward 151 / 148 / 139; 600 x 4 of up to 500, one in ten long, forward 39.5 / 41.9 / 39.6;
 // D = 32, 300 x 3, up to 200 queries against at most 8 keys, 15.1 / 17.0 / 14.8; D = 128, 1024 x 4, 200 queries against up to 200 keys,
-// backward 751 / 708 / 707; fp32, D = 64, 256 x 2 of up to 100, backward 76 / 81 / 76.
+// backward 751 / 708 / 707; fp32, D = 64, 256 x 2 of up to 100, backward 76 / 81 / 76.  With two rounds, most items short and a few long
+// the long ones go to the workgroups at the back: D = 64, 94 x 6 of up to 857, one in ten long, forward 26.5 / 23.5 / 25.3.  (A last round
+// forwards from the second workgroup of each compute unit, the others as in the second column: 16 x 4 157, 4 x 8 126, 94 x 6 26.0.)
 __device__ inline int deal_turn(int64_t total, int grid) {
     const int rounds = (int)((float)((int)total + grid - 1) * __builtin_amdgcn_rcpf((float)grid));
     return (rounds + 1) & 1;
@@ -526,7 +528,10 @@ inline int f32_block_rows(int64_t max_streamed, bool many) {
 //   forward, dQ: a workgroup per compute unit and SIMD pair has to find a tile: 32 x 2 heads of up to 256 rows, D = 64, forward 17 -> 22,
 //   64 x 4 of up to 512 87 -> 69.  Streams of at most 64 rows: 2000 x 2 heads 54 -> 81.  Up to 128 rows: D = 32, 500 x 8 heads of
 //   up to 100, 56 -> 61; D = 64 100 -> 81, but 200 x 2 heads, 200 queries against up to 100 keys (most of them few), 30 -> 34:
-//   there with twice the tiles;
+//   there with twice the tiles.  The tiles are counted from the bound on the lengths: where most samples are short they are few and a long
+//   sample's tile of 128 rows is longer than one of 64.  D = 64, forward and backward, lengths uniform / one in ten long: 17 x 6 of up to
+//   1132 (918 tiles at most) 155 -> 106 and 498 -> 329 / 54 -> 72 and 165 -> 165; 64 x 4 of up to 300 (768) 43 -> 36 and 128 -> 91 / 25 -> 33
+//   and 71 -> 65; 128 x 4 of up to 500 (2048) 152 -> 109 and 476 -> 321 / 48 -> 45 and 141 -> 106;
 //   dK / dV as the queries' kernels: a probability is exp(score - lse), and where one score is most of the log-sum-exp their errors
 //   cancel only if both come from the same arithmetic.  (Split alone, behind the other forward: backward of 32 x 2 heads of up to
 //   256 rows, D = 64, 53 -> 48, but at scores of standard deviation 16, D = 32, dV's error is twice that of either arithmetic alone.)
