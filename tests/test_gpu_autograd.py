@@ -180,3 +180,29 @@ def test_hooks_on_saved_tensors(mode):
         step_with(_raise)
     with pytest.raises(_Raised):
         step_with(lambda t: t, _raise)
+
+
+@pytest.mark.parametrize("mode", ["self", "cross"])
+def test_native_nodes_on_a_stream_of_their_own(mode):
+    """Both directions run on the stream that is current in the forward: behind a long wait on it, on inputs and a dout that are only
+    written after that wait."""
+    call, inputs = _step(mode)
+    expected = torch.autograd.grad(call().square().sum(), inputs)
+    values = [x.detach().clone() for x in inputs]
+    stream = torch.cuda.Stream()
+    with torch.no_grad():
+        for x in inputs:
+            x.fill_(float("nan"))
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(50_000_000)
+        with torch.no_grad():
+            for x, y in zip(inputs, values):
+                x.copy_(y)
+        out = call()
+        dout = torch.full_like(out, float("nan"))
+        torch.cuda._sleep(50_000_000)
+        dout.copy_(2 * out.detach())
+        got = torch.autograd.grad(out, inputs, dout)
+    stream.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, expected))

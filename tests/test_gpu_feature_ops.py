@@ -201,3 +201,19 @@ def test_a_work_table_that_is_new_under_capture(B):
             graphs[i].replay()
             torch.cuda.synchronize()
             assert ops.check(outs[i])
+
+
+@pytest.mark.parametrize("B,D,T", [(37, 32, 64), (6001, 64, 32), (9001, 128, 128)])
+def test_rows_stored_past_the_l2(B, D, T):
+    """A large bound on the lengths makes the operators store past the L2 (and jagged_dense_bmm take the last samples first): the same bits."""
+    from paper_2409_15373_amd import binding
+    ops = Operators(B, D, T, 61)
+    small = ops.run(ops.buffers())
+    assert ops.check(small)
+    bound = 10 ** 8   # rows: more than 256 MB with every B here
+    out = ops.buffers()
+    binding.jfa_jagged_softmax(ops.x, ops.off, bound, y=out[0])
+    binding.jfa_jagged_dense_bmm(ops.x, ops.w, ops.off, bound, out=out[1])
+    binding.jfa_jagged_jagged_bmm(ops.x, ops.y, ops.off, bound, out=out[2])
+    binding.jfa_jagged_softmax_backward(ops.x, ops.x, ops.off, bound, dx=out[3])
+    assert ops.check(out)

@@ -1,6 +1,6 @@
-"""The bf16 kernels for samples of at most 64 queries and keys, one workgroup each, where they can go wrong: lengths around their
-32-row tiles with one and two tiles per sample, batches that do not fill the last round of dies, empty sides, and batches in which
-only some samples are theirs and the others go to the kernels for longer ones."""
+"""The bf16 kernels for samples of at most 128 queries and keys, one workgroup each, where they can go wrong: lengths around their
+32-row tiles with one, two and four tiles per sample, batches that do not fill the last round of dies, empty sides, batches in which
+only some samples are theirs and the others go to the kernels for longer ones, and batches done in two launches."""
 import numpy as np
 import pytest
 import torch
@@ -50,15 +50,50 @@ def test_only_some_samples(D, B, H, max_len, causal):
     gen = torch.Generator(device="cuda").manual_seed(75)
     q, k, v, do = (torch.randn(int(lengths.sum()), H, D, device="cuda", generator=gen).bfloat16() for _ in range(4))
 
-    def everything(tensors, lengths, max_len):
-        off = torch.from_numpy(offsets_from_lengths(lengths)).cuda()
-        out, lse = binding.jfa_forward(*tensors[:3], off, max_len, causal=causal)
-        dq, dk, dv, delta = binding.jfa_backward(*tensors[:3], out, tensors[3], lse, off, max_len, causal=causal)
-        return out, dq, dk, dv, lse.T, delta[0].T
+    compare_parts((q, k, v, do), lengths, lengths, max_len, causal, "self")
 
-    got = everything((q, k, v, do), lengths, max_len)
-    for part, bound in ((lengths <= 64, 64), (lengths > 64, max_len)):
-        rows = torch.from_numpy(np.repeat(part, lengths)).cuda()
-        ref = everything([x[rows].contiguous() for x in (q, k, v, do)], lengths[part], bound)
-        for name, g, r in zip(("out", "dq", "dk", "dv", "lse", "delta"), got, ref):
-            assert torch.equal(g[rows], r), f"{name}, samples of at most {bound} rows"
+
+def compare_parts(tensors, lq, lk, max_len, causal, mode):
+    """A call on all samples and calls on those of at most 64 rows and on the others, bit for bit."""
+    q, k, v, do = tensors
+
+    def everything(q, k, v, do, lq, lk, max_len):
+        oq, ok = (torch.from_numpy(offsets_from_lengths(x)).cuda() for x in (lq, lk))
+        if mode == "cross":
+            out, lse = binding.jfa_forward_cross(q, k, v, oq, ok, max_len, max_len)
+            dq, dk, dv, delta = binding.jfa_backward_cross(q, k, v, out, do, lse, oq, ok, max_len, max_len)
+        else:
+            out, lse = binding.jfa_forward(q, k, v, oq, max_len, causal=causal)
+            dq, dk, dv, delta = binding.jfa_backward(q, k, v, out, do, lse, oq, max_len, causal=causal)
+        assert delta.shape == lse.shape
+        return dict(out=out, dq=dq, lse=lse.T, delta=delta.T), dict(dk=dk, dv=dv)   # by queries, by keys
+
+    got = everything(q, k, v, do, lq, lk, max_len)
+    short = (lq <= 64) & (lk <= 64)
+    for part, bound in ((short, 64), (~short, max_len)):
+        rows = [torch.from_numpy(np.repeat(part, x)).cuda() for x in (lq, lk)]
+        mine = [x[r].contiguous() for x, r in ((q, rows[0]), (k, rows[1]), (v, rows[1]), (do, rows[0]))]
+        ref = everything(*mine, lq[part], lk[part], bound)
+        for g, r, at in zip(got, ref, rows):
+            for name in g:
+                assert torch.equal(g[name][at], r[name]), f"{name}, samples of at most {bound} rows"
+
+
+@pytest.mark.parametrize("mode", ["self", "causal", "cross"])
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_two_launches(D, mode):
+    """At most 128 rows and so many (sample, head) pairs that samples of at most 64 rows are done in a launch of their own: 64 per compute
+    unit (head size 32 and cross attention take one launch in some directions; the bits are the same).  Both parts alone are too small for
+    that and are held to the oracle above."""
+    B, H = 2051, 8
+    rng = np.random.default_rng(76)
+    lq, lk = rng.integers(0, 9, size=B), rng.integers(0, 9, size=B)
+    for first, length in ((10, 63), (11, 64), (12, 65), (13, 128), (14, 96), (15, 127)):
+        lq[first:B:100] = length
+        lk[first + 3:B:100] = length
+    lk = lk if mode == "cross" else lq
+    assert B * H >= 64 * torch.cuda.get_device_properties(0).multi_processor_count
+    gen = torch.Generator(device="cuda").manual_seed(77)
+    q, do = (torch.randn(int(lq.sum()), H, D, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    k, v = (torch.randn(int(lk.sum()), H, D, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    compare_parts((q, k, v, do), lq, lk, 128, mode == "causal", mode)
