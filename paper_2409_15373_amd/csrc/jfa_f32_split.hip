@@ -15,7 +15,7 @@
 // 206 to 252 registers.  Tried: workgroups of two waves (the splitting is then shared by half as many), dK / dV with both operands'
 // planes in one wave (spills): both slower.  Microseconds at B = 256, H = 2, lengths to 512, against the fp32 instructions: D = 64
 // forward 168 -> 108, backward 530 -> 327; D = 32 96 -> 70, 299 -> 212; 32 samples of 4096 rows, one head, D = 64, forward 1255 -> 782,
-// backward 4115 -> 2659.  All NaN: 111 and 334; with one infinity per sample, in v, 2170 and 5260 (see "values that have no split").
+// backward 4115 -> 2659.  All NaN: 111 and 334; with one infinity per sample, in v, 1130 and 3930 (see "values that have no split").
 #include "jfa_f32.h"
 #include "jfa_narrow.h"
 
@@ -166,7 +166,7 @@ __device__ inline void lds_barrier() {
 // An infinity is not a sum of three bf16 numbers: the rest is NaN, and NaN is what the products above make of it, and of factors
 // that scaled round to infinity; scaled products of large factors may overflow.  Results that come out not finite are therefore taken
 // again in plain fp32, one lane per row; the others stay as they are (a product of rows touches no other column).  Lane by lane that
-// costs some twenty times the wave's products; on the matrix instructions masked entries would be 0 times an infinity.
+// costs some ten times the wave's products; on the matrix instructions masked entries would be 0 times an infinity.
 template <int D> __device__ inline void unscale(f32x16 (&acc)[D / 32]) {
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
@@ -205,26 +205,46 @@ template <int D> struct PlainRow {
         return nan || other;
     }
 };
-template <int D> __device__ inline float plain_dot(const PlainRow<D> &a, const float *__restrict__ row, int half) {
-    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+// R of the streamed rows r .. n - 1 at a time (the last one again behind the end): their loads are in flight together.  Two where the
+// registers are there (forward with an infinity per sample, see above, 2.1 -> 1.1 ms; four, or two in dK / dV, spill in ordinary calls too).
+template <int D, int R> struct PlainRows {
+    const float *p[R];
+    __device__ inline PlainRows(const float *__restrict__ base, int64_t row_stride, int r, int n, int half) {
 #pragma unroll
-    for (int g = 0; g < D / 8; ++g) {
-        const float4 f = *reinterpret_cast<const float4 *>(row + g * 8 + half * 4);
-        s[0] = fmaf(a.x[4 * g], f.x, s[0]); s[1] = fmaf(a.x[4 * g + 1], f.y, s[1]);
-        s[2] = fmaf(a.x[4 * g + 2], f.z, s[2]); s[3] = fmaf(a.x[4 * g + 3], f.w, s[3]);
+        for (int u = 0; u < R; ++u) p[u] = base + (r + u < n ? r + u : n - 1) * row_stride + half * 4;
     }
-    return pair_sum((s[0] + s[1]) + (s[2] + s[3]));
-}
-// acc += x row
-template <int D> __device__ inline void plain_add(f32x16 (&acc)[D / 32], float x, const float *__restrict__ row, int half) {
+    __device__ inline void dots(float (&y)[R], const PlainRow<D> &a) const {
+        float s[R][4];
 #pragma unroll
-    for (int g = 0; g < D / 8; ++g) {
-        const float4 f = *reinterpret_cast<const float4 *>(row + g * 8 + half * 4);
-        f32x16 &y = acc[g >> 2];
-        const int e = 4 * (g & 3);
-        y[e] = fmaf(x, f.x, y[e]); y[e + 1] = fmaf(x, f.y, y[e + 1]); y[e + 2] = fmaf(x, f.z, y[e + 2]); y[e + 3] = fmaf(x, f.w, y[e + 3]);
+        for (int g = 0; g < D / 8; ++g) {
+            if (g % 4 == 0) __builtin_amdgcn_sched_barrier(0);   // not all of the rows at once, for which there are no registers
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const float4 f = *reinterpret_cast<const float4 *>(p[u] + g * 8);
+                s[u][0] = fmaf(a.x[4 * g], f.x, g ? s[u][0] : 0.0f); s[u][1] = fmaf(a.x[4 * g + 1], f.y, g ? s[u][1] : 0.0f);
+                s[u][2] = fmaf(a.x[4 * g + 2], f.z, g ? s[u][2] : 0.0f); s[u][3] = fmaf(a.x[4 * g + 3], f.w, g ? s[u][3] : 0.0f);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < R; ++u) y[u] = pair_sum((s[u][0] + s[u][1]) + (s[u][2] + s[u][3]));
     }
-}
+    // acc += the sum of x[u] row[u] over the rows that count: the others, and their x, are not looked at
+    __device__ inline void add(f32x16 (&acc)[D / 32], const float (&x)[R], const bool (&counts)[R]) const {
+#pragma unroll
+        for (int g = 0; g < D / 8; ++g) {
+            if (g % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                float4 f = *reinterpret_cast<const float4 *>(p[u] + g * 8);
+                const float c = counts[u] ? x[u] : 0.0f;
+                f.x = counts[u] ? f.x : 0.0f; f.y = counts[u] ? f.y : 0.0f; f.z = counts[u] ? f.z : 0.0f; f.w = counts[u] ? f.w : 0.0f;
+                f32x16 &y = acc[g >> 2];
+                const int e = 4 * (g & 3);
+                y[e] = fmaf(c, f.x, y[e]); y[e + 1] = fmaf(c, f.y, y[e + 1]); y[e + 2] = fmaf(c, f.z, y[e + 2]); y[e + 3] = fmaf(c, f.w, y[e + 3]);
+            }
+        }
+    }
+};
 // A NaN has no split either, but taken again it is the same NaN, and so the rows are looked through for NaN first, 32 at a time (all
 // of a batch NaN, forward and backward, 31 ms -> 0.44, one NaN per sample 31 -> 0.6; the ordinary call 0.44).
 // nan_row: the first (kLast: the last) of rows from .. n - 1 that holds one, n (kLast: -1) if none does; the same in every lane.
@@ -291,7 +311,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void fwd_split_kernel(
         const float *__restrict__ q, const float *__restrict__ k, const float *__restrict__ v,
         const int64_t *__restrict__ offsets, const int64_t *__restrict__ offsets_kv, bool causal, int B, int H, Schedule s,
         float *__restrict__ out, float *__restrict__ lse) {
-    constexpr int kRows = kF32SplitRows, kStage = sp_stage<D>();
+    constexpr int kRows = kF32SplitRows, kStage = sp_stage<D>(), kRowsAgain = 2;
     __shared__ __attribute__((aligned(1024))) char sm[2 * kStage];   // two stages: the planes of K, then of V
     __shared__ int64_t slot;
     __shared__ SmallWork mine;
@@ -383,20 +403,28 @@ __global__ __launch_bounds__(kSpThreads, 2) void fwd_split_kernel(
                 float m2 = m, l2 = 0.0f;
                 if (__builtin_amdgcn_ballot_w64(scores) != 0) {
                     float top = -INFINITY;
-                    for (int j = 0; j < seen; ++j) {
-                        const float s_j = plain_dot<D>(q_row, kbase + j * row_stride, half) * scale;
-                        if (j < lim) top = fmaxf(top, s_j);
+                    for (int j = 0; j < seen; j += kRowsAgain) {
+                        float y[kRowsAgain];
+                        PlainRows<D, kRowsAgain>(kbase, row_stride, j, seen, half).dots(y, q_row);
+#pragma unroll
+                        for (int u = 0; u < kRowsAgain; ++u)
+                            if (j + u < lim) top = fmaxf(top, y[u] * scale);
                     }
                     if (scores) m2 = top;
                 }
                 f32x16 o2[D / 32];
                 clear<D>(o2);
-                for (int j = 0; j < seen; ++j) {
-                    const float p = exp_f32(fmaf(plain_dot<D>(q_row, kbase + j * row_stride, half), scale, -m2));
-                    if (j < lim) {
-                        l2 += p;
-                        plain_add<D>(o2, p, vbase + j * row_stride, half);
+                for (int j = 0; j < seen; j += kRowsAgain) {
+                    float p[kRowsAgain];
+                    bool counts[kRowsAgain];
+                    PlainRows<D, kRowsAgain>(kbase, row_stride, j, seen, half).dots(p, q_row);
+#pragma unroll
+                    for (int u = 0; u < kRowsAgain; ++u) {
+                        p[u] = exp_f32(fmaf(p[u], scale, -m2));
+                        counts[u] = j + u < lim;
+                        if (counts[u]) l2 += p[u];
                     }
+                    PlainRows<D, kRowsAgain>(vbase, row_stride, j, seen, half).add(o2, p, counts);
                 }
                 if (scores) {
                     m = m2;
@@ -423,7 +451,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void dq_split_kernel(
         const float *__restrict__ out_fwd, const float *__restrict__ dout, const float *__restrict__ lse,
         float *__restrict__ delta, const int64_t *__restrict__ offsets, const int64_t *__restrict__ offsets_kv, bool causal,
         int B, int H, Schedule s, float *__restrict__ dq) {
-    constexpr int kRows = kF32SplitRows, kStage = sp_stage<D>();
+    constexpr int kRows = kF32SplitRows, kStage = sp_stage<D>(), kRowsAgain = 2;
     __shared__ __attribute__((aligned(1024))) char sm[2 * kStage];   // two stages: the planes of K, then of V
     __shared__ int64_t slot;
     __shared__ SmallWork mine;
@@ -503,7 +531,9 @@ __global__ __launch_bounds__(kSpThreads, 2) void dq_split_kernel(
             PlainRow<D> q_row, g_row;
             q_row.load(q + row_e, half_e);
             g_row.load(dout + row_e, half_e);
-            const float delta_e = plain_dot<D>(g_row, out_fwd + row_e, half_e);
+            float same[1];
+            PlainRows<D, 1>(out_fwd + row_e, 0, 0, 1, half_e).dots(same, g_row);
+            const float delta_e = same[0];
             const bool q_nan = q_row.has_nan(), g_nan = g_row.has_nan(), own = q_nan || g_nan || lse_e != lse_e || delta_e != delta_e;
             bool open = !own && !all_finite<D>(acc);
             if (__builtin_amdgcn_ballot_w64(open) != 0) {
@@ -513,11 +543,17 @@ __global__ __launch_bounds__(kSpThreads, 2) void dq_split_kernel(
             if (__builtin_amdgcn_ballot_w64(open) != 0) {
                 f32x16 again[D / 32];
                 clear<D>(again);
-                for (int j = 0; j < seen; ++j) {
-                    const float *const key = kbase + j * row_stride;
-                    const float p = exp_f32(fmaf(plain_dot<D>(q_row, key, half_e), scale, -lse_e));
-                    const float ds = p * (plain_dot<D>(g_row, vbase + j * row_stride, half_e) - delta_e);
-                    if (j < lim) plain_add<D>(again, ds, key, half_e);
+                for (int j = 0; j < seen; j += kRowsAgain) {
+                    float ds[kRowsAgain], dp[kRowsAgain];
+                    bool counts[kRowsAgain];
+                    PlainRows<D, kRowsAgain>(kbase, row_stride, j, seen, half_e).dots(ds, q_row);
+                    PlainRows<D, kRowsAgain>(vbase, row_stride, j, seen, half_e).dots(dp, g_row);
+#pragma unroll
+                    for (int u = 0; u < kRowsAgain; ++u) {
+                        ds[u] = exp_f32(fmaf(ds[u], scale, -lse_e)) * (dp[u] - delta_e);
+                        counts[u] = j + u < lim;
+                    }
+                    PlainRows<D, kRowsAgain>(kbase, row_stride, j, seen, half_e).add(again, ds, counts);
                 }
                 take_where_not_finite<D>(acc, again);
             }
@@ -537,7 +573,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void dkv_split_kernel(
         const int64_t *__restrict__ offsets,   // of the keys
         const int64_t *__restrict__ offsets_q, bool causal, int B, int H, Schedule s, float *__restrict__ dk,
         float *__restrict__ dv) {
-    constexpr int kRows = kF32SplitKeyRows, kStage = sp_stage<D>();
+    constexpr int kRows = kF32SplitKeyRows, kStage = sp_stage<D>(), kRowsAgain = 1;
     __shared__ __attribute__((aligned(1024))) char sm[2 * kStage];   // two stages: the planes of Q, then of dO
     __shared__ __attribute__((aligned(16))) float stat_s[2][2][kSpRows];   // per stage: lse of the streamed rows, then delta
     __shared__ f32x4 px[2][4][64];                                   // per pair: a 32 x 32 block of P on its way from A to B
@@ -662,11 +698,19 @@ __global__ __launch_bounds__(kSpThreads, 2) void dkv_split_kernel(
             if (__builtin_amdgcn_ballot_w64(open) != 0) {
                 f32x16 again[D / 32];
                 clear<D>(again);
-                for (int i = from; i < L; ++i) {
-                    const float *const query = qbase + i * row_stride, *const grad = obase + i * row_stride;
-                    float x = exp_f32(fmaf(plain_dot<D>(k_row, query, half), scale, -lse_rows[i]));
-                    if (!is_a) x *= plain_dot<D>(v_row, grad, half) - delta_rows[i];
-                    if (i >= mine_from) plain_add<D>(again, x, is_a ? grad : query, half);
+                for (int i = from; i < L; i += kRowsAgain) {
+                    float x[kRowsAgain], dp[kRowsAgain];
+                    bool counts[kRowsAgain];
+                    PlainRows<D, kRowsAgain>(qbase, row_stride, i, L, half).dots(x, k_row);
+                    if (!is_a) PlainRows<D, kRowsAgain>(obase, row_stride, i, L, half).dots(dp, v_row);
+#pragma unroll
+                    for (int u = 0; u < kRowsAgain; ++u) {
+                        const int r = i + u < L ? i + u : L - 1;
+                        x[u] = exp_f32(fmaf(x[u], scale, -lse_rows[r]));
+                        if (!is_a) x[u] *= dp[u] - delta_rows[r];
+                        counts[u] = i + u >= mine_from && i + u < L;
+                    }
+                    PlainRows<D, kRowsAgain>(is_a ? obase : qbase, row_stride, i, L, half).add(again, x, counts);
                 }
                 take_where_not_finite<D>(acc, again);
             }
