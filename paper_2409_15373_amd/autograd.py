@@ -17,6 +17,7 @@ import importlib.util
 import warnings
 
 import torch
+from torch.autograd import forward_ad
 
 from . import binding
 from .build import native_path
@@ -82,7 +83,7 @@ def _ordinary(*tensors) -> bool:
         _load_native()
     return (_native is not False and all(type(t) in _PLAIN for t in tensors) and torch._C._get_tracing_state() is None
             and not torch._C._are_functorch_transforms_active() and not torch.compiler.is_compiling()
-            and torch.autograd.forward_ad._current_level < 0)
+            and forward_ad._current_level < 0)
 
 
 def jagged_flash_attention(q, k, v, offsets, max_len: int, causal: bool = False):

@@ -63,13 +63,21 @@ int kind(const Tensor &q) {
     if (q.scalar_type() == at::kFloat) return 1;
     throw Refused{};
 }
-// What the graph gives back for a saved tensor is any tensor that a hook has made of it (and for dout what a hook of the node has made of
-// that): it has to be what the kernels take it for.
+// What the graph gives back for a saved tensor is any tensor that a hook has made of it: it has to be what the kernels take it for.
+// (The engine has made dout one of the output's size and type; a hook of the node comes after that.)
+void check_on_gpu(const Tensor &t) {
+    if (plain(t)) return;
+    pybind11::gil_scoped_acquire gil;
+    raise_from(lib.pointer, pybind11::cast(t));
+}
+int check_dout(const Tensor &dout) {
+    check_on_gpu(dout);
+    TORCH_CHECK(dout.dim() == 3 && (dout.scalar_type() == at::kBFloat16 || dout.scalar_type() == at::kFloat),
+                "jagged attention, backward: a gradient of ", dout.sizes(), " ", dout.scalar_type());
+    return dout.scalar_type() == at::kFloat;
+}
 void check_saved(const Tensor &t, at::IntArrayRef sizes, at::ScalarType type, const Tensor &dout) {
-    if (!t.defined() || !plain(t)) {
-        pybind11::gil_scoped_acquire gil;
-        raise_from(lib.pointer, pybind11::cast(t));
-    }
+    check_on_gpu(t);
     TORCH_CHECK(t.sizes() == sizes && t.scalar_type() == type && t.device() == dout.device(), "jagged attention, backward: a tensor of ", sizes, " ",
                 type, " on ", dout.device(), " was saved, ", t.sizes(), " ", t.scalar_type(), " on ", t.device(), " came back");
 }
@@ -90,27 +98,22 @@ struct SelfAttention : torch::autograd::Function<SelfAttention> {
         }
         if (status != 0) throw Refused{};   // the Python function meets the same error and reports it
         ctx->save_for_backward({q, k, v, out, lse, offsets});
-        ctx->saved_data["max_len"] = max_len;
-        ctx->saved_data["causal"] = causal;
-        ctx->saved_data["type"] = (int64_t)q.scalar_type();
-        ctx->saved_data["q"] = q.sizes();
-        ctx->saved_data["offsets"] = offsets.numel();
+        ctx->saved_data["call"] = std::vector<int64_t>{max_len, causal, offsets.numel()};
         return out;
     }
     static variable_list backward(AutogradContext *ctx, variable_list grads) {
         const variable_list saved = ctx->get_saved_variables();
         const Tensor &q = saved[0], &k = saved[1], &v = saved[2], &out = saved[3], &lse = saved[4], &offsets = saved[5];
         const Tensor dout = grads[0].contiguous();
-        const std::vector<int64_t> sizes = ctx->saved_data["q"].toIntVector(), stats_sizes = {sizes[1], sizes[0]};
-        const at::ScalarType type = (at::ScalarType)ctx->saved_data["type"].toInt();
-        for (const Tensor *t : {&dout, &q, &k, &v, &out}) check_saved(*t, sizes, type, dout);
-        check_saved(lse, stats_sizes, at::kFloat, dout);
-        check_saved(offsets, ctx->saved_data["offsets"].toInt(), at::kLong, dout);
-        const int f32 = type == at::kFloat;
+        const std::vector<int64_t> call = ctx->saved_data["call"].toIntVector();   // max_len, causal, offsets' length
+        const int f32 = check_dout(dout);
+        for (const Tensor *t : {&q, &k, &v, &out}) check_saved(*t, dout.sizes(), dout.scalar_type(), dout);
+        check_saved(lse, {dout.size(1), dout.size(0)}, at::kFloat, dout);
+        check_saved(offsets, call[2], at::kLong, dout);
         const Tensor dq = at::empty_like(q), dk = at::empty_like(q), dv = at::empty_like(q), stats = statistics(q, f32 ? 1 : 2);
-        const Backward fn = (ctx->saved_data["causal"].toBool() ? lib.backward_causal : lib.backward)[f32];
+        const Backward fn = (call[1] ? lib.backward_causal : lib.backward)[f32];
         check_backward(fn(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), dout.data_ptr(), floats(lse), longs(offsets), offsets.numel() - 1,
-                          ctx->saved_data["max_len"].toInt(), (int)q.size(1), (int)q.size(2), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
+                          call[0], (int)q.size(1), (int)q.size(2), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
                           floats(stats), stream()));
         return {dq, dk, dv, Tensor(), Tensor(), Tensor()};
     }
@@ -129,29 +132,22 @@ struct CrossAttention : torch::autograd::Function<CrossAttention> {
         }
         if (status != 0) throw Refused{};
         ctx->save_for_backward({q, k, v, out, lse, offsets_q, offsets_kv});
-        ctx->saved_data["max_len_q"] = max_len_q;
-        ctx->saved_data["max_len_kv"] = max_len_kv;
-        ctx->saved_data["type"] = (int64_t)q.scalar_type();
-        ctx->saved_data["q"] = q.sizes();
-        ctx->saved_data["k"] = k.sizes();
-        ctx->saved_data["offsets"] = offsets_q.numel();
+        ctx->saved_data["call"] = std::vector<int64_t>{max_len_q, max_len_kv, offsets_q.numel(), k.size(0)};
         return out;
     }
     static variable_list backward(AutogradContext *ctx, variable_list grads) {
         const variable_list saved = ctx->get_saved_variables();
         const Tensor &q = saved[0], &k = saved[1], &v = saved[2], &out = saved[3], &lse = saved[4], &offsets_q = saved[5], &offsets_kv = saved[6];
         const Tensor dout = grads[0].contiguous();
-        const std::vector<int64_t> sizes = ctx->saved_data["q"].toIntVector(), key_sizes = ctx->saved_data["k"].toIntVector(), stats_sizes = {sizes[1], sizes[0]};
-        const at::ScalarType type = (at::ScalarType)ctx->saved_data["type"].toInt();
-        for (const Tensor *t : {&dout, &q, &out}) check_saved(*t, sizes, type, dout);
-        for (const Tensor *t : {&k, &v}) check_saved(*t, key_sizes, type, dout);
-        check_saved(lse, stats_sizes, at::kFloat, dout);
-        for (const Tensor *t : {&offsets_q, &offsets_kv}) check_saved(*t, ctx->saved_data["offsets"].toInt(), at::kLong, dout);
-        const int f32 = type == at::kFloat;
+        const std::vector<int64_t> call = ctx->saved_data["call"].toIntVector();   // max_len_q, max_len_kv, offsets' length, rows of k
+        const int f32 = check_dout(dout);
+        for (const Tensor *t : {&q, &out}) check_saved(*t, dout.sizes(), dout.scalar_type(), dout);
+        for (const Tensor *t : {&k, &v}) check_saved(*t, {call[3], dout.size(1), dout.size(2)}, dout.scalar_type(), dout);
+        check_saved(lse, {dout.size(1), dout.size(0)}, at::kFloat, dout);
+        for (const Tensor *t : {&offsets_q, &offsets_kv}) check_saved(*t, call[2], at::kLong, dout);
         const Tensor dq = at::empty_like(q), dk = at::empty_like(k), dv = at::empty_like(v), stats = statistics(q, f32 ? 1 : 2);
         check_backward(lib.backward_cross[f32](q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), dout.data_ptr(), floats(lse), longs(offsets_q),
-                                               longs(offsets_kv), offsets_q.numel() - 1, ctx->saved_data["max_len_q"].toInt(),
-                                               ctx->saved_data["max_len_kv"].toInt(), (int)q.size(1), (int)q.size(2), dq.data_ptr(), dk.data_ptr(),
+                                               longs(offsets_kv), offsets_q.numel() - 1, call[0], call[1], (int)q.size(1), (int)q.size(2), dq.data_ptr(), dk.data_ptr(),
                                                dv.data_ptr(), floats(stats), stream()));
         return {dq, dk, dv, Tensor(), Tensor(), Tensor(), Tensor()};
     }
