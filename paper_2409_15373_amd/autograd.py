@@ -14,6 +14,7 @@ and v; offsets and the length bounds are not differentiable.
 """
 import ctypes
 import importlib.util
+import threading
 import warnings
 
 import torch
@@ -57,24 +58,27 @@ class _CrossAttention(torch.autograd.Function):
 
 
 _native = None   # the C++ nodes; False where they have not been built for this torch
+_loading = threading.Lock()
 _PLAIN = (torch.Tensor, torch.nn.Parameter)
 
 
 def _load_native():
     global _native
-    path = native_path(torch.__version__)
-    try:
-        spec = importlib.util.spec_from_file_location(__package__ + "._native", path)
-        nodes = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(nodes)
-    except ImportError as e:
-        warnings.warn(f"The C++ autograd nodes are not there, the Python functions do their work more slowly ({e}).  "
-                      "They are built by `python -m paper_2409_15373_amd.build`.")
-        _native = False
-        return
-    lib = binding.load()
-    nodes.bind_library(lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value, binding._check, binding._ptr)
-    _native = nodes
+    with _loading:   # several threads may make their first call at once
+        if _native is not None:
+            return
+        try:
+            spec = importlib.util.spec_from_file_location(__package__ + "._native", native_path(torch.__version__))
+            nodes = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(nodes)
+        except ImportError as e:
+            warnings.warn(f"The C++ autograd nodes are not there, the Python functions do their work more slowly ({e}).  "
+                          "They are built by `python -m paper_2409_15373_amd.build`.")
+            _native = False
+            return
+        lib = binding.load()
+        nodes.bind_library(lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value, binding._check, binding._ptr)
+        _native = nodes
 
 
 def _ordinary(*tensors) -> bool:
