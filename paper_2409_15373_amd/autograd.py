@@ -83,11 +83,12 @@ def _load_native():
 
 def _ordinary(*tensors) -> bool:
     """Whether a call may pass torch.autograd.Function by: tracers, function transforms, forward mode and tensor subclasses have to see it."""
+    if torch.compiler.is_compiling():
+        return False
     if _native is None:
         _load_native()
     return (_native is not False and all(type(t) in _PLAIN for t in tensors) and torch._C._get_tracing_state() is None
-            and not torch._C._are_functorch_transforms_active() and not torch.compiler.is_compiling()
-            and forward_ad._current_level < 0)
+            and not torch._C._are_functorch_transforms_active() and forward_ad._current_level < 0)
 
 
 def jagged_flash_attention(q, k, v, offsets, max_len: int, causal: bool = False):
