@@ -97,3 +97,20 @@ def test_two_launches(D, mode):
     q, do = (torch.randn(int(lq.sum()), H, D, device="cuda", generator=gen).bfloat16() for _ in range(2))
     k, v = (torch.randn(int(lk.sum()), H, D, device="cuda", generator=gen).bfloat16() for _ in range(2))
     compare_parts((q, k, v, do), lq, lk, 128, mode == "causal", mode)
+
+
+def test_more_items_than_one_launch_holds():
+    """530001 x 8 (sample, head) pairs are more than the 2^22 workgroups of a launch.  A sample of one row is its own softmax: out is v
+    and dv is dout, bit for bit; dq and dk are zero up to the rounding of two sums of 32 products that are the same (delta and dO . v)."""
+    B, H, D = 530001, 8, 32
+    gen = torch.Generator(device="cuda").manual_seed(78)
+    q, k, v, do = (torch.randn(B, H, D, device="cuda", generator=gen).bfloat16() for _ in range(4))
+    off = torch.arange(B + 1, device="cuda")
+    out, lse = binding.jfa_forward(q, k, v, off, 1)
+    dq, dk, dv, _ = binding.jfa_backward(q, k, v, out, do, lse, off, 1)
+    assert torch.equal(out, v) and torch.equal(dv, do)
+    # each sum's error is at most 32 * 2^-24 of the sum of the products' sizes, (|dO| . |v|); times |k| or |q| and 1 / sqrt(D)
+    bound = 2 * 32 * 2.0 ** -24 * (do.float().abs() * v.float().abs()).sum(2, keepdim=True) / D ** 0.5 * 1.01
+    assert bool((dq.float().abs() <= bound * k.float().abs()).all()) and bool((dk.float().abs() <= bound * q.float().abs()).all())
+    s = (q.float() * k.float()).sum(2).T / D ** 0.5
+    assert bool(((lse - s).abs() <= 1e-5 * (1 + s.abs())).all())
