@@ -7,8 +7,18 @@
 //   * stages travel HBM/L2 -> LDS directly (global_load_lds_dwordx4): no staging registers, no LDS store
 //     instructions.  The tiles are unpadded and XOR-swizzled on 16-byte (K) / 64-byte (V) granules so that
 //     the 16-byte row reads and the transposing reads are conflict-free on the 64-bank LDS;
-//   * three stage buffers, DMA two stages ahead, and a bare s_barrier with a partial vmcnt wait at the end of a
-//     stage (a __syncthreads() would wait for every load in flight);
+//   * three stage buffers each for K and V, copies two stages ahead, and a bare s_barrier with a partial vmcnt wait at the
+//     end of a round (a __syncthreads() would wait for every load in flight);
+//   * the two products and the exponentials of a wave are of three different 32-key blocks and are issued in turn, one
+//     matrix instruction of each product and two exponentials at a time (see stage_body).  A wave's vector instructions
+//     run under its own matrix instructions where they do not depend on them (16 matrix instructions with 64 vector ones
+//     in between take 552 clocks, without any 524; after one another 924).  Taken phase by phase (scores, exponentials, products),
+//     the two waves of a SIMD, which a barrier per stage keeps in step, are in the same phase most of the time: a
+//     stage took 2 910 clocks, now 2 470 to 2 750, of 2 048 that its matrix instructions need.  What is left: the row sum's dot
+//     products, which do not overlap (5 %), LDS latency behind the barrier, and the clock, which falls to 1.7 GHz under this load, so
+//     that long samples run at 1 250 TFLOP/s whatever else is saved.  Forward, microseconds, before -> now: 16 x 8 heads of
+//     8192 rows 3640 -> 3505, causal 2140 -> 1998; 512 x 8 bimodal to 4096 2130 -> 2010, causal 1305 -> 1203; 1024 x 4 of up to
+//     1024 1040 -> 990; 300 x 4 of up to 300 73.7 -> 67.5; 1024 x 4 Zipf to 1024 664 -> 636;
 //   * exponentials are taken against a FIXED reference maximum per query (the maximum over the sample's
 //     first 32 keys): no running maximum, no rescaling, no branch in the hot loop.  A reference below the
 //     true maximum only scales numerator and denominator alike -- probabilities keep their relative
@@ -16,6 +26,7 @@
 //     end of the tile shows that it got too stale, and the workgroup then redoes the tile in the conservative
 //     order (maximum first, online rescaling).  On data whose scores are of one scale this never runs.
 #include "jfa_common.h"
+#include "jfa_lds.h"
 #include "jfa_mfma.h"
 
 namespace jfa {
@@ -28,14 +39,6 @@ constexpr int kDmaTile = kDmaBN * kDmaD * 2;   // bytes of one K or V stage in L
 constexpr int kDmaOpsPerStage = 2 * (kDmaBN / 4) / kDmaWaves;   // DMA instructions per wave per stage (K and V)
 
 template <int N> using IntC = std::integral_constant<int, N>;
-
-// 16 bytes per lane from `base` (wave-uniform, kept in scalar registers) + `byte_offset` (per lane, unsigned
-// 32 bits) into LDS at lds_wave_base + 16 * lane: the scalar-base form needs no 64-bit vector arithmetic.
-__device__ inline void dma16b(const __bf16 *base, uint32_t byte_offset, char *lds_wave_base) {
-    const char *src = reinterpret_cast<const char *>(base) + byte_offset;
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                     (__attribute__((address_space(3))) void *)lds_wave_base, 16, 0, 0);
-}
 
 // CROSS: the keys and values of a sample are the rows of a second offsets array (cross attention); otherwise
 // offsets_kv is not looked at and the code is that of self attention.  CAUSAL (self attention only): query i attends
@@ -53,14 +56,8 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
     constexpr int D = kDmaD;
     constexpr int kKSteps = D / 16;    // 8
     constexpr int kDBlocks = D / 32;   // 4
-    // Separate arrays (not one indexed array) so that the compiler can tell the buffer being filled by the
-    // DMA from the one being read and does not make the reads wait for the loads in flight.
-    __shared__ __attribute__((aligned(1024))) char K0[kDmaTile];
-    __shared__ __attribute__((aligned(1024))) char K1[kDmaTile];
-    __shared__ __attribute__((aligned(1024))) char K2[kDmaTile];
-    __shared__ __attribute__((aligned(1024))) char V0[kDmaTile];
-    __shared__ __attribute__((aligned(1024))) char V1[kDmaTile];
-    __shared__ __attribute__((aligned(1024))) char V2[kDmaTile];
+    // stage buffers: K's three, then V's
+    __shared__ __attribute__((aligned(1024))) char stages[6 * kDmaTile];
     __shared__ WorkSlot slot;   // the NEXT work item, claimed and decoded while the current one starts up
     __shared__ LdsSchedule<CROSS> tab;   // the schedule, copied once per workgroup when it fits
     __shared__ int restart;   // set by a wave whose reference maximum went stale beyond repair
@@ -82,11 +79,12 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
     // V element (row r, 64-byte group g, byte b inside it) sits at r * 256 + ((g ^ (r & 3)) << 6) + b.
     // The transposing read of this lane: row = 4 half + (lane & 15) / 4 (+8 for the second half of the
     // operand, +16 per 16-key step), group = feature block db, bytes 32 * ((lane >> 4) & 1) + 8 * (lane & 3).
-    // Feature block db is at vaddr0 ^ (db << 6).
+    // Feature block db is at vaddr0 ^ (db << 6).  Counted from K's buffer of the same number, so that the way from one
+    // register to any of the three buffers fits an instruction's offset.
     int vaddr0;
     {
         const int r = half * 4 + ((lane & 15) >> 2);
-        vaddr0 = r * 256 + ((r & 3) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+        vaddr0 = 3 * kDmaTile + r * 256 + ((r & 3) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
     }
     auto lds_addresses = [&](int (&kaddr)[kKSteps], int (&vaddr)[kDBlocks]) {
         int kb = kaddr0, vb = vaddr0;
@@ -99,14 +97,12 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
     // ---- DMA: one instruction moves 64 lanes x 16 bytes = 4 rows; wave w, instruction u fills rows 8 w + 4 u .. +3.
     // Lane l lands on physical chunk l & 15 of row 8 w + 4 u + (l >> 4) and so fetches the logical chunk that
     // the swizzle puts there.
-    const int dma_row0 = 8 * wave + (lane >> 4);
-    const int pc = lane & 15;
-
-    // byte offsets of this lane's DMA chunks inside a full stage (K and V differ in the swizzle)
+    // byte offsets of this lane's DMA chunks inside a full stage (K and V differ in the swizzle).  Cross attention has no
+    // registers for them and rebuilds them in every stage (kept, the kernel reloads spilled registers in its rounds: 1.7 times the time).
     uint32_t koffs[2], voffs[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-        const int r = dma_row0 + 4 * u;
+        const int r = 8 * wave + (lane >> 4) + 4 * u, pc = lane & 15;
         koffs[u] = 2u * (uint32_t)(r * (int)row_stride + ((pc ^ (r & 15)) << 3));
         voffs[u] = 2u * (uint32_t)(r * (int)row_stride + ((pc ^ ((r & 3) << 2)) << 3));
     }
@@ -178,16 +174,19 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
             const int L = st.L;
             const int j0 = stage * kDmaBN;
             const __bf16 *sbase = base + (int64_t)j0 * row_stride;
-            if (j0 + kDmaBN <= L) {
+            if (!CROSS && j0 + kDmaBN <= L) {
 #pragma unroll
-                for (int u = 0; u < 2; ++u) dma16b(sbase, is_k ? koffs[u] : voffs[u], tile + (8 * wave + 4 * u) * 256);
+                for (int u = 0; u < 2; ++u) bd_dma16(sbase, is_k ? koffs[u] : voffs[u], tile + (8 * wave + 4 * u) * 256);
             } else {
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    const int r = dma_row0 + 4 * u;
+                    int t_opaque = tid;
+                    asm volatile("" : "+v"(t_opaque));
+                    const int pc = t_opaque & 15;
+                    const int r = 8 * wave + ((t_opaque >> 4) & 3) + 4 * u;
                     const int ch = is_k ? (pc ^ (r & 15)) : (pc ^ ((r & 3) << 2));
                     const int jr = j0 + r < L ? r : L - 1 - j0;   // rows past the end repeat the last key (masked later)
-                    dma16b(sbase, 2u * (uint32_t)(jr * (int)row_stride + ch * 8), tile + (8 * wave + 4 * u) * 256);
+                    bd_dma16(sbase, 2u * (uint32_t)(jr * (int)row_stride + ch * 8), tile + (8 * wave + 4 * u) * 256);
                 }
             }
         };
@@ -202,8 +201,10 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
         for (int db = 0; db < kDBlocks; ++db)
 #pragma unroll
             for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
-        float m = -INFINITY, lsum = 0.0f;
-        f32x16 negm;   // minus the reference maximum, sixteen times: the addend the score products start from
+        float m = -INFINITY, mc = 0.0f, lsum = 0.0f;   // reference maximum as a dot product and as an exponent of two
+        f32x16 zero;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) zero[e] = 0.0f;
 
         // ---- helpers ----
         auto scores = [&](const char *tile, int mb, f32x16 &a) {
@@ -233,10 +234,8 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
         };
         // exponentials of one unit (32 keys x 32 queries) against the reference maximum; the rounded
         // probabilities are what the second product uses, so they are what the row sum adds up
-        // st holds raw dot products (minus the raw reference in the fast order, whose subc is the constant 0); the
-        // softmax scale and the change to base-2 exponentials are one fp32 multiply-add per score
-        auto exps = [&](const f32x16 &st, auto FAST, float subc, bf16x8 (&p)[2]) {
-            constexpr bool kFast = decltype(FAST)::value != 0;
+        // st holds raw dot products; the softmax scale and the change to base-2 exponentials are one fp32 multiply-add per score
+        auto exps = [&](const f32x16 &st, float subc, bf16x8 (&p)[2]) {
 #pragma unroll
             for (int ts = 0; ts < 2; ++ts) {
                 u32x4 pw;
@@ -244,71 +243,121 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
                 for (int e = 0; e < 4; ++e) {
                     bf16x2 pr;
                     const float x0 = st[8 * ts + 2 * e], x1 = st[8 * ts + 2 * e + 1];
-                    pr[0] = (__bf16)fast_exp2(kFast ? x0 * c : fmaf(x0, c, -subc));
-                    pr[1] = (__bf16)fast_exp2(kFast ? x1 * c : fmaf(x1, c, -subc));
+                    pr[0] = (__bf16)fast_exp2(fmaf(x0, c, -subc));
+                    pr[1] = (__bf16)fast_exp2(fmaf(x1, c, -subc));
                     lsum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lsum, false);
                     pw[e] = __builtin_bit_cast(uint32_t, pr);
                 }
                 p[ts] = __builtin_bit_cast(bf16x8, pw);
             }
         };
-        auto mask = [&](f32x16 &st, int key0) {   // keys past the end of the sample (causal: and above the diagonal)
+        // keys of a block from the lane's first on that the lane's query sees; accumulator register e holds key key0 + (e / 4) * 8 + 4 * half + e % 4
+        auto keys_left = [&](int key0) {
             int h = half;
             asm volatile("" : "+v"(h));   // keeps the sixteen thresholds from being computed at tile start and spilled
-            const int lim = (CAUSAL && iq + 1 < L ? iq + 1 : L) - key0 - 4 * h;   // accumulator register e holds key key0 + (e / 4) * 8 + 4 * half + e % 4
+            return (CAUSAL && iq + 1 < L ? iq + 1 : L) - key0 - 4 * h;
+        };
+        auto mask = [&](f32x16 &st, int key0) {   // keys past the end of the sample (causal: and above the diagonal)
+            const int lim = keys_left(key0);
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-                if ((e >> 2) * 8 + (e & 3) >= lim) st[e] = -INFINITY;
+                st[e] = (e >> 2) * 8 + (e & 3) >= lim ? -INFINITY : st[e];
         };
         auto unit_max = [&](const f32x16 &a, float mx) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) mx = fmaxf(mx, a[e]);
             return mx;
         };
-        auto kbuf = [&](int bsel) { return bsel == 0 ? K0 : (bsel == 1 ? K1 : K2); };
-        auto vbuf = [&](int bsel) { return bsel == 0 ? V0 : (bsel == 1 ? V1 : V2); };
+        auto kbuf = [&](int b) { return stages + b * kDmaTile; };
+        auto vbuf = [&](int b) { return stages + (3 + b) * kDmaTile; };
 
-        // pipelined(): fast order against the fixed reference maximum m
-        auto pipelined = [&](auto BUF, auto RAGGED, int j) {
-            constexpr int P = decltype(BUF)::value;   // buffer of this stage: j % 3
-            constexpr bool kRagged = decltype(RAGGED)::value != 0;
-            const char *const Kc = P == 0 ? K0 : (P == 1 ? K1 : K2);
-            const char *const Vc = P == 0 ? V0 : (P == 1 ? V1 : V2);
+        // ---- the fast order, against the fixed reference maximum m ----
+        // Sixteen groups over the two 32-key blocks b of a stage.  A group holds one product of each kind and a pair of
+        // exponentials, none of which needs another's result: O^T += V^T P^T of stage j's block b, the scores of stage
+        // j + 1's block b, and the exponentials of the block between them (stage j's block 1 beside b = 0, stage j + 1's
+        // block 0 beside b = 1).  The groups are kept in this order, operand reads kAhead groups before their use.  The reference is
+        // subtracted in the multiply-add of the exponent: as the score products' addend it would take sixteen registers.
+        constexpr int kAhead = 2;
+        f32x16 sc[2];      // scores of block 0 / 1, until their exponentials are taken
+        u32x4 pw[2][2];    // rounded probabilities of block 0 / 1
+        auto fence = []() { __builtin_amdgcn_sched_barrier(0); };
+        auto exp_pair = [&](const f32x16 &st, int g, u32x4 (&w)[2], auto MASKED, int lim) {   // keys 2 g and 2 g + 1 of this lane's sixteen
+            bf16x2 pr;
+            pr[0] = (__bf16)fast_exp2(fmaf(st[2 * g], c, -mc));
+            pr[1] = (__bf16)fast_exp2(fmaf(st[2 * g + 1], c, -mc));
+            uint32_t both = __builtin_bit_cast(uint32_t, pr);
+            if constexpr (decltype(MASKED)::value != 0) {   // keys from lim on, counted from the lane's first, weigh nothing
+                const int key = (g >> 1) * 8 + (g & 1) * 2;
+                both &= key + 1 < lim ? 0xffffffffu : key < lim ? 0xffffu : 0u;
+            }
+            lsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, both), ones, lsum, false);
+            asm volatile("" : "+v"(both), "+v"(lsum));   // computed here, not where they are used a round later
+            w[g >> 2][g & 3] = both;
+        };
+        auto value_operand = [&](const char *Vc, const int (&vaddr)[kDBlocks], int g) {   // group g of a stage
+            const char *pvp = Vc + ((g >> 3) * 32 + ((g >> 2) & 1) * 16) * 256 + vaddr[g & 3];
+            return concat(lds_read_tr16(pvp), lds_read_tr16(pvp + 8 * 256));
+        };
+        auto stage_body = [&](const char *Kn, const char *Vc, auto MASKED, int key_next) {   // MASKED: stage j + 1's scores
             int kaddr[kKSteps], vaddr[kDBlocks];
             lds_addresses(kaddr, vaddr);
-            f32x16 s0 = negm, s1 = negm;   // the dot products start at minus the (raw) reference: no subtraction later
-            bf16x8 p0[2], p1[2];
-            {
-                bf16x8 ka[kKSteps], kb[kKSteps];
+            bf16x8 kop[2 * kKSteps], vop[2 * kKSteps];
+            int lim = 0;
+            if constexpr (decltype(MASKED)::value != 0) lim = keys_left(key_next);
+            auto read = [&](int g) {
+                kop[g] = lds_read_b128(Kn + (g >> 3) * 32 * 256 + kaddr[g & 7]);
+                vop[g] = value_operand(Vc, vaddr, g);
+            };
 #pragma unroll
-                for (int ks = 0; ks < kKSteps; ++ks) ka[ks] = lds_read_b128(Kc + kaddr[ks]);
+            for (int g = 0; g < kAhead; ++g) read(g);
+            fence();
 #pragma unroll
-                for (int ks = 0; ks < kKSteps; ++ks) kb[ks] = lds_read_b128(Kc + 32 * 256 + kaddr[ks]);
-#pragma unroll
-                for (int ks = 0; ks < kKSteps; ++ks) s0 = mfma_32x32x16(ka[ks], qreg[ks], s0);
-#pragma unroll
-                for (int ks = 0; ks < kKSteps; ++ks) s1 = mfma_32x32x16(kb[ks], qreg[ks], s1);   // scores of key block 1 ...
-                // issue order: the first block's operand reads, then one read of the second block behind each
-                // matrix product of the first, so that LDS latency hides under the matrix pipe
-                __builtin_amdgcn_sched_group_barrier(0x100, kKSteps, 0);
-#pragma unroll
-                for (int ks = 0; ks < kKSteps; ++ks) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                }
-                __builtin_amdgcn_sched_group_barrier(0x008, kKSteps, 0);
+            for (int g = 0; g < 2 * kKSteps; ++g) {
+                const int b = g >> 3, gi = g & 7;
+                if (g + kAhead < 2 * kKSteps) read(g + kAhead);
+                o[gi & 3] = mfma_32x32x16(vop[g], __builtin_bit_cast(bf16x8, pw[b][gi >> 2]), o[gi & 3]);
+                fence();
+                sc[b] = mfma_32x32x16(kop[g], qreg[gi], gi == 0 ? zero : sc[b]);
+                fence();
+                if (b == 0) exp_pair(sc[1], gi, pw[1], IntC<0>{}, 0);
+                else exp_pair(sc[0], gi, pw[0], MASKED, lim);
+                fence();
             }
-            if (kRagged) mask(s0, j * kDmaBN);
-            exps(s0, IntC<1>{}, 0.0f, p0);             // ... VALU: exponentials of key block 0
-            accumulate(Vc, 0, p0, vaddr);              // matrix pipe: O^T += V^T P^T of key block 0 ...
-            if (kRagged) mask(s1, j * kDmaBN + 32);
-            exps(s1, IntC<1>{}, 0.0f, p1);             // ... VALU: exponentials of key block 1
-            accumulate(Vc, 1, p1, vaddr);
+        };
+        // The wave's last stage: scores and block 0's probabilities are there.  two_blocks: block 1 has keys for it.
+        auto last_stage = [&](const char *Vc, bool two_blocks, int key0) {
+            int kaddr[kKSteps], vaddr[kDBlocks];
+            lds_addresses(kaddr, vaddr);
+            bf16x8 vop[2 * kKSteps];
+            auto product = [&](int g) {
+                o[g & 3] = mfma_32x32x16(vop[g], __builtin_bit_cast(bf16x8, pw[g >> 3][(g >> 2) & 1]), o[g & 3]);
+            };
+            constexpr int kEarly = CROSS ? 2 : 4;
+#pragma unroll
+            for (int g = 0; g < kEarly; ++g) vop[g] = value_operand(Vc, vaddr, g);
+            if (two_blocks) {
+                const int lim = keys_left(key0 + 32);
+                fence();
+#pragma unroll
+                for (int g = 0; g < 2 * kKSteps; ++g) {
+                    if (g + kEarly < 2 * kKSteps) vop[g + kEarly] = value_operand(Vc, vaddr, g + kEarly);
+                    product(g);
+                    if (g < kKSteps) exp_pair(sc[1], g, pw[1], IntC<1>{}, lim);
+                    fence();
+                }
+            } else {
+#pragma unroll
+                for (int g = 0; g < kKSteps; ++g) {
+                    if (g + kEarly < kKSteps) vop[g + kEarly] = value_operand(Vc, vaddr, g + kEarly);
+                    product(g);
+                    fence();
+                }
+            }
         };
         // conservative(): maximum first, rescale, then exponentials; used when a tile had to be restarted
         auto conservative = [&](int bsel, int j) {
             const char *const Kc = kbuf(bsel);
-            const char *const Vc = vbuf(bsel);
+            const char *const Vc = kbuf(bsel);   // see vaddr0
             int kaddr[kKSteps], vaddr[kDBlocks];
             lds_addresses(kaddr, vaddr);
             f32x16 s0, s1;
@@ -325,79 +374,102 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
             for (int db = 0; db < kDBlocks; ++db)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) o[db][e] *= a;
-            exps(s0, IntC<0>{}, n * c, p0);
+            exps(s0, n * c, p0);
             accumulate(Vc, 0, p0, vaddr);
-            exps(s1, IntC<0>{}, n * c, p1);
+            exps(s1, n * c, p1);
             accumulate(Vc, 1, p1, vaddr);
         };
 
-        // ---- pass 1: pipelined, three stage buffers, DMA two stages ahead ----
-        // Stage j lives in buffer j % 3.  At the top of stage j the DMA of stage j + 2 is issued into the buffer
-        // that stage j - 1 has just released; at the end of stage j each wave waits until only those newest
-        // DMA operations are outstanding (so stage j + 1 has landed) and meets the others at a bare s_barrier.
-        auto issue_stage = [&](auto BUF, int j) {
-            constexpr int Bf = decltype(BUF)::value;
-            issue(kbase, Bf == 0 ? K0 : (Bf == 1 ? K1 : K2), j, true);
-            issue(vbase, Bf == 0 ? V0 : (Bf == 1 ? V1 : V2), j, false);
-        };
-        auto run_stage = [&](auto BUF, auto RAGGED, int j) {
-            constexpr int Bf = decltype(BUF)::value;
-            const bool ahead = j + 2 < n_stages;
-            if (ahead) issue_stage(IntC<(Bf + 2) % 3>{}, j + 2);
-            if (CAUSAL && decltype(RAGGED)::value != 0) {
-                // A masking stage of a causal tile, seen by one wave: its 32 queries lie inside one 64-key stage.  Earlier
-                // stages hold only keys below all of them (no mask, and all inside the sample), later ones only keys above.
-                const int j_diagonal = (q_tile0 + wave * 32) / kDmaBN;
-                if (wave_active && j < j_diagonal) pipelined(BUF, IntC<0>{}, j);
-                else if (wave_active && j == j_diagonal) pipelined(BUF, IntC<1>{}, j);
-            } else if (wave_active) {
-                pipelined(BUF, RAGGED, j);
-            }
+        // ---- pass 1: three stage buffers for K and three for V, copies two stages ahead ----
+        // Stage j of either lives in buffer j % 3.  Round j multiplies stage j of V and stage j + 1 of K, so the buffers free at
+        // its top are K's j % 3 and V's (j + 2) % 3: the copies of K's stage j + 3 and V's stage j + 2 are sent there.  At its
+        // end each wave waits until only those are outstanding (so what round j + 1 reads has landed) and meets the others
+        // at a bare s_barrier.
+        auto round_end = [&](bool k_ahead, bool v_ahead) {
             asm volatile("" ::: "memory");
-            if (ahead) __builtin_amdgcn_s_waitcnt(0x0070 | kDmaOpsPerStage);   // vmcnt(ops of one stage) lgkmcnt(0)
-            else __builtin_amdgcn_s_waitcnt(0x0070);                           // vmcnt(0) lgkmcnt(0)
+            if (k_ahead) __builtin_amdgcn_s_waitcnt(0x0070 | kDmaOpsPerStage);            // vmcnt(K and V of one stage) lgkmcnt(0)
+            else if (v_ahead) __builtin_amdgcn_s_waitcnt(0x0070 | kDmaOpsPerStage / 2);
+            else __builtin_amdgcn_s_waitcnt(0x0070);
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
         };
+        // The stages this wave needs (causal: its 32 queries lie inside one 64-key stage, which is its last) and whether the
+        // last one's second block has keys for it.
+        const int n_mine = CAUSAL && (q_tile0 + wave * 32) / kDmaBN + 1 < n_stages ? (q_tile0 + wave * 32) / kDmaBN + 1 : n_stages;
+        const bool two_blocks = (n_mine - 1) * kDmaBN + 32 < (CAUSAL && q_tile0 + wave * 32 + 32 < L ? q_tile0 + wave * 32 + 32 : L);
+        auto issue_round = [&](int b, int j) {   // b = j % 3
+            if (j + 3 < n_stages) issue(kbase, kbuf(b), j + 3, true);
+            if (j + 2 < n_stages) issue(vbase, vbuf(b == 0 ? 2 : b - 1), j + 2, false);
+        };
+        auto round = [&](int b, auto MASKED, int j) {   // any but the wave's last
+            issue_round(b, j);
+            stage_body(kbuf(b == 2 ? 0 : b + 1), kbuf(b), MASKED, (j + 1) * kDmaBN);
+            round_end(j + 3 < n_stages, j + 2 < n_stages);
+        };
 
         load_q(t);
-        issue_stage(IntC<0>{}, 0);
-        if (n_stages > 1) issue_stage(IntC<1>{}, 1);
+        issue(kbase, kbuf(0), 0, true);
+        issue(vbase, vbuf(0), 0, false);
+        if (n_stages > 1) {
+            issue(kbase, kbuf(1), 1, true);
+            issue(vbase, vbuf(1), 1, false);
+        }
         if (wave == 0) claim_next();   // overlaps with the loads in flight
 #pragma unroll
         for (int ks = 0; ks < kKSteps; ++ks) asm volatile("" : "+v"(qreg[ks]));   // Q loads complete here
-        // Stage 0 has landed once at most one stage's loads are outstanding: what this wave sent after it is stage 1
-        // (and, on wave 0, the loads of the claim, which it has waited for itself).
-        if (n_stages > 1) __builtin_amdgcn_s_waitcnt(0x0070 | kDmaOpsPerStage); else __builtin_amdgcn_s_waitcnt(0x0070);
-        __syncthreads();
-        if (tid == 0) restart = 0;   // nobody looks at it between the previous tile's check and this barrier
-        if (wave_active) {   // reference maximum: the first 32 keys
-            f32x16 s0;
-            scores(K0, 0, s0);
-            if (CAUSAL || L < 32) mask(s0, 0);
-            m = pair_max(unit_max(s0, -INFINITY));
-        }
+        if (tid == 0) restart = 0;   // nobody looks at it between the barrier at the top of the loop and the next one
+        // K's stage 0 has landed once at most what this wave sent after it is outstanding (on wave 0 also
+        // the loads of the claim, which it has waited for itself).
+        if (n_stages > 1) __builtin_amdgcn_s_waitcnt(0x0070 | (2 * kDmaOpsPerStage - kDmaOpsPerStage / 2));
+        else __builtin_amdgcn_s_waitcnt(0x0070);   // and V's, the only other copies: no second wait
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (n_stages > 2) issue(kbase, kbuf(2), 2, true);
+        if (wave_active) {   // reference maximum: the first 32 keys; their exponentials beside the scores of the next 32
+            int kaddr[kKSteps], vaddr[kDBlocks];
+            lds_addresses(kaddr, vaddr);
+            constexpr int kEarly = CROSS ? 4 : kKSteps;
+            bf16x8 kop[kKSteps];
+            scores(kbuf(0), 0, sc[0]);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) negm[e] = -m;
-        asm volatile("" : "+v"(negm));   // sixteen real registers: the matrix product reads its addend from them
-        {
-            // stages with all 64 keys valid for every query of the tile; the others follow in the masking form:
-            // the sample's ragged last stage, and if causal the stages that reach above the tile's first query
-            const int n_full = (CAUSAL && q_tile0 + 1 < L ? q_tile0 + 1 : L) / kDmaBN;
-            int j = 0;
-            for (; j + 3 <= n_full; j += 3) {
-                run_stage(IntC<0>{}, IntC<0>{}, j);
-                run_stage(IntC<1>{}, IntC<0>{}, j + 1);
-                run_stage(IntC<2>{}, IntC<0>{}, j + 2);
+            for (int g = 0; g < kEarly; ++g) kop[g] = lds_read_b128(kbuf(0) + 32 * 256 + kaddr[g]);
+            fence();
+            if (n_mine == 1) mask(sc[0], 0);
+            m = pair_max(unit_max(sc[0], -INFINITY));
+            mc = m * c;
+#pragma unroll
+            for (int g = 0; g < kKSteps; ++g) {
+                if (g + kEarly < kKSteps) kop[g + kEarly] = lds_read_b128(kbuf(0) + 32 * 256 + kaddr[g + kEarly]);
+                sc[1] = mfma_32x32x16(kop[g], qreg[g], g == 0 ? zero : sc[1]);
+                exp_pair(sc[0], g, pw[0], IntC<0>{}, 0);
+                fence();
             }
-            if (j < n_full) { run_stage(IntC<0>{}, IntC<0>{}, j); ++j; }
-            if (j < n_full) { run_stage(IntC<1>{}, IntC<0>{}, j); ++j; }
-            for (; j < n_stages; ++j) {       // masking stages (one at most unless causal), stage j in buffer j % 3
-                const int r = j % 3;
-                if (r == 0) run_stage(IntC<0>{}, IntC<1>{}, j);
-                else if (r == 1) run_stage(IntC<1>{}, IntC<1>{}, j);
-                else run_stage(IntC<2>{}, IntC<1>{}, j);
+        }
+        // round 0 needs V's stage 0 and K's stage 1; K's stage 2 and V's stage 1 may be on their way
+        if (n_stages > 1) round_end(n_stages > 2, true);
+        int j = 0;
+        if (wave_active) {
+            for (; j + 5 <= n_mine; j += 3) {
+                round(0, IntC<0>{}, j);
+                round(1, IntC<0>{}, j + 1);
+                round(2, IntC<0>{}, j + 2);
             }
+            // One to four rounds are left, which take one copy of the code: the last but one is followed by masked scores (the others'
+            // masks let everything pass), the last has its own form.
+            int b = 0;
+#pragma unroll 1
+            for (; j + 1 < n_mine; ++j) {
+                round(b, IntC<1>{}, j);
+                b = b == 2 ? 0 : b + 1;
+            }
+            issue_round(b, j);
+            last_stage(kbuf(b), two_blocks, j * kDmaBN);
+            if (j + 1 < n_stages) round_end(j + 3 < n_stages, j + 2 < n_stages);
+            ++j;
+        }
+        for (; j + 1 < n_stages; ++j) {   // rounds in which this wave only copies (the last one has nothing to copy)
+            issue_round(j % 3, j);
+            round_end(j + 3 < n_stages, j + 2 < n_stages);
         }
         // a row sum this large (or not finite) means the fixed reference was too far below the true maximum
         if (wave_active && __builtin_amdgcn_ballot_w64(!(lsum < 0x1p62f)) != 0 && lane == 0) restart = 1;
@@ -406,8 +478,8 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
 
         // ---- pass 2 (never on data of one scale): the whole tile again, maximum first, two buffers ----
         if (again) {
-            issue(kbase, K0, 0, true);
-            issue(vbase, V0, 0, false);
+            issue(kbase, kbuf(0), 0, true);
+            issue(vbase, vbuf(0), 0, false);
             __builtin_amdgcn_s_waitcnt(0x0070);
             __syncthreads();
             m = -INFINITY;
@@ -438,7 +510,7 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
         // 16-byte chunk ch at (ch ^ (r & 7)) << 4.
         const float l_total = pair_sum(lsum);
         {
-            char *const region = (wave < 4 ? K2 : V2) + (wave & 3) * 4096;
+            char *const region = (wave < 4 ? kbuf(2) : vbuf(2)) + (wave & 3) * 4096;
             const float inv = 1.0f / l_total;
             int lane_e = lane;   // every address below derives from this copy, which the compiler cannot see
             asm volatile("" : "+v"(lane_e));   // through: otherwise they are computed at tile start and spilled
