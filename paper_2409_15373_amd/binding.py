@@ -7,6 +7,7 @@ CPU fallback.
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 from typing import Optional, Tuple
 
@@ -150,11 +151,36 @@ def _pick(dtype: torch.dtype, bf16_name: str):
     raise TypeError(f"unsupported dtype {dtype}: bf16 or fp32")
 
 
+# Calls that allocate their own results go through C++ where that has been built (csrc/jfa_autograd.cpp); None from
+# there means that the call is not an ordinary one, and the function goes on with it here.
+_calls = None   # the module; False where there is none
+
+
+def _load_calls():
+    global _calls
+    from . import autograd, build
+    if os.path.exists(build.native_path(torch.__version__)):
+        autograd._load_native()
+        _calls = autograd._native
+    else:
+        _calls = False
+    return _calls
+
+
+def _native(name: str, *args):
+    if torch.compiler.is_compiling():
+        return None
+    calls = _load_calls() if _calls is None else _calls
+    return getattr(calls, name)(*args) if calls else None
+
+
 def jfa_forward(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, offsets: torch.Tensor, max_len: int,
                 out: Optional[torch.Tensor] = None, lse: Optional[torch.Tensor] = None, causal: bool = False
                 ) -> Tuple[torch.Tensor, torch.Tensor]:
     """out [sum_B, H, D] (dtype of q) and lse fp32 [H, sum_B]; dispatches on q.dtype (bf16 / fp32).
     causal: row i of a sample attends to rows 0 .. i only (jfa_forward_causal)."""
+    if out is None and lse is None and (pair := _native("forward", q, k, v, offsets, max_len, causal)) is not None:
+        return pair
     sum_B, H, D = q.shape
     assert k.shape == q.shape and v.shape == q.shape and k.dtype == q.dtype and v.dtype == q.dtype
     assert offsets.dtype == torch.int64 and offsets.is_cuda and offsets.dim() == 1
@@ -202,6 +228,8 @@ def jfa_backward(q, k, v, out, dout, lse, offsets, max_len: int, dq=None, dk=Non
 
 def jfa_forward_cross(q, k, v, offsets_q, offsets_kv, max_len_q: int, max_len_kv: int, out=None, lse=None):
     """Cross attention: out [sum_Bq, H, D] and lse fp32 [H, sum_Bq]; q rows follow offsets_q, k and v rows offsets_kv."""
+    if out is None and lse is None and (pair := _native("forward_cross", q, k, v, offsets_q, offsets_kv, max_len_q, max_len_kv)) is not None:
+        return pair
     sum_Bq, H, D = q.shape
     assert k.shape == v.shape and k.shape[1:] == q.shape[1:] and k.dtype == q.dtype == v.dtype
     assert offsets_q.numel() == offsets_kv.numel()
@@ -295,6 +323,9 @@ def jfa_unfused_apply_transposed(array, x, offsets, sq_offsets, max_len: int, ou
     return out
 
 
+_ZERO_IS_ZEROS = (torch.bfloat16, torch.float16, torch.float32)   # types whose 0.0 is a pattern of zeros that _pad_pattern takes
+
+
 def _row_bytes(t: torch.Tensor, lead: int) -> int:
     assert t.is_contiguous()
     n = t.element_size()
@@ -317,6 +348,9 @@ def _pad_pattern(dtype: torch.dtype, pad: float) -> int:
 def jfa_jagged_to_dense(values: torch.Tensor, offsets: torch.Tensor, max_len: int, pad: float = 0.0,
                         dense: Optional[torch.Tensor] = None) -> torch.Tensor:
     """dense [B, max_len, ...] from values [sum_B, ...]: rows i >= L_b of each sample hold `pad`."""
+    if dense is None and type(pad) is float and pad == 0.0 and math.copysign(1.0, pad) > 0.0 and values.dtype in _ZERO_IS_ZEROS and (
+            filled := _native("to_dense", values, offsets, max_len)) is not None:
+        return filled
     B = offsets.numel() - 1
     if dense is None:
         dense = torch.empty((B, max_len) + tuple(values.shape[1:]), dtype=values.dtype, device=values.device)
@@ -327,6 +361,8 @@ def jfa_jagged_to_dense(values: torch.Tensor, offsets: torch.Tensor, max_len: in
 
 def jfa_dense_to_jagged(dense: torch.Tensor, offsets: torch.Tensor, values: torch.Tensor) -> torch.Tensor:
     """values[offsets[b] + i] = dense[b, i] for i < L_b; `values` [sum_B, ...] is caller-provided (the host does not know sum_B)."""
+    if (filled := _native("to_jagged", dense, offsets, values)) is not None:
+        return filled
     B, max_len = dense.shape[0], dense.shape[1]
     assert offsets.numel() - 1 == B and _row_bytes(dense, 2) == _row_bytes(values, 1)
     _check(load().jfa_dense_to_jagged(_ptr(dense), _ptr(offsets), B, max_len, _row_bytes(dense, 2), _ptr(values), _stream()))
@@ -336,6 +372,8 @@ def jfa_dense_to_jagged(dense: torch.Tensor, offsets: torch.Tensor, values: torc
 def jfa_jagged_dense_bmm(x: torch.Tensor, w: torch.Tensor, offsets: torch.Tensor, max_len: int,
                          out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """out [sum_B, T] = x [sum_B, D] times w [B, D, T], sample by sample (bf16)."""
+    if out is None and (made := _native("dense_bmm", x, w, offsets, max_len)) is not None:
+        return made
     B, D, T = w.shape
     assert offsets.numel() - 1 == B and x.shape[1] == D
     out = torch.empty((x.shape[0], T), dtype=x.dtype, device=x.device) if out is None else out
@@ -346,6 +384,8 @@ def jfa_jagged_dense_bmm(x: torch.Tensor, w: torch.Tensor, offsets: torch.Tensor
 def jfa_jagged_jagged_bmm(x: torch.Tensor, y: torch.Tensor, offsets: torch.Tensor, max_len: int,
                           out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """out [B, D, T] = per-sample x^T y for x [sum_B, D], y [sum_B, T] (bf16)."""
+    if out is None and (made := _native("jagged_bmm", x, y, offsets, max_len)) is not None:
+        return made
     B, D, T = offsets.numel() - 1, x.shape[1], y.shape[1]
     out = torch.empty((B, D, T), dtype=x.dtype, device=x.device) if out is None else out
     _check(load().jfa_jagged_jagged_bmm(_ptr(x), _ptr(y), _ptr(offsets), B, max_len, D, T, _ptr(out), _stream()))
@@ -354,6 +394,8 @@ def jfa_jagged_jagged_bmm(x: torch.Tensor, y: torch.Tensor, offsets: torch.Tenso
 
 def jfa_jagged_softmax(x: torch.Tensor, offsets: torch.Tensor, max_len: int, y: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Softmax along each sample's rows, per column, of x [sum_B, D] (bf16)."""
+    if y is None and (made := _native("softmax", x, offsets, max_len)) is not None:
+        return made
     y = torch.empty_like(x) if y is None else y
     _check(load().jfa_jagged_softmax(_ptr(x), _ptr(offsets), offsets.numel() - 1, max_len, x.shape[1], _ptr(y), _stream()))
     return y
@@ -361,6 +403,8 @@ def jfa_jagged_softmax(x: torch.Tensor, offsets: torch.Tensor, max_len: int, y: 
 
 def jfa_jagged_softmax_backward(y: torch.Tensor, dy: torch.Tensor, offsets: torch.Tensor, max_len: int,
                                 dx: Optional[torch.Tensor] = None) -> torch.Tensor:
+    if dx is None and (made := _native("softmax_backward", y, dy, offsets, max_len)) is not None:
+        return made
     dx = torch.empty_like(y) if dx is None else dx
     _check(load().jfa_jagged_softmax_backward(_ptr(y), _ptr(dy), _ptr(offsets), offsets.numel() - 1, max_len, y.shape[1],
                                               _ptr(dx), _stream()))

@@ -10,6 +10,8 @@
 #include <pybind11/functional.h>
 #include <torch/extension.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/jit/frontend/tracer.h>
 #include <c10/hip/HIPStream.h>
 
 namespace {
@@ -27,11 +29,22 @@ using ForwardCross = int (*)(const void *, const void *, const void *, const int
 using BackwardCross = int (*)(const void *, const void *, const void *, const void *, const void *, const float *, const int64_t *,
                               const int64_t *, int64_t, int64_t, int64_t, int, int, void *, void *, void *, float *, void *);
 
+using ToDense = int (*)(const void *, const int64_t *, int64_t, int64_t, int64_t, uint32_t, void *, void *);
+using ToJagged = int (*)(const void *, const int64_t *, int64_t, int64_t, int64_t, void *, void *);
+using Product = int (*)(const void *, const void *, const int64_t *, int64_t, int64_t, int, int, void *, void *);
+using Softmax = int (*)(const void *, const int64_t *, int64_t, int64_t, int, void *, void *);
+using SoftmaxBackward = int (*)(const void *, const void *, const int64_t *, int64_t, int64_t, int, void *, void *);
+
 struct Library {   // [0]: bf16, [1]: fp32
     Forward forward[2], forward_causal[2];
     Backward backward[2], backward_causal[2];
     ForwardCross forward_cross[2];
     BackwardCross backward_cross[2];
+    ToDense to_dense;
+    ToJagged to_jagged;
+    Product dense_bmm, jagged_bmm;
+    Softmax softmax;
+    SoftmaxBackward softmax_backward;
     PyObject *check = nullptr;   // binding._check: raises JfaError for a status that is not JFA_OK
     PyObject *pointer = nullptr;   // binding._ptr: raises AssertionError for a tensor that is not contiguous or not on the GPU
 };
@@ -177,6 +190,169 @@ std::optional<Tensor> cross_attention(const Tensor &q, const Tensor &k, const Te
     }
 }
 
+// ---- the binding's calls without gradients, results allocated here ----
+// What bounds a call on a small batch is the host again: the ctypes call and the Python around it took 7.5 us, twice a small batch's
+// kernel; from here a call takes 4.4 (four bf16 samples of up to 64 rows; fp32, where the kernel takes longer, 6.3).  The functions take the arguments as the interpreter has them; whatever
+// is not exactly what they expect, and whatever goes wrong, is answered with None: the Python function takes the call and raises what there is to raise.
+const Tensor *exact_tensor(PyObject *o) {
+    if (!THPVariable_CheckExact(o)) return nullptr;
+    const Tensor &t = THPVariable_Unpack(o);
+    using c10::DispatchKey;
+    // tensors that stand for others (function transforms, fake and functional tensors) have one of these keys
+    constexpr c10::DispatchKeySet stands_for_others({DispatchKey::Python, DispatchKey::Functionalize, DispatchKey::FuncTorchBatched,
+                                                     DispatchKey::FuncTorchGradWrapper, DispatchKey::BatchedNestedTensor, DispatchKey::Conjugate,
+                                                     DispatchKey::Negative, DispatchKey::ZeroTensor});
+    return t.key_set().has_any(stands_for_others) || !plain(t) ? nullptr : &t;
+}
+bool as_int64(PyObject *o, int64_t *x) {
+    if (!PyLong_CheckExact(o)) return false;
+    int overflow = 0;
+    *x = PyLong_AsLongLongAndOverflow(o, &overflow);
+    return overflow == 0;
+}
+bool nobody_listens() {   // no dispatch mode, function transform or tracer is to see the allocations
+    using c10::DispatchKey;
+    constexpr c10::DispatchKeySet modes({DispatchKey::Python, DispatchKey::PythonTLSSnapshot, DispatchKey::FuncTorchDynamicLayerFrontMode,
+                                         DispatchKey::FuncTorchVmapMode, DispatchKey::Functionalize});
+    return !c10::impl::tls_local_dispatch_key_set().included_.has_any(modes) && !torch::jit::tracer::isTracing();
+}
+// (q, k, v, offsets, max_len, causal), or with offsets_kv, max_len_q, max_len_kv for cross attention
+template <bool kCross> PyObject *forward_call(PyObject *, PyObject *const *args, Py_ssize_t n_args) {
+    HANDLE_TH_ERRORS
+    int64_t max_len = 0, max_len_kv = 0;
+    const Tensor *q, *k, *v, *offsets, *offsets_kv = nullptr;
+    if (n_args != (kCross ? 7 : 6) || !nobody_listens() || !(q = exact_tensor(args[0])) || !(k = exact_tensor(args[1])) || !(v = exact_tensor(args[2])) ||
+        !(offsets = exact_tensor(args[3])) || (kCross && !(offsets_kv = exact_tensor(args[4]))) || !as_int64(args[kCross ? 5 : 4], &max_len) ||
+        (kCross && !as_int64(args[6], &max_len_kv)) || (!kCross && !PyBool_Check(args[5])))
+        Py_RETURN_NONE;
+    const at::ScalarType type = q->scalar_type();
+    const bool shapes = q->dim() == 3 && k->dim() == 3 && k->sizes() == v->sizes() &&
+                        (kCross ? k->size(1) == q->size(1) && k->size(2) == q->size(2) && offsets_kv->numel() == offsets->numel() : k->sizes() == q->sizes());
+    if (!shapes || (type != at::kBFloat16 && type != at::kFloat) || k->scalar_type() != type || v->scalar_type() != type || !plain_offsets(*offsets) ||
+        (kCross && !plain_offsets(*offsets_kv)))
+        Py_RETURN_NONE;
+    const int f32 = type == at::kFloat;
+    Tensor out, lse;
+    int status;
+    {
+        pybind11::gil_scoped_release nogil;
+        out = at::empty(q->sizes(), q->options());
+        lse = at::empty({q->size(1), q->size(0)}, q->options().dtype(at::kFloat));
+        const int64_t B = offsets->numel() - 1;
+        const int H = (int)q->size(1), D = (int)q->size(2);
+        if constexpr (kCross)
+            status = lib.forward_cross[f32](q->data_ptr(), k->data_ptr(), v->data_ptr(), longs(*offsets), longs(*offsets_kv), B, max_len, max_len_kv, H, D,
+                                            out.data_ptr(), floats(lse), stream());
+        else
+            status = (args[5] == Py_True ? lib.forward_causal : lib.forward)[f32](q->data_ptr(), k->data_ptr(), v->data_ptr(), longs(*offsets), B, max_len, H, D,
+                                                                                 out.data_ptr(), floats(lse), stream());
+    }
+    if (status != 0) Py_RETURN_NONE;
+    PyObject *pair = PyTuple_New(2);
+    if (!pair) return nullptr;
+    PyTuple_SET_ITEM(pair, 0, THPVariable_Wrap(std::move(out)));
+    PyTuple_SET_ITEM(pair, 1, THPVariable_Wrap(std::move(lse)));
+    return pair;
+    END_HANDLE_TH_ERRORS
+}
+// (values, offsets, max_len): rows past a sample's end become zeros
+PyObject *to_dense_call(PyObject *, PyObject *const *args, Py_ssize_t n_args) {
+    HANDLE_TH_ERRORS
+    int64_t max_len = 0;
+    const Tensor *values, *offsets;
+    if (n_args != 3 || !nobody_listens() || !(values = exact_tensor(args[0])) || !(offsets = exact_tensor(args[1])) || !as_int64(args[2], &max_len) ||
+        max_len < 0 || values->dim() < 1 || !plain_offsets(*offsets) || offsets->numel() < 1)
+        Py_RETURN_NONE;
+    std::vector<int64_t> sizes{offsets->numel() - 1, max_len};
+    int64_t row_bytes = (int64_t)values->element_size();
+    for (int64_t d = 1; d < values->dim(); ++d) {
+        sizes.push_back(values->size(d));
+        row_bytes *= values->size(d);
+    }
+    Tensor dense;
+    int status;
+    {
+        pybind11::gil_scoped_release nogil;
+        dense = at::empty(sizes, values->options());
+        status = lib.to_dense(values->data_ptr(), longs(*offsets), sizes[0], max_len, row_bytes, 0, dense.data_ptr(), stream());
+    }
+    if (status != 0) Py_RETURN_NONE;
+    return THPVariable_Wrap(std::move(dense));
+    END_HANDLE_TH_ERRORS
+}
+// (dense, offsets, values): values, filled
+PyObject *to_jagged_call(PyObject *, PyObject *const *args, Py_ssize_t n_args) {
+    HANDLE_TH_ERRORS
+    const Tensor *dense, *offsets, *values;
+    if (n_args != 3 || !nobody_listens() || !(dense = exact_tensor(args[0])) || !(offsets = exact_tensor(args[1])) || !(values = exact_tensor(args[2])) ||
+        dense->dim() < 2 || values->dim() < 1 || !plain_offsets(*offsets) || offsets->numel() - 1 != dense->size(0))
+        Py_RETURN_NONE;
+    int64_t row_bytes = (int64_t)dense->element_size(), values_row = (int64_t)values->element_size();
+    for (int64_t d = 2; d < dense->dim(); ++d) row_bytes *= dense->size(d);
+    for (int64_t d = 1; d < values->dim(); ++d) values_row *= values->size(d);
+    if (row_bytes != values_row) Py_RETURN_NONE;
+    int status;
+    {
+        pybind11::gil_scoped_release nogil;
+        status = lib.to_jagged(dense->data_ptr(), longs(*offsets), dense->size(0), dense->size(1), row_bytes, values->data_ptr(), stream());
+    }
+    if (status != 0) Py_RETURN_NONE;
+    Py_INCREF(args[2]);
+    return args[2];
+    END_HANDLE_TH_ERRORS
+}
+// The feature operators on bf16: (x, w or y, offsets, max_len), the softmax (x, offsets, max_len)
+enum class Feature { kDenseBmm, kJaggedBmm, kSoftmax, kSoftmaxBackward };
+template <Feature kOp> PyObject *feature_call(PyObject *, PyObject *const *args, Py_ssize_t n_args) {
+    HANDLE_TH_ERRORS
+    constexpr int kTensors = kOp == Feature::kSoftmax ? 1 : 2;
+    int64_t max_len = 0;
+    const Tensor *a, *b = nullptr, *offsets;
+    if (n_args != kTensors + 2 || !nobody_listens() || !(a = exact_tensor(args[0])) || (kTensors == 2 && !(b = exact_tensor(args[1]))) ||
+        !(offsets = exact_tensor(args[kTensors])) || !as_int64(args[kTensors + 1], &max_len) || !plain_offsets(*offsets) || offsets->numel() < 1 ||
+        a->dim() != 2 || a->scalar_type() != at::kBFloat16 || (b && b->scalar_type() != at::kBFloat16))
+        Py_RETURN_NONE;
+    const int64_t B = offsets->numel() - 1, n = a->size(0), D = a->size(1);
+    if constexpr (kOp == Feature::kDenseBmm)
+        if (b->dim() != 3 || b->size(0) != B || b->size(1) != D) Py_RETURN_NONE;
+    if constexpr (kOp == Feature::kJaggedBmm)
+        if (b->dim() != 2 || b->size(0) != n) Py_RETURN_NONE;
+    if constexpr (kOp == Feature::kSoftmaxBackward)
+        if (b->sizes() != a->sizes()) Py_RETURN_NONE;
+    if (D > 128 || (b && b->size(-1) > 128)) Py_RETURN_NONE;
+    Tensor out;
+    int status;
+    {
+        pybind11::gil_scoped_release nogil;
+        if constexpr (kOp == Feature::kDenseBmm || kOp == Feature::kJaggedBmm) {
+            const int T = (int)b->size(-1);
+            constexpr bool kDense = kOp == Feature::kDenseBmm;
+            out = kDense ? at::empty({n, T}, a->options()) : at::empty({B, D, T}, a->options());
+            status = (kDense ? lib.dense_bmm : lib.jagged_bmm)(a->data_ptr(), b->data_ptr(), longs(*offsets), B, max_len, (int)D, T, out.data_ptr(), stream());
+        } else {
+            out = at::empty(a->sizes(), a->options());
+            if constexpr (kOp == Feature::kSoftmax)
+                status = lib.softmax(a->data_ptr(), longs(*offsets), B, max_len, (int)D, out.data_ptr(), stream());
+            else
+                status = lib.softmax_backward(a->data_ptr(), b->data_ptr(), longs(*offsets), B, max_len, (int)D, out.data_ptr(), stream());
+        }
+    }
+    if (status != 0) Py_RETURN_NONE;
+    return THPVariable_Wrap(std::move(out));
+    END_HANDLE_TH_ERRORS
+}
+#define JFA_CALL(name, function) {name, (PyCFunction)(void (*)())function, METH_FASTCALL, nullptr}
+PyMethodDef calls[] = {JFA_CALL("forward", forward_call<false>),
+                       JFA_CALL("forward_cross", forward_call<true>),
+                       JFA_CALL("to_dense", to_dense_call),
+                       JFA_CALL("to_jagged", to_jagged_call),
+                       JFA_CALL("dense_bmm", feature_call<Feature::kDenseBmm>),
+                       JFA_CALL("jagged_bmm", feature_call<Feature::kJaggedBmm>),
+                       JFA_CALL("softmax", feature_call<Feature::kSoftmax>),
+                       JFA_CALL("softmax_backward", feature_call<Feature::kSoftmaxBackward>),
+                       {nullptr, nullptr, 0, nullptr}};
+#undef JFA_CALL
+
 // entry: name of an entry point -> its address
 void bind_library(const std::function<int64_t(const std::string &)> &entry, pybind11::object check, pybind11::object pointer) {
     const char *suffix[2] = {"", "_f32"};
@@ -189,6 +365,13 @@ void bind_library(const std::function<int64_t(const std::string &)> &entry, pybi
         lib.forward_cross[i] = reinterpret_cast<ForwardCross>(at("jfa_forward_cross", i));
         lib.backward_cross[i] = reinterpret_cast<BackwardCross>(at("jfa_backward_cross", i));
     }
+    auto plain_entry = [&](const char *name) { return (uintptr_t)entry(name); };
+    lib.to_dense = reinterpret_cast<ToDense>(plain_entry("jfa_jagged_to_dense"));
+    lib.to_jagged = reinterpret_cast<ToJagged>(plain_entry("jfa_dense_to_jagged"));
+    lib.dense_bmm = reinterpret_cast<Product>(plain_entry("jfa_jagged_dense_bmm"));
+    lib.jagged_bmm = reinterpret_cast<Product>(plain_entry("jfa_jagged_jagged_bmm"));
+    lib.softmax = reinterpret_cast<Softmax>(plain_entry("jfa_jagged_softmax"));
+    lib.softmax_backward = reinterpret_cast<SoftmaxBackward>(plain_entry("jfa_jagged_softmax_backward"));
     lib.check = check.release().ptr();   // kept for the life of the process
     lib.pointer = pointer.release().ptr();
 }
@@ -199,4 +382,5 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
     m.def("bind_library", &bind_library);
     m.def("self_attention", &self_attention);
     m.def("cross_attention", &cross_attention);
+    if (PyModule_AddFunctions(m.ptr(), calls) != 0) throw pybind11::error_already_set();
 }

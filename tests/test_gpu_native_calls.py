@@ -1,0 +1,83 @@
+"""Calls that go through C++ (results allocated there) against the same calls through ctypes, bit for bit, and what the C++ side
+leaves to the Python functions: their errors stay."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def inputs(dtype=torch.bfloat16, B=5, rows=150, H=2, D=64):
+    g = torch.Generator().manual_seed(5)
+    offsets = torch.tensor([0, 40, 40, 41, 110, rows], dtype=torch.int64).cuda()
+    q, k, v = (torch.randn(rows, H, D, generator=g).to(dtype).cuda() for _ in range(3))
+    return q, k, v, offsets
+
+
+def both(monkeypatch, call):
+    from paper_2409_15373_amd import binding
+    assert binding._load_calls(), "the C++ calls are not built"
+    native = call(binding)
+    with monkeypatch.context() as m:
+        m.setattr(binding, "_calls", False)
+        python = call(binding)
+    native, python = (x if isinstance(x, tuple) else (x,) for x in (native, python))
+    assert len(native) == len(python)
+    for a, b in zip(native, python):
+        assert a.shape == b.shape and a.dtype == b.dtype and a.device == b.device and a.is_contiguous() and a.requires_grad == b.requires_grad
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_forward(monkeypatch, dtype):
+    q, k, v, offsets = inputs(dtype)
+    q.requires_grad_()
+    both(monkeypatch, lambda b: b.jfa_forward(q, k, v, offsets, 70))
+    both(monkeypatch, lambda b: b.jfa_forward(q, k, v, offsets, 70, causal=True))
+    both(monkeypatch, lambda b: b.jfa_forward_cross(q, k, v, offsets, offsets, 70, 70))
+
+
+def test_conversions_and_feature_operators(monkeypatch):
+    q, _, _, offsets = inputs()
+    both(monkeypatch, lambda b: b.jfa_jagged_to_dense(q, offsets, 72))
+    both(monkeypatch, lambda b: b.jfa_jagged_to_dense(q, offsets, 72, pad=-0.0))   # not a pattern of zeros
+    dense = torch.randn(5, 72, 2, 64, device="cuda").bfloat16()
+    both(monkeypatch, lambda b: b.jfa_dense_to_jagged(dense, offsets, torch.zeros_like(q)))
+    x, y, w = q[:, 0].contiguous(), q[:, 1, :32].contiguous(), torch.randn(5, 64, 32, device="cuda").bfloat16()
+    both(monkeypatch, lambda b: b.jfa_jagged_dense_bmm(x, w, offsets, 70))
+    both(monkeypatch, lambda b: b.jfa_jagged_jagged_bmm(x, y, offsets, 70))
+    both(monkeypatch, lambda b: b.jfa_jagged_softmax(x, offsets, 70))
+    both(monkeypatch, lambda b: b.jfa_jagged_softmax_backward(x, x, offsets, 70))
+
+
+def test_errors_stay():
+    from paper_2409_15373_amd import binding
+    q, k, v, offsets = inputs()
+    for call, error in [(lambda: binding.jfa_forward(q, k[1:], v, offsets, 70), AssertionError),
+                        (lambda: binding.jfa_forward(q.half(), k.half(), v.half(), offsets, 70), TypeError),
+                        (lambda: binding.jfa_forward(q.cpu(), k, v, offsets, 70), AssertionError),
+                        (lambda: binding.jfa_forward(q.transpose(0, 1), k.transpose(0, 1), v.transpose(0, 1), offsets, 70), AssertionError),
+                        (lambda: binding.jfa_forward(q, k, v, offsets.int(), 70), AssertionError),
+                        (lambda: binding.jfa_forward(q, k, v, offsets, -1), binding.JfaError),
+                        (lambda: binding.jfa_forward(q[..., :16].contiguous(), k[..., :16].contiguous(), v[..., :16].contiguous(), offsets, 70), binding.JfaError),
+                        (lambda: binding.jfa_forward_cross(q, k, v, offsets, offsets[1:], 70, 70), AssertionError),
+                        (lambda: binding.jfa_jagged_to_dense(q, offsets, -1), RuntimeError),
+                        (lambda: binding.jfa_dense_to_jagged(q[None], offsets, q), AssertionError)]:
+        with pytest.raises(error):
+            call()
+
+
+def test_a_dispatch_mode_sees_the_allocations():
+    from torch.utils._python_dispatch import TorchDispatchMode
+    from paper_2409_15373_amd import binding
+
+    class Seen(TorchDispatchMode):
+        ops = ()
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.ops += (str(func),)
+            return func(*args, **(kwargs or {}))
+
+    q, k, v, offsets = inputs()
+    with Seen() as seen:
+        binding.jfa_forward(q, k, v, offsets, 70)
+    assert any("empty" in op for op in seen.ops)
