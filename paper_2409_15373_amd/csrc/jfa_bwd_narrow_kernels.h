@@ -297,6 +297,82 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 3) void dkv_narrow_kernel(
                     }
                 }
             };
+            // A stage without a mask, its two blocks of 32 queries in turn: the matrix instructions of block 0's scores and dP, of block
+            // 1's, of block 0's gradients, of block 1's; block 0's vector work stands between the second, block 1's between the
+            // third, two or four scores behind each matrix instruction, and operands are read kAhead matrix instructions ahead.
+            // What a wave does between its own matrix instructions costs next to nothing; block by block the other waves of the SIMD had
+            // to fill the gaps.  Microseconds, H * D = 512: 1024 samples of 1 to 1024 rows, D = 64, 1903 -> 1785 (causal 1293 -> 1249),
+            // D = 32 2178 -> 2136; 64 of 4096 rows, D = 64, 4000 -> 3780.
+            auto run_stage = [&](const char *qt) {
+                constexpr int kS = 2 * kKSteps, kG = 4 * kDBlocks;   // matrix instructions of a block's scores and dP; of its gradients
+                const char *const dot = qt + N::kTile;
+                f32x16 sc[2], dp[2];
+                u32x4 pw[2][2], dw[2][2];
+                bf16x8 op[2 * kS + 2 * kG];
+                auto statistics = [&](int mb) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const float *stat = reinterpret_cast<const float *>(qt + N::kStage) + mb * 32 + g * 8 + half * 4;
+                        const f32x4 l4 = *reinterpret_cast<const f32x4 *>(stat), d4 = *reinterpret_cast<const f32x4 *>(stat + 64);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { sc[mb][4 * g + e] = l4[e]; dp[mb][4 * g + e] = d4[e]; }
+                    }
+                };
+                auto read = [&](int n) {
+                    if (n < 2 * kS) {
+                        const int mb = n / kS, i = n % kS;
+                        op[n] = lds_read_b128((i & 1 ? dot : qt) + mb * 32 * N::kRow + at.row[i >> 1]);
+                    } else {
+                        const int mb = (n - 2 * kS) / kG, i = (n - 2 * kS) % kG, ts = i / (2 * kDBlocks), db = (i >> 1) % kDBlocks;
+                        const char *t = (i & 1 ? qt : dot) + (mb * 32 + ts * 16) * N::kRow;
+                        op[n] = concat(lds_read_tr16(t + at.tr[0][db]), lds_read_tr16(t + at.tr[1][db]));
+                    }
+                };
+                auto multiply = [&](int n) {
+                    if (n < 2 * kS) {
+                        const int mb = n / kS, i = n % kS;
+                        if (i & 1) dp[mb] = mfma_32x32x16(op[n], vreg[i >> 1], dp[mb]);
+                        else sc[mb] = mfma_32x32x16(op[n], kreg[i >> 1], sc[mb]);
+                    } else {
+                        const int mb = (n - 2 * kS) / kG, i = (n - 2 * kS) % kG, ts = i / (2 * kDBlocks), db = (i >> 1) % kDBlocks;
+                        if (i & 1) acck[db] = mfma_32x32x16(op[n], __builtin_bit_cast(bf16x8, dw[mb][ts]), acck[db]);
+                        else accv[db] = mfma_32x32x16(op[n], __builtin_bit_cast(bf16x8, pw[mb][ts]), accv[db]);
+                    }
+                };
+                auto weigh = [&](int mb, int g) {   // P and dS of queries 2 g and 2 g + 1 of this lane's sixteen
+                    bf16x2 pr, dr;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const float x = fast_exp2(sc[mb][2 * g + e] * c);
+                        pr[e] = (__bf16)x;
+                        dr[e] = (__bf16)(dp[mb][2 * g + e] * x);
+                    }
+                    pw[mb][g >> 2][g & 3] = __builtin_bit_cast(uint32_t, pr);
+                    dw[mb][g >> 2][g & 3] = __builtin_bit_cast(uint32_t, dr);
+                };
+                constexpr int kAhead = D == 64 ? 3 : 2;   // D = 32 has 168 registers: a third spills
+                statistics(0);
+#pragma unroll
+                for (int n = 0; n < kAhead; ++n) read(n);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int n = 0; n < 2 * kS + 2 * kG; ++n) {
+                    if (n + kAhead < 2 * kS + 2 * kG) read(n + kAhead);
+                    if (n == kS / 2) statistics(1);
+                    multiply(n);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (n >= kS && n < 2 * kS) {
+#pragma unroll
+                        for (int u = 0; u < 8 / kS; ++u) weigh(0, (n - kS) * (8 / kS) + u);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (n >= 2 * kS && n < 2 * kS + kG) {
+#pragma unroll
+                        for (int u = 0; u < 8 / kG; ++u) weigh(1, (n - 2 * kS) * (8 / kG) + u);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            };
             // causal: the wave's 32 keys meet the diagonal in one stage, earlier ones are before all of them
             const int diagonal = CAUSAL ? k0 / kNwStageRows : 0;
             narrow_end_stage();   // the first stage has landed
@@ -305,10 +381,10 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 3) void dkv_narrow_kernel(
             for (int jj = first; jj < n_stages; ++jj) {
                 for (; !(jj & 1) && jj >= plain && jj + 3 <= n_full; jj += 2) {   // two steady stages at a time, buffers 0 and 1
                     issue(std::true_type{}, jj + 1, st + kBuffer);
-                    if (wave_active) run_block(st, jj, false);
+                    if (wave_active) run_stage(st);
                     narrow_end_stage();
                     issue(std::true_type{}, jj + 2, st);
-                    if (wave_active) run_block(st + kBuffer, jj + 1, false);
+                    if (wave_active) run_stage(st + kBuffer);
                     narrow_end_stage();
                 }
                 if (jj + 1 < n_stages) issue(std::false_type{}, jj + 1, st + (~jj & 1) * kBuffer);
