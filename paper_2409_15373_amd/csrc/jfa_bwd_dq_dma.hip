@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
                                                                      const __bf16 *__restrict__ v,
                                                                      const __bf16 *__restrict__ dout,
                                                                      const float *__restrict__ lse,
-                                                                     const __bf16 *__restrict__ out_fwd,   // dQ only; see below
+                                                                     const __bf16 *__restrict__ out_fwd,
                                                                      float *delta,
                                                                      const int64_t *__restrict__ offsets,
                                                                      const int64_t *__restrict__ offsets_other, int B, int H,
@@ -40,11 +40,6 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
     __shared__ __attribute__((aligned(1024))) char B0[kBdTile];
     __shared__ __attribute__((aligned(1024))) char B1[kBdTile];
     __shared__ __attribute__((aligned(1024))) char B2[kBdTile];
-    // Per lane, four copies each of minus lse * sqrt(D) (the log-sum-exp in units of the raw dot product) and
-    // minus delta of the lane's query.  The score and dP accumulators of every block start from these (four 16-byte
-    // LDS reads each, no VALU work, no registers held across the stage): P = exp2(c * acc) with c = log2(e) / sqrt(D)
-    // applied in fp32, and dS = P * acc.
-    __shared__ float4 lane_init[kBdThreads * 2];
     __shared__ WorkSlot slot;   // the NEXT work item, claimed and decoded while the current one starts up
     __shared__ LdsSchedule<CROSS> tab;   // the schedule, copied once per workgroup when it fits
 
@@ -70,11 +65,10 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
             for (int db = 0; db < kDBlocks; ++db)
                 taddr[h2][db] = (r + 8 * h2) * 256 + (((db * 4 + chunk_in_group) ^ swz(r + 8 * h2)) << 4) + byte_in_chunk;
     }
-    // What streams past a tile: first rows of K and V, the tile's queries' statistics, number of keys of the sample
+    // What streams past a tile: first rows of K and V, number of keys of the sample
     // and of stages (causal tiles need only a part of the sample).
     struct Stream {
         const __bf16 *abase, *bbase;
-        const float *delta_rows, *lse2_rows;   // plane 0 of the statistics buffer: delta; plane 1: -lse * sqrt(D)
         int L, Lc, js, n_stages;
     };
     auto stream_of = [&](const Work &w) {
@@ -89,9 +83,6 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
         const int64_t head_off = srow0 * row_stride + (int64_t)w.head * D;
         st.abase = k + head_off;
         st.bbase = v + head_off;
-        const int64_t qrow0 = w.row0;   // first query row of the sample
-        st.delta_rows = delta + (int64_t)w.head * sum_B + qrow0;
-        st.lse2_rows = delta + (int64_t)(H + w.head) * sum_B + qrow0;
         return st;
     };
     // The per-lane byte offsets of the two DMA chunks of a full stage are the same for every stage and both tensors:
@@ -176,7 +167,7 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
                 __bf16 *grow = grad + (t.row0 + i) * row_stride + (int64_t)t.head * D + (lane >> 5) * (D / 2);
 #pragma unroll
                 for (int e = 0; e < D / 2; e += 8) *reinterpret_cast<u32x4 *>(grow + e) = u32x4{0, 0, 0, 0};
-                if (out_fwd != nullptr && lane < 32) {   // out = 0 there: delta = 0; lse = -inf
+                if (lane < 32) {   // out = 0 there: delta = 0; lse = -inf
                     delta[(int64_t)t.head * sum_B + t.row0 + i] = 0.0f;
                     delta[(int64_t)(H + t.head) * sum_B + t.row0 + i] = INFINITY;
                 }
@@ -185,8 +176,6 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
             have = load_work<CROSS>(&slot, t);
             continue;
         }
-        const float *const delta_rows = cur.delta_rows;
-        const float *const lse2_rows = cur.lse2_rows;
 
         const int i = t.block * kDmaBlockRows + wave * 32 + col;
         const int ic = i < Ls ? i : Ls - 1;
@@ -196,6 +185,7 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
         if (n_stages - js > 1) issue_stage_from(cur, IntB<1>{}, js + 1);
         if (wave == 0) claim_next();   // overlaps with the loads in flight
         f32x16 acc[kDBlocks];
+        float my_lse2 = 0.0f, my_delta = 0.0f;   // this lane's query: log-sum-exp as an exponent of two, delta
 #pragma unroll
         for (int db = 0; db < kDBlocks; ++db)
 #pragma unroll
@@ -208,7 +198,7 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
             // addresses: the eight of the transposing reads are kept, of the row reads only one, and the others are
             // rebuilt per block with one XOR each (the swizzle makes them differ by a constant bit pattern); the empty
             // asm keeps the compiler from hoisting the rebuilt values back out of the loop.  (Keeping the row
-            // addresses too, or this lane's address in lane_init, spills in the stages and costs 10 %.)
+            // addresses too spills in the stages and costs 10 %.)
             int ra[kKSteps], ta[2][kDBlocks];
             {
                 int rb = raddr[0];
@@ -224,18 +214,6 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
             f32x16 sc, dp;
 #pragma unroll
             for (int e = 0; e < 16; ++e) { sc[e] = 0.0f; dp[e] = 0.0f; }
-            {   // both accumulators start at this lane's query's statistics: P = exp2(c * acc), dS = P * acc
-                int t_opaque = tid;
-                asm volatile("" : "+v"(t_opaque));   // the address is rebuilt here, not carried through the stage
-                int mine = (t_opaque >> 6) * 128 + (t_opaque & 63);   // index of this lane's first 16-byte slot
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    asm volatile("" : "+v"(mine));   // four separate loads: one load and twelve register copies would be VALU work
-                    const float4 l4 = lane_init[mine], d4 = lane_init[mine + 64];
-                    sc[4 * g] = l4.x; sc[4 * g + 1] = l4.y; sc[4 * g + 2] = l4.z; sc[4 * g + 3] = l4.w;
-                    dp[4 * g] = d4.x; dp[4 * g + 1] = d4.y; dp[4 * g + 2] = d4.z; dp[4 * g + 3] = d4.w;
-                }
-            }
             // operands are fetched four at a time to keep the register footprint at two waves per SIMD
 #pragma unroll
             for (int k4 = 0; k4 < kKSteps; k4 += 4) {
@@ -258,11 +236,11 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
             for (int g = 0; g < 4; ++g) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    float p = fast_exp2(sc[4 * g + e] * c);   // the scale is applied in fp32: operands stay exact
+                    float p = fast_exp2(fmaf(sc[4 * g + e], c, -my_lse2));   // the scale is applied in fp32: operands stay exact
                     const int r = j0 + mb * 32 + g * 8 + half * 4 + e;   // this register's streamed row
                     if (ragged && r >= (CAUSAL && ic + 1 < L ? ic + 1 : L)) p = 0.0f;   // past the sample's end, or above the diagonal
                     sc[4 * g + e] = p;
-                    dp[4 * g + e] = p * dp[4 * g + e];
+                    dp[4 * g + e] = p * (dp[4 * g + e] - my_delta);
                 }
             }
             // gradient accumulation: contraction over the 32 streamed rows in two steps of 16
@@ -278,6 +256,69 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
                 }
 #pragma unroll
                 for (int db = 0; db < kDBlocks; ++db) acc[db] = mfma_32x32x16(top[db], pb, acc[db]);
+            }
+        };
+        // A stage without a mask, its two blocks of 32 keys in turn: 48 matrix instructions, 32 of them (scores and dP) of block 0, then
+        // of block 1, 16 of the gradient.  Block 0's vector work stands between block 1's scores, block 1's between block 0's
+        // gradient products, and operands are read kAhead matrix instructions ahead.  The statistics are a register each, subtracted where
+        // the scores are scaled and from every dP; as the products' addends (four 16-byte reads per block and accumulator, a fifth of the
+        // stage's LDS traffic, which at 165 of 192 clocks per block came close to the matrix instructions' time) they cost more than the
+        // sixteen subtractions.  Microseconds, before -> now: 1024 x 4 of up to 1024 rows 1470 -> 1395; 512 x 8 bimodal to 4096, causal,
+        // 2005 -> 1914; 300 x 4 of up to 300 107 -> 104.
+        auto full_stage = [&](const char *At, const char *Bt) {
+            constexpr int kS = 2 * kKSteps, kG = 2 * kDBlocks;   // matrix instructions of a block's scores and dP; of its gradient
+            constexpr int kAhead = 3;
+            int ra0 = raddr[0];
+            asm volatile("" : "+v"(ra0));
+            f32x16 sc[2], dp[2];
+            u32x4 ds[2][2];
+            bf16x8 op[2 * kS + 2 * kG];
+            auto read = [&](int n) {
+                if (n < 2 * kS) {
+                    const int mb = n / kS, i = n % kS;
+                    op[n] = lds_read_b128((i & 1 ? Bt : At) + mb * 32 * 256 + (ra0 ^ ((i >> 1) << 5)));
+                } else {
+                    const int mb = (n - 2 * kS) / kG, i = (n - 2 * kS) % kG, ts = i / kDBlocks, db = i % kDBlocks;
+                    const char *base = At + (mb * 32 + ts * 16) * 256;
+                    op[n] = concat(lds_read_tr16(base + taddr[0][db]), lds_read_tr16(base + taddr[1][db]));
+                }
+            };
+            f32x16 zero;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) zero[e] = 0.0f;
+            auto multiply = [&](int n) {
+                if (n < 2 * kS) {
+                    const int mb = n / kS, i = n % kS;
+                    if (i & 1) dp[mb] = mfma_32x32x16(op[n], yreg[i >> 1], i == 1 ? zero : dp[mb]);
+                    else sc[mb] = mfma_32x32x16(op[n], xreg[i >> 1], i == 0 ? zero : sc[mb]);
+                } else {
+                    const int mb = (n - 2 * kS) / kG, i = (n - 2 * kS) % kG, ts = i / kDBlocks, db = i % kDBlocks;
+                    acc[db] = mfma_32x32x16(op[n], __builtin_bit_cast(bf16x8, ds[mb][ts]), acc[db]);
+                }
+            };
+            auto weigh = [&](int mb, int g) {   // dS of keys 2 g and 2 g + 1 of this lane's sixteen
+                bf16x2 dr;
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    dr[e] = (__bf16)((dp[mb][2 * g + e] - my_delta) * fast_exp2(fmaf(sc[mb][2 * g + e], c, -my_lse2)));
+                ds[mb][g >> 2][g & 3] = __builtin_bit_cast(uint32_t, dr);
+            };
+#pragma unroll
+            for (int n = 0; n < kAhead; ++n) read(n);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int n = 0; n < 2 * kS + 2 * kG; ++n) {
+                if (n + kAhead < 2 * kS + 2 * kG) read(n + kAhead);
+                multiply(n);
+                __builtin_amdgcn_sched_barrier(0);
+                if (n >= kS && n < 2 * kS && (n & 1)) {
+                    weigh(0, (n - kS) >> 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (n >= 2 * kS && n < 2 * kS + kG) {
+                    weigh(1, n - 2 * kS);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
         };
         auto issue_stage = [&](auto BUF, int j) { issue_stage_from(cur, BUF, j); };
@@ -302,9 +343,11 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
                         if (theirs * 32 >= Lc) continue;
                         if (theirs <= mine) run_block(RAGGED, At, Bt, mb, j0);
                     }
+                } else if (!ragged) {
+                    full_stage(At, Bt);
                 } else {
                     run_block(RAGGED, At, Bt, 0, j0);
-                    if (!ragged || j0 + 32 < Lc) run_block(RAGGED, At, Bt, 1, j0);
+                    if (j0 + 32 < Lc) run_block(RAGGED, At, Bt, 1, j0);
                 }
             }
             asm volatile("" ::: "memory");
@@ -319,34 +362,23 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
             asm volatile("" : "+v"(yreg[ks]));
         }
         {
-            // This lane's query's statistics: minus lse * sqrt(D) and minus delta = rowsum(dO o O).  With out_fwd given,
-            // this kernel is the first of the backward and computes them itself from the rows it holds (each lane of
-            // a pair has half of the row), leaving both planes of the statistics buffer for the dK / dV kernel;
-            // otherwise an earlier kernel has filled the buffer.
-            float nl, nd;
-            if (out_fwd != nullptr) {
-                const int64_t off = (t.row0 + ic) * row_stride + (int64_t)t.head * D + 8 * half;
-                float dot = 0.0f;
+            // This lane's query's statistics: log-sum-exp and delta = rowsum(dO o O), formed here from the rows the lanes hold (each
+            // lane of a pair has half of the row) and left in both planes of the statistics buffer for the dK / dV kernel.
+            const int64_t off = (t.row0 + ic) * row_stride + (int64_t)t.head * D + 8 * half;
+            float dot = 0.0f;
 #pragma unroll
-                for (int ks = 0; ks < kKSteps; ++ks) {
-                    const bf16x8 o = *reinterpret_cast<const bf16x8 *>(out_fwd + off + 16 * ks);
+            for (int ks = 0; ks < kKSteps; ++ks) {
+                const bf16x8 o = *reinterpret_cast<const bf16x8 *>(out_fwd + off + 16 * ks);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) dot = fmaf((float)o[e], (float)yreg[ks][e], dot);
-                }
-                dot = pair_sum(dot);
-                nl = -lse[(int64_t)t.head * sum_B + t.row0 + ic] * sqrtf((float)D);
-                nd = -dot;
-                if (i < Ls && half == 0) {
-                    delta[(int64_t)t.head * sum_B + t.row0 + i] = dot;
-                    delta[(int64_t)(H + t.head) * sum_B + t.row0 + i] = nl;
-                }
-            } else {
-                nl = lse2_rows[ic];
-                nd = -delta_rows[ic];
+                for (int e = 0; e < 8; ++e) dot = fmaf((float)o[e], (float)yreg[ks][e], dot);
             }
-            float4 *mine = lane_init + wave * 128 + lane;   // consecutive lanes, consecutive 16-byte slots: no bank
-            mine[0] = make_float4(nl, nl, nl, nl);          // conflicts; written and read by the same lane: no barrier
-            mine[64] = make_float4(nd, nd, nd, nd);
+            my_delta = pair_sum(dot);
+            const float l = lse[(int64_t)t.head * sum_B + t.row0 + ic];
+            my_lse2 = l * 1.4426950408889634f;
+            if (i < Ls && half == 0) {
+                delta[(int64_t)t.head * sum_B + t.row0 + i] = my_delta;
+                delta[(int64_t)(H + t.head) * sum_B + t.row0 + i] = -l * sqrtf((float)D);
+            }
         }
         // The first stage has landed once at most one stage's loads are outstanding: what this wave sent after it is
         // the second stage (and, on wave 0, the loads of the claim, which it has waited for itself).
