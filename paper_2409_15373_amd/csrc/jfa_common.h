@@ -28,6 +28,8 @@ struct Schedule {
     int build_rows = 0;
     bool static_only = false;
     int fixed_items = 4;   // up to this many items per workgroup are dealt without claims (kernels that walk with NarrowWalk)
+    // Blocks of every (sample, head), each a workgroup of its own, with no schedule at all (0: there is one); see direct_blocks()
+    int direct_blocks = 0;
 };
 
 // The chip has 8 accelerator dies (XCDs), each with its own L2, and workgroups are dealt to them round-robin
@@ -409,6 +411,24 @@ __device__ inline void claim_and_decode(WorkSlot *slot, const Schedule &s, const
     }
 }
 
+// Without a schedule (Schedule::direct_blocks) the item is the workgroup's index; false where the sample has no such block.
+__device__ inline bool direct_item(Work &t, const Schedule &s, const int64_t *offsets, const int64_t *offsets_other, int H, int block_rows) {
+    const int per_sample = H * s.direct_blocks, b = (int)blockIdx.x / per_sample, r = (int)blockIdx.x - b * per_sample;
+    t.sample = b;
+    t.head = r / s.direct_blocks;
+    t.block = r - t.head * s.direct_blocks;
+    t.row0 = offsets[b];
+    t.len = (int)(offsets[b + 1] - t.row0);
+    const int64_t *const oo = offsets_other ? offsets_other : offsets;
+    t.orow0 = oo[b];
+    t.olen = (int)(oo[b + 1] - t.orow0);
+    return t.block * block_rows < t.len;
+}
+template <auto Kernel, int AtLeast = 1>
+inline int item_grid(int threads, int B, int H, const Schedule &s, int cus) {
+    return s.direct_blocks ? B * H * s.direct_blocks : persistent_grid<Kernel, AtLeast>(threads, cus);
+}
+
 // A workgroup's LDS copy of a schedule of at most kTabCap samples (position p of the sorted order: first tile,
 // sample, rows): decoding a claimed work id then costs a few LDS reads instead of a chain of dependent global loads.
 // Declare it __shared__; CROSS adds the other side's rows.
@@ -511,6 +531,17 @@ struct ScheduleJob {
 hipError_t launch_schedules(const ScheduleJob *jobs, int n_jobs, int B, int32_t *counters, int n_counters, hipStream_t stream);
 hipError_t launch_check_offsets(const int64_t *offsets, int B, int64_t max_len, int *flags, hipStream_t stream);
 
+// Blocks per (sample, head) where every block that the bound on the lengths admits gets a workgroup of its own (those past a sample's
+// end leave at once) and there is no schedule; 0: there is one.  As long as there is a compute unit for each, nothing is to be
+// balanced and the schedule (a launch, or a sort in every workgroup) is all there is to save.  Fp32, microseconds of the kernels, with
+// and without a schedule: four samples of up to 64 rows, D = 32, forward 8.7 and 7.2, with backward 28.9 and 24.3; 8 x 2 of up to 600,
+// D = 64, 35.9 and 33.9, 147 and 141; 16 x 1 bimodal to 1000, D = 128, 93.9 and 92.1.  With more blocks than compute units the order, longest
+// first, is worth more: 300 x 2 of up to 100, D = 64, 32.9 and 35.3, 110 and 143; 2000 x 4 bimodal to 128, D = 128, 375 and 629.
+inline int direct_blocks(int64_t B, int64_t max_len, int H, int block_rows, int cus) {
+    const int64_t blocks = (max_len + block_rows - 1) / block_rows;
+    return blocks > 0 && blocks <= cus && B <= cus && B * H * blocks <= cus ? (int)blocks : 0;
+}
+
 // fp32 path
 // Rows per block (and per streamed stage) of an fp32 kernel, which is its workgroup size: 64 rows are four waves, the quarters
 // of a 64 x 64 square, 32 rows one wave.  Where at most 32 rows stream past a block two or three of the four waves have nothing
@@ -546,6 +577,15 @@ inline F32Form f32_form(int D, int64_t B, int64_t max_len, int H, int64_t max_st
 inline F32Form f32_key_form(const F32Form &queries, int64_t max_streamed, bool many) {
     if (queries.split) return {true, kF32SplitKeyRows};
     return {false, f32_block_rows(max_streamed, many)};
+}
+// The same on the fp32 matrix instructions, where a call whose samples have one block each at most needs no schedule either, however
+// many there are: streams are short, and the workgroups are dealt as places get free.  300 x 2 of up to 64 rows, D = 64, 23.7 -> 17.6,
+// with backward 87 -> 72; 2000 x 4 of up to 30, D = 32, 37 -> 23, 104 -> 88; 3000 x 4 bimodal to 30, D = 64, 64 -> 49, 210 -> 183;
+// 4000 x 4 of up to 20, D = 128, 203 -> 159, 763 -> 693.
+inline int f32_direct_blocks(const F32Form &form, int64_t B, int64_t max_len, int H, int64_t max_streamed, int cus) {
+    if (form.split) return 0;
+    if (max_len > 0 && max_len <= form.rows && max_streamed <= 128 && B * H < (int64_t)1 << 31) return 1;
+    return direct_blocks(B, max_len, H, form.rows, cus);
 }
 // Cross attention: offsets = the queries' offsets, offsets_kv = the keys' (nullptr: the same array); schedules are
 // built over the stationary side's offsets (s, s_dq: queries; s_dkv: keys).

@@ -181,14 +181,14 @@ __global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void fwd_f32_kerne
     const float scale = 1.0f / sqrtf((float)D);
     const bool small = s.build_rows != 0;   // small problem: no scheduler launch has run, the schedule is built here, in LDS
     if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
-    const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
+    const int64_t total = small || s.direct_blocks ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets[B];
     const int64_t row_stride = (int64_t)H * D;
 
     WorkCursor cursor;
     cursor.static_only = s.static_only || total <= f32_static_items<D>() * (int64_t)gridDim.x;
     Work t;   // keys: rows orow0 .. orow0 + olen - 1
-    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot); ++item) {
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot, kRows); ++item) {
         const int L = t.olen;
         const int q0 = t.block * kRows + rg * 32;      // first query of the wave
         const int i = q0 + col;                        // this lane's query
@@ -288,14 +288,14 @@ __global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void dq_f32_kernel
     const float scale = 1.0f / sqrtf((float)D);
     const bool small = s.build_rows != 0;
     if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
-    const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
+    const int64_t total = small || s.direct_blocks ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets[B];
     const int64_t row_stride = (int64_t)H * D;
 
     WorkCursor cursor;
     cursor.static_only = s.static_only || total <= f32_static_items<D>() * (int64_t)gridDim.x;
     Work t;
-    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot); ++item) {
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot, kRows); ++item) {
         const int L = t.olen;
         const int q0 = t.block * kRows + rg * 32;
         const int i = q0 + col;
@@ -381,14 +381,14 @@ __global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void dkv_f32_kerne
     const float scale = 1.0f / sqrtf((float)D);
     const bool small = s.build_rows != 0;
     if (small) build_small_work(offsets, offsets_q, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
-    const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
+    const int64_t total = small || s.direct_blocks ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets_q ? offsets_q[B] : offsets[B];   // lse and delta are indexed by query rows
     const int64_t row_stride = (int64_t)H * D;
 
     WorkCursor cursor;
     cursor.static_only = s.static_only || total <= f32_static_items<D>() * (int64_t)gridDim.x;
     Work t;   // queries: rows orow0 .. orow0 + olen - 1
-    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_q, B, H, cursor, total, &slot); ++item) {
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_q, B, H, cursor, total, &slot, kRows); ++item) {
         const int L = t.olen;
         const int k0 = t.block * kRows + rg * 32;      // first key of the wave
         const int j = k0 + col;                        // this lane's key
@@ -491,7 +491,7 @@ hipError_t launch_fwd_f32(const float *q, const float *k, const float *v, const 
     if (form.split) return launch_fwd_f32_split(q, k, v, offsets, offsets_kv, causal, B, H, D, s, out, lse, cus, stream);
 #define JFA_CASE(DD, W)                                                                                           \
     case DD * 1000 + f32_rows<W>():                                                                               \
-        hipLaunchKernelGGL((fwd_f32_kernel<DD, W>), dim3(persistent_grid<fwd_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
+        hipLaunchKernelGGL((fwd_f32_kernel<DD, W>), dim3(item_grid<fwd_f32_kernel<DD, W>>(64 * W, B, H, s, cus)), dim3(64 * W), 0, stream, \
                            q, k, v, offsets, offsets_kv, causal, B, H, s, out, lse);                              \
         break;
     switch (D * 1000 + form.rows) {
@@ -508,7 +508,7 @@ hipError_t launch_dq_f32(const float *q, const float *k, const float *v, const f
     if (form.split) return launch_dq_f32_split(q, k, v, out, dout, lse, offsets, offsets_kv, causal, B, H, D, s, dq, delta, cus, stream);
 #define JFA_CASE(DD, W)                                                                                            \
     case DD * 1000 + f32_rows<W>():                                                                                \
-        hipLaunchKernelGGL((dq_f32_kernel<DD, W>), dim3(persistent_grid<dq_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
+        hipLaunchKernelGGL((dq_f32_kernel<DD, W>), dim3(item_grid<dq_f32_kernel<DD, W>>(64 * W, B, H, s, cus)), dim3(64 * W), 0, stream, \
                            q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, B, H, s, dq);              \
         break;
     switch (D * 1000 + form.rows) {
@@ -525,7 +525,7 @@ hipError_t launch_dkv_f32(const float *q, const float *k, const float *v, const 
     if (form.split) return launch_dkv_f32_split(q, k, v, dout, lse, delta, offsets, offsets_q, causal, B, H, D, s, dk, dv, cus, stream);
 #define JFA_CASE(DD, W)                                                                                            \
     case DD * 1000 + f32_rows<W>():                                                                                \
-        hipLaunchKernelGGL((dkv_f32_kernel<DD, W>), dim3(persistent_grid<dkv_f32_kernel<DD, W>>(64 * W, cus)), dim3(64 * W), 0, stream, \
+        hipLaunchKernelGGL((dkv_f32_kernel<DD, W>), dim3(item_grid<dkv_f32_kernel<DD, W>>(64 * W, B, H, s, cus)), dim3(64 * W), 0, stream, \
                            q, k, v, dout, lse, delta, offsets, offsets_q, causal, B, H, s, dk, dv);                \
         break;
     switch (D * 1000 + form.rows) {
