@@ -354,6 +354,7 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
     sc.fixed_items = jfa::narrow_fixed_items(max_len_kv);
     const bool narrow = !f32 && D < 128;
     if (f32) sc.direct_blocks = jfa::f32_direct_blocks(form, B, max_len, H, max_len_kv, w.cus);
+    else if (dma) sc.direct_blocks = jfa::direct_blocks(B, max_len, H, block_rows, w.cus);
     if (sc.direct_blocks) {
         sc.static_only = true;   // no schedule
     } else if (!dma && (narrow ? narrow_small_problem(B, max_len, H, block_rows, w.cus) : small_problem(B, max_len, H, block_rows, w.cus))) {
@@ -421,8 +422,8 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     };
     const bool in_kernel = !dma && small(max_len, block_rows) && small(max_len_kv, key_rows);
     // (or no schedule at all, where neither side needs one)
-    int direct_q = f32 ? jfa::f32_direct_blocks(form_q, B, max_len, H, max_len_kv, w.cus) : 0;
-    int direct_k = f32 ? jfa::f32_direct_blocks(form_k, B, max_len_kv, H, max_len, w.cus) : 0;
+    int direct_q = f32 ? jfa::f32_direct_blocks(form_q, B, max_len, H, max_len_kv, w.cus) : dma ? jfa::direct_blocks(B, max_len, H, block_rows, w.cus) : 0;
+    int direct_k = f32 ? jfa::f32_direct_blocks(form_k, B, max_len_kv, H, max_len, w.cus) : dma ? jfa::direct_blocks(B, max_len_kv, H, key_rows, w.cus) : 0;
     if (!direct_q || !direct_k) direct_q = direct_k = 0;
     if (!in_kernel && !direct_q) {
         const int short_rows = f32 ? 0 : jfa::short_sample_rows(offsets_kv != nullptr, D, B, max_len, H, w.cus);
@@ -461,6 +462,8 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
         // 128-key blocks (schedule 1: blocks of keys, for cross attention from the keys' offsets)
         jfa::Schedule s_dq{w.order[0], w.tile_start[0], w.counters};
         jfa::Schedule s_dkv{w.order[1], w.tile_start[1], w.counters + 1};
+        s_dq.direct_blocks = direct_q;
+        s_dkv.direct_blocks = direct_k;
         { ScopedTimer tm("dq_bf16_dma", s); e = jfa::launch_bwd_dq_dma(q, k, v, out, dout, lse, delta, offsets, offsets_kv, causal, (int)B, H, D, s_dq, dq, w.cus, s); }
         if (e != hipSuccess) return hip_fail("dq_bf16_dma", e);
         { ScopedTimer tm("dkv_bf16_dma", s); e = jfa::launch_bwd_dkv_dma(q, k, v, dout, delta, offsets_k, offsets_q_other, causal, (int)B, H, D, s_dkv, dk, dv, w.cus, s); }

@@ -91,7 +91,8 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dkv_dma_kernel(const __bf16
     const bool is_a = wave < 4;
     const float scale = 1.0f / sqrtf((float)D);
     const float c = 1.4426950408889634f * scale;
-    const int64_t total = (int64_t)s.tile_start[B] * H;
+    const bool direct = s.direct_blocks != 0;   // no schedule: the item is the workgroup's index
+    const int64_t total = direct ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = CROSS ? offsets_other[B] : offsets[B];   // query rows
     const int64_t row_stride = (int64_t)H * D;
 
@@ -213,9 +214,13 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dkv_dma_kernel(const __bf16
         for (int ks = 0; ks < kKSteps; ++ks) sreg[ks] = *reinterpret_cast<const bf16x8 *>(src + off + 16 * ks);
     };
 
-    const bool tabled = B <= kTabCap;
+    const bool tabled = B <= kTabCap && !direct;
     WorkCursor cursor;
     auto claim_next = [&]() {   // wave 0, every lane
+        if (direct) {
+            if (lane == 0) slot.valid = 0;
+            return;
+        }
         if (!tabled) {
             claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_other : nullptr);
             return;
@@ -225,12 +230,12 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dkv_dma_kernel(const __bf16
         tab.decode(&slot, B, H, uniform64(w));
     };
     if (tid < kDkvPairs) handed[tid] = 0;
-    if (wave == 0) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_other : nullptr);
+    if (wave == 0 && !direct) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_other : nullptr);
     if (tabled) tab.fill(s, offsets, offsets_other, B);
     __syncthreads();
     uint32_t blocks_done = 0;   // P blocks this wave has written (A) or taken (B) since the kernel started
     Work t;
-    bool have = load_work<CROSS>(&slot, t);
+    bool have = direct ? direct_item(t, s, offsets, CROSS ? offsets_other : nullptr, H, kDkvBlockRows) : load_work<CROSS>(&slot, t);
     while (have) {
         __syncthreads();   // every wave has read the slot before wave 0 refills it
         const Stream cur = stream_of(t);
@@ -510,7 +515,7 @@ hipError_t launch_bwd_dkv_dma(const void *q, const void *k, const void *v, const
     if (D != kBdD || (causal && offsets_other)) return hipErrorInvalidValue;
 #define JFA_LAUNCH(CROSS, CAUSAL)                                                                                           \
     hipLaunchKernelGGL((bwd_dkv_dma_kernel<CROSS, CAUSAL>),                                                                \
-                       dim3(persistent_grid<bwd_dkv_dma_kernel<CROSS, CAUSAL>>(kBdThreads, cus)), dim3(kBdThreads), 0,      \
+                       dim3(item_grid<bwd_dkv_dma_kernel<CROSS, CAUSAL>>(kBdThreads, B, H, s, cus)), dim3(kBdThreads), 0,      \
                        stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, stats,        \
                        offsets, offsets_other, B, H, s, (__bf16 *)dk, (__bf16 *)dv)
     if (offsets_other) JFA_LAUNCH(true, false);

@@ -47,7 +47,8 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
     const int col = lane & 31, half = lane >> 5;
     const float scale = 1.0f / sqrtf((float)D);
     const float c = 1.4426950408889634f * scale;
-    const int64_t total = (int64_t)s.tile_start[B] * H;
+    const bool direct = s.direct_blocks != 0;   // no schedule: the item is the workgroup's index
+    const int64_t total = direct ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets[B];   // query rows: lse and delta are indexed by them
     const int64_t row_stride = (int64_t)H * D;
 
@@ -135,9 +136,13 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
 
     // The claim of the next item runs while a tile's first loads travel, and the tile cannot start before it is done:
     // with the schedule in LDS it is one atomic and a few LDS reads instead of five dependent trips to memory.
-    const bool tabled = B <= kTabCap;
+    const bool tabled = B <= kTabCap && !direct;
     WorkCursor cursor;
     auto claim_next = [&]() {   // wave 0, every lane
+        if (direct) {
+            if (lane == 0) slot.valid = 0;
+            return;
+        }
         if (!tabled) {
             claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_other : nullptr);
             return;
@@ -146,11 +151,11 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
         if (lane == 0) w = next_work(s.counter, cursor, total);
         tab.decode(&slot, B, H, uniform64(w));
     };
-    if (wave == 0) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_other : nullptr);
+    if (wave == 0 && !direct) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_other : nullptr);
     if (tabled) tab.fill(s, offsets, offsets_other, B);
     __syncthreads();   // the slot and the tables are written
     Work t;
-    bool have = load_work<CROSS>(&slot, t);
+    bool have = direct ? direct_item(t, s, offsets, CROSS ? offsets_other : nullptr, H, kDmaBlockRows) : load_work<CROSS>(&slot, t);
     while (have) {
         __syncthreads();   // every wave has read the slot before wave 0 refills it
         const Stream cur = stream_of(t);
@@ -467,7 +472,7 @@ hipError_t launch_bwd_dq_dma(const void *q, const void *k, const void *v, const 
                              int D, Schedule s, void *dq, int cus, hipStream_t stream) {
     if (D != kBdD || (causal && offsets_other)) return hipErrorInvalidValue;
 #define JFA_LAUNCH(CROSS, CAUSAL)                                                                                           \
-    hipLaunchKernelGGL((bwd_dq_dma_kernel<CROSS, CAUSAL>), dim3(persistent_grid<bwd_dq_dma_kernel<CROSS, CAUSAL>>(kBdThreads, cus)), \
+    hipLaunchKernelGGL((bwd_dq_dma_kernel<CROSS, CAUSAL>), dim3(item_grid<bwd_dq_dma_kernel<CROSS, CAUSAL>>(kBdThreads, B, H, s, cus)), \
                        dim3(kBdThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v,                \
                        (const __bf16 *)dout, lse, (const __bf16 *)out, delta, offsets, offsets_other, B, H, s, (__bf16 *)dq)
     if (offsets_other) JFA_LAUNCH(true, false);

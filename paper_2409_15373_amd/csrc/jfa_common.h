@@ -537,6 +537,8 @@ hipError_t launch_check_offsets(const int64_t *offsets, int B, int64_t max_len, 
 // and without a schedule: four samples of up to 64 rows, D = 32, forward 8.7 and 7.2, with backward 28.9 and 24.3; 8 x 2 of up to 600,
 // D = 64, 35.9 and 33.9, 147 and 141; 16 x 1 bimodal to 1000, D = 128, 93.9 and 92.1.  With more blocks than compute units the order, longest
 // first, is worth more: 300 x 2 of up to 100, D = 64, 32.9 and 35.3, 110 and 143; 2000 x 4 bimodal to 128, D = 128, 375 and 629.
+// bf16, D = 128, more than 256 rows: 8 x 4 of up to 600, forward 31.5 and 23.5, causal 30.1 and 20.2, with backward 98 and 84.5; 12 x 1 of up
+// to 1884 60.4 and 50.1, 194 and 174; 4 x 4 of 4096 140 and 127, 612 and 596.
 inline int direct_blocks(int64_t B, int64_t max_len, int H, int block_rows, int cus) {
     const int64_t blocks = (max_len + block_rows - 1) / block_rows;
     return blocks > 0 && blocks <= cus && B <= cus && B * H * blocks <= cus ? (int)blocks : 0;

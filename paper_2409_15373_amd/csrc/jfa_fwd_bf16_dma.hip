@@ -65,7 +65,8 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
     const float c = 1.4426950408889634f / sqrtf((float)D);
-    const int64_t total = (int64_t)s.tile_start[B] * H;
+    const bool direct = s.direct_blocks != 0;   // no schedule: the item is the workgroup's index
+    const int64_t total = direct ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets[B];
     const int64_t row_stride = (int64_t)H * D;
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
@@ -131,9 +132,13 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
     };
     // The claim of the next item runs while a tile's first loads travel, and the tile cannot start before it is done:
     // with the schedule in LDS it is one atomic and a few LDS reads instead of five dependent trips to memory.
-    const bool tabled = B <= kTabCap;
+    const bool tabled = B <= kTabCap && !direct;
     WorkCursor cursor;
     auto claim_next = [&]() {   // wave 0, every lane
+        if (direct) {
+            if (lane == 0) slot.valid = 0;
+            return;
+        }
         if (!tabled) {
             claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_kv : nullptr);
             return;
@@ -142,11 +147,11 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
         if (lane == 0) w = next_work(s.counter, cursor, total);
         tab.decode(&slot, B, H, uniform64(w));
     };
-    if (wave == 0) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_kv : nullptr);
+    if (wave == 0 && !direct) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_kv : nullptr);
     if (tabled) tab.fill(s, offsets, offsets_kv, B);
     __syncthreads();   // the slot and the tables are written
     Work t;
-    bool have = load_work<CROSS>(&slot, t);
+    bool have = direct ? direct_item(t, s, offsets, CROSS ? offsets_kv : nullptr, H, kDmaBlockRows) : load_work<CROSS>(&slot, t);
     while (have) {
         __syncthreads();   // every wave has read the slot before wave 0 refills it
         const Stream cur = stream_of(t);
@@ -551,7 +556,7 @@ hipError_t launch_fwd_bf16_dma(const void *q, const void *k, const void *v, cons
                                int cus, hipStream_t stream) {
     if (D != kDmaD || (causal && offsets_kv)) return hipErrorInvalidValue;
 #define JFA_LAUNCH(CROSS, CAUSAL)                                                                                          \
-    hipLaunchKernelGGL((fwd_bf16_dma_kernel<CROSS, CAUSAL>), dim3(persistent_grid<fwd_bf16_dma_kernel<CROSS, CAUSAL>>(kDmaThreads, cus)), \
+    hipLaunchKernelGGL((fwd_bf16_dma_kernel<CROSS, CAUSAL>), dim3(item_grid<fwd_bf16_dma_kernel<CROSS, CAUSAL>>(kDmaThreads, B, H, s, cus)), \
                        dim3(kDmaThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, offsets,     \
                        offsets_kv, B, H, s, (__bf16 *)out, lse)
     if (offsets_kv) JFA_LAUNCH(true, false);
