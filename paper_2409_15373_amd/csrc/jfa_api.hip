@@ -354,9 +354,10 @@ int forward_impl(const char *who, bool f32, bool causal, const void *q, const vo
     sc.fixed_items = jfa::narrow_fixed_items(max_len_kv);
     const bool narrow = !f32 && D < 128;
     if (f32) sc.direct_blocks = jfa::f32_direct_blocks(form, B, max_len, H, max_len_kv, w.cus);
-    else if (dma) sc.direct_blocks = jfa::direct_blocks(B, max_len, H, block_rows, w.cus);
-    if (sc.direct_blocks) {
-        sc.static_only = true;   // no schedule
+    else if (dma || narrow) sc.direct_blocks = jfa::direct_blocks(B, max_len, H, block_rows, w.cus);
+    if (sc.direct_blocks) {   // no schedule
+        sc.build_rows = block_rows;
+        sc.static_only = true;
     } else if (!dma && (narrow ? narrow_small_problem(B, max_len, H, block_rows, w.cus) : small_problem(B, max_len, H, block_rows, w.cus))) {
         sc.build_rows = block_rows;
         sc.static_only = true;
@@ -421,9 +422,11 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
         return !f32 && D < 128 ? narrow_small_problem(B, longest_stationary, H, rows, w.cus) : small_problem(B, longest_stationary, H, rows, w.cus);
     };
     const bool in_kernel = !dma && small(max_len, block_rows) && small(max_len_kv, key_rows);
-    // (or no schedule at all, where neither side needs one)
-    int direct_q = f32 ? jfa::f32_direct_blocks(form_q, B, max_len, H, max_len_kv, w.cus) : dma ? jfa::direct_blocks(B, max_len, H, block_rows, w.cus) : 0;
-    int direct_k = f32 ? jfa::f32_direct_blocks(form_k, B, max_len_kv, H, max_len, w.cus) : dma ? jfa::direct_blocks(B, max_len_kv, H, key_rows, w.cus) : 0;
+    // (or no schedule at all, where neither side needs one; the fp32 dK / dV kernel at D = 128 has no registers for that)
+    const int places = dma || D < 128 ? w.cus : 0;
+    int direct_q = f32 ? jfa::f32_direct_blocks(form_q, B, max_len, H, max_len_kv, w.cus) : jfa::direct_blocks(B, max_len, H, block_rows, places);
+    int direct_k = f32 ? jfa::f32_direct_blocks(form_k, B, max_len_kv, H, max_len, w.cus) : jfa::direct_blocks(B, max_len_kv, H, key_rows, places);
+    if (f32 && D == 128) direct_k = 0;
     if (!direct_q || !direct_k) direct_q = direct_k = 0;
     if (!in_kernel && !direct_q) {
         const int short_rows = f32 ? 0 : jfa::short_sample_rows(offsets_kv != nullptr, D, B, max_len, H, w.cus);
@@ -440,14 +443,13 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     if (f32) {
         jfa::Schedule s_dq{w.order[0], w.tile_start[0], w.counters};
         jfa::Schedule s_dkv{w.order[kv], w.tile_start[kv], w.counters + 1};
-        if (in_kernel) {   // every kernel builds the schedule of its own work items, in LDS
+        if (in_kernel || direct_q) {   // every kernel builds the schedule of its own work items, in LDS, or needs none
             s_dq.static_only = s_dkv.static_only = true;
             s_dq.build_rows = block_rows;
             s_dkv.build_rows = key_rows;
         }
         s_dq.direct_blocks = direct_q;
         s_dkv.direct_blocks = direct_k;
-        if (direct_q) s_dq.build_rows = s_dkv.build_rows = 0;
         ScopedTimer tm_bwd("bwd_f32", s);
         e = jfa::launch_dq_f32((const float *)q, (const float *)k, (const float *)v, (const float *)out, (const float *)dout, lse,
                                offsets, offsets_kv, causal, (int)B, H, D, s_dq, form_q, (float *)dq, delta, w.cus, s);
@@ -472,11 +474,13 @@ int backward_impl(const char *who, bool f32, bool causal, const void *q, const v
     }
     jfa::Schedule s_dq{w.order[0], w.tile_start[0], w.counters};
     jfa::Schedule s_dkv{w.order[kv], w.tile_start[kv], w.counters + 1};
-    if (in_kernel) {   // every kernel builds the schedule of its own work items, in LDS
+    if (in_kernel || direct_q) {   // every kernel builds the schedule of its own work items, in LDS, or needs none
         s_dq.static_only = s_dkv.static_only = true;
         s_dq.build_rows = block_rows;
         s_dkv.build_rows = key_rows;
     }
+    s_dq.direct_blocks = direct_q;
+    s_dkv.direct_blocks = direct_k;
     s_dq.fixed_items = jfa::narrow_fixed_items(max_len_kv);
     s_dkv.fixed_items = jfa::narrow_fixed_items(max_len);
     // the dQ kernel goes first: it computes delta = rowsum(dO o O) for its own rows and leaves it for the dK / dV kernel

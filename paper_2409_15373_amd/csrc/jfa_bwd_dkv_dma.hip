@@ -216,9 +216,11 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dkv_dma_kernel(const __bf16
 
     const bool tabled = B <= kTabCap && !direct;
     WorkCursor cursor;
-    auto claim_next = [&]() {   // wave 0, every lane
-        if (direct) {
-            if (lane == 0) slot.valid = 0;
+    auto claim_next = [&](const Work &now) {   // wave 0, every lane; now: the present item
+        if (direct) {   // the next block of a sample that is longer than the bound admits
+            Work next = now;
+            next.block += s.direct_blocks;
+            if (lane == 0) park_work<CROSS>(&slot, next, next.block * kDkvBlockRows < next.len);
             return;
         }
         if (!tabled) {
@@ -230,12 +232,14 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dkv_dma_kernel(const __bf16
         tab.decode(&slot, B, H, uniform64(w));
     };
     if (tid < kDkvPairs) handed[tid] = 0;
-    if (wave == 0 && !direct) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_other : nullptr);
+    if (direct) {
+        if (tid == 0) direct_first(&slot, s, offsets, CROSS ? offsets_other : nullptr, H, kDkvBlockRows);
+    } else if (wave == 0) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_other : nullptr);
     if (tabled) tab.fill(s, offsets, offsets_other, B);
     __syncthreads();
     uint32_t blocks_done = 0;   // P blocks this wave has written (A) or taken (B) since the kernel started
     Work t;
-    bool have = direct ? direct_item(t, s, offsets, CROSS ? offsets_other : nullptr, H, kDkvBlockRows) : load_work<CROSS>(&slot, t);
+    bool have = load_work<CROSS>(&slot, t);
     while (have) {
         __syncthreads();   // every wave has read the slot before wave 0 refills it
         const Stream cur = stream_of(t);
@@ -244,7 +248,7 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dkv_dma_kernel(const __bf16
         const int tile0 = t.block * kDkvBlockRows;
         const int n_stages = cur.n_stages;
         if (CROSS && L == 0) {   // no query streams past these keys: their gradients are zero
-            if (wave == 0) claim_next();
+            if (wave == 0) claim_next(t);
             const int i = tile0 + pair * 32 + (lane & 31);
             if (i < Ls) {
                 __bf16 *grow = (is_a ? dv : dk) + (t.row0 + i) * row_stride + (int64_t)t.head * D + (lane >> 5) * (D / 2);
@@ -261,7 +265,7 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dkv_dma_kernel(const __bf16
         const int js = cur.js;
         issue_stage_from(cur, IntB<0>{}, js);
         if (n_stages - js > 1) issue_stage_from(cur, IntB<1>{}, js + 1);
-        if (wave == 0) claim_next();   // overlaps with the loads in flight
+        if (wave == 0) claim_next(t);   // overlaps with the loads in flight
         f32x16 acc[kDBlocks];
 #pragma unroll
         for (int db = 0; db < kDBlocks; ++db)

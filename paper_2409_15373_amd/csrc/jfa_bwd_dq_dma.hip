@@ -138,9 +138,11 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
     // with the schedule in LDS it is one atomic and a few LDS reads instead of five dependent trips to memory.
     const bool tabled = B <= kTabCap && !direct;
     WorkCursor cursor;
-    auto claim_next = [&]() {   // wave 0, every lane
-        if (direct) {
-            if (lane == 0) slot.valid = 0;
+    auto claim_next = [&](const Work &now) {   // wave 0, every lane; now: the present item
+        if (direct) {   // the next block of a sample that is longer than the bound admits
+            Work next = now;
+            next.block += s.direct_blocks;
+            if (lane == 0) park_work<CROSS>(&slot, next, next.block * kDmaBlockRows < next.len);
             return;
         }
         if (!tabled) {
@@ -151,11 +153,13 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
         if (lane == 0) w = next_work(s.counter, cursor, total);
         tab.decode(&slot, B, H, uniform64(w));
     };
-    if (wave == 0 && !direct) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_other : nullptr);
+    if (direct) {
+        if (tid == 0) direct_first(&slot, s, offsets, CROSS ? offsets_other : nullptr, H, kDmaBlockRows);
+    } else if (wave == 0) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_other : nullptr);
     if (tabled) tab.fill(s, offsets, offsets_other, B);
     __syncthreads();   // the slot and the tables are written
     Work t;
-    bool have = direct ? direct_item(t, s, offsets, CROSS ? offsets_other : nullptr, H, kDmaBlockRows) : load_work<CROSS>(&slot, t);
+    bool have = load_work<CROSS>(&slot, t);
     while (have) {
         __syncthreads();   // every wave has read the slot before wave 0 refills it
         const Stream cur = stream_of(t);
@@ -166,7 +170,7 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
         const int js = cur.js;                     // first stage of the stream
         const int n_stages = cur.n_stages;
         if (CROSS && L == 0) {   // nothing streams past these rows: their gradient is zero
-            if (wave == 0) claim_next();
+            if (wave == 0) claim_next(t);
             const int i = t.block * kDmaBlockRows + wave * 32 + (lane & 31);
             if (i < Ls) {
                 __bf16 *grow = grad + (t.row0 + i) * row_stride + (int64_t)t.head * D + (lane >> 5) * (D / 2);
@@ -188,7 +192,7 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
         load_stationary(t);
         issue_stage_from(cur, IntB<0>{}, js);
         if (n_stages - js > 1) issue_stage_from(cur, IntB<1>{}, js + 1);
-        if (wave == 0) claim_next();   // overlaps with the loads in flight
+        if (wave == 0) claim_next(t);   // overlaps with the loads in flight
         f32x16 acc[kDBlocks];
         float my_lse2 = 0.0f, my_delta = 0.0f;   // this lane's query: log-sum-exp as an exponent of two, delta
 #pragma unroll

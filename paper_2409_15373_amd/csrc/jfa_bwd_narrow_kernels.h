@@ -412,7 +412,7 @@ hipError_t launch_dq_narrow_waves(const void *q, const void *k, const void *v, c
                                   int cus, hipStream_t stream) {
     if (causal && offsets_kv) return hipErrorInvalidValue;
 #define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                        \
-    hipLaunchKernelGGL((dq_narrow_kernel<DD, W, CROSS, CAUSAL>), dim3(persistent_grid<dq_narrow_kernel<DD, W, CROSS, CAUSAL>, W == 2 ? 2 : 1>(64 * W, cus)), \
+    hipLaunchKernelGGL((dq_narrow_kernel<DD, W, CROSS, CAUSAL>), dim3(item_grid<dq_narrow_kernel<DD, W, CROSS, CAUSAL>, W == 2 ? 2 : 1>(64 * W, B, H, s, cus)), \
                        dim3(64 * W), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, lse, \
                        (const __bf16 *)out, stats, offsets, offsets_kv, B, H, s, (__bf16 *)dq)
 #define JFA_CASE(DD)                                                                                         \
@@ -437,7 +437,7 @@ hipError_t launch_dkv_narrow_waves(const void *q, const void *k, const void *v, 
                                    hipStream_t stream) {
     if (causal && offsets_q) return hipErrorInvalidValue;
 #define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                        \
-    hipLaunchKernelGGL((dkv_narrow_kernel<DD, W, CROSS, CAUSAL>), dim3(persistent_grid<dkv_narrow_kernel<DD, W, CROSS, CAUSAL>, W == 2 ? 2 : 1>(64 * W, cus)), \
+    hipLaunchKernelGGL((dkv_narrow_kernel<DD, W, CROSS, CAUSAL>), dim3(item_grid<dkv_narrow_kernel<DD, W, CROSS, CAUSAL>, W == 2 ? 2 : 1>(64 * W, B, H, s, cus)), \
                        dim3(64 * W), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, stats, \
                        offsets, offsets_q, B, H, s, (__bf16 *)dk, (__bf16 *)dv)
 #define JFA_CASE(DD)                                                                                         \

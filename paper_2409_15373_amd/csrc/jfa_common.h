@@ -411,18 +411,50 @@ __device__ inline void claim_and_decode(WorkSlot *slot, const Schedule &s, const
     }
 }
 
-// Without a schedule (Schedule::direct_blocks) the item is the workgroup's index; false where the sample has no such block.
-__device__ inline bool direct_item(Work &t, const Schedule &s, const int64_t *offsets, const int64_t *offsets_other, int H, int block_rows) {
+// The reverse of load_work, by one lane.  (CROSS: see there.)
+template <bool CROSS>
+__device__ inline void park_work(WorkSlot *slot, const Work &t, bool valid) {
+    slot->valid = valid;
+    slot->sample = t.sample;
+    slot->head = t.head;
+    slot->block = t.block;
+    slot->len = t.len;
+    slot->row0_lo = (int)(uint32_t)t.row0;
+    slot->row0_hi = (int)(uint32_t)((uint64_t)t.row0 >> 32);
+    if (CROSS) {
+        slot->olen = t.olen;
+        slot->orow0_lo = (int)(uint32_t)t.orow0;
+        slot->orow0_hi = (int)(uint32_t)((uint64_t)t.orow0 >> 32);
+    }
+}
+
+// Without a schedule (Schedule::direct_blocks) a workgroup's item is its index: a block of a (sample, head); `mine` is filled by one
+// lane.  A sample that is longer than the bound admits has its further blocks done by the same workgroups, up to kSmallItems each.
+// The kernels' walks stay as they are: decoded there, as scalars, the items of calls with a schedule took up to 0.4 us longer to start.
+__device__ inline void direct_first(WorkSlot *slot, const Schedule &s, const int64_t *offsets, const int64_t *offsets_other, int H, int block_rows) {
     const int per_sample = H * s.direct_blocks, b = (int)blockIdx.x / per_sample, r = (int)blockIdx.x - b * per_sample;
+    const int64_t *const oo = offsets_other ? offsets_other : offsets;
+    Work t;
     t.sample = b;
     t.head = r / s.direct_blocks;
     t.block = r - t.head * s.direct_blocks;
     t.row0 = offsets[b];
     t.len = (int)(offsets[b + 1] - t.row0);
-    const int64_t *const oo = offsets_other ? offsets_other : offsets;
     t.orow0 = oo[b];
     t.olen = (int)(oo[b + 1] - t.orow0);
-    return t.block * block_rows < t.len;
+    park_work<true>(slot, t, t.block * block_rows < t.len);
+}
+__device__ inline void direct_small_work(SmallWork *mine, const Schedule &s, const int64_t *offsets, const int64_t *offsets_other, int H, int block_rows) {
+    if (threadIdx.x == 0) {
+        direct_first(&mine->item[0], s, offsets, offsets_other, H, block_rows);
+        int n = mine->item[0].valid;
+        while (n && n < kSmallItems && (mine->item[n - 1].block + s.direct_blocks) * block_rows < mine->item[0].len) {
+            mine->item[n] = mine->item[n - 1];
+            mine->item[n++].block += s.direct_blocks;
+        }
+        mine->count = n;
+    }
+    __syncthreads();
 }
 template <auto Kernel, int AtLeast = 1>
 inline int item_grid(int threads, int B, int H, const Schedule &s, int cus) {
@@ -539,6 +571,8 @@ hipError_t launch_check_offsets(const int64_t *offsets, int B, int64_t max_len, 
 // first, is worth more: 300 x 2 of up to 100, D = 64, 32.9 and 35.3, 110 and 143; 2000 x 4 bimodal to 128, D = 128, 375 and 629.
 // bf16, D = 128, more than 256 rows: 8 x 4 of up to 600, forward 31.5 and 23.5, causal 30.1 and 20.2, with backward 98 and 84.5; 12 x 1 of up
 // to 1884 60.4 and 50.1, 194 and 174; 4 x 4 of 4096 140 and 127, 612 and 596.
+// D = 64: 5 x 2 of up to 300 12.4 and 10.9, 40.9 and 36.4; 8 x 4 of up to 600 17.0 and 15.9, 57.9 and 53.3; with two blocks per compute
+// unit 20 x 3 Zipf to 700 loses, 18.3 and 19.7, 65 and 73.
 inline int direct_blocks(int64_t B, int64_t max_len, int H, int block_rows, int cus) {
     const int64_t blocks = (max_len + block_rows - 1) / block_rows;
     return blocks > 0 && blocks <= cus && B <= cus && B * H * blocks <= cus ? (int)blocks : 0;
@@ -583,7 +617,7 @@ inline F32Form f32_key_form(const F32Form &queries, int64_t max_streamed, bool m
 // The same on the fp32 matrix instructions, where a call whose samples have one block each at most needs no schedule either, however
 // many there are: streams are short, and the workgroups are dealt as places get free.  300 x 2 of up to 64 rows, D = 64, 23.7 -> 17.6,
 // with backward 87 -> 72; 2000 x 4 of up to 30, D = 32, 37 -> 23, 104 -> 88; 3000 x 4 bimodal to 30, D = 64, 64 -> 49, 210 -> 183;
-// 4000 x 4 of up to 20, D = 128, 203 -> 159, 763 -> 693.
+// 4000 x 4 of up to 20, D = 128, forward 203 -> 159.
 inline int f32_direct_blocks(const F32Form &form, int64_t B, int64_t max_len, int H, int64_t max_streamed, int cus) {
     if (form.split) return 0;
     if (max_len > 0 && max_len <= form.rows && max_streamed <= 128 && B * H < (int64_t)1 << 31) return 1;

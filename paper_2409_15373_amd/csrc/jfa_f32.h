@@ -37,10 +37,9 @@ template <int D> __device__ inline void store_row(float *dst, const f32x16 (&acc
 }
 
 // The workgroup's next work item into `t`, false when nothing is left; ends with a barrier, so that the stage buffers
-// are free (without a schedule there is one item at most and no barrier).  item: number of items taken so far.
+// are free.  item: number of items taken so far.
 __device__ inline bool next_item(Work &t, const SmallWork &mine, bool small, int item, const Schedule &s, const int64_t *offsets,
-                                 const int64_t *offsets_other, int B, int H, WorkCursor &cursor, int64_t total, int64_t *slot, int block_rows) {
-    if (s.direct_blocks) return item == 0 && direct_item(t, s, offsets, offsets_other, H, block_rows);
+                                 const int64_t *offsets_other, int B, int H, WorkCursor &cursor, int64_t total, int64_t *slot) {
     if (small) {   // the workgroup's items were decoded when the schedule was built
         __syncthreads();
         return item < __builtin_amdgcn_readfirstlane(mine.count) && load_work<true>(&mine.item[item], t);

@@ -180,15 +180,16 @@ __global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void fwd_f32_kerne
     const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
     const float scale = 1.0f / sqrtf((float)D);
     const bool small = s.build_rows != 0;   // small problem: no scheduler launch has run, the schedule is built here, in LDS
-    if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
-    const int64_t total = small || s.direct_blocks ? 0 : (int64_t)s.tile_start[B] * H;
+    if (s.direct_blocks) direct_small_work(&mine, s, offsets, offsets_kv, H, kRows);
+    else if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
+    const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets[B];
     const int64_t row_stride = (int64_t)H * D;
 
     WorkCursor cursor;
     cursor.static_only = s.static_only || total <= f32_static_items<D>() * (int64_t)gridDim.x;
     Work t;   // keys: rows orow0 .. orow0 + olen - 1
-    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot, kRows); ++item) {
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot); ++item) {
         const int L = t.olen;
         const int q0 = t.block * kRows + rg * 32;      // first query of the wave
         const int i = q0 + col;                        // this lane's query
@@ -287,15 +288,16 @@ __global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void dq_f32_kernel
     const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
     const float scale = 1.0f / sqrtf((float)D);
     const bool small = s.build_rows != 0;
-    if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
-    const int64_t total = small || s.direct_blocks ? 0 : (int64_t)s.tile_start[B] * H;
+    if (s.direct_blocks) direct_small_work(&mine, s, offsets, offsets_kv, H, kRows);
+    else if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
+    const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets[B];
     const int64_t row_stride = (int64_t)H * D;
 
     WorkCursor cursor;
     cursor.static_only = s.static_only || total <= f32_static_items<D>() * (int64_t)gridDim.x;
     Work t;
-    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot, kRows); ++item) {
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot); ++item) {
         const int L = t.olen;
         const int q0 = t.block * kRows + rg * 32;
         const int i = q0 + col;
@@ -380,15 +382,16 @@ __global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void dkv_f32_kerne
     const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
     const float scale = 1.0f / sqrtf((float)D);
     const bool small = s.build_rows != 0;
-    if (small) build_small_work(offsets, offsets_q, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
-    const int64_t total = small || s.direct_blocks ? 0 : (int64_t)s.tile_start[B] * H;
+    if (D < 128 && s.direct_blocks) direct_small_work(&mine, s, offsets, offsets_q, H, kRows);   // at D = 128 it would make the kernel spill
+    else if (small) build_small_work(offsets, offsets_q, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
+    const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets_q ? offsets_q[B] : offsets[B];   // lse and delta are indexed by query rows
     const int64_t row_stride = (int64_t)H * D;
 
     WorkCursor cursor;
     cursor.static_only = s.static_only || total <= f32_static_items<D>() * (int64_t)gridDim.x;
     Work t;   // queries: rows orow0 .. orow0 + olen - 1
-    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_q, B, H, cursor, total, &slot, kRows); ++item) {
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_q, B, H, cursor, total, &slot); ++item) {
         const int L = t.olen;
         const int k0 = t.block * kRows + rg * 32;      // first key of the wave
         const int j = k0 + col;                        // this lane's key

@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void fwd_split_kernel(
     WorkCursor cursor;
     cursor.static_only = s.static_only;
     Work t;   // keys: rows orow0 .. orow0 + olen - 1
-    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot, 0); ++item) {
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot); ++item) {
         const int L = t.olen;
         const int q0 = t.block * kRows + wave * 32;    // first query of the wave
         const int i = q0 + col;                        // this lane's query
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void dq_split_kernel(
     WorkCursor cursor;
     cursor.static_only = s.static_only;
     Work t;
-    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot, 0); ++item) {
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_kv, B, H, cursor, total, &slot); ++item) {
         const int L = t.olen;
         const int q0 = t.block * kRows + wave * 32;
         const int i = q0 + col;
@@ -595,7 +595,7 @@ __global__ __launch_bounds__(kSpThreads, 2) void dkv_split_kernel(
     WorkCursor cursor;
     cursor.static_only = s.static_only;
     Work t;   // queries: rows orow0 .. orow0 + olen - 1
-    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_q, B, H, cursor, total, &slot, 0); ++item) {
+    for (int item = 0; next_item(t, mine, small, item, s, offsets, offsets_q, B, H, cursor, total, &slot); ++item) {
         const int L = t.olen;
         const int k0 = t.block * kRows + pair * 32;    // first key of the pair
         const int j = k0 + col;                        // this lane's key

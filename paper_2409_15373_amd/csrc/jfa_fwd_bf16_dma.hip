@@ -134,9 +134,11 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
     // with the schedule in LDS it is one atomic and a few LDS reads instead of five dependent trips to memory.
     const bool tabled = B <= kTabCap && !direct;
     WorkCursor cursor;
-    auto claim_next = [&]() {   // wave 0, every lane
-        if (direct) {
-            if (lane == 0) slot.valid = 0;
+    auto claim_next = [&](const Work &now) {   // wave 0, every lane; now: the present item
+        if (direct) {   // the next block of a sample that is longer than the bound admits
+            Work next = now;
+            next.block += s.direct_blocks;
+            if (lane == 0) park_work<CROSS>(&slot, next, next.block * kDmaBlockRows < next.len);
             return;
         }
         if (!tabled) {
@@ -147,11 +149,13 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
         if (lane == 0) w = next_work(s.counter, cursor, total);
         tab.decode(&slot, B, H, uniform64(w));
     };
-    if (wave == 0 && !direct) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_kv : nullptr);
+    if (direct) {
+        if (tid == 0) direct_first(&slot, s, offsets, CROSS ? offsets_kv : nullptr, H, kDmaBlockRows);
+    } else if (wave == 0) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_kv : nullptr);
     if (tabled) tab.fill(s, offsets, offsets_kv, B);
     __syncthreads();   // the slot and the tables are written
     Work t;
-    bool have = direct ? direct_item(t, s, offsets, CROSS ? offsets_kv : nullptr, H, kDmaBlockRows) : load_work<CROSS>(&slot, t);
+    bool have = load_work<CROSS>(&slot, t);
     while (have) {
         __syncthreads();   // every wave has read the slot before wave 0 refills it
         const Stream cur = stream_of(t);
@@ -162,7 +166,7 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
         const __bf16 *const kbase = cur.kbase;
         const __bf16 *const vbase = cur.vbase;
         if (CROSS && L == 0) {   // no keys: an empty softmax, out = 0 and lse = -inf
-            if (wave == 0) claim_next();
+            if (wave == 0) claim_next(t);
             const int i = t.block * kDmaBlockRows + wave * 32 + (lane & 31);
             if (i < Lq) {
                 __bf16 *orow = out + (t.row0 + i) * row_stride + (int64_t)t.head * D + (lane >> 5) * (D / 2);
@@ -419,7 +423,7 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
             issue(kbase, kbuf(1), 1, true);
             issue(vbase, vbuf(1), 1, false);
         }
-        if (wave == 0) claim_next();   // overlaps with the loads in flight
+        if (wave == 0) claim_next(t);   // overlaps with the loads in flight
 #pragma unroll
         for (int ks = 0; ks < kKSteps; ++ks) asm volatile("" : "+v"(qreg[ks]));   // Q loads complete here
         if (tid == 0) restart = 0;   // nobody looks at it between the barrier at the top of the loop and the next one

@@ -212,7 +212,7 @@ hipError_t launch_fwd_narrow(const void *q, const void *k, const void *v, const 
                              int B, int H, int D, Schedule s, int block_rows, void *out, float *lse, int cus, hipStream_t stream) {
     if (causal && offsets_kv) return hipErrorInvalidValue;
 #define JFA_LAUNCH(DD, W, CROSS, CAUSAL)                                                                     \
-    hipLaunchKernelGGL((fwd_narrow_kernel<DD, W, CROSS, CAUSAL>), dim3(persistent_grid<fwd_narrow_kernel<DD, W, CROSS, CAUSAL>, W == 2 ? 2 : 1>(64 * W, cus)), \
+    hipLaunchKernelGGL((fwd_narrow_kernel<DD, W, CROSS, CAUSAL>), dim3(item_grid<fwd_narrow_kernel<DD, W, CROSS, CAUSAL>, W == 2 ? 2 : 1>(64 * W, B, H, s, cus)), \
                        dim3(64 * W), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, offsets, offsets_kv, B, H, s, \
                        (__bf16 *)out, lse)
 #define JFA_CASE(DD, W)                                                                                      \

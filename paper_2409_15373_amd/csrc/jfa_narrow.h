@@ -126,7 +126,9 @@ struct NarrowWalk {
         small = s.build_rows != 0;
         grid = (int)gridDim.x;
         asm volatile("" : "+s"(grid));   // read once: the dispatch packet it comes from is a slow place to read
-        if (small) {
+        if (s.direct_blocks) {
+            direct_small_work(&sh->mine, s, offsets, CROSS ? offsets_other : nullptr, H, s.build_rows);
+        } else if (small) {
             build_small_work(offsets, CROSS ? offsets_other : nullptr, B, H, s.build_rows, scratch, &sh->mine);
         } else {
             const int tiles = s.tile_start[B];

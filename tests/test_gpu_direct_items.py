@@ -32,14 +32,15 @@ def test_fp32_cross(q_longest, k_longest):
     compare(got, ref, "f32", oq, ok, Lq, Lk)
 
 
-@pytest.mark.parametrize("B,H,longest", [(1, 1, 257), (5, 2, 300), (64, 2, 300), (43, 3, 300), (7, 1, 1030)])
-@pytest.mark.parametrize("D", [128])
+@pytest.mark.parametrize("B,H,longest", [(1, 1, 257), (5, 2, 300), (64, 2, 300), (43, 3, 300), (7, 1, 1030), (128, 2, 140), (129, 2, 140)])
+@pytest.mark.parametrize("D", [32, 64, 128])
 def test_bf16(B, H, longest, D):
     run_causal(make_custom("direct", lengths(B, longest, B + longest), H, D, dtype="bf16", seed=B), longest)
 
 
 @pytest.mark.parametrize("q_longest,k_longest", [(33, 300), (300, 40), (513, 257)])
-def test_bf16_cross(q_longest, k_longest):
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_bf16_cross(q_longest, k_longest, D):
     Lq, Lk = lengths(7, q_longest, 1), lengths(7, k_longest, 2)
-    got, ref, oq, ok = run_cross(Lq, Lk, 2, 128, "bf16", 3, q_longest, k_longest)
+    got, ref, oq, ok = run_cross(Lq, Lk, 2, D, "bf16", 3, q_longest, k_longest)
     compare(got, ref, "bf16", oq, ok, Lq, Lk)
