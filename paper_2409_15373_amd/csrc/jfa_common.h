@@ -566,7 +566,7 @@ hipError_t launch_check_offsets(const int64_t *offsets, int B, int64_t max_len, 
 // Blocks per (sample, head) where every block that the bound on the lengths admits gets a workgroup of its own (those past a sample's
 // end leave at once) and there is no schedule; 0: there is one.  As long as there is a compute unit for each, nothing is to be
 // balanced and the schedule (a launch, or a sort in every workgroup) is all there is to save.  Fp32, microseconds of the kernels, with
-// and without a schedule: four samples of up to 64 rows, D = 32, forward 8.7 and 7.2, with backward 28.9 and 24.3; 8 x 2 of up to 600,
+// and without a schedule: four samples of up to 64 rows, D = 32, forward 8.7 and 7.5, with backward 28.7 and 25.1; 8 x 2 of up to 600,
 // D = 64, 35.9 and 33.9, 147 and 141; 16 x 1 bimodal to 1000, D = 128, 93.9 and 92.1.  With more blocks than compute units the order, longest
 // first, is worth more: 300 x 2 of up to 100, D = 64, 32.9 and 35.3, 110 and 143; 2000 x 4 bimodal to 128, D = 128, 375 and 629.
 // bf16, D = 128, more than 256 rows: 8 x 4 of up to 600, forward 31.5 and 23.5, causal 30.1 and 20.2, with backward 98 and 84.5; 12 x 1 of up
@@ -615,9 +615,8 @@ inline F32Form f32_key_form(const F32Form &queries, int64_t max_streamed, bool m
     return {false, f32_block_rows(max_streamed, many)};
 }
 // The same on the fp32 matrix instructions, where a call whose samples have one block each at most needs no schedule either, however
-// many there are: streams are short, and the workgroups are dealt as places get free.  300 x 2 of up to 64 rows, D = 64, 23.7 -> 17.6,
-// with backward 87 -> 72; 2000 x 4 of up to 30, D = 32, 37 -> 23, 104 -> 88; 3000 x 4 bimodal to 30, D = 64, 64 -> 49, 210 -> 183;
-// 4000 x 4 of up to 20, D = 128, forward 203 -> 159.
+// many there are: streams are short, and the workgroups are dealt as places get free.  300 x 2 of up to 64 rows, D = 64, 23.3 -> 20.0,
+// with backward 87.5 -> 76; 2000 x 4 of up to 30, D = 32, 38.2 -> 24.4, 106 -> 93; 4000 x 4 of up to 20, D = 128, forward 206 -> 170.
 inline int f32_direct_blocks(const F32Form &form, int64_t B, int64_t max_len, int H, int64_t max_streamed, int cus) {
     if (form.split) return 0;
     if (max_len > 0 && max_len <= form.rows && max_streamed <= 128 && B * H < (int64_t)1 << 31) return 1;

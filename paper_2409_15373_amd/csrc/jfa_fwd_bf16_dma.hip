@@ -42,9 +42,8 @@ template <int N> using IntC = std::integral_constant<int, N>;
 
 // CROSS: the keys and values of a sample are the rows of a second offsets array (cross attention); otherwise
 // offsets_kv is not looked at and the code is that of self attention.  CAUSAL (self attention only): query i attends
-// to keys 0 .. i.  A tile then streams the keys up to its last query; the stages whose keys all lie at or below the
-// tile's first query run unmasked, the others (up to five) run in the masking form of a stage with the per-lane
-// limit min(L, i + 1) in place of L.
+// to keys 0 .. i.  A tile then streams the keys up to its last query; a wave's 32 queries lie inside one 64-key stage, the
+// last that it takes part in and the only one it masks, with the per-lane limit min(L, i + 1) in place of L.
 template <bool CROSS, bool CAUSAL>
 __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf16 *__restrict__ q,
                                                                       const __bf16 *__restrict__ k,
