@@ -616,11 +616,13 @@ inline F32Form f32_key_form(const F32Form &queries, int64_t max_streamed, bool m
 }
 // The same on the fp32 matrix instructions, where a call whose samples have one block each at most needs no schedule either, as long as
 // its items fit one launch (a grid's threads are counted in 32 bits): streams are short, and the workgroups are dealt as places get free.  300 x 2 of up to 64 rows, D = 64, 23.3 -> 20.0,
-// with backward 87.5 -> 76; 2000 x 4 of up to 30, D = 32, 38.2 -> 24.4, 106 -> 93; 4000 x 4 of up to 20, D = 128, forward 206 -> 170.
+// with backward 87.5 -> 76; 2000 x 4 of up to 30, D = 32, 38.2 -> 24.4, 106 -> 93; 4000 x 4 of up to 20, D = 128, forward 206 -> 170; cross,
+// forward, up to 30 queries against up to 64 keys, one sample in ten long, 3000 x 4, D = 64, 66.4 -> 60.6, D = 128 146 -> 134.  Against up to 128
+// keys the order matters again: up to 64 queries, one in ten long on both sides, 2000 x 4, D = 128, 330 -> 349, 3000 x 4, D = 64, 225 -> 232.
 constexpr int64_t kF32DirectItems = (int64_t)1 << 22;
 inline int f32_direct_blocks(const F32Form &form, int64_t B, int64_t max_len, int H, int64_t max_streamed, int cus) {
     if (form.split) return 0;
-    if (max_len > 0 && max_len <= form.rows && max_streamed <= 128 && B <= kF32DirectItems && B * H <= kF32DirectItems) return 1;
+    if (max_len > 0 && max_len <= form.rows && max_streamed <= 64 && B <= kF32DirectItems && B * H <= kF32DirectItems) return 1;
     return direct_blocks(B, max_len, H, form.rows, cus);
 }
 // Cross attention: offsets = the queries' offsets, offsets_kv = the keys' (nullptr: the same array); schedules are

@@ -43,3 +43,10 @@ def test_a_launch_without_a_schedule_fits_a_grid(direct_blocks):
     beyond = [(32, line + 1, 20, 1, 20), (32, line // 8 + 1, 32, 8, 32), (64, line // 8 + 1, 64, 8, 64), (32, 1 << 26, 20, 1, 20),
               (64, 1 << 21, 64, 8, 128), (32, (1 << 30) - 1, 1, 1, 1)]
     assert direct_blocks(*beyond) == [0] * len(beyond)
+
+
+def test_longer_streams_keep_their_order(direct_blocks):
+    """One block per sample is no reason to give up the order, longest first, where more than 64 rows stream past it and there are more
+    blocks than compute units."""
+    assert direct_blocks((64, 2000, 64, 4, 65), (64, 3000, 64, 4, 128), (32, 300, 32, 4, 100)) == [0, 0, 0]
+    assert direct_blocks((32, 3000, 30, 4, 64), (64, 200, 64, 4, 64), (64, 64, 64, 4, 128), (64, 64, 64, 4, 1000)) == [1, 1, 1, 1]
