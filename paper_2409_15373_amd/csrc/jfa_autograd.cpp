@@ -12,6 +12,7 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/hip/HIPStream.h>
 
 namespace {
@@ -210,11 +211,11 @@ bool as_int64(PyObject *o, int64_t *x) {
     *x = PyLong_AsLongLongAndOverflow(o, &overflow);
     return overflow == 0;
 }
-bool nobody_listens() {   // no dispatch mode, function transform or tracer is to see the allocations
+bool nobody_listens() {   // no function mode, dispatch mode, function transform or tracer is to see the allocations
     using c10::DispatchKey;
     constexpr c10::DispatchKeySet modes({DispatchKey::Python, DispatchKey::PythonTLSSnapshot, DispatchKey::FuncTorchDynamicLayerFrontMode,
                                          DispatchKey::FuncTorchVmapMode, DispatchKey::Functionalize});
-    return !c10::impl::tls_local_dispatch_key_set().included_.has_any(modes) && !torch::jit::tracer::isTracing();
+    return !c10::impl::tls_local_dispatch_key_set().included_.has_any(modes) && !torch::jit::tracer::isTracing() && !at::impl::torch_function_mode_enabled();
 }
 // (q, k, v, offsets, max_len, causal), or with offsets_kv, max_len_q, max_len_kv for cross attention
 template <bool kCross> PyObject *forward_call(PyObject *, PyObject *const *args, Py_ssize_t n_args) {

@@ -81,3 +81,60 @@ def test_a_dispatch_mode_sees_the_allocations():
     with Seen() as seen:
         binding.jfa_forward(q, k, v, offsets, 70)
     assert any("empty" in op for op in seen.ops)
+
+
+def test_a_function_mode_sees_the_allocations():
+    from torch.overrides import TorchFunctionMode
+    from paper_2409_15373_amd import binding
+
+    class Seen(TorchFunctionMode):
+        functions = ()
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            self.functions += (func,)
+            return func(*args, **(kwargs or {}))
+
+    q, k, v, offsets = inputs()
+    x, w = q[:, 0].contiguous(), torch.randn(5, 64, 32, device="cuda").bfloat16()
+    for call, allocation in [(lambda: binding.jfa_forward(q, k, v, offsets, 70), torch.empty),
+                             (lambda: binding.jfa_forward_cross(q, k, v, offsets, offsets, 70, 70), torch.empty),
+                             (lambda: binding.jfa_jagged_to_dense(q, offsets, 70), torch.empty),
+                             (lambda: binding.jfa_jagged_dense_bmm(x, w, offsets, 70), torch.empty),
+                             (lambda: binding.jfa_jagged_softmax(x, offsets, 70), torch.empty_like)]:
+        with Seen() as seen:
+            call()
+        assert allocation in seen.functions
+
+
+def test_listeners_have_the_python_function_called(monkeypatch):
+    """Function transforms (their own tensors and others inside them), the tracer, fake tensors, both kinds of mode and compilation:
+    the C++ call leaves the call to the Python function."""
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    from torch.overrides import BaseTorchFunctionMode
+    from torch.utils._python_dispatch import TorchDispatchMode
+    from paper_2409_15373_amd import binding
+
+    class Pass(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    q, _, _, offsets = inputs()
+    native, answers = binding._load_calls(), []
+
+    def ask(t):
+        answers.append(native.forward(t, t, t, offsets, 70, False))
+        answers.append(native.to_dense(t, offsets, 70))
+        return t.float().sum()
+
+    ask(q)
+    assert all(a is not None for a in answers)
+    answers.clear()
+    torch.func.vmap(lambda t: (ask(t), ask(q))[0])(q[None])
+    torch.func.grad(lambda t: (ask(t), ask(q))[0])(q)
+    torch.jit.trace(ask, q, check_trace=False)
+    for mode in (FakeTensorMode(allow_non_fake_inputs=True), BaseTorchFunctionMode(), Pass()):
+        with mode:
+            ask(q)
+    assert len(answers) == 2 * 8 and all(a is None for a in answers)
+    monkeypatch.setattr(torch.compiler, "is_compiling", lambda: True)
+    assert binding._native("forward", q, q, q, offsets, 70, False) is None
