@@ -61,7 +61,9 @@ __device__ inline void lds_load_2x_b128(uint32_t addr, u32x4 &lo, u32x4 &hi) {
 // of a stage that also handles the sample's ragged end.
 // CROSS (cross attention): `offsets` belongs to the keys (the stationary rows), offsets_other to the queries that
 // stream past them; the row statistics are indexed by query rows.  Otherwise offsets_other is not looked at.
-template <bool CROSS, bool CAUSAL>
+// DIRECT: 1 without a schedule (the item is the workgroup's index), 0 with one, kEither: as the call says (see the launch).
+constexpr int kEither = -1;
+template <bool CROSS, bool CAUSAL, int DIRECT>
 __global__ __launch_bounds__(kBdThreads, 2) void bwd_dkv_dma_kernel(const __bf16 *__restrict__ q,
                                                                     const __bf16 *__restrict__ k,
                                                                     const __bf16 *__restrict__ v,
@@ -91,7 +93,7 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dkv_dma_kernel(const __bf16
     const bool is_a = wave < 4;
     const float scale = 1.0f / sqrtf((float)D);
     const float c = 1.4426950408889634f * scale;
-    const bool direct = s.direct_blocks != 0;   // no schedule: the item is the workgroup's index
+    const bool direct = DIRECT == kEither ? s.direct_blocks != 0 : DIRECT != 0;
     const int64_t total = direct ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = CROSS ? offsets_other[B] : offsets[B];   // query rows
     const int64_t row_stride = (int64_t)H * D;
@@ -517,14 +519,19 @@ hipError_t launch_bwd_dkv_dma(const void *q, const void *k, const void *v, const
                               const int64_t *offsets, const int64_t *offsets_other, bool causal, int B, int H, int D,
                               Schedule s, void *dk, void *dv, int cus, hipStream_t stream) {
     if (D != kBdD || (causal && offsets_other)) return hipErrorInvalidValue;
-#define JFA_LAUNCH(CROSS, CAUSAL)                                                                                           \
-    hipLaunchKernelGGL((bwd_dkv_dma_kernel<CROSS, CAUSAL>),                                                                \
-                       dim3(item_grid<bwd_dkv_dma_kernel<CROSS, CAUSAL>>(kBdThreads, B, H, s, cus)), dim3(kBdThreads), 0,      \
-                       stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, stats,        \
+#define JFA_LAUNCH(CROSS, CAUSAL, DIRECT)                                                                                  \
+    hipLaunchKernelGGL((bwd_dkv_dma_kernel<CROSS, CAUSAL, DIRECT>),                                                        \
+                       dim3(item_grid<bwd_dkv_dma_kernel<CROSS, CAUSAL, DIRECT>>(kBdThreads, B, H, s, cus)), dim3(kBdThreads), 0, \
+                       stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, stats,       \
                        offsets, offsets_other, B, H, s, (__bf16 *)dk, (__bf16 *)dv)
-    if (offsets_other) JFA_LAUNCH(true, false);
-    else if (causal) JFA_LAUNCH(false, true);
-    else JFA_LAUNCH(false, false);
+    // With a schedule, cross and causal calls take the instance that holds both walks: as the compiler has arranged it, it is the faster
+    // one (us, two instances -> one: causal 1024 x 4 of up to 1024 rows 1364 -> 1274, 300 x 4 of up to 300 112.7 -> 103.7; cross, 512 x 8, 256
+    // queries against bimodal keys to 4096, 690 -> 682).  Self attention 300 x 4 of up to 300 is faster with two, 122.8 -> 120.8.
+    if (offsets_other && s.direct_blocks) JFA_LAUNCH(true, false, 1);
+    else if (offsets_other) JFA_LAUNCH(true, false, kEither);
+    else if (causal) JFA_LAUNCH(false, true, kEither);
+    else if (s.direct_blocks) JFA_LAUNCH(false, false, 1);
+    else JFA_LAUNCH(false, false, 0);
 #undef JFA_LAUNCH
     return hipGetLastError();
 }

@@ -19,7 +19,8 @@ namespace jfa {
 // CAUSAL (self attention only): query i sees keys 0 .. i.  A tile streams the keys up to its last query and masks above
 // the diagonal in the stages that reach past the tile's first query, in the form of a stage that also handles the
 // sample's ragged end.
-template <bool CROSS, bool CAUSAL>
+// DIRECT: no schedule, the item is the workgroup's index.
+template <bool CROSS, bool CAUSAL, bool DIRECT>
 __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 *__restrict__ q,
                                                                      const __bf16 *__restrict__ k,
                                                                      const __bf16 *__restrict__ v,
@@ -47,8 +48,7 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
     const int col = lane & 31, half = lane >> 5;
     const float scale = 1.0f / sqrtf((float)D);
     const float c = 1.4426950408889634f * scale;
-    const bool direct = s.direct_blocks != 0;   // no schedule: the item is the workgroup's index
-    const int64_t total = direct ? 0 : (int64_t)s.tile_start[B] * H;
+    const int64_t total = DIRECT ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets[B];   // query rows: lse and delta are indexed by them
     const int64_t row_stride = (int64_t)H * D;
 
@@ -136,10 +136,10 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
 
     // The claim of the next item runs while a tile's first loads travel, and the tile cannot start before it is done:
     // with the schedule in LDS it is one atomic and a few LDS reads instead of five dependent trips to memory.
-    const bool tabled = B <= kTabCap && !direct;
+    const bool tabled = B <= kTabCap && !DIRECT;
     WorkCursor cursor;
     auto claim_next = [&](const Work &now) {   // wave 0, every lane; now: the present item
-        if (direct) {   // the next block of a sample that is longer than the bound admits
+        if constexpr (DIRECT) {   // the next block of a sample that is longer than the bound admits
             Work next = now;
             next.block += s.direct_blocks;
             if (lane == 0) park_work<CROSS>(&slot, next, next.block * kDmaBlockRows < next.len);
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kBdThreads, 2) void bwd_dq_dma_kernel(const __bf16 
         if (lane == 0) w = next_work(s.counter, cursor, total);
         tab.decode(&slot, B, H, uniform64(w));
     };
-    if (direct) {
+    if constexpr (DIRECT) {
         if (tid == 0) direct_first(&slot, s, offsets, CROSS ? offsets_other : nullptr, H, kDmaBlockRows);
     } else if (wave == 0) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_other : nullptr);
     if (tabled) tab.fill(s, offsets, offsets_other, B);
@@ -475,13 +475,19 @@ hipError_t launch_bwd_dq_dma(const void *q, const void *k, const void *v, const 
                              float *delta, const int64_t *offsets, const int64_t *offsets_other, bool causal, int B, int H,
                              int D, Schedule s, void *dq, int cus, hipStream_t stream) {
     if (D != kBdD || (causal && offsets_other)) return hipErrorInvalidValue;
-#define JFA_LAUNCH(CROSS, CAUSAL)                                                                                           \
-    hipLaunchKernelGGL((bwd_dq_dma_kernel<CROSS, CAUSAL>), dim3(item_grid<bwd_dq_dma_kernel<CROSS, CAUSAL>>(kBdThreads, B, H, s, cus)), \
-                       dim3(kBdThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v,                \
+#define JFA_LAUNCH(CROSS, CAUSAL, DIRECT)                                                                                  \
+    hipLaunchKernelGGL((bwd_dq_dma_kernel<CROSS, CAUSAL, DIRECT>), dim3(item_grid<bwd_dq_dma_kernel<CROSS, CAUSAL, DIRECT>>(kBdThreads, B, H, s, cus)), \
+                       dim3(kBdThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v,               \
                        (const __bf16 *)dout, lse, (const __bf16 *)out, delta, offsets, offsets_other, B, H, s, (__bf16 *)dq)
-    if (offsets_other) JFA_LAUNCH(true, false);
-    else if (causal) JFA_LAUNCH(false, true);
-    else JFA_LAUNCH(false, false);
+#define JFA_FORM(CROSS, CAUSAL)                                                                                            \
+    do {                                                                                                                   \
+        if (s.direct_blocks) JFA_LAUNCH(CROSS, CAUSAL, true);                                                              \
+        else JFA_LAUNCH(CROSS, CAUSAL, false);                                                                             \
+    } while (0)
+    if (offsets_other) JFA_FORM(true, false);
+    else if (causal) JFA_FORM(false, true);
+    else JFA_FORM(false, false);
+#undef JFA_FORM
 #undef JFA_LAUNCH
     return hipGetLastError();
 }

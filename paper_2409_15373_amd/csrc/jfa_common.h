@@ -431,6 +431,10 @@ __device__ inline void park_work(WorkSlot *slot, const Work &t, bool valid) {
 // Without a schedule (Schedule::direct_blocks) a workgroup's item is its index: a block of a (sample, head); `mine` is filled by one
 // lane.  A sample that is longer than the bound admits has its further blocks done by the same workgroups, up to kSmallItems each.
 // The kernels' walks stay as they are: decoded there, as scalars, the items of calls with a schedule took up to 0.4 us longer to start.
+// The bf16 kernels of long samples at D = 128 have instances of their own for it: chosen at run time, the two walks side by side cost both of
+// them registers.  One instance and two, us: without a schedule 8 x 4 of up to 600 rows forward 18.5 -> 17.8, backward 51.0 -> 48.6 (cross
+// 21.1 -> 19.5, 48.6 -> 46.2); with one, 300 x 4 of up to 300 63.4 -> 62.8, 224 -> 221; cross, 512 x 8, 256 queries against bimodal keys to
+// 4096, 287 -> 281, 1070 -> 1057.  See launch_bwd_dkv_dma() for the two forms that keep one.
 __device__ inline void direct_first(WorkSlot *slot, const Schedule &s, const int64_t *offsets, const int64_t *offsets_other, int H, int block_rows) {
     const int per_sample = H * s.direct_blocks, b = (int)blockIdx.x / per_sample, r = (int)blockIdx.x - b * per_sample;
     const int64_t *const oo = offsets_other ? offsets_other : offsets;

@@ -44,7 +44,8 @@ template <int N> using IntC = std::integral_constant<int, N>;
 // offsets_kv is not looked at and the code is that of self attention.  CAUSAL (self attention only): query i attends
 // to keys 0 .. i.  A tile then streams the keys up to its last query; a wave's 32 queries lie inside one 64-key stage, the
 // last that it takes part in and the only one it masks, with the per-lane limit min(L, i + 1) in place of L.
-template <bool CROSS, bool CAUSAL>
+// DIRECT: no schedule, the item is the workgroup's index.
+template <bool CROSS, bool CAUSAL, bool DIRECT>
 __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf16 *__restrict__ q,
                                                                       const __bf16 *__restrict__ k,
                                                                       const __bf16 *__restrict__ v,
@@ -64,8 +65,7 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, half = lane >> 5;
     const float c = 1.4426950408889634f / sqrtf((float)D);
-    const bool direct = s.direct_blocks != 0;   // no schedule: the item is the workgroup's index
-    const int64_t total = direct ? 0 : (int64_t)s.tile_start[B] * H;
+    const int64_t total = DIRECT ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets[B];
     const int64_t row_stride = (int64_t)H * D;
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
@@ -131,10 +131,10 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
     };
     // The claim of the next item runs while a tile's first loads travel, and the tile cannot start before it is done:
     // with the schedule in LDS it is one atomic and a few LDS reads instead of five dependent trips to memory.
-    const bool tabled = B <= kTabCap && !direct;
+    const bool tabled = B <= kTabCap && !DIRECT;
     WorkCursor cursor;
     auto claim_next = [&](const Work &now) {   // wave 0, every lane; now: the present item
-        if (direct) {   // the next block of a sample that is longer than the bound admits
+        if constexpr (DIRECT) {   // the next block of a sample that is longer than the bound admits
             Work next = now;
             next.block += s.direct_blocks;
             if (lane == 0) park_work<CROSS>(&slot, next, next.block * kDmaBlockRows < next.len);
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kDmaThreads, 2) void fwd_bf16_dma_kernel(const __bf
         if (lane == 0) w = next_work(s.counter, cursor, total);
         tab.decode(&slot, B, H, uniform64(w));
     };
-    if (direct) {
+    if constexpr (DIRECT) {
         if (tid == 0) direct_first(&slot, s, offsets, CROSS ? offsets_kv : nullptr, H, kDmaBlockRows);
     } else if (wave == 0) claim_and_decode(&slot, s, offsets, B, H, total, cursor, CROSS ? offsets_kv : nullptr);
     if (tabled) tab.fill(s, offsets, offsets_kv, B);
@@ -558,13 +558,19 @@ hipError_t launch_fwd_bf16_dma(const void *q, const void *k, const void *v, cons
                                const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, void *out, float *lse,
                                int cus, hipStream_t stream) {
     if (D != kDmaD || (causal && offsets_kv)) return hipErrorInvalidValue;
-#define JFA_LAUNCH(CROSS, CAUSAL)                                                                                          \
-    hipLaunchKernelGGL((fwd_bf16_dma_kernel<CROSS, CAUSAL>), dim3(item_grid<fwd_bf16_dma_kernel<CROSS, CAUSAL>>(kDmaThreads, B, H, s, cus)), \
+#define JFA_LAUNCH(CROSS, CAUSAL, DIRECT)                                                                                  \
+    hipLaunchKernelGGL((fwd_bf16_dma_kernel<CROSS, CAUSAL, DIRECT>), dim3(item_grid<fwd_bf16_dma_kernel<CROSS, CAUSAL, DIRECT>>(kDmaThreads, B, H, s, cus)), \
                        dim3(kDmaThreads), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, offsets,     \
                        offsets_kv, B, H, s, (__bf16 *)out, lse)
-    if (offsets_kv) JFA_LAUNCH(true, false);
-    else if (causal) JFA_LAUNCH(false, true);
-    else JFA_LAUNCH(false, false);
+#define JFA_FORM(CROSS, CAUSAL)                                                                                            \
+    do {                                                                                                                   \
+        if (s.direct_blocks) JFA_LAUNCH(CROSS, CAUSAL, true);                                                              \
+        else JFA_LAUNCH(CROSS, CAUSAL, false);                                                                             \
+    } while (0)
+    if (offsets_kv) JFA_FORM(true, false);
+    else if (causal) JFA_FORM(false, true);
+    else JFA_FORM(false, false);
+#undef JFA_FORM
 #undef JFA_LAUNCH
     return hipGetLastError();
 }

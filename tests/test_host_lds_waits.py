@@ -112,3 +112,26 @@ def test_the_head_size_64_gradient_kernels_use_no_scratch_memory():
     listing = check_lds_waits.listing_of(os.path.join(build.CSRC, "jfa_bwd_narrow.hip"))
     sizes = dict(re.findall(r"\.amdhsa_kernel (\S*Li64\S*)\s+(?:\.\S.*\s+)*?\.amdhsa_private_segment_fixed_size (\d+)", listing))
     assert len(sizes) == 6 and set(sizes.values()) == {"0"}, sizes
+
+
+def scratch_sizes(source, kernel):
+    """{template arguments as mangled: bytes of scratch per lane} of a kernel's instances"""
+    listing = check_lds_waits.listing_of(os.path.join(build.CSRC, source))
+    found = re.findall(r"\.amdhsa_kernel \S*%sI(\S*?)EEv\S*\s+(?:\.\S.*\s+)*?\.amdhsa_private_segment_fixed_size (\d+)" % kernel, listing)
+    return {args: int(size) for args, size in found}
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs hipcc")
+@pytest.mark.parametrize("source,kernel,direct,scheduled", [
+    ("jfa_fwd_bf16_dma.hip", "fwd_bf16_dma_kernel", "Lb1", "Lb0"), ("jfa_bwd_dq_dma.hip", "bwd_dq_dma_kernel", "Lb1", "Lb0"),
+    ("jfa_bwd_dkv_dma.hip", "bwd_dkv_dma_kernel", "Li1", "Li0|Lin1")])
+def test_long_samples_without_a_schedule_have_instances_of_their_own(source, kernel, direct, scheduled):
+    """The walk without a schedule beside the one with it costs both of them registers: apart, the former uses no more scratch memory."""
+    sizes = scratch_sizes(source, kernel)
+    pairs = 0
+    for args, size in sizes.items():
+        form = re.fullmatch(r"(Lb\dELb\dE)(%s)E" % direct, args)
+        if form:
+            pairs += 1
+            assert size <= min(s for a, s in sizes.items() if re.fullmatch(form.group(1) + "(%s)E" % scheduled, a)), sizes
+    assert pairs >= 2, sizes
