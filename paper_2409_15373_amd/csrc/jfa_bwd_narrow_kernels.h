@@ -350,7 +350,9 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 3) void dkv_narrow_kernel(
                     pw[mb][g >> 2][g & 3] = __builtin_bit_cast(uint32_t, pr);
                     dw[mb][g >> 2][g & 3] = __builtin_bit_cast(uint32_t, dr);
                 };
-                constexpr int kAhead = D == 64 ? 3 : 2;   // D = 32 has 168 registers: a third spills
+                // D = 32 has 168 registers: a third spills, under the mask a second (12 bytes of scratch, backward of 256 x 4 heads of up to 400
+                // rows 78.8 us, 77.7 without; 64 x 2 of up to 300 21.7 and 21.5; 1024 x 8 of up to 1024 1266 and 1258).
+                constexpr int kAhead = D == 64 ? 3 : CAUSAL ? 1 : 2;
                 statistics(0);
 #pragma unroll
                 for (int n = 0; n < kAhead; ++n) read(n);

@@ -135,3 +135,10 @@ def test_long_samples_without_a_schedule_have_instances_of_their_own(source, ker
             pairs += 1
             assert size <= min(s for a, s in sizes.items() if re.fullmatch(form.group(1) + "(%s)E" % scheduled, a)), sizes
     assert pairs >= 2, sizes
+
+
+@pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="needs hipcc")
+@pytest.mark.parametrize("kernel,instances", [("dq_narrow_kernel", 3), ("dkv_narrow_kernel", 3)])
+def test_the_head_size_32_gradient_kernels_use_no_scratch_memory(kernel, instances):
+    sizes = {a: n for a, n in scratch_sizes("jfa_bwd_narrow.hip", kernel).items() if a.startswith("Li32")}
+    assert len(sizes) == instances and set(sizes.values()) == {0}, sizes
