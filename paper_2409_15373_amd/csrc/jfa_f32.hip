@@ -288,7 +288,7 @@ __global__ __launch_bounds__(64 * W, f32_waves_per_simd<D>()) void dq_f32_kernel
     const int row_at = row_read_at<D>(col, half), elem_at = element_read_at<D>(col, half);
     const float scale = 1.0f / sqrtf((float)D);
     const bool small = s.build_rows != 0;
-    if (s.direct_blocks) direct_small_work(&mine, s, offsets, offsets_kv, H, kRows);
+    if (D < 128 && s.direct_blocks) direct_small_work(&mine, s, offsets, offsets_kv, H, kRows);   // D = 128: as dK / dV, which has no registers for it
     else if (small) build_small_work(offsets, offsets_kv, B, H, s.build_rows, reinterpret_cast<int *>(sm), &mine);
     const int64_t total = small ? 0 : (int64_t)s.tile_start[B] * H;
     const int64_t sum_B = offsets[B];
