@@ -25,7 +25,8 @@ import tempfile
 from . import build as _build
 
 # the sources whose kernels copy with bd_dma16 / bd_dma4 (jfa_lds.h)
-HAND_WRITTEN_COPIES = ["jfa_bwd_cross_fewq.hip", "jfa_bwd_dkv_dma.hip", "jfa_bwd_dq_dma.hip", "jfa_bwd_narrow.hip", "jfa_bwd_narrow_short.hip", "jfa_one_tile.hip",
+HAND_WRITTEN_COPIES = ["jfa_bwd_cross_fewq.hip", "jfa_bwd_dkv_dma.hip", "jfa_bwd_dq_dma.hip", "jfa_bwd_narrow.hip", "jfa_bwd_narrow_direct.hip",
+                       "jfa_bwd_narrow_short.hip", "jfa_one_tile.hip",
                        "jfa_fwd_bf16_dma.hip", "jfa_fwd_cross_fewq.hip", "jfa_fwd_narrow.hip"]
 
 _REG = re.compile(r"\bv\[(\d+):(\d+)\]|\bv(\d+)\b")

@@ -62,7 +62,6 @@ __device__ inline void lds_load_2x_b128(uint32_t addr, u32x4 &lo, u32x4 &hi) {
 // CROSS (cross attention): `offsets` belongs to the keys (the stationary rows), offsets_other to the queries that
 // stream past them; the row statistics are indexed by query rows.  Otherwise offsets_other is not looked at.
 // DIRECT: 1 without a schedule (the item is the workgroup's index), 0 with one, kEither: as the call says (see the launch).
-constexpr int kEither = -1;
 template <bool CROSS, bool CAUSAL, int DIRECT>
 __global__ __launch_bounds__(kBdThreads, 2) void bwd_dkv_dma_kernel(const __bf16 *__restrict__ q,
                                                                     const __bf16 *__restrict__ k,

@@ -38,7 +38,7 @@ __device__ inline void narrow_end_stage() {
 }
 
 // CROSS: `offsets` belongs to the queries, offsets_kv to the keys and values; CAUSAL: query i sees keys 0 .. i.
-template <int D, int W, bool CROSS, bool CAUSAL>
+template <int D, int W, bool CROSS, bool CAUSAL, int DIRECT>
 __global__ __launch_bounds__(64 * W, D == 64 ? (W == 4 ? 3 : 2) : 4) void dq_narrow_kernel(
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, const __bf16 *__restrict__ dout,
     const float *__restrict__ lse, const __bf16 *__restrict__ out_fwd, float *__restrict__ stats, const int64_t *__restrict__ offsets,
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? (W == 4 ? 3 : 2) : 4) void dq_nar
     constexpr int kKSteps = D / 16, kDBlocks = D / 32, kRows = 32 * W;   // kRows: stationary rows of a tile
     constexpr bool kSubtract = D == 64;   // delta is subtracted from every dP: as their sums' addend it takes sixteen registers
     __shared__ __attribute__((aligned(1024))) char st[kNwStages * N::kStage];   // buffer b: K at b * kStage, V behind it
-    __shared__ typename NarrowWalk<CROSS>::Shared walk_mem;
+    __shared__ typename NarrowWalk<CROSS, DIRECT>::Shared walk_mem;
     static_assert(sizeof(st) >= kInlineScratchInts * sizeof(int), "the stage buffers double as the scheduler's scratch");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? (W == 4 ? 3 : 2) : 4) void dq_nar
     const int64_t sum_q = offsets[B];   // query rows; loaded once, a tile's first loads hang on it
     const NarrowAddresses<D> at(lane);
     const NarrowCopier<D, W> copier(wave, lane, row_stride);
-    NarrowWalk<CROSS> walk(&walk_mem, s, offsets, offsets_kv, B, H, reinterpret_cast<int *>(st));
+    NarrowWalk<CROSS, DIRECT> walk(&walk_mem, s, offsets, offsets_kv, B, H, reinterpret_cast<int *>(st));
 
     Work t{};
     int have = walk.small && walk.next(t);
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? (W == 4 ? 3 : 2) : 4) void dq_nar
 
 // CROSS: `offsets` belongs to the keys (the stationary rows), offsets_q to the queries that stream past them.  CAUSAL: key j is
 // seen by queries j .. L - 1: the stream starts at the stage that holds the tile's first key.
-template <int D, int W, bool CROSS, bool CAUSAL>
+template <int D, int W, bool CROSS, bool CAUSAL, int DIRECT>
 __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 3) void dkv_narrow_kernel(
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v, const __bf16 *__restrict__ dout,
     const float *__restrict__ stats, const int64_t *__restrict__ offsets, const int64_t *__restrict__ offsets_q, int B, int H,
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 3) void dkv_narrow_kernel(
     constexpr int kKSteps = D / 16, kDBlocks = D / 32, kRows = 32 * W;   // kRows: stationary rows of a tile
     constexpr int kBuffer = N::kStage + 1024;   // Q, dO, then 64 x minus lse * sqrt(D) and 64 x delta (512 bytes; 1 KB keeps the alignment)
     __shared__ __attribute__((aligned(1024))) char st[kNwStages * kBuffer];
-    __shared__ typename NarrowWalk<CROSS>::Shared walk_mem;
+    __shared__ typename NarrowWalk<CROSS, DIRECT>::Shared walk_mem;
     static_assert(sizeof(st) >= kInlineScratchInts * sizeof(int), "the stage buffers double as the scheduler's scratch");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 3) void dkv_narrow_kernel(
     const int64_t sum_q = CROSS ? offsets_q[B] : offsets[B];   // query rows; loaded once, a tile's first loads hang on it
     const NarrowAddresses<D> at(lane);
     const NarrowCopier<D, W> copier(wave, lane, row_stride);
-    NarrowWalk<CROSS> walk(&walk_mem, s, offsets, offsets_q, B, H, reinterpret_cast<int *>(st));
+    NarrowWalk<CROSS, DIRECT> walk(&walk_mem, s, offsets, offsets_q, B, H, reinterpret_cast<int *>(st));
 
     Work t{};
     int have = walk.small && walk.next(t);
@@ -407,16 +407,23 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 3) void dkv_narrow_kernel(
     }
 }
 
-// Launchers for workgroups of W waves
-template <int W>
+// The instance for calls with a schedule: one of its own but where that for both walks, as the compiler has arranged it, is the faster (backward,
+// us, one of its own and that for both: 1000 x 4 heads, 60 queries against 300 keys, D = 64, 149.4 and 146.9, 2000 x 2, 64 against 200, 113.5 and 112.1; 3000 x 4, 40
+// against 250, D = 32, 159.2 and 158.7.  Own: D = 64, 1414 x 4 of up to 209 rows, 261.8 and 264.0; D = 32, 2000 x 2, 64 against 200, 80.5
+// and 81.2).
+template <int D, int W, bool CROSS> constexpr int kWithSchedule = CROSS && (D == 64 || W == 2) ? kEither : 0;
+
+// Launchers for workgroups of W waves; DIRECT: calls without a schedule
+template <int W, bool DIRECT>
 hipError_t launch_dq_narrow_waves(const void *q, const void *k, const void *v, const void *out, const void *dout, const float *lse, float *stats,
                                   const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, void *dq,
                                   int cus, hipStream_t stream) {
     if (causal && offsets_kv) return hipErrorInvalidValue;
-#define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                        \
-    hipLaunchKernelGGL((dq_narrow_kernel<DD, W, CROSS, CAUSAL>), dim3(item_grid<dq_narrow_kernel<DD, W, CROSS, CAUSAL>, W == 2 ? 2 : 1>(64 * W, B, H, s, cus)), \
+#define JFA_LAUNCH_AS(DD, CROSS, CAUSAL, WALK)                                                                        \
+    hipLaunchKernelGGL((dq_narrow_kernel<DD, W, CROSS, CAUSAL, WALK>), dim3(item_grid<dq_narrow_kernel<DD, W, CROSS, CAUSAL, WALK>, W == 2 ? 2 : 1>(64 * W, B, H, s, cus)), \
                        dim3(64 * W), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, lse, \
                        (const __bf16 *)out, stats, offsets, offsets_kv, B, H, s, (__bf16 *)dq)
+#define JFA_LAUNCH(DD, CROSS, CAUSAL) JFA_LAUNCH_AS(DD, CROSS, CAUSAL, (DIRECT ? 1 : kWithSchedule<DD, W, CROSS>))
 #define JFA_CASE(DD)                                                                                         \
     case DD:                                                                                                 \
         if (offsets_kv) JFA_LAUNCH(DD, true, false);                                                         \
@@ -430,18 +437,20 @@ hipError_t launch_dq_narrow_waves(const void *q, const void *k, const void *v, c
     }
 #undef JFA_CASE
 #undef JFA_LAUNCH
+#undef JFA_LAUNCH_AS
     return hipGetLastError();
 }
 
-template <int W>
+template <int W, bool DIRECT>
 hipError_t launch_dkv_narrow_waves(const void *q, const void *k, const void *v, const void *dout, const float *stats, const int64_t *offsets,
                                    const int64_t *offsets_q, bool causal, int B, int H, int D, Schedule s, void *dk, void *dv, int cus,
                                    hipStream_t stream) {
     if (causal && offsets_q) return hipErrorInvalidValue;
-#define JFA_LAUNCH(DD, CROSS, CAUSAL)                                                                        \
-    hipLaunchKernelGGL((dkv_narrow_kernel<DD, W, CROSS, CAUSAL>), dim3(item_grid<dkv_narrow_kernel<DD, W, CROSS, CAUSAL>, W == 2 ? 2 : 1>(64 * W, B, H, s, cus)), \
+#define JFA_LAUNCH_AS(DD, CROSS, CAUSAL, WALK)                                                                        \
+    hipLaunchKernelGGL((dkv_narrow_kernel<DD, W, CROSS, CAUSAL, WALK>), dim3(item_grid<dkv_narrow_kernel<DD, W, CROSS, CAUSAL, WALK>, W == 2 ? 2 : 1>(64 * W, B, H, s, cus)), \
                        dim3(64 * W), 0, stream, (const __bf16 *)q, (const __bf16 *)k, (const __bf16 *)v, (const __bf16 *)dout, stats, \
                        offsets, offsets_q, B, H, s, (__bf16 *)dk, (__bf16 *)dv)
+#define JFA_LAUNCH(DD, CROSS, CAUSAL) JFA_LAUNCH_AS(DD, CROSS, CAUSAL, (DIRECT ? 1 : kWithSchedule<DD, W, CROSS>))
 #define JFA_CASE(DD)                                                                                         \
     case DD:                                                                                                 \
         if (offsets_q) JFA_LAUNCH(DD, true, false);                                                          \
@@ -455,6 +464,7 @@ hipError_t launch_dkv_narrow_waves(const void *q, const void *k, const void *v, 
     }
 #undef JFA_CASE
 #undef JFA_LAUNCH
+#undef JFA_LAUNCH_AS
     return hipGetLastError();
 }
 

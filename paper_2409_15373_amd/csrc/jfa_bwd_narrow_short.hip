@@ -6,13 +6,13 @@ namespace jfa {
 hipError_t launch_dq_narrow_short(const void *q, const void *k, const void *v, const void *out, const void *dout, const float *lse, float *stats,
                                   const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, void *dq,
                                   int cus, hipStream_t stream) {
-    return launch_dq_narrow_waves<2>(q, k, v, out, dout, lse, stats, offsets, offsets_kv, causal, B, H, D, s, dq, cus, stream);
+    return launch_dq_narrow_waves<2, false>(q, k, v, out, dout, lse, stats, offsets, offsets_kv, causal, B, H, D, s, dq, cus, stream);
 }
 
 hipError_t launch_dkv_narrow_short(const void *q, const void *k, const void *v, const void *dout, const float *stats, const int64_t *offsets,
                                    const int64_t *offsets_q, bool causal, int B, int H, int D, Schedule s, void *dk, void *dv, int cus,
                                    hipStream_t stream) {
-    return launch_dkv_narrow_waves<2>(q, k, v, dout, stats, offsets, offsets_q, causal, B, H, D, s, dk, dv, cus, stream);
+    return launch_dkv_narrow_waves<2, false>(q, k, v, dout, stats, offsets, offsets_q, causal, B, H, D, s, dk, dv, cus, stream);
 }
 
 }  // namespace jfa

@@ -460,6 +460,9 @@ __device__ inline void direct_small_work(SmallWork *mine, const Schedule &s, con
     }
     __syncthreads();
 }
+// Kernels with instances of their own for calls without a schedule have a template argument DIRECT: 1 without, 0 with one, kEither: as
+// the call says (Schedule::direct_blocks).
+constexpr int kEither = -1;
 template <auto Kernel, int AtLeast = 1>
 inline int item_grid(int threads, int B, int H, const Schedule &s, int cus) {
     return s.direct_blocks ? B * H * s.direct_blocks : persistent_grid<Kernel, AtLeast>(threads, cus);
@@ -743,6 +746,12 @@ hipError_t launch_dq_narrow_short(const void *q, const void *k, const void *v, c
 hipError_t launch_dkv_narrow_short(const void *q, const void *k, const void *v, const void *dout, const float *stats, const int64_t *offsets,
                                    const int64_t *offsets_q, bool causal, int B, int H, int D, Schedule s, void *dk, void *dv, int cus,
                                    hipStream_t stream);
+hipError_t launch_dq_narrow_direct(const void *q, const void *k, const void *v, const void *out, const void *dout, const float *lse, float *stats,
+                                   const int64_t *offsets, const int64_t *offsets_kv, bool causal, int B, int H, int D, Schedule s, void *dq,
+                                   int cus, hipStream_t stream);
+hipError_t launch_dkv_narrow_direct(const void *q, const void *k, const void *v, const void *dout, const float *stats, const int64_t *offsets,
+                                    const int64_t *offsets_q, bool causal, int B, int H, int D, Schedule s, void *dk, void *dv, int cus,
+                                    hipStream_t stream);
 hipError_t launch_fwd_narrow(const void *q, const void *k, const void *v, const int64_t *offsets, const int64_t *offsets_kv, bool causal,
                              int B, int H, int D, Schedule s, int block_rows, void *out, float *lse, int cus, hipStream_t stream);
 

@@ -104,8 +104,11 @@ struct NarrowCopier {
 // as 16-bit LDS copies, and decoding is a search in LDS and one trip to memory for the sample's offsets.  Where work is
 // dealt without claims, filling them pays for smaller batches only: 1000 samples of at most 20 rows, H = 2, D = 32, backward
 // 30.0 us with, 27.8 without; 300 of at most 300, H = 8, D = 64, cross forward 32.2 with, 34.2 without.
+// DIRECT: no schedule (Schedule::direct_blocks), as kernels of their own: with one branch more here, every other call was up to 1.4 % slower
+// (D = 64, forward, 1414 x 4 of up to 209 rows 95.5 us and 94.3, causal 92.3 and 91.1), and apart it has registers to spare (8 x 4
+// of up to 600 rows, D = 64, forward 11.8 -> 10.7, backward 28.8 -> 27.2; 10 x 2 of up to 300, D = 32, 6.6 -> 6.2, 17.6 -> 16.4).
 constexpr int kTabCapFixed = 512;
-template <bool CROSS>
+template <bool CROSS, int DIRECT>
 struct NarrowWalk {
     struct Shared {
         WorkSlot slot;
@@ -123,10 +126,10 @@ struct NarrowWalk {
     __device__ inline NarrowWalk(Shared *sh_, const Schedule &s_, const int64_t *offsets_, const int64_t *offsets_other_, int B_, int H_,
                                  int *scratch)
         : sh(sh_), offsets(offsets_), offsets_other(offsets_other_), s(s_), B(B_), H(H_) {
-        small = s.build_rows != 0;
+        small = DIRECT == 1 || s.build_rows != 0;
         grid = (int)gridDim.x;
         asm volatile("" : "+s"(grid));   // read once: the dispatch packet it comes from is a slow place to read
-        if (s.direct_blocks) {
+        if (DIRECT == kEither ? s.direct_blocks != 0 : DIRECT != 0) {
             direct_small_work(&sh->mine, s, offsets, CROSS ? offsets_other : nullptr, H, s.build_rows);
         } else if (small) {
             build_small_work(offsets, CROSS ? offsets_other : nullptr, B, H, s.build_rows, scratch, &sh->mine);
