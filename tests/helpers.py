@@ -77,3 +77,14 @@ def sentinel_stats(shape) -> torch.Tensor:
 
 def assert_guard_rows_untouched(name, t: torch.Tensor, n_valid: int):
     assert (t[n_valid:] == GUARD).all(), f"guard rows of {name} were written"
+
+
+def launched(call):
+    """What `call` returns, and the names of the launches it made (as jfa_timing reports them: "schedule" is the scheduler kernel)."""
+    from paper_2409_15373_amd import binding
+    binding.jfa_timing_enable(True)
+    try:
+        result = call()
+        return result, set(binding.jfa_timing_read(32))
+    finally:
+        binding.jfa_timing_enable(False)

@@ -1,6 +1,7 @@
 """The fp32 matrix-core kernels at the edges of their tiles: a workgroup's four waves are the quarters of a 64 x 64 square,
-so lengths around 32, 64, 96 and 128 leave waves idle, blocks ragged, or one wave of a pair without anything to add.  With a
-large max_len the same batch goes through the scheduler kernel, with a tight one the kernels build their schedule."""
+so lengths around 32, 64, 96 and 128 leave waves idle, blocks ragged, or one wave of a pair without anything to add.  With a tight
+max_len there is no schedule (D = 128, backward: the kernels build it), with 4096 the kernels build it, with 8192 the scheduler kernel
+does, for the fp32 instructions at D = 128 and the split products at D = 32 and 64."""
 import pytest
 
 from paper_2409_15373_amd.synthetic import make_custom
@@ -12,19 +13,19 @@ pytestmark = pytest.mark.gpu
 EDGES = [1, 31, 32, 33, 0, 63, 64, 65, 95, 96, 97, 127, 128, 129, 200]
 
 
-@pytest.mark.parametrize("max_len", [200, 4096])
+@pytest.mark.parametrize("max_len", [200, 4096, 8192])
 @pytest.mark.parametrize("D", [32, 64, 128])
 def test_self(oracle, D, max_len):
     test_gpu_f32.run_case(oracle, make_custom("edges", EDGES, 1, D, dtype="f32", seed=31 + D, max_len=max_len))
 
 
-@pytest.mark.parametrize("max_len", [200, 4096])
+@pytest.mark.parametrize("max_len", [200, 4096, 8192])
 @pytest.mark.parametrize("D", [32, 64, 128])
 def test_causal(D, max_len):
     test_gpu_causal.run(make_custom("edges", EDGES, 1, D, dtype="f32", seed=32 + D), max_len)
 
 
-@pytest.mark.parametrize("max_len", [200, 4096])
+@pytest.mark.parametrize("max_len", [200, 4096, 8192])
 @pytest.mark.parametrize("D", [32, 64, 128])
 def test_cross(D, max_len):
     keys = EDGES[4:] + EDGES[:4]
@@ -63,12 +64,47 @@ def test_an_infinity_in_the_last_row_stays_in_its_column(D, mode):
     assert np.isfinite(test_gpu_f32.f64(others(inf_out, 3))).all()
 
 
-@pytest.mark.parametrize("B", [300, 5000, 13000])   # up to four items per workgroup, up to sixteen (dealt without claims at D <= 64), more (claimed)
+@pytest.mark.parametrize("B", [300, 5000, 13000])   # no schedule but for the backward at D = 128: built in the kernel, then claimed
 @pytest.mark.parametrize("D", [32, 64, 128])
 def test_many_short_samples(oracle, D, B):
     import numpy as np
     lengths = np.random.default_rng(35).integers(0, 21, size=B)
     test_gpu_f32.run_case(oracle, make_custom("many", lengths, 2, D, dtype="f32", seed=36 + D, max_len=20))
+
+
+# (samples, heads, longest, bound) on the fp32 instructions, where a bound of more than one block and more blocks than compute units keep a
+# schedule, and whether the scheduler kernel makes it.  Workgroups: 256 x 1 to 12 by registers; four, at D <= 64 sixteen, items each
+# are dealt without claims.
+WALKS = [pytest.param(200, 2, 65, 65, False, id="schedule in the kernel"),
+         pytest.param(300, 2, 100, 100, True, id="dealt"),
+         pytest.param(5000, 2, 20, 33, True, id="one wave, dealt"),          # D = 128: claimed
+         pytest.param(30000, 2, 6, 33, True, id="one wave, claimed")]
+
+
+@pytest.mark.parametrize("B,H,longest,bound,scheduler", WALKS)
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_walks_through_a_schedule(oracle, D, B, H, longest, bound, scheduler):
+    import numpy as np
+    from helpers import launched
+    lengths = np.random.default_rng(42).integers(0, longest + 1, size=B)
+    w = make_custom("walk", lengths, H, D, dtype="f32", seed=43 + D, max_len=bound)
+    _, names = launched(lambda: test_gpu_f32.run_case(oracle, w))
+    assert names == {"fwd_f32", "bwd_f32"} | ({"schedule"} if scheduler else set())
+
+
+@pytest.mark.parametrize("B,scheduler", [(100, False), (300, True), (4000, True)])   # built in the kernel; dealt; claimed
+@pytest.mark.parametrize("D", [32, 64, 128])
+def test_walks_of_four_wave_workgroups_against_longer_streams(D, B, scheduler):
+    """At most 64 queries against at most 128 keys: blocks of 64 queries that keep a schedule, longest stream first."""
+    import numpy as np
+    from helpers import launched
+    rng = np.random.default_rng(44)
+    lq, lk = rng.integers(0, 9, size=B), np.where(rng.random(B) < 0.1, rng.integers(65, 129, size=B), rng.integers(0, 20, size=B))
+    lq[0], lk[0], lq[1], lk[1] = 64, 128, 0, 0
+    (got, ref, oq, ok), names = launched(lambda: test_gpu_cross.run(lq, lk, 4, D, "f32", 45 + D, 64, 128))
+    test_gpu_cross.compare(got, ref, "f32", oq, ok, lq, lk)
+    assert names == {"fwd_f32", "bwd_f32"} | ({"schedule"} if scheduler else set())
+
 
 
 SHORT = [1, 31, 32, 0, 7, 8, 9, 16, 30, 2]

@@ -1,6 +1,6 @@
 """The direct-to-LDS kernels for head sizes 32 and 64 where they can go wrong: lengths around their 32-row waves, 64-row
 stages and 128-row tiles (odd and even numbers of stages, ragged ones, idle waves), every way in which their work is dealt
-(schedule built in the kernel; scheduler kernel with the schedule copied to LDS and with batches too large for that, claimed
+(no schedule; schedule built in the kernel; scheduler kernel with the schedule copied to LDS and with batches too large for that, claimed
 dynamically), a reference maximum that goes stale, and rows too wide for 32-bit offsets inside a stage."""
 import numpy as np
 import pytest
@@ -15,7 +15,7 @@ from helpers import f64, gate_bf16
 
 pytestmark = pytest.mark.gpu
 EDGES = [1, 31, 32, 33, 0, 63, 64, 65, 127, 128, 129, 191, 192, 193, 256, 257, 321, 449]
-SIZES = [pytest.param(449, id="schedule in the kernel"), pytest.param(16384, id="scheduler kernel")]
+SIZES = [pytest.param(449, id="no schedule"), pytest.param(1024, id="schedule in the kernel"), pytest.param(16384, id="scheduler kernel")]
 
 
 def run_self(oracle, w):
@@ -214,7 +214,8 @@ def everything(form, D, lq, lk, max_q, max_k, seed):
     return (out, lse) + tuple(binding.jfa_backward(q, k, v, out, do, lse, oq, max_q, causal=form == "causal"))
 
 
-@pytest.mark.parametrize("copies", [1, 400])   # schedule built in the kernel; scheduler kernel, and a fixed deal of several rounds
+# few queries, few keys: no schedule; one built in the kernel; scheduler kernel, and a fixed deal of several rounds
+@pytest.mark.parametrize("copies", [1, 10, 400])
 @pytest.mark.parametrize("form", ["few queries", "few keys", "keys in shorter blocks", "causal, keys in shorter blocks"])
 @pytest.mark.parametrize("D", [32, 64])
 def test_two_wave_workgroups(D, form, copies):

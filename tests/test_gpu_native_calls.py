@@ -13,10 +13,14 @@ def inputs(dtype=torch.bfloat16, B=5, rows=150, H=2, D=64):
     return q, k, v, offsets
 
 
-def both(monkeypatch, call):
+def both(monkeypatch, call, answered=True):
     from paper_2409_15373_amd import binding
     assert binding._load_calls(), "the C++ calls are not built"
-    native = call(binding)
+    answers, ask = [], binding._native
+    with monkeypatch.context() as m:
+        m.setattr(binding, "_native", lambda *args: answers.append(ask(*args)) or answers[-1])
+        native = call(binding)
+    assert [a is not None for a in answers] == [True] * answered, "the C++ function did not answer, or was asked where it is not to be"
     with monkeypatch.context() as m:
         m.setattr(binding, "_calls", False)
         python = call(binding)
@@ -39,7 +43,7 @@ def test_forward(monkeypatch, dtype):
 def test_conversions_and_feature_operators(monkeypatch):
     q, _, _, offsets = inputs()
     both(monkeypatch, lambda b: b.jfa_jagged_to_dense(q, offsets, 72))
-    both(monkeypatch, lambda b: b.jfa_jagged_to_dense(q, offsets, 72, pad=-0.0))   # not a pattern of zeros
+    both(monkeypatch, lambda b: b.jfa_jagged_to_dense(q, offsets, 72, pad=-0.0), answered=False)   # not a pattern of zeros
     dense = torch.randn(5, 72, 2, 64, device="cuda").bfloat16()
     both(monkeypatch, lambda b: b.jfa_dense_to_jagged(dense, offsets, torch.zeros_like(q)))
     x, y, w = q[:, 0].contiguous(), q[:, 1, :32].contiguous(), torch.randn(5, 64, 32, device="cuda").bfloat16()
@@ -80,7 +84,9 @@ def test_a_dispatch_mode_sees_the_allocations():
     q, k, v, offsets = inputs()
     with Seen() as seen:
         binding.jfa_forward(q, k, v, offsets, 70)
+        assert binding._native("forward", q, k, v, offsets, 70, False) is None
     assert any("empty" in op for op in seen.ops)
+    assert binding._native("forward", q, k, v, offsets, 70, False) is not None
 
 
 def test_a_function_mode_sees_the_allocations():

@@ -36,8 +36,10 @@ def test_two_calls_in_a_row_match_jfa_forward(oracle):
     from paper_2409_15373_amd import binding
     lib = binding.load()
     cases = [case(71, 900, 700, 2, 128, 1024),      # direct-to-LDS kernel, several work items per workgroup
-             case(72, 9, 300, 2, 128, 1024),        # the same kernel on a much smaller batch: stale table contents behind it
-             case(73, 40, 200, 3, 64, 256)]         # register-staged kernel
+             case(75, 70, 300, 2, 128, 1024),       # the same kernel on a much smaller batch: stale table contents behind it
+             case(72, 9, 300, 2, 128, 1024),        # at most a block per compute unit: no schedule
+             case(73, 40, 200, 3, 64, 256),         # the kernels for narrow heads without a schedule
+             case(76, 80, 200, 3, 64, 256)]         # the schedule built in the kernel
     for w in cases:
         d = to_device(w, names=("q", "k", "v"))
         n = w.sum_B
