@@ -193,7 +193,7 @@ std::optional<Tensor> cross_attention(const Tensor &q, const Tensor &k, const Te
 
 // ---- the binding's calls without gradients, results allocated here ----
 // What bounds a call on a small batch is the host again: the ctypes call and the Python around it took 7.5 us, twice a small batch's
-// kernel; from here a call takes 4.4 (four bf16 samples of up to 64 rows; fp32, where the kernel takes longer, 6.3).  The functions take the arguments as the interpreter has them; whatever
+// kernel; from here a call takes 4.4 (four bf16 samples of up to 64 rows; fp32, where the kernel takes longer, 5.4).  The functions take the arguments as the interpreter has them; whatever
 // is not exactly what they expect, and whatever goes wrong, is answered with None: the Python function takes the call and raises what there is to raise.
 const Tensor *exact_tensor(PyObject *o) {
     if (!THPVariable_CheckExact(o)) return nullptr;
