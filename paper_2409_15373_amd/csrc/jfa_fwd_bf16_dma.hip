@@ -16,7 +16,7 @@
 //     the two waves of a SIMD, which a barrier per stage keeps in step, are in the same phase most of the time: a
 //     stage took 2 910 clocks, now 2 750, of 2 048 that its matrix instructions need (a skeleton without the row sum 2 470).  What is
 //     left: the row sum's dot products, which do not overlap (5 %), LDS latency behind the barrier, the starts of tiles; and the clock
-//     falls as the pipes fill: 512 x 8 bimodal to 4096, by counters, 31.2 -> 27.2 million clocks, matrix pipes 51 -> 58 % busy, but
+//     falls as the pipes fill: 512 x 8 bimodal to 4096, by counters, 3.90 -> 3.40 million clocks, matrix pipes 51 -> 58 % busy, but
 //     1.94 -> 1.82 GHz, so that of 13 % fewer clocks 7 % are left in time.  Forward, microseconds, before -> now: 16 x 8 heads of
 //     8192 rows 3640 -> 3505, causal 2140 -> 1998; 512 x 8 bimodal to 4096 2130 -> 2010, causal 1305 -> 1203; 1024 x 4 of up to
 //     1024 1040 -> 990; 300 x 4 of up to 300 73.7 -> 67.5; 1024 x 4 Zipf to 1024 664 -> 636;
