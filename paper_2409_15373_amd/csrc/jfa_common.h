@@ -579,7 +579,8 @@ hipError_t launch_check_offsets(const int64_t *offsets, int B, int64_t max_len, 
 // bf16, D = 128, more than 256 rows: 8 x 4 of up to 600, forward 31.5 and 23.5, causal 30.1 and 20.2, with backward 98 and 84.5; 12 x 1 of up
 // to 1884 60.4 and 50.1, 194 and 174; 4 x 4 of 4096 140 and 127, 612 and 596.
 // D = 64: 5 x 2 of up to 300 12.4 and 10.9, 40.9 and 36.4; 8 x 4 of up to 600 17.0 and 15.9, 57.9 and 53.3; with two blocks per compute
-// unit 20 x 3 Zipf to 700 loses, 18.3 and 19.7, 65 and 73.
+// unit 20 x 3 Zipf to 700 loses, 18.3 and 19.7, 65 and 73.  (The bf16 figures with one kernel for both; those of their own take another 6 to 9 %
+// off the calls without a schedule at D = 32 and 64, 4 to 11 % at D = 128.)
 inline int direct_blocks(int64_t B, int64_t max_len, int H, int block_rows, int cus) {
     const int64_t blocks = (max_len + block_rows - 1) / block_rows;
     return blocks > 0 && blocks <= cus && B <= cus && B * H * blocks <= cus ? (int)blocks : 0;
